@@ -12,9 +12,9 @@
 //   NestedFP16 : lane loads 16 B upper + 16 B lower, merges them (Sec. 4.2, Alg. 1) -> same
 //   E4M3       : lane loads 2 x 16 B of E4M3 bytes (upper plane) -> 1 x v_mfma_f32_16x16x128_f8f6f4
 // Every kind exists for two storage orders of the weights: row-major [N,K] (the two byte tensors
-// of Sec. 4 "Overview" as they are: a lane's 16 bytes are 16 consecutive columns of its row, a wave
-// instruction gathers 64-byte pieces of 16 rows) and packed blocks of 16 rows x 64 columns whose
-// chunk order is the lane order, so that every load of a wave is one contiguous kilobyte.
+// of Sec. 4 "Overview" as they are, fetched in 128-byte pieces of 8 rows and regrouped through LDS) and
+// packed blocks of 16 rows x 64 columns whose chunk order is the lane order, so that every load of a
+// wave is one contiguous kilobyte.
 // Columns past K and rows past N are never multiplied: their loads are sent out of the buffer's
 // range and return zero, whatever the memory behind them holds.
 #include <algorithm>
@@ -44,6 +44,7 @@ struct SmallParams {
     int k_passes;           // K slices each wave walks through in turn
     int tiles_per_wg;       // 16-row weight tiles each workgroup walks through
     int tile_stride;        // distance between a workgroup's consecutive tiles (1 or gridDim.x)
+    int rotate;             // 1: the waves' K-slices are rotated from workgroup to workgroup
     int vec_store;          // 1: 8-byte fp16 stores allowed
 };
 
@@ -62,40 +63,95 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rsrc(const uint8_t *bas
 
 constexpr uint32_t kDead = 0x80000000u;               // an offset no weight array reaches
 
-// Where the weights of a K-step sit.  `voff` = lane part + tile part + the wave's slice; step S adds
-// an immediate.  Row-major kinds: lane l = row l % 16, columns 16 (l / 16) .. + 15 of the step's 64
-// (E4M3: of each 64-column half of the step's 128).  Packed kinds: lane l = chunk l of the block.
+// Where the weights of a K-step sit.
+// Packed kinds: lane l takes chunk l of a block, which is its MFMA operand; `voff` = lane part + tile
+// part + the wave's slice; step S adds an immediate.
+// Row-major kinds are fetched in pieces of 16 rows x 128 bytes by two instructions of 8 rows x 128
+// bytes (lane l: row l / 8 of the eight, 16-byte chunk l % 8) and brought into operand order (lane l:
+// row l % 16) through two kilobytes of LDS per wave, see regroup().  Fetched in operand order instead
+// -- 16 rows x 64 bytes per instruction -- every line is touched by two instructions, far enough apart
+// to be requested twice, and non-temporal loads, which would keep the stream out of L2, cost a second
+// trip to memory: a load-only kernel with the shape of this one reads (28672, 4096) in 47.8 us so, in
+// 35.0 us by whole lines with the skew of the K-slices (see the kernel), and in 35.4 us from packed planes.
 template <int KIND> struct WLayout {
     static constexpr bool PACKED = kind_is_packed(KIND);
     static constexpr int EB = kind_elem_bytes(KIND);
     static constexpr int KSTEP = StepK<KIND>::value;
     // bytes between consecutive K-steps of one tile
-    static constexpr int STEP = PACKED ? (KSTEP / 64) * 1024 * EB : KSTEP * EB;
-    // the second 16 bytes of a lane's step, relative to the first (NestedFP: the other plane, same offset)
-    static constexpr int SECOND = kind_is_nested(KIND) ? 0
-                                  : (KIND == kPlainF16 ? 16 : (PACKED ? 1024 : 64));
-    // Cache policy of the weight loads.  Every weight is read once per launch.  Packed kinds fetch whole
-    // 128-byte lines (a contiguous kilobyte per instruction) and mark them non-temporal (nt, bit 1),
-    // so that they pass through L2 without displacing the activations and partial sums: the decode step
-    // runs 5-8 % faster.  Row-major kinds take 64-byte pieces of a line, the other half follows in a
-    // later instruction, and the same hint makes them 4-12 % slower (measured), so they keep the default.
-#ifndef NFP_SMALL_POLICY
-#define NFP_SMALL_POLICY 2
-#endif
-    static constexpr int POLICY = PACKED ? NFP_SMALL_POLICY : 0;
+    static constexpr int STEP = (KSTEP / 64) * 1024 * EB;
+    // packed: the second 16 bytes of a lane's step, relative to the first (NestedFP: the other plane, same offset)
+    static constexpr int SECOND = kind_is_nested(KIND) ? 0 : 1024;
+    // row-major: the chunks of a 128-byte row piece that lane group g holds: C0 and C1
+    static __device__ __forceinline__ int c0(int g) { return KIND == kPlainF16 ? 2 * g : g; }
+    static __device__ __forceinline__ int c1(int g) { return KIND == kPlainF16 ? 2 * g + 1 : 4 + g; }
 };
 
-// Weights of K-step `S` of the wave's slice.  The whole offset is in the range-checked VGPR part of
-// the address (the scalar offset is not range-checked).  va / vb: the lane's columns of the first /
+// Cache policy of the weight loads.  Every weight is read once per launch; where every load instruction
+// fetches whole 128-byte lines, they are marked non-temporal (nt, bit 1): the lines pass through L2
+// without displacing the activations and partial sums (packed decode step 5-8 % faster; row-major
+// (28672, 4096) at 16 tokens 44.6 -> 41.0 us).  Packed planes always do; row-major ones if the rows start
+// on lines.  Otherwise two pieces share a line, which then has to stay in L2 (K = 4112: 51.8 us with
+// the default policy, 58.6 us non-temporal).
+constexpr int kStream = 2, kCached = 0;
+
+// 128-byte row pieces per wave, tile and weight array
+template <int KIND, int SPW> constexpr int row_pieces() { return kind_is_nested(KIND) ? SPW / 2 : SPW; }
+
+// Packed weights of K-step `S` of the wave's slice.  The whole offset is in the range-checked VGPR part
+// of the address (the scalar offset is not range-checked).  va / vb: the lane's columns of the first /
 // second 16 bytes lie inside K; otherwise the load is sent out of range and returns zero.
-template <int KIND, int S>
+template <int KIND, int POL, int S>
 __device__ __forceinline__ void load_w(WItem &r, __amdgpu_buffer_rsrc_t r0, __amdgpu_buffer_rsrc_t r1,
                                        uint32_t voff, bool va, bool vb) {
     typedef WLayout<KIND> L;
     const uint32_t oa = va ? voff : kDead, ob = vb ? voff : kDead;
-    r.a = __builtin_amdgcn_raw_buffer_load_b128(r0, oa + S * L::STEP, 0, L::POLICY);
-    r.b = __builtin_amdgcn_raw_buffer_load_b128(r1, ob + S * L::STEP + L::SECOND, 0, L::POLICY);
+    r.a = __builtin_amdgcn_raw_buffer_load_b128(r0, oa + S * L::STEP, 0, POL);
+    r.b = __builtin_amdgcn_raw_buffer_load_b128(r1, ob + S * L::STEP + L::SECOND, 0, POL);
 }
+
+// Row-major weights of one tile as they come: for each piece the rows 0 .. 7 and 8 .. 15 of the tile.
+// NestedFP keeps a piece (two K-steps) of the upper plane in the first members of its two steps and
+// that of the lower plane in the second ones; the other kinds keep a piece (one K-step) in its step.
+// kv[q]: the lane's chunk of piece q lies inside K.
+template <int KIND, int SPW, int POL>
+__device__ __forceinline__ void load_rows(WItem (&w)[SPW], __amdgpu_buffer_rsrc_t r0, __amdgpu_buffer_rsrc_t r1,
+                                          uint32_t lo, uint32_t hi, const bool (&kv)[SPW]) {
+    if constexpr (kind_is_nested(KIND)) {
+#pragma unroll
+        for (int q = 0; q < SPW / 2; ++q) {
+            w[2 * q].a = __builtin_amdgcn_raw_buffer_load_b128(r0, (kv[q] ? lo : kDead) + q * 128, 0, POL);
+            w[2 * q + 1].a = __builtin_amdgcn_raw_buffer_load_b128(r0, (kv[q] ? hi : kDead) + q * 128, 0, POL);
+        }
+#pragma unroll
+        for (int q = 0; q < SPW / 2; ++q) {
+            w[2 * q].b = __builtin_amdgcn_raw_buffer_load_b128(r1, (kv[q] ? lo : kDead) + q * 128, 0, POL);
+            w[2 * q + 1].b = __builtin_amdgcn_raw_buffer_load_b128(r1, (kv[q] ? hi : kDead) + q * 128, 0, POL);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < SPW; ++q) {
+            w[q].a = __builtin_amdgcn_raw_buffer_load_b128(r0, (kv[q] ? lo : kDead) + q * 128, 0, POL);
+            w[q].b = __builtin_amdgcn_raw_buffer_load_b128(r0, (kv[q] ? hi : kDead) + q * 128, 0, POL);
+        }
+    }
+}
+
+// One piece from load order into operand order through the wave's own 2 KB of LDS: chunk c of row r sits
+// at r * 128 + 16 (c ^ (r / 2 % 8)), so that the 16 rows a quarter wave reads hit all 64 banks.  The LDS
+// serves a wave's accesses in order, so consecutive pieces share the 2 KB without waiting for each other;
+// the empty asm statements keep the compiler from exchanging a lane's read with another lane's write.
+struct Regroup {
+    uint8_t *wlo, *whi;                               // where this lane's two loaded chunks go
+    const uint8_t *r0, *r1;                           // where its two operand chunks are
+    __device__ __forceinline__ void run(u32x4 &a, u32x4 &b) const {
+        *reinterpret_cast<u32x4 *>(wlo) = a;
+        *reinterpret_cast<u32x4 *>(whi) = b;
+        asm volatile("" ::: "memory");
+        a = *reinterpret_cast<const u32x4 *>(r0);
+        b = *reinterpret_cast<const u32x4 *>(r1);
+        asm volatile("" ::: "memory");
+    }
+};
 
 // Activations of one K-step for 16 tokens (32 bytes per lane); zero outside M and K.
 template <int KIND>
@@ -150,7 +206,7 @@ __device__ __forceinline__ floatx4 mma_step(const u32x4 &w_lo, const u32x4 &w_hi
     }
 }
 
-template <int KIND, int SPW, int S = 0>
+template <int KIND, int SPW, int POL, int S = 0>
 struct FetchTile {
     static __device__ __forceinline__ void run(WItem (&w)[SPW], __amdgpu_buffer_rsrc_t r0,
                                                __amdgpu_buffer_rsrc_t r1, uint32_t voff,
@@ -162,18 +218,18 @@ struct FetchTile {
             typedef WLayout<KIND> L;
 #pragma unroll
             for (int q = 0; q < SPW; ++q)
-                w[q].a = __builtin_amdgcn_raw_buffer_load_b128(r0, (va[q] ? voff : kDead) + q * L::STEP, 0, L::POLICY);
+                w[q].a = __builtin_amdgcn_raw_buffer_load_b128(r0, (va[q] ? voff : kDead) + q * L::STEP, 0, POL);
 #pragma unroll
             for (int q = 0; q < SPW; ++q)
-                w[q].b = __builtin_amdgcn_raw_buffer_load_b128(r1, (vb[q] ? voff : kDead) + q * L::STEP + L::SECOND, 0, L::POLICY);
+                w[q].b = __builtin_amdgcn_raw_buffer_load_b128(r1, (vb[q] ? voff : kDead) + q * L::STEP + L::SECOND, 0, POL);
         } else {
-            load_w<KIND, S>(w[S], r0, r1, voff, va[S], vb[S]);
-            FetchTile<KIND, SPW, S + 1>::run(w, r0, r1, voff, va, vb);
+            load_w<KIND, POL, S>(w[S], r0, r1, voff, va[S], vb[S]);
+            FetchTile<KIND, SPW, POL, S + 1>::run(w, r0, r1, voff, va, vb);
         }
     }
 };
-template <int KIND, int SPW>
-struct FetchTile<KIND, SPW, SPW> {
+template <int KIND, int SPW, int POL>
+struct FetchTile<KIND, SPW, POL, SPW> {
     static __device__ __forceinline__ void run(WItem (&)[SPW], __amdgpu_buffer_rsrc_t, __amdgpu_buffer_rsrc_t,
                                                uint32_t, const bool (&)[SPW], const bool (&)[SPW]) {}
 };
@@ -186,16 +242,17 @@ struct FetchTile<KIND, SPW, SPW> {
 //   (no copies, no branch in the loop body): the loads of tile t+1 are in flight while
 //   tile t is merged and multiplied.  Per-tile partial sums go to LDS and are reduced
 //   across the waves once, at the end, in fixed wave order.
-template <int KIND, int MT, int SPW, bool MULTIPASS>
+template <int KIND, int MT, int SPW, bool MULTIPASS, int POL>
 __global__ void __launch_bounds__((MT == 4 || SPW == 8) ? 512 : 1024)
 small_gemm_kernel(SmallParams p) {
-    extern __shared__ float lds[];                    // [tile][wave][MT][64] x float4
+    extern __shared__ float lds[];                    // [tile][wave][MT][64] x float4, then (row-major kinds) 2 KB per wave
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int waves = blockDim.x >> 6;
     const int g = lane >> 4;
     const int r16 = lane & 15;
     const int slice = blockIdx.y;
+    typedef WLayout<KIND> L;
     constexpr int KSTEP = StepK<KIND>::value;
     constexpr int KLANE = 16;                         // first column of lane group g within a step: 16*g
     const int tiles_total = (p.N + 15) >> 4;
@@ -206,10 +263,12 @@ small_gemm_kernel(SmallParams p) {
     const int T = tstride == 1 ? min(p.tiles_per_wg, tiles_total - tile0)
                                : (tiles_total - tile0 + tstride - 1) / tstride;
     floatx4 *slots = reinterpret_cast<floatx4 *>(lds);
+    // Which K-slice of the workgroup's this wave takes (see `rotate` in launch_small_gemm; the sums do
+    // not depend on it).
+    const int ks = !L::PACKED && p.rotate ? (int)((wave + (blockIdx.x >> 3) * 5u) % (unsigned)waves) : wave;
     const __amdgpu_buffer_rsrc_t rs0 = weight_rsrc(p.W0, p.w_bytes);
     const __amdgpu_buffer_rsrc_t rs1 = weight_rsrc(kind_is_nested(KIND) ? p.W1 : p.W0, p.w_bytes);
     const uint32_t tile_bytes = p.tile_bytes;
-    typedef WLayout<KIND> L;
 
     // with several K passes this wave's partial tiles live in LDS and start at zero
     // (the spare slot of an odd T included)
@@ -217,25 +276,46 @@ small_gemm_kernel(SmallParams p) {
         for (int tile = 0; tile < ((T + 1) & ~1); ++tile)
 #pragma unroll
             for (int i = 0; i < MT; ++i)
-                slots[((tile * waves + wave) * MT + i) * 64 + lane] = floatx4{0.f, 0.f, 0.f, 0.f};
+                slots[((tile * waves + ks) * MT + i) * 64 + lane] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     // Long rows take several passes: in pass q the wave owns K-slice (slice*passes + q)*waves
-    // + wave, reloads the activations of that slice and walks the same tiles again, adding
+    // + ks, reloads the activations of that slice and walks the same tiles again, adding
     // to its partial tiles in LDS.
     u32x4 xa[SPW][MT], xb[SPW][MT];
     uint32_t voff = 0;
-    bool va[SPW], vb[SPW];                            // this lane's columns of step s lie inside K
+    bool va[SPW], vb[SPW];                            // packed: this lane's columns of step s lie inside K; row-major: va, of piece s
+    Regroup rg;
+    if (!L::PACKED) {
+        uint8_t *own = reinterpret_cast<uint8_t *>(slots + ((T + 1) & ~1) * waves * MT * 64) + wave * 2048;
+        const int wr = lane >> 3;                     // (row >> 1) & 7 of rows wr and 8 + wr: wr / 2, wr / 2 + 4
+        rg.wlo = own + wr * 128 + (((lane & 7) ^ (wr >> 1)) << 4);
+        rg.whi = own + (8 + wr) * 128 + (((lane & 7) ^ (4 + (wr >> 1))) << 4);
+        rg.r0 = own + r16 * 128 + ((L::c0(g) ^ (r16 >> 1)) << 4);
+        rg.r1 = own + r16 * 128 + ((L::c1(g) ^ (r16 >> 1)) << 4);
+    }
 
     auto fetch = [&](WItem (&w)[SPW], int tile) {
         // past the last tile every lane is sent out of range
         const uint32_t base = tile < T ? voff + (uint32_t)(tile0 + tile * tstride) * tile_bytes : kDead;
-        FetchTile<KIND, SPW>::run(w, rs0, rs1, base, va, vb);
+        if constexpr (L::PACKED) FetchTile<KIND, SPW, POL>::run(w, rs0, rs1, base, va, vb);
+        else load_rows<KIND, SPW, POL>(w, rs0, rs1, base, base + 8u * p.w_row_bytes, va);
     };
-    auto consume = [&](const WItem (&w)[SPW], int tile) {
+    auto consume = [&](WItem (&w)[SPW], int tile) {
         floatx4 acc[MT];
+        if constexpr (!L::PACKED) {
+            if constexpr (kind_is_nested(KIND)) {
+#pragma unroll
+                for (int s = 0; s < SPW; s += 2) rg.run(w[s].a, w[s + 1].a);
+#pragma unroll
+                for (int s = 0; s < SPW; s += 2) rg.run(w[s].b, w[s + 1].b);
+            } else {
+#pragma unroll
+                for (int s = 0; s < SPW; ++s) rg.run(w[s].a, w[s].b);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < MT; ++i)
-            acc[i] = MULTIPASS ? slots[((tile * waves + wave) * MT + i) * 64 + lane] : floatx4{0.f, 0.f, 0.f, 0.f};
+            acc[i] = MULTIPASS ? slots[((tile * waves + ks) * MT + i) * 64 + lane] : floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < SPW; ++s) {
             u32x4 w_lo, w_hi;
@@ -244,21 +324,28 @@ small_gemm_kernel(SmallParams p) {
             for (int i = 0; i < MT; ++i) acc[i] = mma_step<KIND>(w_lo, w_hi, xa[s][i], xb[s][i], acc[i]);
         }
 #pragma unroll
-        for (int i = 0; i < MT; ++i) slots[((tile * waves + wave) * MT + i) * 64 + lane] = acc[i];
+        for (int i = 0; i < MT; ++i) slots[((tile * waves + ks) * MT + i) * 64 + lane] = acc[i];
     };
 
     WItem buf0[SPW], buf1[SPW];
-    __shared__ uint32_t row_max[16 * 16];             // kE4M3Quant: per wave and token row
+    __shared__ uint32_t row_max[KIND == kE4M3Quant ? 16 * 16 : 1];   // per wave and token row
     float row_scale = 1.0f;
     const int passes = MULTIPASS ? p.k_passes : 1;
     for (int pass = 0; pass < passes; ++pass) {
-        const int k_wave = ((slice * passes + pass) * waves + wave) * (SPW * KSTEP) + KLANE * g;
-        if (L::PACKED) voff = (uint32_t)lane * 16u + (uint32_t)((k_wave - KLANE * g) >> 6) * (1024u * L::EB);   // block column of the slice
-        else voff = (uint32_t)r16 * p.w_row_bytes + (uint32_t)k_wave * (uint32_t)L::EB;
+        const int k_slice = ((slice * passes + pass) * waves + ks) * (SPW * KSTEP);
+        const int k_wave = k_slice + KLANE * g;
+        if (L::PACKED) {
+            voff = (uint32_t)lane * 16u + (uint32_t)(k_slice >> 6) * (1024u * L::EB);   // block column of the slice
 #pragma unroll
-        for (int s = 0; s < SPW; ++s) {
-            va[s] = k_wave + s * KSTEP < p.K;
-            vb[s] = kind_is_fp8(KIND) ? k_wave + s * KSTEP + 64 < p.K : va[s];
+            for (int s = 0; s < SPW; ++s) {
+                va[s] = k_wave + s * KSTEP < p.K;
+                vb[s] = kind_is_fp8(KIND) ? k_wave + s * KSTEP + 64 < p.K : va[s];
+            }
+        } else {
+            const int kb = k_slice * L::EB + (lane & 7) * 16;      // byte column of the lane's chunk of the first piece
+            voff = (uint32_t)(lane >> 3) * p.w_row_bytes + (uint32_t)kb;
+#pragma unroll
+            for (int q = 0; q < SPW; ++q) va[q] = q < row_pieces<KIND, SPW>() && kb + 128 * q < p.K * L::EB;
         }
         if (KIND == kE4M3Quant) {
             // Fused activation quantisation (Sec. 2.2 per-token scaling; one token tile, the
@@ -416,9 +503,9 @@ small_gemm_kernel(SmallParams p) {
     // a ticket; the one that draws the last ticket adds the slices in slice order -- the order of
     // the stand-alone reduction kernel, so the result does not depend on who came last -- and
     // leaves the counter at zero for the next launch.  Nobody waits for anybody.
-    __shared__ uint32_t ticket;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this lane's write-through stores are done
     __syncthreads();
+    uint32_t &ticket = *reinterpret_cast<uint32_t *>(lds);         // (the partial sums in LDS are used up)
     if (threadIdx.x == 0)
         ticket = __hip_atomic_fetch_add(&p.counters[blockIdx.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
@@ -617,17 +704,25 @@ size_t small_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K) {
     return c.split > 1 ? (size_t)c.split * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
-template <int KIND, int MT, int SPW>
+template <int KIND, int MT, int SPW, int POL = kStream>
 static void launch_small_t(const SmallParams &p, const SmallConfig &c, dim3 grid, hipStream_t stream) {
-    size_t lds = (size_t)((c.tiles_per_wg + 1) & ~1) * c.waves * MT * 64 * sizeof(floatx4);
-    auto kern1 = small_gemm_kernel<KIND, MT, SPW, false>;
-    auto kernp = small_gemm_kernel<KIND, MT, SPW, true>;
+    if constexpr (!kind_is_packed(KIND) && POL == kStream) {      // rows that do not start on lines (see kStream)
+        if ((p.w_row_bytes & 127) != 0 || (reinterpret_cast<uintptr_t>(p.W0) & 127) != 0 ||
+            (reinterpret_cast<uintptr_t>(p.W1) & 127) != 0) {
+            launch_small_t<KIND, MT, SPW, kCached>(p, c, grid, stream);
+            return;
+        }
+    }
+    size_t lds = (size_t)((c.tiles_per_wg + 1) & ~1) * c.waves * MT * 64 * sizeof(floatx4) +
+                 (kind_is_packed(KIND) ? 0 : (size_t)c.waves * 2048);
+    auto kern1 = small_gemm_kernel<KIND, MT, SPW, false, POL>;
+    auto kernp = small_gemm_kernel<KIND, MT, SPW, true, POL>;
     static std::atomic<bool> attr_set{false};                    // once per instantiation
     if (!attr_set.load(std::memory_order_acquire)) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern1),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernp),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         attr_set.store(true, std::memory_order_release);
     }
     if (c.passes > 1) kernp<<<grid, c.waves * 64, lds, stream>>>(p);
@@ -637,8 +732,8 @@ static void launch_small_t(const SmallParams &p, const SmallConfig &c, dim3 grid
 // The fused-quantisation kind exists for one token tile, one K pass and no grid split only.
 static void launch_small_quant(const SmallParams &p, const SmallConfig &c, dim3 grid, hipStream_t stream) {
     size_t lds = (size_t)((c.tiles_per_wg + 1) & ~1) * c.waves * 64 * sizeof(floatx4);
-    auto k2 = small_gemm_kernel<kE4M3Quant, 1, 2, false>;
-    auto k4 = small_gemm_kernel<kE4M3Quant, 1, 4, false>;
+    auto k2 = small_gemm_kernel<kE4M3Quant, 1, 2, false, kStream>;
+    auto k4 = small_gemm_kernel<kE4M3Quant, 1, 4, false, kStream>;
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k2), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
@@ -703,6 +798,14 @@ int launch_small_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     p.counters = fused_reduce ? a.counters : nullptr;
     p.k_passes = c.passes;
     p.tile_stride = (tuning().small_interleave != 0 && c.tiles_per_wg > 1) ? (int)grid_x : 1;
+    // Rows that are a multiple of 4 KB long put the 16 rows of a slice on the same memory channels, and as
+    // the workgroups start together, wave by wave, the whole chip asks for one group of channels after
+    // the other; with the slices rotated from workgroup to workgroup of an XCD it does not (16 tokens,
+    // FP16 mode: (28672, 4096) 44.2 -> 39.5 us, (57344, 8192) 174 -> 154 us).  Other row lengths lose up to
+    // 3 % by it, and plain FP16 weights, whose slices are a kilobyte long, gain only from rows of 16 KB on
+    // ((57344, 8192) 172 -> 150 us, (28672, 4096) 37.2 -> 38.4 us).
+    const uint32_t channels = kind == kPlainF16 ? 16384u : 4096u;
+    p.rotate = !kind_is_packed(kind) && p.w_row_bytes % channels == 0 ? 1 : 0;
     p.vec_store = ((a.N & 3) == 0 && (a.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 7) == 0) ? 1 : 0;
     if (c.split > 1 && (a.partials == nullptr ||
                         a.partial_bytes < (size_t)c.split * a.M * a.N * sizeof(float)))

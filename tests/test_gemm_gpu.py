@@ -652,6 +652,37 @@ def test_memory_outside_the_matrix_never_reaches_the_result(nfp, M):
         assert np.isnan(yb[:, 16:32]).all()
 
 
+@pytest.mark.parametrize("M,N,K,knobs", [
+    (1, 17, 16, {}), (7, 15, 48, {}), (8, 33, 64, {}), (9, 40, 112, {}), (16, 24, 128, {}), (3, 100, 144, {}),   # a piece, more, less
+    (15, 330, 4096, {"small_tiles": 1, "small_split": 1}),        # rows of 4 KB: K-slices rotated over 21 workgroups
+    (16, 330, 8192, {"small_tiles": 2, "small_spw": 4}),          # plain FP16 rows of 16 KB as well
+    (5, 200, 4096 + 16, {"small_spw": 8}), (16, 200, 4096 + 80, {"small_spw": 8, "small_split": 2}),   # rows that start inside a line
+    (25, 50, 4096 + 128, {"small_tiles": 3, "small_max_m": 64}), (64, 70, 2048 + 208, {"small_max_m": 64}),   # several token tiles
+    (16, 40, 36864 + 48, {"small_split": 1}),                     # several passes over K
+])
+def test_streaming_kernel_on_row_pieces(nfp, M, N, K, knobs):
+    # row-major weights and the activations are fetched in pieces of 16 rows x 128 bytes and regrouped
+    # through LDS: tails of pieces, of tiles and of the token tile, against the oracle and the packed planes
+    try:
+        for k, v in knobs.items():
+            nfp.tune(k, v)
+        # (eight K-steps per wave exist for row-major weights only)
+        layouts = (False,) if knobs.get("small_spw") == 8 else (False, True)
+        run_both_modes(nfp, workloads.act_host(M, K, seed=N), workloads.weight_host(N, K, seed=M),
+                       "%d x %d, M=%d" % (N, K, M), layouts=layouts)
+    finally:
+        for k in knobs:
+            nfp.tune(k, -1)
+    # FP16 weights whose rows start on lines (stride 64 halves) and inside them, strided activations
+    X = to_dev(workloads.act_host(M, K + 64, seed=3))[:, 16:16 + K]
+    W = workloads.weight_host(N, K, seed=4)
+    ref = oracle.gemm_fp16(X.cpu().numpy(), W)
+    for pad in (64 - K % 64, 8):
+        Wd = torch.full((N, K + pad), float("nan"), dtype=torch.float16, device="cuda:0")
+        Wd[:, :K] = to_dev(W)
+        assert_gemm_close(nfp.plain_gemm_fp16(X, Wd[:, :K]).cpu().numpy(), ref, "row stride %d" % (K + pad))
+
+
 @pytest.mark.parametrize("M,N,K,knobs", [(16, 4096 + 8, 14336, {}), (4, 300, 28672, {}),
                                          (16, 520, 4096, {"small_split": 4, "small_tiles": 2}),
                                          (40, 304, 2048 + 64, {"small_split": 3, "small_tiles": 3}),
