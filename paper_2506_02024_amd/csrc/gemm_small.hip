@@ -68,7 +68,7 @@ constexpr uint32_t kDead = 0x80000000u;               // an offset no weight arr
 // part + the wave's slice; step S adds an immediate.
 // Row-major kinds are fetched in pieces of 16 rows x 128 bytes by two instructions of 8 rows x 128
 // bytes (lane l: row l / 8 of the eight, 16-byte chunk l % 8) and brought into operand order (lane l:
-// row l % 16) through two kilobytes of LDS per wave, see regroup().  Fetched in operand order instead
+// row l % 16) through two kilobytes of LDS per wave, see Regroup.  Fetched in operand order instead
 // -- 16 rows x 64 bytes per instruction -- every line is touched by two instructions, far enough apart
 // to be requested twice, and non-temporal loads, which would keep the stream out of L2, cost a second
 // trip to memory: a load-only kernel with the shape of this one reads (28672, 4096) in 47.8 us so, in
@@ -81,9 +81,6 @@ template <int KIND> struct WLayout {
     static constexpr int STEP = (KSTEP / 64) * 1024 * EB;
     // packed: the second 16 bytes of a lane's step, relative to the first (NestedFP: the other plane, same offset)
     static constexpr int SECOND = kind_is_nested(KIND) ? 0 : 1024;
-    // row-major: the chunks of a 128-byte row piece that lane group g holds: C0 and C1
-    static __device__ __forceinline__ int c0(int g) { return KIND == kPlainF16 ? 2 * g : g; }
-    static __device__ __forceinline__ int c1(int g) { return KIND == kPlainF16 ? 2 * g + 1 : 4 + g; }
 };
 
 // Cache policy of the weight loads.  Every weight is read once per launch; where every load instruction
@@ -136,39 +133,42 @@ __device__ __forceinline__ void load_rows(WItem (&w)[SPW], __amdgpu_buffer_rsrc_
     }
 }
 
-// One piece from load order into operand order through the wave's own 2 KB of LDS: chunk c of row r sits
-// at r * 128 + 16 (c ^ (r / 2 % 8)), so that the 16 rows a quarter wave reads hit all 64 banks.  The LDS
-// serves a wave's accesses in order, so consecutive pieces share the 2 KB without waiting for each other;
-// the empty asm statements keep the compiler from exchanging a lane's read with another lane's write.
+// One piece of 16 rows x 128 bytes from load order (a: rows 0 .. 7, b: rows 8 .. 15, lane l holding chunk
+// l % 8 of row l / 8) into operand order (row l % 16, the chunks that lane group l / 16 multiplies) through
+// the wave's own 2 KB of LDS: chunk c of row r sits at r * 128 + 16 (c ^ (r / 2 % 8)), so that the 16 rows
+// a quarter wave reads hit all 64 banks.  The LDS serves a wave's accesses in order, so consecutive pieces
+// share the 2 KB without waiting for each other; the empty asm statements keep the compiler from
+// exchanging a lane's read with another lane's write.
+// NEIGHBOURS: lane group g takes chunks 2 g and 2 g + 1 (16-bit elements), otherwise g and 4 + g (bytes).
+template <bool NEIGHBOURS>
 struct Regroup {
-    uint8_t *wlo, *whi;                               // where this lane's two loaded chunks go
-    const uint8_t *r0, *r1;                           // where its two operand chunks are
+    uint8_t *lds;
+    uint32_t put, get;                                // offsets of the first chunk a lane writes / reads
+    __device__ __forceinline__ Regroup(uint8_t *lds_, uint32_t own, int lane) : lds(lds_) {
+        const int row = lane >> 3, r16 = lane & 15, g = lane >> 4;
+        put = own + row * 128 + (((lane & 7) ^ (row >> 1)) << 4);
+        get = own + r16 * 128 + (((NEIGHBOURS ? 2 * g : g) ^ (r16 >> 1)) << 4);
+    }
     __device__ __forceinline__ void run(u32x4 &a, u32x4 &b) const {
-        *reinterpret_cast<u32x4 *>(wlo) = a;
-        *reinterpret_cast<u32x4 *>(whi) = b;
+        *reinterpret_cast<u32x4 *>(lds + put) = a;
+        *reinterpret_cast<u32x4 *>(lds + ((put ^ 64u) + 1024u)) = b;      // row + 8: the swizzle's top bit flips
         asm volatile("" ::: "memory");
-        a = *reinterpret_cast<const u32x4 *>(r0);
-        b = *reinterpret_cast<const u32x4 *>(r1);
+        a = *reinterpret_cast<const u32x4 *>(lds + get);
+        b = *reinterpret_cast<const u32x4 *>(lds + (get ^ (NEIGHBOURS ? 16u : 64u)));
         asm volatile("" ::: "memory");
     }
 };
 
-// Activations of one K-step for 16 tokens (32 bytes per lane); zero outside M and K.
+// Activations of one K-step for 16 tokens (128 bytes per token: 64 FP16 or 128 E4M3 values), in load order;
+// zero outside M and K.  They take the same way as row-major weights: in operand order a workgroup's
+// 16 x K gather, 16 bytes of 16 rows at a time, cost 0.4-1 us per launch at 16 tokens.
 template <int KIND>
-__device__ __forceinline__ void load_x(u32x4 &xa, u32x4 &xb, const SmallParams &p, int m, int k) {
+__device__ __forceinline__ void load_x(u32x4 &xa, u32x4 &xb, const SmallParams &p, int m, int kb) {
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    bool row_ok = m < p.M;
-    if (kind_is_fp8(KIND)) {
-        // same column order as the weight operand: 16 columns of each 64-column half
-        const uint8_t *src = p.X + (int64_t)m * p.x_row_bytes + k;
-        xa = (row_ok && k < p.K) ? *reinterpret_cast<const u32x4 *>(src) : zero;
-        xb = (row_ok && (k + 64) < p.K) ? *reinterpret_cast<const u32x4 *>(src + 64) : zero;
-    } else {
-        const uint8_t *src = p.X + (int64_t)m * p.x_row_bytes + 2 * (int64_t)k;
-        bool ok = row_ok && k < p.K;
-        xa = ok ? *reinterpret_cast<const u32x4 *>(src) : zero;
-        xb = ok ? *reinterpret_cast<const u32x4 *>(src + 16) : zero;
-    }
+    const bool ok = kb < p.K * (kind_is_fp8(KIND) ? 1 : 2);
+    const uint8_t *src = p.X + (int64_t)m * p.x_row_bytes + kb;
+    xa = ok && m < p.M ? *reinterpret_cast<const u32x4 *>(src) : zero;
+    xb = ok && m + 8 < p.M ? *reinterpret_cast<const u32x4 *>(src + 8 * p.x_row_bytes) : zero;
 }
 
 __device__ __forceinline__ half8 as_half8(const u32x4 &v) {
@@ -245,7 +245,7 @@ struct FetchTile<KIND, SPW, POL, SPW> {
 template <int KIND, int MT, int SPW, bool MULTIPASS, int POL>
 __global__ void __launch_bounds__((MT == 4 || SPW == 8) ? 512 : 1024)
 small_gemm_kernel(SmallParams p) {
-    extern __shared__ float lds[];                    // [tile][wave][MT][64] x float4, then (row-major kinds) 2 KB per wave
+    extern __shared__ float lds[];                    // [tile][wave][MT][64] x float4, then 2 KB per wave
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int waves = blockDim.x >> 6;
@@ -284,15 +284,9 @@ small_gemm_kernel(SmallParams p) {
     u32x4 xa[SPW][MT], xb[SPW][MT];
     uint32_t voff = 0;
     bool va[SPW], vb[SPW];                            // packed: this lane's columns of step s lie inside K; row-major: va, of piece s
-    Regroup rg;
-    if (!L::PACKED) {
-        uint8_t *own = reinterpret_cast<uint8_t *>(slots + ((T + 1) & ~1) * waves * MT * 64) + wave * 2048;
-        const int wr = lane >> 3;                     // (row >> 1) & 7 of rows wr and 8 + wr: wr / 2, wr / 2 + 4
-        rg.wlo = own + wr * 128 + (((lane & 7) ^ (wr >> 1)) << 4);
-        rg.whi = own + (8 + wr) * 128 + (((lane & 7) ^ (4 + (wr >> 1))) << 4);
-        rg.r0 = own + r16 * 128 + ((L::c0(g) ^ (r16 >> 1)) << 4);
-        rg.r1 = own + r16 * 128 + ((L::c1(g) ^ (r16 >> 1)) << 4);
-    }
+    const uint32_t own = (uint32_t)(((T + 1) & ~1) * waves * MT * 1024 + wave * 2048);     // behind the slots
+    const Regroup<!kind_is_fp8(KIND)> rx(reinterpret_cast<uint8_t *>(lds), own, lane);
+    const Regroup<KIND == kPlainF16> rw(reinterpret_cast<uint8_t *>(lds), own, lane);
 
     auto fetch = [&](WItem (&w)[SPW], int tile) {
         // past the last tile every lane is sent out of range
@@ -305,12 +299,12 @@ small_gemm_kernel(SmallParams p) {
         if constexpr (!L::PACKED) {
             if constexpr (kind_is_nested(KIND)) {
 #pragma unroll
-                for (int s = 0; s < SPW; s += 2) rg.run(w[s].a, w[s + 1].a);
+                for (int s = 0; s < SPW; s += 2) rw.run(w[s].a, w[s + 1].a);
 #pragma unroll
-                for (int s = 0; s < SPW; s += 2) rg.run(w[s].b, w[s + 1].b);
+                for (int s = 0; s < SPW; s += 2) rw.run(w[s].b, w[s + 1].b);
             } else {
 #pragma unroll
-                for (int s = 0; s < SPW; ++s) rg.run(w[s].a, w[s].b);
+                for (int s = 0; s < SPW; ++s) rw.run(w[s].a, w[s].b);
             }
         }
 #pragma unroll
@@ -406,11 +400,18 @@ small_gemm_kernel(SmallParams p) {
                 }
             }
         } else {
+            // (the first weights travel while the activations are regrouped)
 #pragma unroll
             for (int s = 0; s < SPW; ++s)
 #pragma unroll
-                for (int i = 0; i < MT; ++i) load_x<KIND>(xa[s][i], xb[s][i], p, 16 * i + r16, k_wave + s * KSTEP);
+                for (int i = 0; i < MT; ++i)
+                    load_x<KIND>(xa[s][i], xb[s][i], p, 16 * i + (lane >> 3),
+                                 (k_slice + s * KSTEP) * (kind_is_fp8(KIND) ? 1 : 2) + (lane & 7) * 16);
             fetch(buf0, 0);
+#pragma unroll
+            for (int s = 0; s < SPW; ++s)
+#pragma unroll
+                for (int i = 0; i < MT; ++i) rx.run(xa[s][i], xb[s][i]);
         }
         // The scheduling barriers keep the compiler from sinking the look-ahead loads below the
         // multiplies (which would turn every wait into a full drain).  For odd T the last
@@ -714,7 +715,7 @@ static void launch_small_t(const SmallParams &p, const SmallConfig &c, dim3 grid
         }
     }
     size_t lds = (size_t)((c.tiles_per_wg + 1) & ~1) * c.waves * MT * 64 * sizeof(floatx4) +
-                 (kind_is_packed(KIND) ? 0 : (size_t)c.waves * 2048);
+                 (size_t)c.waves * 2048;
     auto kern1 = small_gemm_kernel<KIND, MT, SPW, false, POL>;
     auto kernp = small_gemm_kernel<KIND, MT, SPW, true, POL>;
     static std::atomic<bool> attr_set{false};                    // once per instantiation
