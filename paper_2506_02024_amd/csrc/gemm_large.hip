@@ -93,6 +93,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const uint8_t *base,
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(base + row0 * row_bytes), 0, bytes, 0x00020000);
 }
 
+// The K loops load a few K-tiles ahead.  Past the end of a workgroup's K-slice those loads are sent out of
+// range like the ones past K: nobody uses them, and a slice of 16 K-tiles would otherwise fetch 2 to 4
+// of the next slice's as well.  Returns the slice's end in bytes of a row of tokens (128 per K-tile).
+__device__ __forceinline__ uint32_t slice_end(const LargeParams &p, int kt_end) {
+    return (uint32_t)min((int64_t)p.k_bytes, (int64_t)kt_end * 128);
+}
+
 // raw buffer over the 16-row tiles of a packed plane (blocks of block_bytes) that hold rows row0 .. row0+rows-1
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const uint8_t *base, int64_t row0, int rows, int kblocks,
                                                              int block_bytes) {
@@ -461,8 +468,9 @@ struct LargeKernel {
             : tile_rsrc(p.W0, n0, min(TN, p.N - n0), p.w_row_bytes, p.k_bytes);
         DmaOffsets dof;
         make_dma_offsets(dof, p, wave, lane);
-        const uint32_t x_lim = (uint32_t)p.k_bytes;
-        const uint32_t w_lim = PACKED_W ? (uint32_t)p.kblocks : (uint32_t)p.k_bytes;
+        // (no load ahead of the K loop reaches into the next slice of a split: see slice_end)
+        const uint32_t x_lim = slice_end(p, kt_end);
+        const uint32_t w_lim = PACKED_W ? (uint32_t)min(p.kblocks, 2 * kt_end) : x_lim;
 
         // NST LDS stages; tokens and weights go straight from global memory into LDS.
         if (wave < DW) {
@@ -514,8 +522,8 @@ large_gemm_kernel(LargeParams p) {
 // Eight waves side by side along the weight rows: a wave owns TN/8 weight rows and all TM tokens
 // of the tile, so every weight is needed by exactly one wave.  The wave loads 16 bytes of each
 // plane per lane straight into registers (lane l: row l % 16, columns 16 * (l / 16) .. +15 of a
-// 64-column block -- 16 rows x 64 bytes per instruction from row-major planes, one contiguous
-// kilobyte from packed ones), merges them there (Sec. 4.2, Alg. 1) and feeds the result to the MFMA
+// 64-column block -- one contiguous kilobyte per instruction from packed planes; row-major ones by
+// 128-byte pieces of 8 rows, regrouped through LDS, see PAIR), merges them there (Sec. 4.2, Alg. 1) and feeds the result to the MFMA
 // as it is (WK = kPlainF16Packed: FP16 weights in packed blocks, no merge): the sum over k
 // does not care about the order of k, so substep s of a K-tile takes columns 16 g + 8 s .. + 7
 // from lane group g, and the token fragments are read from LDS in the same order (chunk
@@ -534,7 +542,12 @@ struct BypassKernel {
     // instruction) are then marked non-temporal, as in the streaming kernel.  The 64-token tiles always
     // are; the 128-token tiles on the large layers (timed: 6-10 % faster from about 100 Mi weights on at
     // M = 96 and 128, a few per cent slower on the small ones).
-    static constexpr int POLICY = (!ROWMAJOR && (NT || TM == 64)) ? 2 : 0;
+    static constexpr int POLICY = (NT || (!ROWMAJOR && TM == 64)) ? 2 : 0;
+    // PAIR: row-major planes are fetched for two K-tiles at a time, 128 bytes of 8 rows per instruction, and
+    // regrouped through 2 KB of LDS per wave one K-tile before the first of the two is merged.  Fetched
+    // for one K-tile, 64 bytes of 16 rows per instruction, every line is requested twice: (28672, 5120) at 48
+    // tokens took 80 us against 57 from packed planes.  (A wave with 32 weight rows has no registers for it.)
+    static constexpr bool PAIR = ROWMAJOR && TN == 128;
     static constexpr int BLOCK_BYTES = 1024 * kind_elem_bytes(WK);   // packed kinds: one 16 x 64 block
     typedef TileStore<kNestedF16, TM, TN, 1, 8> Store;
     static constexpr int DW = 4;                               // waves that issue the token loads
@@ -545,11 +558,14 @@ struct BypassKernel {
     // no faster for the 64-token tiles)
     static constexpr int NST = DEEP ? 8 : 4;                   // LDS stages of the token tile
     static constexpr int XA = DEEP ? 6 : 3;                    // token loads run this many K-tiles ahead
-    static constexpr int NRAW = DEEP ? 4 : 2;                  // plane blocks are loaded this many K-tiles ahead
-    static_assert(XA >= 3 && XA < NST && NRAW <= XA && NRAW >= 2, "the stage being filled is neither the one in use nor the next");
+        static constexpr int NRAW = DEEP || PAIR ? 4 : 2;          // register sets of plane blocks, one K-tile each: loaded this many K-tiles ahead
+    static_assert(XA >= 3 && XA < NST && (NRAW <= XA || PAIR) && NRAW >= 2, "the stage being filled is neither the one in use nor the next");
     static_assert(NST * TM * 128 <= 160 * 1024, "LDS stages");
     static constexpr int STAGE = TM * 128;
-    static constexpr int LDS_BYTES = NST * STAGE > TM * TN * 2 ? NST * STAGE : TM * TN * 2;
+    static constexpr int RING_BYTES = NST * STAGE > TM * TN * 2 ? NST * STAGE : TM * TN * 2;
+    static constexpr int LDS_BYTES = RING_BYTES + (PAIR ? 8 * 2048 : 0);     // (behind the ring: 2 KB per wave to regroup in)
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+    static constexpr int RGS = FMB / 2;                        // PAIR: slots between the 2 FNB regroupings of a pair
     static constexpr int XG = TM / 8 / DW;                     // loads per loading wave per K-tile
     static constexpr int LEAD = 2;                             // token fragments are read this many blocks ahead
     static constexpr int NMQ = 2 * FNB;                        // merges of four weights per substep
@@ -573,6 +589,7 @@ struct BypassKernel {
         lds_byte *lds3;
         int wave, lane;
         int kt, st;                                            // K-tile, its LDS stage
+        const Regroup<false> &rg;                              // PAIR
     };
 
     template <int J>
@@ -592,6 +609,27 @@ struct BypassKernel {
             if (MERGE) r.l[i] = __builtin_amdgcn_raw_buffer_load_b128(c.rw1, off, 0, POLICY);
             else r.l[i] = __builtin_amdgcn_raw_buffer_load_b128(c.rw0, off + 1024u, 0, POLICY);
         }
+    }
+
+    // PAIR: both planes of K-tiles kt and kt + 1 in load order, rows 0 .. 7 of a tile in r0, 8 .. 15 in r1
+    static __device__ __forceinline__ void load_pair(Raw &r0, Raw &r1, const Ctx &c, int kt) {
+        const uint32_t kill = ((uint32_t)kt * 64u + c.w_kpos < c.w_lim) ? 0u : 0x80000000u;
+        const uint32_t half = c.w_istep >> 1;                  // 8 rows
+#pragma unroll
+        for (int i = 0; i < FNB; ++i) {
+            const uint32_t off = (c.w_off + (uint32_t)i * c.w_istep + (uint32_t)kt * 64u) | kill;
+            r0.u[i] = __builtin_amdgcn_raw_buffer_load_b128(c.rw0, off, 0, POLICY);
+            r1.u[i] = __builtin_amdgcn_raw_buffer_load_b128(c.rw0, off + half, 0, POLICY);
+            r0.l[i] = __builtin_amdgcn_raw_buffer_load_b128(c.rw1, off, 0, POLICY);
+            r1.l[i] = __builtin_amdgcn_raw_buffer_load_b128(c.rw1, off + half, 0, POLICY);
+        }
+    }
+
+    // ... and into operand order, r0 for K-tile kt and r1 for kt + 1; J: row tile and plane
+    template <int J>
+    static __device__ __forceinline__ void regroup(Raw &r0, Raw &r1, const Ctx &c) {
+        if constexpr (J < FNB) c.rg.run(r0.u[J], r1.u[J]);
+        else c.rg.run(r0.l[J - FNB], r1.l[J - FNB]);
     }
 
     // four weights of row tile I: dwords H (substep 0) or 2 + H (substep 1) of the lane's chunk of
@@ -639,7 +677,13 @@ struct BypassKernel {
             else merge_part<0, m / 2, m % 2>(c.a[0][m / 2], c.raw[(PAR + 1) % NRAW]);
         }
         if constexpr (OLDER && S == 0 && Q % DQS == 0) dma_x(c, Q / DQS, c.kt + XA);
-        if constexpr (S == 1 && Q == 0) load_raw(c.raw[PAR], c, c.kt + NRAW);  // its blocks are merged
+        if constexpr (!PAIR) {
+            if constexpr (S == 1 && Q == 0) load_raw(c.raw[PAR], c, c.kt + NRAW);  // its blocks are merged
+        } else if constexpr (PAR % 2 == 1) {
+            // second K-tile of a pair: the next pair has landed, this one is merged
+            if constexpr (S == 0 && Q % RGS == 0 && Q / RGS < 2 * FNB) regroup<Q / RGS>(c.raw[(PAR + 1) % NRAW], c.raw[(PAR + 2) % NRAW], c);
+            if constexpr (S == 1 && Q == 0) load_pair(c.raw[PAR - 1], c.raw[PAR], c, c.kt - 1 + NRAW);
+        }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (Q + 1 < MF) slot<OLDER, S, PAR, Q + 1>(c);
     }
@@ -652,8 +696,11 @@ struct BypassKernel {
         // The token loads of K-tile kt+2 (issued during kt+2-XA) must have landed before anybody
         // reads them (from the tail of kt+1 on).  Younger than them in this wave, and allowed to
         // be in flight: the plane loads of that K-tile and all loads of the XA-2 K-tiles since
-        // (for XA = 3 the count is rounded down to this K-tile's loads).
-        if constexpr (OLDER) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(XA == 3 ? XG + 2 * FNB : 2 * FNB + (XA - 2) * (XG + 2 * FNB)) : "memory");
+        // (for XA = 3 the count is rounded down to this K-tile's loads).  PAIR: 4 FNB plane loads at the end of
+        // every second K-tile, which fall on XA / 2 of the XA - 1 K-tiles since, or one less.
+        constexpr int kInFlight = PAIR ? (XA - 2) * XG + ((XA - 1 + (PAR & 1)) / 2) * 4 * FNB
+                                       : (XA == 3 ? XG + 2 * FNB : 2 * FNB + (XA - 2) * (XG + 2 * FNB));
+        if constexpr (OLDER) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kInFlight) : "memory");
         // a bare barrier: __syncthreads() carries a release fence, which would drain the token loads
         // issued in this K-tile.  What the fence would order is ordered by the wait above (loads
         // that have to be visible) and by the MFMAs, which have consumed every LDS read of the
@@ -668,8 +715,15 @@ struct BypassKernel {
         // no branch inside the loop body: the compiler then counts the loads in flight exactly
         // instead of draining them at the loop head
         int kt = kt_begin;
-        for (; kt + NRAW <= kt_end; kt += NRAW) k_tiles<OLDER, 0, NRAW>(c, kt);
-        tail<OLDER, 0>(c, kt, kt_end);
+        if constexpr (PAIR) {
+            // whole pairs: the second K-tile of the last one may lie past the slice, where tokens and weights
+            // are zero.  (A tail of 1 .. 3 single K-tiles cost registers that the loop spilled.)
+            for (; kt + NRAW - 2 < kt_end; kt += NRAW) k_tiles<OLDER, 0, NRAW>(c, kt);
+            pair_tail<OLDER, 0>(c, kt, kt_end);
+        } else {
+            for (; kt + NRAW <= kt_end; kt += NRAW) k_tiles<OLDER, 0, NRAW>(c, kt);
+            tail<OLDER, 0>(c, kt, kt_end);
+        }
     }
 
     // K-tiles kt + P .. kt + END - 1, on register sets P .. END - 1
@@ -681,7 +735,18 @@ struct BypassKernel {
         if constexpr (P + 1 < END) k_tiles<OLDER, P + 1, END>(c, kt);
     }
 
-    // the last 0 .. NRAW - 1 K-tiles
+    // the last 0 .. NRAW / 2 - 1 pairs
+    template <bool OLDER, int P>
+    static __device__ __forceinline__ void pair_tail(Ctx &c, int kt, int kt_end) {
+        if constexpr (P + 2 < NRAW) {
+            if (kt + P < kt_end) {
+                k_tiles<OLDER, P, P + 2>(c, kt);
+                pair_tail<OLDER, P + 2>(c, kt, kt_end);
+            }
+        }
+    }
+
+    // the last 0 .. NRAW - 1 K-tiles (not PAIR)
     template <bool OLDER, int P>
     static __device__ __forceinline__ void tail(Ctx &c, int kt, int kt_end) {
         if constexpr (P + 1 < NRAW) {
@@ -710,29 +775,31 @@ struct BypassKernel {
             for (int j = 0; j < FMB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
         intx4 a[2][FNB], b[2][FMB];
         Raw raw[NRAW];
+        const Regroup<false> rg(lds, (uint32_t)(RING_BYTES + wave * 2048), lane);
         const int w_rows = min(TN, p.N - n0);
         Ctx c{acc, a, b, raw,
               tile_rsrc(p.X, m0, min(TM, p.M - m0), p.x_row_bytes, p.k_bytes),
               ROWMAJOR ? tile_rsrc(p.W0, n0, w_rows, p.w_row_bytes, p.K) : plane_rsrc(p.W0, n0, w_rows, p.kblocks, BLOCK_BYTES),
               ROWMAJOR ? tile_rsrc(p.W1, n0, w_rows, p.w_row_bytes, p.K)
                        : plane_rsrc(MERGE ? p.W1 : p.W0, n0, w_rows, p.kblocks, BLOCK_BYTES),
-              0u, (uint32_t)(DW * 8) * (uint32_t)p.x_row_bytes, 0u, (uint32_t)p.k_bytes, 0u, 0u, 0u, 0u, lds, lds3, wave, lane,
-              kt_begin, 0};
+              0u, (uint32_t)(DW * 8) * (uint32_t)p.x_row_bytes, 0u, slice_end(p, kt_end), 0u, 0u, 0u, 0u, lds, lds3, wave, lane,
+              kt_begin, 0, rg};
         {
             const int pc = lane & 7;
             const int ch = fp16_chunk_of_slot(pc ^ ((((wave & 1) << 2) + (lane >> 4)) & 7));   // (row >> 1) & 7 for row = gid*8 + lane/8
             c.x_kpos = 16u * ch;
             c.x_off = (uint32_t)(wave * 8 + (lane >> 3)) * (uint32_t)p.x_row_bytes + 16u * ch;
             if (ROWMAJOR) {
-                c.w_off = (uint32_t)(FNB * wave * 16 + (lane & 15)) * (uint32_t)p.w_row_bytes + 16u * (uint32_t)(lane >> 4);
+                const uint32_t row = PAIR ? lane >> 3 : lane & 15, chunk = PAIR ? lane & 7 : lane >> 4;
+                c.w_off = (uint32_t)(FNB * wave * 16 + row) * (uint32_t)p.w_row_bytes + 16u * chunk;
                 c.w_istep = 16u * (uint32_t)p.w_row_bytes;
-                c.w_kpos = 16u * (uint32_t)(lane >> 4);
-                c.w_lim = (uint32_t)p.K;
+                c.w_kpos = 16u * chunk;
+                c.w_lim = slice_end(p, kt_end) >> 1;
             } else {
                 c.w_off = (uint32_t)(FNB * wave * p.kblocks) * (uint32_t)BLOCK_BYTES + (uint32_t)lane * 16u;
                 c.w_istep = (uint32_t)p.kblocks * (uint32_t)BLOCK_BYTES;
                 c.w_kpos = 0u;
-                c.w_lim = (uint32_t)p.kblocks * 64u;
+                c.w_lim = (uint32_t)min(p.kblocks, kt_end) * 64u;
             }
         }
         // token tiles of the first XA K-tiles, plane blocks of the first NRAW
@@ -743,9 +810,20 @@ struct BypassKernel {
                 for (int i = 0; i < XG; ++i) dma_x(c, i, kt_begin + d);
         }
 #pragma unroll
-        for (int d = 0; d < NRAW; ++d) load_raw(raw[d], c, kt_begin + d);
+        for (int d = 0; d < NRAW; ++d) {
+            if constexpr (!PAIR) load_raw(raw[d], c, kt_begin + d);
+            else if (d % 2 == 0) load_pair(raw[d], raw[d + 1], c, kt_begin + d);
+        }
         // (in order: once the first plane blocks are here, the token loads issued before them are too)
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NRAW - 1) * 2 * FNB) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PAIR ? 4 * FNB : (NRAW - 1) * 2 * FNB) : "memory");
+        if constexpr (PAIR) {
+            regroup<0>(raw[0], raw[1], c);
+            regroup<1>(raw[0], raw[1], c);
+            if constexpr (FNB > 1) {
+                regroup<2>(raw[0], raw[1], c);
+                regroup<3>(raw[0], raw[1], c);
+            }
+        }
         merge_part<0, 0, 0>(a[0][0], raw[0]);
         merge_part<0, 0, 1>(a[0][0], raw[0]);
         if constexpr (FNB > 1) {
@@ -795,7 +873,10 @@ nested_bypass_kernel(LargeParams p) {
 // bytes, which is one operand of v_mfma_f32_16x16x128_f8f6f4, and reads the same bytes of its token
 // (chunks g and 4 + g of the row).  A token block's fragment of K-tile kt + 1 is read right behind
 // the block's MFMAs of K-tile kt, into the same registers.
-template <int TM, int TN, bool ROWMAJOR>
+// Row-major planes: a K-tile's 128 bytes of 16 rows are fetched as 128 bytes of 8 rows per instruction and
+// regrouped through 2 KB of LDS per wave during the K-tile before (see Regroup); NT: the rows start on
+// lines, which are then read once and marked non-temporal.
+template <int TM, int TN, bool ROWMAJOR, bool NT = false>
 struct E4m3BypassKernel {
     typedef TileStore<kE4M3, TM, TN, 1, 8, 16> Store;
     static constexpr int DW = 4;                               // waves that issue the token loads
@@ -805,13 +886,14 @@ struct E4m3BypassKernel {
     static constexpr int XA = 6;                               // token loads run this many K-tiles ahead
     static constexpr int NRAW = 4;                             // plane blocks are loaded this many K-tiles ahead
     static constexpr int STAGE = TM * 128;
-    static constexpr int LDS_BYTES = NST * STAGE > TM * TN * 2 ? NST * STAGE : TM * TN * 2;
+    static constexpr int RING_BYTES = NST * STAGE > TM * TN * 2 ? NST * STAGE : TM * TN * 2;
+    static constexpr int LDS_BYTES = RING_BYTES + (ROWMAJOR ? 8 * 2048 : 0);
     static constexpr int XG = TM / 8 / DW;                     // loads per loading wave per K-tile
     static_assert(XG >= 1 && FNB >= 1 && FNB <= 2, "tile shape");
     static_assert(XA >= 3 && XA < NST && NRAW <= XA, "the stage being filled is neither the one in use nor the next");
     typedef __attribute__((address_space(3))) uint8_t lds_byte;
 
-    static constexpr int POLICY = (!ROWMAJOR && TM == 64) ? 2 : 0;   // packed blocks, read once per launch: non-temporal
+    static constexpr int POLICY = (NT || (!ROWMAJOR && TM == 64)) ? 2 : 0;   // whole lines, read once per launch: non-temporal
     struct Raw { intx4 u[FNB][2]; };                           // one K-tile of the wave's plane blocks
     struct Tok { intx4 q[FMB][2]; };                           // one K-tile of token fragments
 
@@ -826,16 +908,38 @@ struct E4m3BypassKernel {
         lds_byte *lds3;
         int wave, lane;
         int kt;
+        const Regroup<false> &rg;                              // row-major planes
     };
 
+    // row-major: rows 0 .. 7 / 8 .. 15 of the 16 into u[i][0] / u[i][1]
+    static __device__ __forceinline__ void regroup(Raw &r, const Ctx &c) {
+#pragma unroll
+        for (int i = 0; i < FNB; ++i) {
+            u32x4 a = __builtin_bit_cast(u32x4, r.u[i][0]), b = __builtin_bit_cast(u32x4, r.u[i][1]);
+            c.rg.run(a, b);
+            r.u[i][0] = __builtin_bit_cast(intx4, a);
+            r.u[i][1] = __builtin_bit_cast(intx4, b);
+        }
+    }
+
     static __device__ __forceinline__ void load_raw(Raw &r, const Ctx &c, int kt) {
+        if constexpr (ROWMAJOR) {
+            const uint32_t kill = ((uint32_t)kt * 128u + c.w_kpos < c.w_lim) ? 0u : 0x80000000u;
+#pragma unroll
+            for (int i = 0; i < FNB; ++i) {
+                const uint32_t off = (c.w_off + (uint32_t)i * c.w_istep + (uint32_t)kt * 128u) | kill;
+                r.u[i][0] = __builtin_bit_cast(intx4, __builtin_amdgcn_raw_buffer_load_b128(c.rw, off, 0, POLICY));
+                r.u[i][1] = __builtin_bit_cast(intx4, __builtin_amdgcn_raw_buffer_load_b128(c.rw, off + (c.w_istep >> 1), 0, POLICY));
+            }
+            return;
+        }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const uint32_t kill = ((uint32_t)(2 * kt + h) * 64u + c.w_kpos < c.w_lim) ? 0u : 0x80000000u;
 #pragma unroll
             for (int i = 0; i < FNB; ++i)
                 r.u[i][h] = __builtin_bit_cast(intx4, __builtin_amdgcn_raw_buffer_load_b128(
-                    c.rw, (c.w_off + (uint32_t)i * c.w_istep + (uint32_t)(2 * kt + h) * (ROWMAJOR ? 64u : 1024u)) | kill, 0, POLICY));
+                    c.rw, (c.w_off + (uint32_t)i * c.w_istep + (uint32_t)(2 * kt + h) * 1024u) | kill, 0, POLICY));
         }
     }
 
@@ -873,6 +977,7 @@ struct E4m3BypassKernel {
 #pragma unroll
             for (int i = 0; i < XG; ++i) dma_x(c, i, c.kt + XA);
         }
+        if constexpr (ROWMAJOR) regroup(c.raw[(PAR + 1) % NRAW], c);
         block<0>(c, c.raw[PAR], c.lds + ((c.kt + 1) & (NST - 1)) * STAGE);
         load_raw(c.raw[PAR], c, c.kt + NRAW);                  // its blocks are used up
         // The token loads of K-tile kt+2 (issued during kt+2-XA) must have landed before anybody
@@ -932,26 +1037,27 @@ struct E4m3BypassKernel {
             for (int j = 0; j < FMB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
         Raw raw[NRAW];
         Tok tok;
+        const Regroup<false> rg(lds, (uint32_t)(RING_BYTES + wave * 2048), lane);
         const int w_rows = min(TN, p.N - n0);
         Ctx c{acc, raw, tok,
               tile_rsrc(p.X, m0, min(TM, p.M - m0), p.x_row_bytes, p.k_bytes),
               ROWMAJOR ? tile_rsrc(p.W0, n0, w_rows, p.w_row_bytes, p.K) : plane_rsrc(p.W0, n0, w_rows, p.kblocks, 1024),
-              0u, (uint32_t)(DW * 8) * (uint32_t)p.x_row_bytes, 0u, (uint32_t)p.k_bytes, 0u, 0u, 0u, 0u, lds, lds3, wave, lane,
-              kt_begin};
+              0u, (uint32_t)(DW * 8) * (uint32_t)p.x_row_bytes, 0u, slice_end(p, kt_end), 0u, 0u, 0u, 0u, lds, lds3, wave, lane,
+              kt_begin, rg};
         {
             const int ch = (lane & 7) ^ ((((wave & 1) << 2) + (lane >> 4)) & 7);    // (row >> 1) & 7 for row = gid*8 + lane/8
             c.x_kpos = 16u * ch;
             c.x_off = (uint32_t)(wave * 8 + (lane >> 3)) * (uint32_t)p.x_row_bytes + 16u * ch;
             if (ROWMAJOR) {
-                c.w_off = (uint32_t)(FNB * wave * 16 + (lane & 15)) * (uint32_t)p.w_row_bytes + 16u * (uint32_t)(lane >> 4);
+                c.w_off = (uint32_t)(FNB * wave * 16 + (lane >> 3)) * (uint32_t)p.w_row_bytes + 16u * (uint32_t)(lane & 7);
                 c.w_istep = 16u * (uint32_t)p.w_row_bytes;
-                c.w_kpos = 16u * (uint32_t)(lane >> 4);
-                c.w_lim = (uint32_t)p.K;
+                c.w_kpos = 16u * (uint32_t)(lane & 7);
+                c.w_lim = slice_end(p, kt_end);
             } else {
                 c.w_off = (uint32_t)(FNB * wave * p.kblocks) * 1024u + (uint32_t)lane * 16u;
                 c.w_istep = (uint32_t)p.kblocks * 1024u;
                 c.w_kpos = 0u;
-                c.w_lim = (uint32_t)p.kblocks * 64u;
+                c.w_lim = (uint32_t)min(p.kblocks, 2 * kt_end) * 64u;
             }
         }
         // token tiles of the first XA K-tiles, plane blocks of the first NRAW
@@ -967,6 +1073,7 @@ struct E4m3BypassKernel {
         // and the plane loads has landed
         if (wave < DW) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((XA - 2) * XG + NRAW * 2 * FNB) : "memory");
         __syncthreads();
+        if constexpr (ROWMAJOR) regroup(raw[0], c);
         {
             const uint8_t *st0 = lds + (kt_begin & (NST - 1)) * STAGE;
             read_tok<0>(tok, st0, lane);
@@ -990,11 +1097,11 @@ struct E4m3BypassKernel {
     }
 };
 
-template <int TM, int TN, bool ROWMAJOR>
+template <int TM, int TN, bool ROWMAJOR, bool NT>
 __global__ void __launch_bounds__(512)
 e4m3_bypass_kernel(LargeParams p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
-    typedef E4m3BypassKernel<TM, TN, ROWMAJOR> Kern;
+    typedef E4m3BypassKernel<TM, TN, ROWMAJOR, NT> Kern;
     Kern::run(p, lds_raw, (typename Kern::lds_byte *)lds_raw);
 }
 
@@ -1163,6 +1270,13 @@ static void launch_large_t(const LargeParams &p, dim3 grid, hipStream_t stream) 
     kern<<<grid, 64 * WAVES_M * WAVES_N, lds, stream>>>(p);
 }
 
+// Row-major planes that are read once (one token tile) and whose rows start on 128-byte lines are marked
+// non-temporal like packed ones; where two pieces share a line it has to stay in L2.
+static bool streams_rows(const LargeParams &p) {
+    return p.tiles_m == 1 && (p.w_row_bytes & 127) == 0 && (reinterpret_cast<uintptr_t>(p.W0) & 127) == 0 &&
+           (reinterpret_cast<uintptr_t>(p.W1) & 127) == 0;
+}
+
 template <int TM, int TN, int WK, bool DEEP = false, bool NT = false>
 static void launch_bypass(const LargeParams &p, dim3 grid, hipStream_t stream) {
     auto kern = nested_bypass_kernel<TM, TN, WK, DEEP, NT>;
@@ -1175,10 +1289,16 @@ static void launch_bypass(const LargeParams &p, dim3 grid, hipStream_t stream) {
     kern<<<grid, 512, lds, stream>>>(p);
 }
 
-template <int TM, int TN, bool ROWMAJOR>
+template <int TM, int TN, bool ROWMAJOR, bool NT = false>
 static void launch_e4m3_bypass(const LargeParams &p, dim3 grid, hipStream_t stream) {
-    auto kern = e4m3_bypass_kernel<TM, TN, ROWMAJOR>;
-    constexpr int lds = E4m3BypassKernel<TM, TN, ROWMAJOR>::LDS_BYTES;
+    if constexpr (ROWMAJOR && !NT) {
+        if (streams_rows(p)) {
+            launch_e4m3_bypass<TM, TN, ROWMAJOR, true>(p, grid, stream);
+            return;
+        }
+    }
+    auto kern = e4m3_bypass_kernel<TM, TN, ROWMAJOR, NT>;
+    constexpr int lds = E4m3BypassKernel<TM, TN, ROWMAJOR, NT>::LDS_BYTES;
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1209,13 +1329,15 @@ static void launch_large_k(const LargeParams &p, const LargeConfig &c, dim3 grid
 // weights through registers: NestedFP16 in either storage order, packed FP16
 template <int WK>
 static void launch_nested(const LargeParams &p, const LargeConfig &c, dim3 grid, hipStream_t stream) {
-    if (c.tm == 64) launch_bypass<64, 128, WK>(p, grid, stream);
-    else if (c.tm == 256 && c.tn == 256) launch_bypass<256, 256, WK>(p, grid, stream);
+    if (c.tm == 64) {
+        if (WK == kNestedF16Row && streams_rows(p)) launch_bypass<64, 128, WK, false, WK == kNestedF16Row>(p, grid, stream);
+        else launch_bypass<64, 128, WK>(p, grid, stream);
+    } else if (c.tm == 256 && c.tn == 256) launch_bypass<256, 256, WK>(p, grid, stream);
     else if (c.tm == 256) launch_bypass<256, 128, WK>(p, grid, stream);
     else {
-        // one token tile over a large packed layer: weights marked non-temporal (see BypassKernel)
-        if constexpr (WK != kNestedF16Row) {
-            if (p.tiles_m == 1 && (int64_t)p.N * p.K >= ((int64_t)100 << 20)) {
+        // one token tile over a large layer: weights marked non-temporal (see BypassKernel)
+        {
+            if (p.tiles_m == 1 && (int64_t)p.N * p.K >= ((int64_t)100 << 20) && (WK != kNestedF16Row || streams_rows(p))) {
                 if (c.tn == 256) {
                     if (c.deep) launch_bypass<128, 256, WK, true, true>(p, grid, stream);
                     else launch_bypass<128, 256, WK, false, true>(p, grid, stream);

@@ -133,32 +133,6 @@ __device__ __forceinline__ void load_rows(WItem (&w)[SPW], __amdgpu_buffer_rsrc_
     }
 }
 
-// One piece of 16 rows x 128 bytes from load order (a: rows 0 .. 7, b: rows 8 .. 15, lane l holding chunk
-// l % 8 of row l / 8) into operand order (row l % 16, the chunks that lane group l / 16 multiplies) through
-// the wave's own 2 KB of LDS: chunk c of row r sits at r * 128 + 16 (c ^ (r / 2 % 8)), so that the 16 rows
-// a quarter wave reads hit all 64 banks.  The LDS serves a wave's accesses in order, so consecutive pieces
-// share the 2 KB without waiting for each other; the empty asm statements keep the compiler from
-// exchanging a lane's read with another lane's write.
-// NEIGHBOURS: lane group g takes chunks 2 g and 2 g + 1 (16-bit elements), otherwise g and 4 + g (bytes).
-template <bool NEIGHBOURS>
-struct Regroup {
-    uint8_t *lds;
-    uint32_t put, get;                                // offsets of the first chunk a lane writes / reads
-    __device__ __forceinline__ Regroup(uint8_t *lds_, uint32_t own, int lane) : lds(lds_) {
-        const int row = lane >> 3, r16 = lane & 15, g = lane >> 4;
-        put = own + row * 128 + (((lane & 7) ^ (row >> 1)) << 4);
-        get = own + r16 * 128 + (((NEIGHBOURS ? 2 * g : g) ^ (r16 >> 1)) << 4);
-    }
-    __device__ __forceinline__ void run(u32x4 &a, u32x4 &b) const {
-        *reinterpret_cast<u32x4 *>(lds + put) = a;
-        *reinterpret_cast<u32x4 *>(lds + ((put ^ 64u) + 1024u)) = b;      // row + 8: the swizzle's top bit flips
-        asm volatile("" ::: "memory");
-        a = *reinterpret_cast<const u32x4 *>(lds + get);
-        b = *reinterpret_cast<const u32x4 *>(lds + (get ^ (NEIGHBOURS ? 16u : 64u)));
-        asm volatile("" ::: "memory");
-    }
-};
-
 // Activations of one K-step for 16 tokens (128 bytes per token: 64 FP16 or 128 E4M3 values), in load order;
 // zero outside M and K.  They take the same way as row-major weights: in operand order a workgroup's
 // 16 x K gather, 16 bytes of 16 rows at a time, cost 0.4-1 us per launch at 16 tokens.

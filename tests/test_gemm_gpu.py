@@ -683,6 +683,30 @@ def test_streaming_kernel_on_row_pieces(nfp, M, N, K, knobs):
         assert_gemm_close(nfp.plain_gemm_fp16(X, Wd[:, :K]).cpu().numpy(), ref, "row stride %d" % (K + pad))
 
 
+@pytest.mark.parametrize("M,N,K,bm,bn,split,deep", [
+    (5, 17, 16, 64, 128, 1, -1), (33, 40, 64, 64, 128, 1, -1), (48, 136, 64 + 16, 64, 128, 1, -1),      # less than a pair, one K-tile, 1 1/4
+    (64, 250, 3 * 64 + 48, 64, 128, 1, -1), (60, 130, 9 * 64, 64, 128, 3, -1), (20, 264, 11 * 64 + 16, 64, 128, 2, -1),
+    (100, 200, 5 * 64, 128, 128, 1, -1), (130, 264, 7 * 128 + 32, 128, 128, 3, -1), (70, 136, 13 * 64, 128, 128, 2, 1),
+    (200, 140, 6 * 64 + 16, 256, 128, 1, -1), (257, 264, 11 * 64, 256, 128, 4, -1),
+    (130, 300, 7 * 128 + 32, 128, 256, 3, -1), (257, 264, 11 * 64, 256, 256, 2, -1),
+])
+def test_tiled_kernels_on_row_pieces_and_slice_ends(nfp, M, N, K, bm, bn, split, deep):
+    # row-major planes are fetched for two 64-column K-tiles at a time (FP8 mode: one of 128 columns):
+    # odd counts of K-tiles, slices of a split that start and end inside a pair, K inside a piece; and no
+    # kernel's look-ahead takes anything from the next slice (both plane layouts, LDS kernels included)
+    knobs = {"small_max_m": 0, "large_bm": bm, "large_bn": bn, "large_split": split, "large_deep": deep}
+    try:
+        for k, v in knobs.items():
+            nfp.tune(k, v)
+        run_both_modes(nfp, workloads.act_host(M, K, seed=N), workloads.weight_host(N, K, seed=M),
+                       "%d x %d, M=%d %s" % (N, K, M, knobs), check_plain=False)
+        X, W = workloads.act_host(M, K, seed=5), workloads.weight_host(N, K, seed=6)
+        assert_gemm_close(nfp.plain_gemm_fp16(to_dev(X), to_dev(W)).cpu().numpy(), oracle.gemm_fp16(X, W), "plain FP16")
+    finally:
+        for k in knobs:
+            nfp.tune(k, -1)
+
+
 @pytest.mark.parametrize("M,N,K,knobs", [(16, 4096 + 8, 14336, {}), (4, 300, 28672, {}),
                                          (16, 520, 4096, {"small_split": 4, "small_tiles": 2}),
                                          (40, 304, 2048 + 64, {"small_split": 3, "small_tiles": 3}),
