@@ -37,7 +37,8 @@ struct LargeParams {
     int kblocks;            // 64-column blocks per row tile of a packed plane: ceil(K / 64)
     uint16_t *Y;
     int64_t ldy;
-    float *partials;
+    float *partials;        // rows of ldp floats (see partial_ld)
+    int ldp;
     int tiles_m, tiles_n;
     int ktiles_total, ktiles_per_split;
     int vec_store;
@@ -184,12 +185,7 @@ struct TileStore {
                     if (n >= p.N) continue;
                     const float x[4] = {acc[i][j][4 * v], acc[i][j][4 * v + 1], acc[i][j][4 * v + 2], acc[i][j][4 * v + 3]};
                     if (gridDim.y > 1) {
-                        float *dst = p.partials + ((int64_t)split * p.M + m) * p.N + n;
-                        if ((p.N & 3) == 0) {
-                            *reinterpret_cast<floatx4 *>(dst) = floatx4{x[0], x[1], x[2], x[3]};
-                        } else {
-                            for (int e = 0; e < 4 && n + e < p.N; ++e) dst[e] = x[e];
-                        }
+                        *reinterpret_cast<floatx4 *>(p.partials + ((int64_t)split * p.M + m) * p.ldp + n) = floatx4{x[0], x[1], x[2], x[3]};
                     } else {
                         uint16_t *dst = p.Y + (int64_t)m * p.ldy + n;
                         if (p.vec_store) {
@@ -533,7 +529,7 @@ large_gemm_kernel(LargeParams p) {
 // DEEP: a ring of eight token stages with the token loads six and the plane loads four K-tiles ahead
 // (tiles of at most 128 tokens, launches that do not fill the chip: there a K-tile's MFMAs are
 // short against the latency of a load) instead of four stages and three / two K-tiles.
-template <int TM, int TN, int WK, bool DEEP = false, bool NT = false>
+template <int TM, int TN, int WK, bool DEEP = false, bool NT = false, bool PAIRS = false>
 struct BypassKernel {
     static_assert(WK == kNestedF16 || WK == kNestedF16Row || WK == kPlainF16Packed, "weights that go through registers");
     static constexpr bool MERGE = kind_is_nested(WK);
@@ -546,8 +542,11 @@ struct BypassKernel {
     // PAIR: row-major planes are fetched for two K-tiles at a time, 128 bytes of 8 rows per instruction, and
     // regrouped through 2 KB of LDS per wave one K-tile before the first of the two is merged.  Fetched
     // for one K-tile, 64 bytes of 16 rows per instruction, every line is requested twice: (28672, 5120) at 48
-    // tokens took 80 us against 57 from packed planes.  (A wave with 32 weight rows has no registers for it.)
-    static constexpr bool PAIR = ROWMAJOR && TN == 128;
+    // tokens took 77 us against 56 from packed planes, and takes 60 so.  It costs 16 registers for the second
+    // pair and as many for the longer loop, which a wave with 32 weight rows does not have (and which leave
+    // room for one workgroup per CU instead of two; capped to 128 registers the kernel is 3 % slower).
+    static constexpr bool PAIR = PAIRS;
+    static_assert(!PAIR || (ROWMAJOR && TN == 128), "pairs of K-tiles: row-major planes, 16 weight rows per wave");
     static constexpr int BLOCK_BYTES = 1024 * kind_elem_bytes(WK);   // packed kinds: one 16 x 64 block
     typedef TileStore<kNestedF16, TM, TN, 1, 8> Store;
     static constexpr int DW = 4;                               // waves that issue the token loads
@@ -830,7 +829,10 @@ struct BypassKernel {
             merge_part<0, FNB - 1, 0>(a[0][FNB - 1], raw[0]);
             merge_part<0, FNB - 1, 1>(a[0][FNB - 1], raw[0]);
         }
-        __syncthreads();
+        // (a bare barrier, as in the loop: the later plane loads stay in flight)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
         c.st = kt_begin & (NST - 1);
         {
             const uint8_t *st0 = lds + c.st * STAGE;
@@ -857,11 +859,11 @@ struct BypassKernel {
     }
 };
 
-template <int TM, int TN, int WK, bool DEEP, bool NT>
+template <int TM, int TN, int WK, bool DEEP, bool NT, bool PAIRS>
 __global__ void __launch_bounds__(512)
 nested_bypass_kernel(LargeParams p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
-    typedef BypassKernel<TM, TN, WK, DEEP, NT> Kern;
+    typedef BypassKernel<TM, TN, WK, DEEP, NT, PAIRS> Kern;
     Kern::run(p, lds_raw, (typename Kern::lds_byte *)lds_raw);
 }
 
@@ -1072,7 +1074,10 @@ struct E4m3BypassKernel {
         // the token tiles of the first two K-tiles: in order, everything but the later token loads
         // and the plane loads has landed
         if (wave < DW) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((XA - 2) * XG + NRAW * 2 * FNB) : "memory");
-        __syncthreads();
+        // (a bare barrier, as in the loop: the other loads stay in flight)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
         if constexpr (ROWMAJOR) regroup(raw[0], c);
         {
             const uint8_t *st0 = lds + (kt_begin & (NST - 1)) * STAGE;
@@ -1105,7 +1110,7 @@ e4m3_bypass_kernel(LargeParams p) {
     Kern::run(p, lds_raw, (typename Kern::lds_byte *)lds_raw);
 }
 
-struct LargeConfig { int tm, tn, split, deep; };
+struct LargeConfig { int tm, tn, split, deep; double cost; };
 
 // Tile shape and K split from a small cost model.  The workgroups are dealt round-robin to the
 // 256 CUs; a workgroup costs a fixed part plus a time per K-tile that depends on the tile shape
@@ -1179,7 +1184,15 @@ static LargeConfig choose_tile64(int cls, int64_t M, int64_t N, int kt) {
         if (time < best) { best = time;  c.split = split; }
         if (t.large_split > 0) break;
     }
+    c.cost = best;
     return c;
+}
+
+double tile64_cost(int kind, int64_t M, int64_t N, int64_t K) {
+    static thread_local PlanCache<double> cache;
+    return cache.get(kind, M, N, K, [&] {
+        return choose_tile64(kind_class(kind), M, N, (int)(((kind_is_fp8(kind) ? K : 2 * K) + 127) / 128)).cost;
+    });
 }
 
 // Launch shapes that were timed faster than the cost model's choice, for the layer shapes of the
@@ -1204,8 +1217,9 @@ static bool tuned_large(int cls, int64_t M, int64_t N, int64_t K, LargeConfig &c
     return false;
 }
 
-static LargeConfig choose_large(int kind, int64_t M, int64_t N, int64_t K) {
+static LargeConfig compute_large(int kind, int64_t M, int64_t N, int64_t K) {
     LargeConfig c;
+    c.cost = 0.0;
     const Tuning &t = tuning();
     const int cls = kind_class(kind);                  // cost tables: plain FP16 through LDS, FP16 through registers, E4M3
     const int kt = (int)(((kind_is_fp8(kind) ? K : 2 * K) + 127) / 128);
@@ -1252,9 +1266,14 @@ static LargeConfig choose_large(int kind, int64_t M, int64_t N, int64_t K) {
     return c;
 }
 
+static LargeConfig choose_large(int kind, int64_t M, int64_t N, int64_t K) {
+    static thread_local PlanCache<LargeConfig> cache;
+    return cache.get(kind, M, N, K, [&] { return compute_large(kind, M, N, K); });
+}
+
 size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K) {
     LargeConfig c = choose_large(kind, M, N, K);
-    return c.split > 1 ? (size_t)c.split * (size_t)M * (size_t)N * sizeof(float) : 0;
+    return c.split > 1 ? (size_t)c.split * (size_t)M * (size_t)partial_ld(N) * sizeof(float) : 0;
 }
 
 template <int KIND, int TM, int TN, int WAVES_M, int WAVES_N, int NST = 2>
@@ -1277,10 +1296,10 @@ static bool streams_rows(const LargeParams &p) {
            (reinterpret_cast<uintptr_t>(p.W1) & 127) == 0;
 }
 
-template <int TM, int TN, int WK, bool DEEP = false, bool NT = false>
+template <int TM, int TN, int WK, bool DEEP = false, bool NT = false, bool PAIRS = false>
 static void launch_bypass(const LargeParams &p, dim3 grid, hipStream_t stream) {
-    auto kern = nested_bypass_kernel<TM, TN, WK, DEEP, NT>;
-    constexpr int lds = BypassKernel<TM, TN, WK, DEEP, NT>::LDS_BYTES;
+    auto kern = nested_bypass_kernel<TM, TN, WK, DEEP, NT, PAIRS>;
+    constexpr int lds = BypassKernel<TM, TN, WK, DEEP, NT, PAIRS>::LDS_BYTES;
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1326,18 +1345,40 @@ static void launch_large_k(const LargeParams &p, const LargeConfig &c, dim3 grid
     }
 }
 
+// Row-major planes on tiles of 128 weight rows: by pairs of K-tiles (see BypassKernel::PAIR; 1-38 % faster
+// over 140 problems of 37 layer shapes at 48 ... 300 tokens), unless the slices of a K split have an odd number
+// of K-tiles: every second slice then starts in the middle of a line, its pieces take two lines each, and
+// fetching K-tile by K-tile is 1-20 % faster.  (Rows that do not start on lines gain by pairs either way.)  Slices
+// of less than a dozen K-tiles are over before the longer look-ahead pays (3-8 % behind).
+template <int TM, bool DEEP = false>
+static void launch_rows128(const LargeParams &p, dim3 grid, hipStream_t stream) {
+    const bool nt = streams_rows(p) && (TM == 64 || (TM == 128 && (int64_t)p.N * p.K >= ((int64_t)100 << 20)));
+    const bool pairs = p.ktiles_per_split >= 12 &&
+                       (grid.y == 1 || (p.ktiles_per_split & 1) == 0 || (p.w_row_bytes & 127) != 0);
+    if (!pairs) launch_bypass<TM, 128, kNestedF16Row, DEEP>(p, grid, stream);
+    else if (nt) launch_bypass<TM, 128, kNestedF16Row, DEEP, TM != 256, true>(p, grid, stream);
+    else launch_bypass<TM, 128, kNestedF16Row, DEEP, false, true>(p, grid, stream);
+}
+
 // weights through registers: NestedFP16 in either storage order, packed FP16
 template <int WK>
 static void launch_nested(const LargeParams &p, const LargeConfig &c, dim3 grid, hipStream_t stream) {
-    if (c.tm == 64) {
-        if (WK == kNestedF16Row && streams_rows(p)) launch_bypass<64, 128, WK, false, WK == kNestedF16Row>(p, grid, stream);
-        else launch_bypass<64, 128, WK>(p, grid, stream);
-    } else if (c.tm == 256 && c.tn == 256) launch_bypass<256, 256, WK>(p, grid, stream);
+    if constexpr (WK == kNestedF16Row) {
+        if (c.tn == 128) {
+            if (c.tm == 64) launch_rows128<64>(p, grid, stream);
+            else if (c.tm == 256) launch_rows128<256>(p, grid, stream);
+            else if (c.deep) launch_rows128<128, true>(p, grid, stream);
+            else launch_rows128<128>(p, grid, stream);
+            return;
+        }
+    }
+    if (c.tm == 64) launch_bypass<64, 128, WK>(p, grid, stream);
+    else if (c.tm == 256 && c.tn == 256) launch_bypass<256, 256, WK>(p, grid, stream);
     else if (c.tm == 256) launch_bypass<256, 128, WK>(p, grid, stream);
     else {
-        // one token tile over a large layer: weights marked non-temporal (see BypassKernel)
-        {
-            if (p.tiles_m == 1 && (int64_t)p.N * p.K >= ((int64_t)100 << 20) && (WK != kNestedF16Row || streams_rows(p))) {
+        // one token tile over a large packed layer: weights marked non-temporal (see BypassKernel)
+        if constexpr (WK != kNestedF16Row) {
+            if (p.tiles_m == 1 && (int64_t)p.N * p.K >= ((int64_t)100 << 20)) {
                 if (c.tn == 256) {
                     if (c.deep) launch_bypass<128, 256, WK, true, true>(p, grid, stream);
                     else launch_bypass<128, 256, WK, false, true>(p, grid, stream);
@@ -1386,6 +1427,7 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     p.kblocks = (int)((a.K + 63) / 64);
     p.Y = a.Y;  p.ldy = a.ldy;
     p.partials = a.partials;
+    p.ldp = (int)partial_ld(a.N);
     p.tiles_m = (int)((a.M + c.tm - 1) / c.tm);
     p.tiles_n = (int)((a.N + c.tn - 1) / c.tn);
     p.ktiles_total = (p.k_bytes + 127) / 128;
@@ -1396,7 +1438,7 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     p.row_store = ((a.N & 7) == 0 && (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) ? 1 : 0;
     if (tuning().large_epilogue == 0) p.row_store = 0;
     if (c.split > 1 && (a.partials == nullptr ||
-                        a.partial_bytes < (size_t)c.split * a.M * a.N * sizeof(float)))
+                        a.partial_bytes < (size_t)c.split * a.M * partial_ld(a.N) * sizeof(float)))
         return kErrWorkspace;
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)c.split);
     switch (kind) {

@@ -18,6 +18,7 @@
 // Columns past K and rows past N are never multiplied: their loads are sent out of the buffer's
 // range and return zero, whatever the memory behind them holds.
 #include <algorithm>
+#include <cmath>
 
 #include "nfp_device.h"
 #include "nfp_host.h"
@@ -39,7 +40,8 @@ struct SmallParams {
     int M, N, K;
     uint16_t *Y;
     int64_t ldy;
-    float *partials;        // [S][M][N] when S > 1
+    float *partials;        // [S][M][ldp] when S > 1
+    int ldp;                // see partial_ld
     uint32_t *counters;     // one arrival counter per workgroup column (zero between launches), or NULL
     int k_passes;           // K slices each wave walks through in turn
     int tiles_per_wg;       // 16-row weight tiles each workgroup walks through
@@ -431,8 +433,7 @@ small_gemm_kernel(SmallParams p) {
     // it -- made the kernel four times slower (measured).
     const bool fused = gridDim.y > 1 && p.counters != nullptr;
     constexpr int kThrough = 1 | 16;                  // buffer cache policy: sc0 | sc1
-    const bool part_vec = (p.N & 3) == 0;
-    const int64_t slice_elems = (int64_t)p.M * p.N;
+    const int64_t slice_elems = (int64_t)p.M * p.ldp;
     const __amdgpu_buffer_rsrc_t rpart = __builtin_amdgcn_make_buffer_rsrc(
         p.partials, 0, fused ? (uint32_t)(gridDim.y * slice_elems * 4) : 0u, 0x00020000);
     for (int item = wave; item < T * MT; item += waves) {
@@ -446,27 +447,13 @@ small_gemm_kernel(SmallParams p) {
         const int n = (tile0 + tile * tstride) * 16 + 4 * g;
         if (m >= p.M || n >= p.N) continue;
         if (gridDim.y > 1) {
-            const int64_t e = ((int64_t)slice * p.M + m) * p.N + n;
-            if (fused) {
-                const uint32_t off = (uint32_t)(e * 4);
-                if (part_vec) {
-                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(sum.x), __float_as_uint(sum.y),
-                                                                 __float_as_uint(sum.z), __float_as_uint(sum.w)},
-                                                           rpart, off, 0, kThrough);
-                } else {
-                    const float v[4] = {sum.x, sum.y, sum.z, sum.w};
-                    for (int q = 0; q < 4 && n + q < p.N; ++q)
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[q]), rpart, off + 4 * q, 0, kThrough);
-                }
-            } else {
-                float *dst = p.partials + e;
-                if (part_vec) {
-                    *reinterpret_cast<floatx4 *>(dst) = sum;
-                } else {
-                    float v[4] = {sum.x, sum.y, sum.z, sum.w};
-                    for (int q = 0; q < 4 && n + q < p.N; ++q) dst[q] = v[q];
-                }
-            }
+            const int64_t e = ((int64_t)slice * p.M + m) * p.ldp + n;
+            if (fused)
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(sum.x), __float_as_uint(sum.y),
+                                                             __float_as_uint(sum.z), __float_as_uint(sum.w)},
+                                                       rpart, (uint32_t)(e * 4), 0, kThrough);
+            else
+                *reinterpret_cast<floatx4 *>(p.partials + e) = sum;
         } else {
             store_y(sum, m, n);
         }
@@ -490,87 +477,69 @@ small_gemm_kernel(SmallParams p) {
         const int m = 16 * i + r16;
         const int n = (tile0 + tile * tstride) * 16 + 4 * g;
         if (m >= p.M || n >= p.N) continue;
-        const uint32_t off = (uint32_t)(((int64_t)m * p.N + n) * 4);
+        const uint32_t off = (uint32_t)(((int64_t)m * p.ldp + n) * 4);
         const uint32_t sstep = (uint32_t)(slice_elems * 4);
-        floatx4 sum;
-        if (part_vec) {
-            u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rpart, off, 0, kThrough);
-            sum = floatx4{__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
-            for (int s2 = 1; s2 < (int)gridDim.y; ++s2) {
-                v = __builtin_amdgcn_raw_buffer_load_b128(rpart, off + s2 * sstep, 0, kThrough);
-                sum.x += __uint_as_float(v.x); sum.y += __uint_as_float(v.y);
-                sum.z += __uint_as_float(v.z); sum.w += __uint_as_float(v.w);
-            }
-        } else {
-            float v[4] = {0.f, 0.f, 0.f, 0.f};
-            for (int q = 0; q < 4 && n + q < p.N; ++q) {
-                v[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rpart, off + 4 * q, 0, kThrough));
-                for (int s2 = 1; s2 < (int)gridDim.y; ++s2)
-                    v[q] += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rpart, off + s2 * sstep + 4 * q, 0, kThrough));
-            }
-            sum = floatx4{v[0], v[1], v[2], v[3]};
+        u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rpart, off, 0, kThrough);
+        floatx4 sum = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+        for (int s2 = 1; s2 < (int)gridDim.y; ++s2) {
+            v = __builtin_amdgcn_raw_buffer_load_b128(rpart, off + s2 * sstep, 0, kThrough);
+            sum.x += __uint_as_float(v.x); sum.y += __uint_as_float(v.y);
+            sum.z += __uint_as_float(v.z); sum.w += __uint_as_float(v.w);
         }
         store_y(sum, m, n);
     }
     if (threadIdx.x == 0) __hip_atomic_store(&p.counters[blockIdx.x], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Sums the S split-K partials in slice order, applies the FP8-mode scale, writes fp16.
-// VEC: four consecutive columns per lane (needs N % 4 == 0 and 8-byte aligned output rows).
+// Sums the S split-K partials (rows of ldp floats) in slice order, four columns per lane, applies the
+// FP8-mode scale, writes fp16.  VEC: 8-byte stores (N % 4 == 0 and 8-byte aligned output rows).
 template <bool VEC>
 __global__ void __launch_bounds__(256)
-splitk_reduce_kernel(const float *__restrict__ partials, int S, int M, int N, const float *scales,
+splitk_reduce_kernel(const float *__restrict__ partials, int S, int M, int N, int ldp, const float *scales,
                      float w_scale, uint16_t *__restrict__ Y, int64_t ldy) {
-    constexpr int W = VEC ? 4 : 1;
-    const int64_t total = (int64_t)M * N;
-    const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * W;
+    const int64_t total = (int64_t)M * ldp;
+    const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (idx >= total) return;
-    const int m = (int)(idx / N), n = (int)(idx - (int64_t)m * N);
-    float v[W];
-    if (VEC) {
-        floatx4 t = *reinterpret_cast<const floatx4 *>(partials + idx);
-        v[0] = t.x; v[W > 1 ? 1 : 0] = t.y; v[W > 2 ? 2 : 0] = t.z; v[W > 3 ? 3 : 0] = t.w;
-        for (int s = 1; s < S; ++s) {
-            floatx4 u = *reinterpret_cast<const floatx4 *>(partials + (int64_t)s * total + idx);
-            v[0] += u.x; v[W > 1 ? 1 : 0] += u.y; v[W > 2 ? 2 : 0] += u.z; v[W > 3 ? 3 : 0] += u.w;
-        }
-    } else {
-        v[0] = partials[idx];
-        for (int s = 1; s < S; ++s) v[0] += partials[(int64_t)s * total + idx];
+    const int m = (int)(idx / ldp), n = (int)(idx - (int64_t)m * ldp);
+    floatx4 v = *reinterpret_cast<const floatx4 *>(partials + idx);
+    for (int s = 1; s < S; ++s) {
+        const floatx4 u = *reinterpret_cast<const floatx4 *>(partials + (int64_t)s * total + idx);
+        v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
     }
-    const float sc = scales ? scales[m] * w_scale : 1.0f;
+    if (scales) {
+        const float sc = scales[m] * w_scale;
+        v.x = scale_f32(v.x, sc); v.y = scale_f32(v.y, sc); v.z = scale_f32(v.z, sc); v.w = scale_f32(v.w, sc);
+    }
     uint16_t *dst = Y + (int64_t)m * ldy + n;
     if (VEC) {
         u32x2 o;
-        o.x = float2_to_half2_bits(scales ? scale_f32(v[0], sc) : v[0], scales ? scale_f32(v[W > 1 ? 1 : 0], sc) : v[W > 1 ? 1 : 0]);
-        o.y = float2_to_half2_bits(scales ? scale_f32(v[W > 2 ? 2 : 0], sc) : v[W > 2 ? 2 : 0],
-                                   scales ? scale_f32(v[W > 3 ? 3 : 0], sc) : v[W > 3 ? 3 : 0]);
+        o.x = float2_to_half2_bits(v.x, v.y);
+        o.y = float2_to_half2_bits(v.z, v.w);
         *reinterpret_cast<u32x2 *>(dst) = o;
     } else {
-        union { _Float16 f; uint16_t u; } c;
-        c.f = (_Float16)(scales ? scale_f32(v[0], sc) : v[0]);
-        dst[0] = c.u;
+        const float x[4] = {v.x, v.y, v.z, v.w};
+        for (int q = 0; q < 4 && n + q < N; ++q) {
+            union { _Float16 f; uint16_t u; } c;
+            c.f = (_Float16)x[q];
+            dst[q] = c.u;
+        }
     }
 }
 
 int launch_splitk_reduce(const float *partials, int S, int64_t M, int64_t N, const float *scales,
                          float w_scale, uint16_t *Y, int64_t ldy, hipStream_t stream) {
-    const int64_t total = M * N;
-    const bool vec = (N & 3) == 0 && (ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(Y) & 7) == 0 &&
-                     (reinterpret_cast<uintptr_t>(partials) & 15) == 0;
-    if (vec)
-        splitk_reduce_kernel<true><<<(unsigned)((total / 4 + 255) / 256), 256, 0, stream>>>(
-            partials, S, (int)M, (int)N, scales, w_scale, Y, ldy);
-    else
-        splitk_reduce_kernel<false><<<(unsigned)((total + 255) / 256), 256, 0, stream>>>(
-            partials, S, (int)M, (int)N, scales, w_scale, Y, ldy);
+    const int64_t ldp = partial_ld(N), total = M * ldp;
+    const bool vec = (N & 3) == 0 && (ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(Y) & 7) == 0;
+    const unsigned blocks = (unsigned)((total / 4 + 255) / 256);
+    if (vec) splitk_reduce_kernel<true><<<blocks, 256, 0, stream>>>(partials, S, (int)M, (int)N, (int)ldp, scales, w_scale, Y, ldy);
+    else splitk_reduce_kernel<false><<<blocks, 256, 0, stream>>>(partials, S, (int)M, (int)N, (int)ldp, scales, w_scale, Y, ldy);
     return hip_ok(hipGetLastError());
 }
 
 // ---- host-side configuration ---------------------------------------------------------
-struct SmallConfig { int mt, spw, waves, split, passes, tiles_per_wg; };
+struct SmallConfig { int mt, spw, waves, split, passes, tiles_per_wg; double cost; };
 
-// Launch shapes of the streaming kernel that were timed faster than the rules below choose, on the
+// Launch shapes of the streaming kernel that were timed faster than what the cost model below chooses, on the
 // layer shapes of the models the paper evaluates (Sec. 5.1), for batches of up to 16 tokens.
 struct TunedSmall { int cls, N, K, spw, split, tiles; };
 static const TunedSmall kTunedSmall[] = {
@@ -578,94 +547,112 @@ static const TunedSmall kTunedSmall[] = {
     {-1, 0, 0, 0, 0, 0},
 };
 
-static SmallConfig choose_small(int kind, int64_t M, int64_t N, int64_t K) {
+// What a launch costs, in microseconds.  Least-squares fit to 34 000 timings (33 layer shapes of 1 to 470 Mi
+// weights x 1, 4, 16, 24, 32 and 64 tokens x three classes x every K split, slice length and tile count;
+// weights cold, replayed graphs), 4-5 % rms; on those the cheapest candidate is within 1-2.5 % of the
+// fastest launch on average.  What it says, and the rules it replaced did not: a K split costs 1.5 us and 0.5 us per slice
+// (the last workgroup's three trips to memory), more than it gives on small layers, where eight slices took
+// 10 us against 4.3 for one ((1560, 1040), 1 token); a CU takes in weights at 45 GB/s at most.
+struct SmallCost {
+    double base;            // launch, first load, reduction over the waves
+    double chip_rate, cu_rate;      // bytes per microsecond of the weight stream: whole chip, one CU
+    double split, slice;    // K split: once, per slice
+    double x_rate;          // bytes per microsecond at which a CU fetches activations
+    double round;           // workgroups beyond what fits the chip at a time, per round
+    double part_rate;       // bytes per microsecond of partial sums
+    double pass;            // a further pass over K
+};
+static const SmallCost kSmallCost[2] = {
+    // FP16 mode; plain FP16 too (its own fit is within 3 % of this one), so that the same knobs give both
+    // the same launch shape
+    {3.75, 7.42e6, 45.6e3, 0.40, 0.52, 103e3, 2.03, 1.24e6, 0.86},
+    {3.49, 7.36e6, 45.6e3, 0.34, 0.58, 108e3, 1.51, 1.08e6, 0.91},      // E4M3
+};
+
+static double price_small(int kind, const SmallConfig &c, int64_t M, int64_t N, int64_t K) {
+    const bool fp8 = kind_is_fp8(kind);
+    const SmallCost &k = kSmallCost[fp8 ? 1 : 0];
+    const double wb = fp8 ? 1.0 : 2.0;                            // bytes per weight, and per activation
+    const int64_t tiles = (N + 15) / 16;
+    const int64_t wgs = ((tiles + c.tiles_per_wg - 1) / c.tiles_per_wg) * c.split;
+    const int64_t lds = (int64_t)((c.tiles_per_wg + 1) & ~1) * c.waves * c.mt * 1024 + c.waves * 2048;
+    const int waves_cu = c.mt == 1 ? (c.spw == 2 ? 28 : (c.spw == 4 ? 16 : 8)) : (c.mt == 2 ? 20 : 16);   // by registers
+    const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(160 * 1024 / lds, waves_cu / c.waves));
+    const double k_wg = (double)c.waves * c.passes * c.spw * (fp8 ? 128 : 64);      // columns of a workgroup
+    const double wg_cu = (double)((wgs + 255) / 256);             // workgroups of the busiest CU
+    const double chip = (double)N * (double)K * wb / k.chip_rate;
+    const double cu = wg_cu * c.tiles_per_wg * 16.0 * std::min(k_wg, (double)K) * wb / k.cu_rate;
+    const double a = chip * chip, b = cu * cu;
+    double t = k.base + std::sqrt(std::sqrt(a * a + b * b));
+    t += wg_cu * (double)std::min<int64_t>(M, 16 * c.mt) * k_wg * wb / k.x_rate;
+    t += k.round * (double)((wgs + 256 * slots - 1) / (256 * slots) - 1) + k.pass * (c.passes - 1);
+    if (c.split > 1) t += k.split + k.slice * c.split + (double)c.split * (double)M * (double)N * 4.0 / k.part_rate;
+    return t;
+}
+
+static SmallConfig compute_small(int kind, int64_t M, int64_t N, int64_t K) {
     const Tuning &t = tuning();
-    SmallConfig c;
-    c.mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
-    // knobs first; with none set, the table of timed shapes; otherwise the rules
+    const int mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
+    // knobs first; with none set, the table of timed shapes; otherwise the cheapest candidate
     int64_t k_spw = t.small_spw, k_split = t.small_split, k_tiles = t.small_tiles;
-    if (k_spw <= 0 && k_split <= 0 && k_tiles <= 0 && t.tuned_table != 0 && c.mt == 1) {
+    if (k_spw <= 0 && k_split <= 0 && k_tiles <= 0 && t.tuned_table != 0 && mt == 1) {
         for (const TunedSmall &e : kTunedSmall)
             if (e.cls == kind_class(kind) && e.N == N && e.K == K) {
                 k_spw = e.spw;  k_split = e.split;  k_tiles = e.tiles;
                 break;
             }
     }
-    const bool fp8 = kind_is_fp8(kind), nested = kind_class(kind) == 1;
+    const bool fp8 = kind_is_fp8(kind);
     const int kstep = fp8 ? 128 : 64;
     const int steps = (int)((K + kstep - 1) / kstep);
-    // Row-major FP16 weights (the plain baseline) stream best in long runs per row: 8 K-steps per
-    // wave (512 contiguous bytes of each row), 8 waves (measured: 8-10 % faster than 4 x 16);
-    // the packed planes are contiguous per tile whatever the slice and gain nothing from it.
-    const bool can_long = (kind == kPlainF16 || kind == kNestedF16Row) && M <= 16 && (K + 63) / 64 >= 64;
-    const bool long_slices = can_long && (k_spw == 8 || (kind == kPlainF16 && k_spw <= 0));
-    const int max_waves = (c.mt == 4 || long_slices) ? 8 : 16;     // four token tiles need 256 VGPRs per wave
-    const int64_t tiles = (N + 15) / 16;
-    // K-steps per wave: 2 with several token tiles (their activations need the registers) and
-    // for large layers (measured: two passes of short slices beat one pass of long ones);
-    // otherwise 4, or 2 if that still lets one workgroup cover all of K
-    c.spw = 4;
-    if ((steps + 3) / 4 < 16 && steps >= 2) c.spw = 2;
-    if (tiles >= 1024 && !nested) c.spw = 2;
-    if (k_spw == 2 || k_spw == 4) c.spw = (int)k_spw;
-    if (c.mt > 1) c.spw = 2;
-    if (long_slices) c.spw = 8;
-    const int slices = (steps + c.spw - 1) / c.spw;               // wave-sized K slices
-    // Grid-level split of K (fp32 partials + a second kernel): small layers run faster as
-    // about a thousand short workgroups than as a few hundred wide ones, so K is split by
-    // the largest power of two that keeps tiles*split <= 1024 (at most 8: the scratch stays
-    // below 8*M*N floats).  What 16 waves x split do not cover is walked in passes.
-    const int rounds = (slices + max_waves - 1) / max_waves;
-    // E4M3 layers move half the bytes: half as many workgroups, unless K needs passes anyway
-    const int64_t wg_target = (fp8 && rounds == 1) ? 512 : 1024;
-    int split = 1;
-    while (split < 8 && tiles * (split * 2) <= wg_target) split *= 2;
-    // measured with packed planes: a single token tile whose K fits one pass is as fast
-    // unsplit once there is a tile per CU, and saves the reduction launch
-    if (c.mt == 1 && rounds == 1 && tiles >= 256) split = 1;
-    // ... except FP16 weights on layers of one or two tiles per CU: two K slices per tile column and
-    // twice the tiles per workgroup leave the workgroup count alone, halve the activations every
-    // workgroup has to fetch, and the last workgroup of a column sums the two slices itself
-    // (measured on 4096 x 4096 and 6144 x 4096 at 16 tokens: 13.3 -> 12.0 and 16.1 -> 15.3 us per call)
-    const bool pair_slices = !fp8 && c.mt == 1 && rounds == 1 && tiles >= 256 && tiles <= 512 && slices >= 2 &&
-                             t.fused_reduce != 0;
-    if (pair_slices) split = 2;
-    if (k_split > 0) split = (int)k_split;
-    if (split > slices) split = slices;
-    c.split = split;
-    c.passes = (rounds + split - 1) / split;
-    c.waves = (slices + split * c.passes - 1) / (split * c.passes);
-    if (c.waves > max_waves) {                                    // cannot happen; keep the launch legal
-        c.waves = max_waves;
-        c.passes = (slices + split * max_waves - 1) / (split * max_waves);
+    // K-steps per wave: 2 or 4; 2 with several token tiles (their activations need the registers); 8 where
+    // it is asked for and exists (row-major weights of a long K: 512 bytes or more of each row)
+    const bool can_long = (kind == kPlainF16 || kind == kNestedF16Row) && mt == 1 && (K + 63) / 64 >= 64;
+    int spws[2] = {2, 4}, n_spw = 2;
+    if (mt > 1) n_spw = 1;
+    else if (k_spw == 2 || k_spw == 4 || (k_spw == 8 && can_long)) { spws[0] = (int)k_spw;  n_spw = 1; }
+    else if (k_spw == 8) { spws[0] = 4;  n_spw = 1; }
+    SmallConfig best;
+    best.cost = 1e30;
+    for (int q = 0; q < n_spw; ++q) {
+        SmallConfig c;
+        c.mt = mt;
+        c.spw = spws[q];
+        const int max_waves = (mt == 4 || c.spw == 8) ? 8 : 16;   // (these need up to 256 VGPRs per wave)
+        const int slices = (steps + c.spw - 1) / c.spw;           // wave-sized K slices
+        const int rounds = (slices + max_waves - 1) / max_waves;
+        for (int split : {1, 2, 3, 4, 6, 8}) {
+            if (k_split > 0) split = (int)std::min<int64_t>(k_split, slices);
+            // a split's scratch has to leave room in the fixed scratch of nestedfp_gemm_static, which takes
+            // every problem that fits it unsplit
+            else if (split > 1 && (split > slices || (double)split * (double)M * (double)N * 4.0 +
+                                                     (fp8 ? (double)M * (double)K : 0.0) > 30.0 * 1024 * 1024)) break;
+            // what the waves of all grid slices do not cover at once is walked in passes
+            c.split = split;
+            c.passes = (rounds + split - 1) / split;
+            c.waves = (slices + split * c.passes - 1) / (split * c.passes);
+            // a workgroup keeps a kilobyte of partial sums per tile, token tile and wave in LDS (an even
+            // number of tiles, 128 KB at most)
+            int per_max = (128 / (c.waves * mt)) & ~1;
+            per_max = std::max(1, std::min(per_max, 16));
+            for (int per = 1; per <= per_max; ++per) {
+                c.tiles_per_wg = k_tiles > 0 ? (int)std::min<int64_t>(k_tiles, per_max) : per;
+                c.cost = price_small(kind, c, M, N, K);
+                if (c.cost < best.cost) best = c;
+                if (k_tiles > 0) break;
+            }
+            if (k_split > 0) break;
+        }
     }
-    // Tiles per workgroup.  A workgroup keeps a kilobyte of partial sums per tile and wave in LDS (an
-    // even number of slots, 128 KB at most).  The launch runs in rounds of one workgroup per CU and is
-    // bound by the weight stream, which 224 workgroups fill; with fewer each one gets faster, but only
-    // up to about twice as fast on an empty chip.  A round of R workgroups therefore costs its tiles
-    // times R / 256 from 224 workgroups on and 0.875 (1 - 0.43 (224 - R) / 224) below (fitted to
-    // timings of 1 ... 12 tiles per workgroup on eight layer shapes), plus half a tile for its ramp and
-    // tail.  Cheapest wins, the larger count on a tie (fewer workgroups fetch the activations).
-    const int slots_max = 128 / (c.waves * c.mt);
-    int per_max = slots_max & ~1;                      // (an odd count takes a spare slot)
-    if (per_max < 1) per_max = 1;
-    if (per_max > 16) per_max = 16;
-    int64_t per = 1;
-    double best = 1e30;
-    for (int cand = 1; cand <= per_max; ++cand) {
-        const int64_t wgs = ((tiles + cand - 1) / cand) * c.split;
-        const int64_t full = wgs / 256, rem = wgs % 256;
-        const double part = rem >= 224 ? (double)rem / 256.0 : 0.875 * (1.0 - 0.43 * (double)(224 - rem) / 224.0);
-        double cost = (double)cand * ((double)full + (rem ? part : 0.0)) + 0.5 * (double)(full + (rem ? 1 : 0));
-        if (cost <= best) { best = cost;  per = cand; }
-    }
-    if (pair_slices && k_split <= 0) per = 2 * ((tiles + 255) / 256);
-    if (k_tiles > 0) per = k_tiles;
-    if (per > per_max) per = per_max;
-    if (per < 1) per = 1;
-    c.tiles_per_wg = (int)per;
-    return c;
+    return best;
 }
+
+static SmallConfig choose_small(int kind, int64_t M, int64_t N, int64_t K) {
+    static thread_local PlanCache<SmallConfig> cache;
+    return cache.get(kind, M, N, K, [&] { return compute_small(kind, M, N, K); });
+}
+
+double small_gemm_cost(int kind, int64_t M, int64_t N, int64_t K) { return choose_small(kind, M, N, K).cost; }
 
 bool small_gemm_supports(int kind, int64_t M, int64_t N, int64_t K, int64_t ldw) {
     // the weight array must be addressable with 31-bit byte offsets (bit 31 marks a load as dead),
@@ -676,7 +663,7 @@ bool small_gemm_supports(int kind, int64_t M, int64_t N, int64_t K, int64_t ldw)
 
 size_t small_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K) {
     SmallConfig c = choose_small(kind, M, N, K);
-    return c.split > 1 ? (size_t)c.split * (size_t)M * (size_t)N * sizeof(float) : 0;
+    return c.split > 1 ? (size_t)c.split * (size_t)M * (size_t)partial_ld(N) * sizeof(float) : 0;
 }
 
 template <int KIND, int MT, int SPW, int POL = kStream>
@@ -764,12 +751,13 @@ int launch_small_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     p.M = (int)a.M;  p.N = (int)a.N;  p.K = (int)a.K;
     p.Y = a.Y;  p.ldy = a.ldy;
     p.partials = a.partials;
+    p.ldp = (int)partial_ld(a.N);
     p.tiles_per_wg = c.tiles_per_wg;
     const int64_t tiles = (a.N + 15) / 16;
     const unsigned grid_x = (unsigned)((tiles + c.tiles_per_wg - 1) / c.tiles_per_wg);
     // the last workgroup of a tile column sums the K slices itself where there is a counter for it
     const bool fused_reduce = c.split > 1 && a.counters != nullptr && grid_x <= (unsigned)kMaxCounters &&
-                              (int64_t)c.split * a.M * a.N * 4 < ((int64_t)1 << 32) && tuning().fused_reduce != 0;
+                              (int64_t)c.split * a.M * partial_ld(a.N) * 4 < ((int64_t)1 << 32) && tuning().fused_reduce != 0;
     p.counters = fused_reduce ? a.counters : nullptr;
     p.k_passes = c.passes;
     p.tile_stride = (tuning().small_interleave != 0 && c.tiles_per_wg > 1) ? (int)grid_x : 1;
@@ -783,7 +771,7 @@ int launch_small_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     p.rotate = !kind_is_packed(kind) && p.w_row_bytes % channels == 0 ? 1 : 0;
     p.vec_store = ((a.N & 3) == 0 && (a.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 7) == 0) ? 1 : 0;
     if (c.split > 1 && (a.partials == nullptr ||
-                        a.partial_bytes < (size_t)c.split * a.M * a.N * sizeof(float)))
+                        a.partial_bytes < (size_t)c.split * a.M * partial_ld(a.N) * sizeof(float)))
         return kErrWorkspace;
     dim3 grid(grid_x, (unsigned)c.split);
     if (kind == kE4M3Quant && !(c.mt == 1 && c.split == 1 && c.passes == 1)) return kErrArg;   // caller checks first

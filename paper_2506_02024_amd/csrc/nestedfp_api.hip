@@ -15,6 +15,9 @@ Tuning &tuning() {
     return t;
 }
 
+static std::atomic<uint32_t> g_tuning_epoch{0};
+uint32_t tuning_epoch() { return g_tuning_epoch.load(std::memory_order_relaxed); }
+
 bool use_small_gemm(int64_t M) {
     int64_t lim = tuning().small_max_m >= 0 ? tuning().small_max_m : 64;
     if (lim > 64) lim = 64;
@@ -38,20 +41,18 @@ struct Workspace {
 static bool route_small(int kind, int64_t M, int64_t N, int64_t K, int64_t ldw) {
     if (!use_small_gemm(M) || !small_gemm_supports(kind, M, N, K, ldw)) return false;
     if (tuning().small_max_m >= 0) return true;
-    const int cls = kind_class(kind);
-    // Timed on the 18 layer shapes of the paper's five models at 12 ... 64 tokens, all three classes:
-    // with three or four token tiles per wave (33 tokens and more) the streaming kernel is behind
-    // the 64-token tiles of the tiled kernels (split along K) on every shape, by 9-97 %;
-    if (M > 32) return false;
-    // with two token tiles (17 ... 32 tokens) it is behind by 5-30 % except on the smallest layers
-    // (and, for plain row-major FP16 weights, on layers of 4096 rows); up to 16 tokens it stays
-    const int64_t weights = N * K;
-    if (M > 16) {
-        if (cls == 1 && weights >= ((int64_t)20 << 20)) return false;
-        if (cls == 2 && weights >= ((int64_t)50 << 20)) return false;
-        if (cls == 0 && N >= 5120) return false;
-    }
-    return true;
+    if (M <= 16) return true;
+    // 17 ... 64 tokens: the streaming kernel (two or four token tiles per wave) against the 64-token tiles of
+    // the tiled kernels, by their cost models.  The models were fitted apart; factor and offset line them
+    // up with timings of both kernels on 33 layer shapes (1 to 470 Mi weights) at 24, 32 and 64 tokens, where the
+    // rule's choice is within 1 % of the faster one on average.  With four token tiles the streaming
+    // kernel never wins on the largest layers ((35840, 5120) at 64 tokens: 95 against 88 us).
+    if (M > 32 && N * K >= ((int64_t)100 << 20)) return false;
+    // Plain FP16 weights go where FP16 mode goes, so that the two can be pinned to one launch shape.
+    static const double kFactor[2][2] = {{1.20, 1.10}, {1.20, 1.20}};      // [FP16, E4M3][17 ... 32, 33 ... 64 tokens]
+    static const double kOffset[2][2] = {{5.0, 2.5}, {5.0, 5.0}};          // microseconds
+    const int f = kind_is_fp8(kind) ? 1 : 0, m = M > 32 ? 1 : 0, priced = f ? kE4M3 : kNestedF16;
+    return small_gemm_cost(priced, M, N, K) * kFactor[f][m] <= tile64_cost(priced, M, N, K) + kOffset[f][m];
 }
 
 static size_t partial_bytes_for(int kind, int64_t M, int64_t N, int64_t K) {
@@ -581,6 +582,7 @@ int nestedfp_tune(const char *knob, int64_t value) {
     if (knob == nullptr) return NESTEDFP_ERR_ARG;
     Tuning &t = tuning();
     if (value < 0) value = -1;
+    g_tuning_epoch.fetch_add(1, std::memory_order_relaxed);
     if (!strcmp(knob, "small_max_m")) t.small_max_m = value;
     else if (!strcmp(knob, "small_split")) t.small_split = value;
     else if (!strcmp(knob, "small_spw")) t.small_spw = value;

@@ -85,6 +85,28 @@ struct Tuning {
     int64_t quant_onepass;   // 1 / 0: force / forbid the single-pass activation quantisation (rows kept in registers) where it fits
 };
 Tuning &tuning();
+uint32_t tuning_epoch();                               // counts the changes of the knobs
+
+// Launch shapes already worked out in this host thread, by problem: choosing one prices a hundred or so
+// candidates (5-10 us of host time), and every call asks several times.  Keyed by sizes and kind alone;
+// a fixed number of entries, dropped when a knob changes.
+template <typename Config>
+struct PlanCache {
+    struct Entry { int64_t M, N, K; int kind; uint32_t epoch; bool set; Config config; };
+    Entry entries[64] = {};
+    template <typename Choose>
+    const Config &get(int kind, int64_t M, int64_t N, int64_t K, Choose choose) {
+        const uint64_t h = ((uint64_t)M * 0x9e3779b97f4a7c15ull) ^ ((uint64_t)N * 0xc2b2ae3d27d4eb4full) ^
+                           ((uint64_t)K * 0x165667b19e3779f9ull) ^ (uint64_t)kind * 0x27d4eb2f165667c5ull;
+        Entry &e = entries[(h >> 58) & 63];
+        const uint32_t epoch = tuning_epoch();
+        if (!e.set || e.epoch != epoch || e.M != M || e.N != N || e.K != K || e.kind != kind) {
+            e.config = choose();
+            e.M = M;  e.N = N;  e.K = K;  e.kind = kind;  e.epoch = epoch;  e.set = true;
+        }
+        return e.config;
+    }
+};
 
 int launch_decompose(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, uint8_t *upper,
                      uint8_t *lower, uint64_t *counter, bool packed, hipStream_t stream);
@@ -103,11 +125,18 @@ int launch_quantize_act(const uint16_t *X, int64_t M, int64_t K, int64_t ldx,
 
 // streaming (small-M) and tiled (large-M) GEMM families
 bool small_gemm_supports(int kind, int64_t M, int64_t N, int64_t K, int64_t ldw);
+double small_gemm_cost(int kind, int64_t M, int64_t N, int64_t K);     // priced microseconds of the chosen launch shape
+double tile64_cost(int kind, int64_t M, int64_t N, int64_t K);         // the same for the 64-token tiles
 bool small_gemm_fuses_quant(int64_t M, int64_t N, int64_t K);
 size_t small_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K);
 int launch_small_gemm(int kind, const GemmArgs &a, hipStream_t stream);
 size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K);
 int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream);
+
+// Row stride of the split-K partial sums [slice][token][ld]: whole groups of four columns, so that they are
+// written and read 16 bytes per lane whatever N is (with N itself, odd layers paid four narrow accesses
+// each: (2903, 9168) in FP16 mode at 40 tokens 29.6 us against 21).
+constexpr int64_t partial_ld(int64_t N) { return (N + 3) & ~(int64_t)3; }
 
 int launch_splitk_reduce(const float *partials, int S, int64_t M, int64_t N, const float *scales,
                          float w_scale, uint16_t *Y, int64_t ldy, hipStream_t stream);
