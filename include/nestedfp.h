@@ -26,8 +26,8 @@
  *     16-byte chunk of row 16i+r, columns 64j+16g .. 64j+16g+15 at chunk index r + 16g
  *     (r = 0..15, g = 0..3), bytes in column order.  Rows >= N and columns >= K are zero.
  *     That is the order in which the 64 lanes of a wave hold an MFMA operand, so one 128-bit
- *     load per lane reads a block front to back; the weight stream of a decode-sized batch
- *     runs 10-30 % faster from it than from row-major planes.  nestedfp_pack_plane /
+ *     load per lane reads a block front to back.  Decode-sized batches run level from either
+ *     storage; FP16 mode on larger batches is 5-10 % faster from packed planes.  nestedfp_pack_plane /
  *     nestedfp_unpack_plane convert; footprint and contents are otherwise the same.
  *   - K must be a positive multiple of 16 and at most 2^21; ldw, ldx must be multiples of 8,
  *     >= K and at most 2^21; ldy must be a multiple of 4 and >= N when N % 4 == 0, else any
