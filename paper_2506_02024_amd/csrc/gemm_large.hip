@@ -1158,7 +1158,8 @@ static const Tile64Cost kTile64Cost[3] = {
     {0.466, 0.4, 512, 5.25e6, 5.5e6, 0.5},    // NestedFP16 (register path, two per CU)
     {0.35, 0.4, 256, 5.5e6, 5.5e6, 0.3},      // E4M3 (register path, one per CU)
 };
-static LargeConfig choose_tile64(int cls, int64_t M, int64_t N, int kt) {
+static LargeConfig choose_tile64(int cls, int64_t M, int64_t N, int64_t K, int max_split = 8) {
+    const int kt = (int)(((cls == 2 ? K : 2 * K) + 127) / 128);
     const Tuning &t = tuning();
     const Tile64Cost &tc = kTile64Cost[cls];
     LargeConfig c;
@@ -1167,7 +1168,7 @@ static LargeConfig choose_tile64(int cls, int64_t M, int64_t N, int kt) {
     double best = 1e30;
     for (int split : {1, 2, 3, 4, 6, 8}) {
         if (t.large_split > 0) split = (int)(t.large_split < kt ? t.large_split : kt);
-        else if (split > 1 && split > kt / 4) break;
+        else if (split > 1 && (split > kt / 4 || split > max_split)) break;
         const int per = (kt + split - 1) / split;
         const int slices = (kt + per - 1) / per;
         const int64_t wgs = tiles * slices;
@@ -1185,14 +1186,14 @@ static LargeConfig choose_tile64(int cls, int64_t M, int64_t N, int kt) {
         if (t.large_split > 0) break;
     }
     c.cost = best;
+    // (a split whose scratch the padding of the rows has pushed past the fixed one: the best smaller split)
+    if (t.large_split <= 0 && !padded_split_fits(c.split, M, N, K, cls == 2)) return choose_tile64(cls, M, N, K, c.split - 1);
     return c;
 }
 
 double tile64_cost(int kind, int64_t M, int64_t N, int64_t K) {
     static thread_local PlanCache<double> cache;
-    return cache.get(kind, M, N, K, [&] {
-        return choose_tile64(kind_class(kind), M, N, (int)(((kind_is_fp8(kind) ? K : 2 * K) + 127) / 128)).cost;
-    });
+    return cache.get(kind, M, N, K, [&] { return choose_tile64(kind_class(kind), M, N, K).cost; });
 }
 
 // Launch shapes that were timed faster than the cost model's choice, for the layer shapes of the
@@ -1217,7 +1218,7 @@ static bool tuned_large(int cls, int64_t M, int64_t N, int64_t K, LargeConfig &c
     return false;
 }
 
-static LargeConfig compute_large(int kind, int64_t M, int64_t N, int64_t K) {
+static LargeConfig compute_large(int kind, int64_t M, int64_t N, int64_t K, int max_split = 8) {
     LargeConfig c;
     c.cost = 0.0;
     const Tuning &t = tuning();
@@ -1227,7 +1228,7 @@ static LargeConfig compute_large(int kind, int64_t M, int64_t N, int64_t K) {
         tuned_large(cls, M, N, K, c))
         return c;
     if (t.large_bm == 64 || (M <= 64 && t.large_bm < 0 && t.large_bn < 0))
-        return choose_tile64(cls, M, N, kt);
+        return choose_tile64(cls, M, N, K);
     double best = 1e30;
     c.tm = c.tn = 256;
     c.split = 1;
@@ -1246,7 +1247,7 @@ static LargeConfig compute_large(int kind, int64_t M, int64_t N, int64_t K) {
             const TileCost &tc = deep ? kDeepTileCost[cls][sh] : kTileCost[cls][sh];
             for (int split : kSplits) {
                 if (t.large_split > 0) split = (int)(t.large_split < kt ? t.large_split : kt);
-                else if (split > 1 && split > kt / 4) break;
+                else if (split > 1 && (split > kt / 4 || split > max_split)) break;
                 const int per = (kt + split - 1) / split;                     // K-tiles per workgroup
                 const int slices = (kt + per - 1) / per;
                 const int64_t rounds = (tiles * slices + 255) / 256;
@@ -1263,6 +1264,7 @@ static LargeConfig compute_large(int kind, int64_t M, int64_t N, int64_t K) {
             }
         }
     }
+    if (t.large_split <= 0 && !padded_split_fits(c.split, M, N, K, cls == 2)) return compute_large(kind, M, N, K, c.split - 1);
     return c;
 }
 

@@ -25,11 +25,10 @@ bool use_small_gemm(int64_t M) {
 }
 
 static inline bool aligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
-static inline size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 constexpr int64_t kMaxK = (int64_t)1 << 21;            // K and leading dimensions: 256 rows stay below 2^31 bytes
 
-// workspace layout: [arrival counters : kCounterBytes][Xq : M*K bytes][scales : M floats][split-K partials]
+// the parts of a workspace (its layout: see workspace_need)
 struct Workspace {
     uint32_t *counters;
     uint8_t *xq;
@@ -61,9 +60,7 @@ static size_t partial_bytes_for(int kind, int64_t M, int64_t N, int64_t K) {
 }
 
 static size_t workspace_bytes_for(int kind, int64_t M, int64_t N, int64_t K, bool quantize) {
-    size_t b = round256(partial_bytes_for(kind, M, N, K));
-    if (quantize) b += round256((size_t)M * (size_t)K) + round256((size_t)M * sizeof(float));
-    return b > 0 ? b + kCounterBytes : 0;
+    return workspace_need(partial_bytes_for(kind, M, N, K), M, K, quantize);
 }
 
 static bool carve(void *ws, size_t ws_bytes, int kind, int64_t M, int64_t N, int64_t K, bool quantize,
@@ -308,6 +305,7 @@ static int plain_fp8_impl(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, 
 // at its own address until the process ends.  In host code the array's name is only a handle for
 // hipGetSymbolAddress; the address it returns (per device) is what kernels and fills are given.
 static __device__ __align__(256) unsigned char scratch[NESTEDFP_STATIC_SCRATCH_BYTES];
+static_assert(NESTEDFP_STATIC_SCRATCH_BYTES == nfp::kStaticScratch, "the launch shapes are chosen for this scratch");
 
 namespace nfp {
 

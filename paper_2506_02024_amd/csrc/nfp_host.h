@@ -138,6 +138,27 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream);
 // each: (2903, 9168) in FP16 mode at 40 tokens 29.6 us against 21).
 constexpr int64_t partial_ld(int64_t N) { return (N + 3) & ~(int64_t)3; }
 
+// Workspace layout: [arrival counters : kCounterBytes][Xq : M*K bytes][scales : M floats][split-K partials],
+// each part rounded up to 256 bytes; 0 if nothing but the counters would be in it.
+constexpr size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
+constexpr size_t workspace_need(size_t partial_bytes, int64_t M, int64_t K, bool quantize) {
+    const size_t b = round256(partial_bytes) +
+                     (quantize ? round256((size_t)M * (size_t)K) + round256((size_t)M * sizeof(float)) : 0);
+    return b > 0 ? b + kCounterBytes : 0;
+}
+
+// The entry point without a workspace argument has a fixed scratch, and takes every problem whose split fits
+// it with rows of N floats.  A split that only the padding of the rows would push past it is not taken -- by
+// any entry point, so that all of them give the same bits: (1221, 167, 22112) in FP8 mode needs 33545472
+// bytes in three slices unpadded, 33584384 padded.
+constexpr size_t kStaticScratch = (size_t)32 << 20;
+constexpr bool padded_split_fits(int split, int64_t M, int64_t N, int64_t K, bool quantize) {
+    if (split <= 1) return true;
+    const size_t rows = (size_t)split * (size_t)M * sizeof(float);
+    return workspace_need(rows * (size_t)partial_ld(N), M, K, quantize) <= kStaticScratch ||
+           workspace_need(rows * (size_t)N, M, K, quantize) > kStaticScratch;
+}
+
 int launch_splitk_reduce(const float *partials, int S, int64_t M, int64_t N, const float *scales,
                          float w_scale, uint16_t *Y, int64_t ldy, hipStream_t stream);
 

@@ -63,6 +63,17 @@ def test_workspace_query_never_scales_with_weight_count(L):
     assert ws(-1, 4096, 4096, 0) == 0
 
 
+@pytest.mark.parametrize("M,N,K,mode", [
+    (1221, 167, 22112, 1), (6988, 21, 4080, 1), (642, 3054, 15584, 1), (1244, 615, 17104, 1), (240, 5, 139552, 1),
+    (8053, 23, 3792, 1), (8035, 130, 27712, 0),                   # N % 4 != 0: rows of N floats fit, padded ones do not
+    (8035, 128, 27712, 0), (1221, 168, 21984, 1),                 # N % 4 == 0, just below the limit
+])
+def test_problems_that_just_fit_the_fixed_scratch_unpadded_are_taken(L, M, N, K, mode):
+    # the entry point without a workspace takes every problem of at most 32 MiB, and the padding of the
+    # partial sums' rows may not push one past that
+    assert 0 < L.nestedfp_gemm_workspace_size(M, N, K, mode) <= 32 << 20
+
+
 def test_argument_errors_are_reported_before_any_launch(L):
     P = ctypes.c_void_p
     fake = P(0x1000)         # aligned, never dereferenced: every call below fails validation first

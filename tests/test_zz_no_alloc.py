@@ -44,6 +44,12 @@ def test_two_calls_in_a_row_share_the_fixed_scratch(nfp):
     _both(nfp, 16, 4096 + 8, 14336, seed=3)
 
 
+def test_problem_that_fills_the_fixed_scratch(nfp):
+    # FP8 mode: 33 545 472 of 33 554 432 bytes in three K slices with rows of 167 partial sums, which is more
+    # than there is with the rows padded to 168: taken, in a smaller split, with the bits of nestedfp_gemm
+    _both(nfp, 1221, 167, 22112, seed=9)
+
+
 def test_problems_beyond_the_fixed_scratch_are_refused(nfp):
     M, N, K = 16384, 1024, 4096                        # 64 MiB of quantised activations
     assert nfp.gemm_workspace_size(M, N, K, nfp.MODE_FP8) > nfp.STATIC_SCRATCH_BYTES
