@@ -1416,6 +1416,11 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     // the register-path kernels take the deeper pipeline only where it is asked for (knob) or was
     // timed faster (table), and only on the tiles of 128 tokens
     if (kind_class(kind) == 1) c.deep = (tuning().large_deep > 0 || (c.deep && tuning().large_deep != 0)) && c.tm == 128;
+    // Workspaces are sized without the row stride of FP16 weights.  A matrix that spans 2 GiB or more comes here
+    // with the scratch of the streaming kernel, which cannot address it: as many K slices as that holds.
+    const size_t slice_bytes = (size_t)a.M * (size_t)partial_ld(a.N) * sizeof(float);
+    const size_t room = a.partials != nullptr ? a.partial_bytes / slice_bytes : 0;
+    if ((size_t)c.split > room) c.split = room > 1 ? (int)room : 1;
     LargeParams p;
     p.X = static_cast<const uint8_t *>(a.X);
     p.x_row_bytes = kind_is_fp8(kind) ? a.ldx : 2 * a.ldx;
@@ -1439,9 +1444,6 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     p.vec_store = ((a.N & 3) == 0 && (a.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 7) == 0) ? 1 : 0;
     p.row_store = ((a.N & 7) == 0 && (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) ? 1 : 0;
     if (tuning().large_epilogue == 0) p.row_store = 0;
-    if (c.split > 1 && (a.partials == nullptr ||
-                        a.partial_bytes < (size_t)c.split * a.M * partial_ld(a.N) * sizeof(float)))
-        return kErrWorkspace;
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)c.split);
     switch (kind) {
         case kPlainF16: launch_large_k<kPlainF16>(p, c, grid, stream); break;

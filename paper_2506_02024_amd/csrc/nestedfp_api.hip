@@ -72,7 +72,7 @@ static bool carve(void *ws, size_t ws_bytes, int kind, int64_t M, int64_t N, int
     out.scales = nullptr;
     out.partials = nullptr;
     out.partial_bytes = 0;
-    if (need == 0) return true;
+    if (need == 0 && (ws == nullptr || ws_bytes <= kCounterBytes || !aligned(ws, 16))) return true;
     uint8_t *p = static_cast<uint8_t *>(ws);
     out.counters = reinterpret_cast<uint32_t *>(p);  p += kCounterBytes;
     if (quantize) {
@@ -80,7 +80,7 @@ static bool carve(void *ws, size_t ws_bytes, int kind, int64_t M, int64_t N, int
         out.scales = reinterpret_cast<float *>(p);  p += round256((size_t)M * sizeof(float));
     }
     out.partials = reinterpret_cast<float *>(p);
-    out.partial_bytes = partial_bytes_for(kind, M, N, K);
+    out.partial_bytes = ws_bytes - (size_t)(p - static_cast<uint8_t *>(ws));
     return true;
 }
 

@@ -436,6 +436,21 @@ def test_strided_activations_and_output(nfp):
     assert np.all(got[:, N:] == np.float16(7.0))
 
 
+@pytest.mark.parametrize("M", [1, 16, 40])
+def test_strided_weights_beyond_the_streaming_kernels_reach(nfp, M):
+    # FP16 weights as a view of a matrix of more than 2 GiB: too far apart for the streaming kernel, so the tiled
+    # one gets the scratch of the streaming kernel's launch (unsplit here: none), or whatever the caller has
+    N, K, ld = 1000, 4096 + 16, (1 << 20) + 64
+    big = torch.empty((N, ld), dtype=torch.float16, device="cuda:0")
+    W, X = workloads.weight_host(N, K, seed=30), workloads.act_host(M, K, seed=31)
+    big[:, :K] = to_dev(W)
+    ref = oracle.gemm_fp16(X, W)
+    room = nfp.new_workspace(16 * M * N * 4 + (1 << 20), "cuda:0")
+    for ws in (None, room):
+        y = nfp.plain_gemm_fp16(to_dev(X), big[:, :K], workspace=ws)
+        assert_gemm_close(y.cpu().numpy(), ref, "M=%d, rows 2 MiB apart" % M)
+
+
 def test_results_are_deterministic(nfp):
     W = workloads.weight_host(1024, 4096, seed=4)
     Wd = to_dev(W)
