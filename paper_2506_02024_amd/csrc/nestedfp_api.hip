@@ -16,7 +16,7 @@ Tuning &tuning() {
 }
 
 static std::atomic<uint32_t> g_tuning_epoch{0};
-uint32_t tuning_epoch() { return g_tuning_epoch.load(std::memory_order_relaxed); }
+uint32_t tuning_epoch() { return g_tuning_epoch.load(std::memory_order_acquire); }
 
 bool use_small_gemm(int64_t M) {
     int64_t lim = tuning().small_max_m >= 0 ? tuning().small_max_m : 64;
@@ -597,7 +597,6 @@ int nestedfp_tune(const char *knob, int64_t value) {
     if (knob == nullptr) return NESTEDFP_ERR_ARG;
     Tuning &t = tuning();
     if (value < 0) value = -1;
-    g_tuning_epoch.fetch_add(1, std::memory_order_relaxed);
     if (!strcmp(knob, "small_max_m")) t.small_max_m = value;
     else if (!strcmp(knob, "small_split")) t.small_split = value;
     else if (!strcmp(knob, "small_spw")) t.small_spw = value;
@@ -615,6 +614,8 @@ int nestedfp_tune(const char *knob, int64_t value) {
     else if (!strcmp(knob, "tuned_table")) t.tuned_table = value;
     else if (!strcmp(knob, "quant_onepass")) t.quant_onepass = value;
     else return NESTEDFP_ERR_ARG;
+    // after the knob: a launch shape worked out from its old value is remembered under the old count
+    g_tuning_epoch.fetch_add(1, std::memory_order_release);
     return NESTEDFP_OK;
 }
 
