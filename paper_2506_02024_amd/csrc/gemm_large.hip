@@ -1193,7 +1193,7 @@ static LargeConfig choose_tile64(int cls, int64_t M, int64_t N, int64_t K, int m
 
 double tile64_cost(int kind, int64_t M, int64_t N, int64_t K) {
     static thread_local PlanCache<double> cache;
-    return cache.get(kind, M, N, K, [&] { return choose_tile64(kind_class(kind), M, N, K).cost; });
+    return cache.get(kind_class(kind), M, N, K, [&] { return choose_tile64(kind_class(kind), M, N, K).cost; });
 }
 
 // Launch shapes that were timed faster than the cost model's choice, for the layer shapes of the
@@ -1218,12 +1218,12 @@ static bool tuned_large(int cls, int64_t M, int64_t N, int64_t K, LargeConfig &c
     return false;
 }
 
-static LargeConfig compute_large(int kind, int64_t M, int64_t N, int64_t K, int max_split = 8) {
+static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, int max_split = 8) {
     LargeConfig c;
     c.cost = 0.0;
     const Tuning &t = tuning();
-    const int cls = kind_class(kind);                  // cost tables: plain FP16 through LDS, FP16 through registers, E4M3
-    const int kt = (int)(((kind_is_fp8(kind) ? K : 2 * K) + 127) / 128);
+    const bool fp8 = cls == 2;                         // cls: cost tables of plain FP16 through LDS, FP16 through registers, E4M3
+    const int kt = (int)(((fp8 ? K : 2 * K) + 127) / 128);
     if (t.tuned_table != 0 && t.large_bm < 0 && t.large_bn < 0 && t.large_split <= 0 && t.large_deep < 0 &&
         tuned_large(cls, M, N, K, c))
         return c;
@@ -1235,7 +1235,7 @@ static LargeConfig compute_large(int kind, int64_t M, int64_t N, int64_t K, int 
     c.deep = 0;
     const int want_m = (t.large_bm == 128 || t.large_bm == 256) ? (int)t.large_bm : 0;
     const int want_n = (t.large_bn == 128 || t.large_bn == 256) ? (int)t.large_bn : want_m;
-    const double w_bytes = (double)N * (double)K * (kind_is_fp8(kind) ? 1.0 : 2.0);
+    const double w_bytes = (double)N * (double)K * (fp8 ? 1.0 : 2.0);
     for (int sh = 0; sh < 4; ++sh) {
         const int bm = kTileShapes[sh][0], bn = kTileShapes[sh][1];
         if (want_m && bm != want_m) continue;
@@ -1264,13 +1264,13 @@ static LargeConfig compute_large(int kind, int64_t M, int64_t N, int64_t K, int 
             }
         }
     }
-    if (t.large_split <= 0 && !padded_split_fits(c.split, M, N, K, cls == 2)) return compute_large(kind, M, N, K, c.split - 1);
+    if (t.large_split <= 0 && !padded_split_fits(c.split, M, N, K, fp8)) return compute_large(cls, M, N, K, c.split - 1);
     return c;
 }
 
 static LargeConfig choose_large(int kind, int64_t M, int64_t N, int64_t K) {
     static thread_local PlanCache<LargeConfig> cache;
-    return cache.get(kind, M, N, K, [&] { return compute_large(kind, M, N, K); });
+    return cache.get(kind_class(kind), M, N, K, [&] { return compute_large(kind_class(kind), M, N, K); });
 }
 
 size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K) {

@@ -649,7 +649,8 @@ static SmallConfig compute_small(int kind, int64_t M, int64_t N, int64_t K) {
 
 static SmallConfig choose_small(int kind, int64_t M, int64_t N, int64_t K) {
     static thread_local PlanCache<SmallConfig> cache;
-    return cache.get(kind, M, N, K, [&] { return compute_small(kind, M, N, K); });
+    // (row-major planes can take 8 K-steps where packed ones cannot)
+    return cache.get(kind == kNestedF16Row ? 3 : kind_class(kind), M, N, K, [&] { return compute_small(kind, M, N, K); });
 }
 
 double small_gemm_cost(int kind, int64_t M, int64_t N, int64_t K) { return choose_small(kind, M, N, K).cost; }

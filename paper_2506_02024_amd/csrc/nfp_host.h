@@ -4,6 +4,7 @@
 #include <stddef.h>
 #include <stdint.h>
 #include <atomic>
+#include <utility>
 
 namespace nfp {
 
@@ -88,23 +89,33 @@ Tuning &tuning();
 uint32_t tuning_epoch();                               // counts the changes of the knobs
 
 // Launch shapes already worked out in this host thread, by problem: choosing one prices a hundred or so
-// candidates (5-10 us of host time), and every call asks several times.  Keyed by sizes and kind alone;
-// a fixed number of entries, dropped when a knob changes.
+// candidates (1-3 us of host time), and every call asks several times.  Keyed by sizes and a class of kinds
+// alone; a fixed number of entries (20-40 KB), dropped when a knob changes.  512 entries in pairs hold the four
+// linears of a layer in two modes at 64 batch sizes; with 64 single ones, batches of 1 ... 16 tokens in turn
+// were worked out anew each time (workspace queries of 4.1 us on average against 0.5).
 template <typename Config>
 struct PlanCache {
-    struct Entry { int64_t M, N, K; int kind; uint32_t epoch; bool set; Config config; };
-    Entry entries[64] = {};
-    template <typename Choose>
-    const Config &get(int kind, int64_t M, int64_t N, int64_t K, Choose choose) {
-        const uint64_t h = ((uint64_t)M * 0x9e3779b97f4a7c15ull) ^ ((uint64_t)N * 0xc2b2ae3d27d4eb4full) ^
-                           ((uint64_t)K * 0x165667b19e3779f9ull) ^ (uint64_t)kind * 0x27d4eb2f165667c5ull;
-        Entry &e = entries[(h >> 58) & 63];
-        const uint32_t epoch = tuning_epoch();
-        if (!e.set || e.epoch != epoch || e.M != M || e.N != N || e.K != K || e.kind != kind) {
-            e.config = choose();
-            e.M = M;  e.N = N;  e.K = K;  e.kind = kind;  e.epoch = epoch;  e.set = true;
+    struct Entry {
+        int64_t M, N, K;
+        int cls;
+        uint32_t epoch;
+        bool set;
+        Config config;
+        bool is(int cls_, int64_t M_, int64_t N_, int64_t K_, uint32_t epoch_) const {
+            return set && epoch == epoch_ && M == M_ && N == N_ && K == K_ && cls == cls_;
         }
-        return e.config;
+    };
+    Entry entries[256][2] = {};
+    template <typename Choose>
+    const Config &get(int cls, int64_t M, int64_t N, int64_t K, Choose choose) {
+        const uint64_t h = ((uint64_t)M * 0x9e3779b97f4a7c15ull) ^ ((uint64_t)N * 0xc2b2ae3d27d4eb4full) ^
+                           ((uint64_t)K * 0x165667b19e3779f9ull) ^ (uint64_t)cls * 0x27d4eb2f165667c5ull;
+        Entry *e = entries[h >> 56];
+        const uint32_t epoch = tuning_epoch();
+        if (e[0].is(cls, M, N, K, epoch)) return e[0].config;
+        if (!e[1].is(cls, M, N, K, epoch)) e[1] = {M, N, K, cls, epoch, true, choose()};
+        std::swap(e[0], e[1]);                                 // the entry used last is kept longest
+        return e[0].config;
     }
 };
 
