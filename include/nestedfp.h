@@ -10,7 +10,9 @@
  * Conventions shared by every call
  *   - All tensor pointers are DEVICE pointers unless the parameter name ends in `_host`.
  *     The caller owns every buffer; the library never allocates or frees device memory
- *     and never writes to an input.
+ *     and never writes to an input.  The first call that returns a count to the host
+ *     (`out_of_range_host`, nestedfp_layer_prepare) allocates 512 bytes of pinned HOST memory,
+ *     which the process keeps; nothing is freed, and no HIP call made, when a thread ends.
  *   - FP16 data travels as uint16_t bit patterns.  W is [N,K] row-major (K contiguous,
  *     row stride ldw elements), X is [M,K] (row stride ldx), Y is [M,N] (row stride ldy);
  *     Y = X * W^T.  Quantised activations are dense row-major bytes.

@@ -137,29 +137,44 @@ static int fp8_gemm(const uint8_t *Xq, const float *scales, int64_t M, int64_t K
     return run_gemm(w_kind, a, stream);
 }
 
-// Eight bytes of pinned host memory per host thread, given back when the thread ends: a count copied into
-// pageable memory goes through a staging buffer of the runtime, which cost 8 us per layer (the four linears of an 8B decoder layer: 290 -> 258 us).
-struct PinnedCount {
-    uint64_t *slot = nullptr;
-    ~PinnedCount() { if (slot) (void)hipHostFree(slot); }
-    uint64_t *get() {
-        if (slot == nullptr && hipHostMalloc(reinterpret_cast<void **>(&slot), sizeof(uint64_t), hipHostMallocPortable) != hipSuccess) {
-            slot = nullptr;
+// Where counts land on the host: 64 words of pinned memory, allocated by the first call that wants a count and
+// kept until the process ends.  A count copied into pageable memory goes through a staging buffer of the
+// runtime, which cost 8 us per layer (the four linears of an 8B decoder layer: 290 -> 258 us).  A call holds a
+// word while it waits, one that finds none free copies into the caller's memory.  Nothing is freed when a host
+// thread ends: the runtime refuses that, as an error of the capture, while another thread captures a graph.
+class PinnedCounts {
+    std::mutex mutex;
+    uint64_t *words = nullptr, taken = 0;
+public:
+    uint64_t *take() {
+        std::lock_guard<std::mutex> lock(mutex);
+        if (words == nullptr && hipHostMalloc(reinterpret_cast<void **>(&words), 64 * sizeof(uint64_t), hipHostMallocPortable) != hipSuccess) {
+            words = nullptr;
             (void)hipGetLastError();
         }
-        return slot;
+        if (words == nullptr || ~taken == 0) return nullptr;
+        const int i = __builtin_ctzll(~taken);
+        taken |= (uint64_t)1 << i;
+        return words + i;
+    }
+    void give_back(const uint64_t *word) {
+        std::lock_guard<std::mutex> lock(mutex);
+        taken &= ~((uint64_t)1 << (word - words));
     }
 };
 
 static int finish_count(uint64_t *dev, uint64_t *host, hipStream_t stream) {
     if (host == nullptr) return NESTEDFP_OK;
-    static thread_local PinnedCount pinned;
-    uint64_t *to = pinned.get() != nullptr ? pinned.get() : host;
-    if (hipMemcpyAsync(to, dev, sizeof(uint64_t), hipMemcpyDeviceToHost, stream) != hipSuccess)
-        return NESTEDFP_ERR_HIP;
-    if (hipStreamSynchronize(stream) != hipSuccess) return NESTEDFP_ERR_HIP;
-    *host = *to;
-    return *host == 0 ? NESTEDFP_OK : NESTEDFP_ERR_RANGE;
+    static PinnedCounts *const counts = new PinnedCounts;         // (never destroyed: calls may come until the process ends)
+    uint64_t *const word = counts->take();
+    uint64_t *const to = word != nullptr ? word : host;
+    const bool queued = hipMemcpyAsync(to, dev, sizeof(uint64_t), hipMemcpyDeviceToHost, stream) == hipSuccess;
+    if (queued && hipStreamSynchronize(stream) != hipSuccess) return NESTEDFP_ERR_HIP;   // (the word may still be written: kept)
+    const uint64_t n = queued ? *to : 0;
+    if (word != nullptr) counts->give_back(word);
+    if (!queued) return NESTEDFP_ERR_HIP;
+    *host = n;
+    return n == 0 ? NESTEDFP_OK : NESTEDFP_ERR_RANGE;
 }
 
 static int decompose_impl(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, uint8_t *upper, uint8_t *lower,

@@ -64,3 +64,77 @@ def test_mixed_stack_switches_only_the_applicable_layers(nfp):
     for i in (0, 1, 3):
         assert not np.array_equal(out16[i], out8[i])   # the others really change precision
         assert_gemm_close(out16[i].view(np.float16), oracle.gemm_fp16(X, Ws[i]), "layer %d" % i)
+
+
+@pytest.mark.parametrize("mode", ["global", "thread_local"])
+def test_loader_thread_beside_a_capture(nfp, mode):
+    # a thread that has prepared layers ends while another one captures a graph; where the capture leaves other
+    # threads alone ("thread_local"; a "global" one forbids them to wait for a stream), it starts
+    # and prepares its layers during the capture as well.  Neither side may break the other.
+    import threading
+    import time
+
+    N, K, M = 272, 1040, 16
+    W = workloads.weight_host(N, K, seed=50)
+    W_bad = W.copy()
+    W_bad[7, 9] = np.float16(2.0)
+    Xd, Wd, Wd_bad = to_dev(workloads.act_host(M, K, seed=51)), to_dev(W), to_dev(W_bad)
+    layer = nfp.Layer(Wd)
+    out = torch.zeros((M, N), dtype=torch.float16, device="cuda:0")
+    ws = nfp.new_workspace(nfp.gemm_workspace_size(M, N, K, nfp.MODE_FP16), "cuda:0")
+    nfp.linear(Xd, layer, nfp.MODE_FP16, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    want = bits(out)
+    got, errors = [], []
+    side = torch.cuda.Stream()
+    loaded, end = threading.Event(), threading.Event()
+
+    def load():
+        try:
+            with torch.cuda.stream(side):
+                got.extend([nfp.Layer(Wd), nfp.Layer(Wd_bad), nfp.Layer(Wd, packed=True)])
+        except Exception as e:                             # reported by the main thread
+            errors.append(e)
+        loaded.set()
+        end.wait(60)
+
+    t = threading.Thread(target=load)
+    if mode == "global":
+        t.start()
+        assert loaded.wait(60)
+        torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode=mode):
+        nfp.linear(Xd, layer, nfp.MODE_FP16, out=out, workspace=ws)
+        if mode != "global":
+            t.start()
+            assert loaded.wait(60)
+        end.set()
+        t.join()
+        time.sleep(0.2)                                    # the native thread is gone too
+        nfp.linear(Xd, layer, nfp.MODE_FP16, out=out, workspace=ws)
+    assert not errors, errors
+    assert [l.out_of_range for l in got] == [0, 1, 0]
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(bits(out), want)
+    assert np.array_equal(bits(nfp.linear(Xd, got[0], nfp.MODE_FP16)), want)
+
+
+def test_counts_of_many_threads_at_once(nfp):
+    # out-of-range counts are handed over through a fixed number of host words: more threads than words,
+    # each with a count of its own
+    from concurrent.futures import ThreadPoolExecutor
+
+    N, K = 64, 256
+    mats = []
+    for i in range(8):
+        W = workloads.weight_host(N, K, seed=60 + i)
+        W.reshape(-1)[:3 * i] = np.float16(-1.875)
+        mats.append(to_dev(W))
+    torch.cuda.synchronize()
+    with ThreadPoolExecutor(max_workers=80) as pool:
+        counts = list(pool.map(lambda j: nfp.range_check(mats[j % 8]), range(800)))
+    assert counts == [3 * (j % 8) for j in range(800)]
