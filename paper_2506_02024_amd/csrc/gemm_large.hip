@@ -1191,9 +1191,12 @@ static LargeConfig choose_tile64(int cls, int64_t M, int64_t N, int64_t K, int m
     return c;
 }
 
-double tile64_cost(int kind, int64_t M, int64_t N, int64_t K) {
-    static thread_local PlanCache<double> cache;
-    return cache.get(kind_class(kind), M, N, K, [&] { return choose_tile64(kind_class(kind), M, N, K).cost; });
+Tile64Plan tile64_plan(int kind, int64_t M, int64_t N, int64_t K) {
+    static thread_local PlanCache<Tile64Plan> cache;
+    return cache.get(kind_class(kind), M, N, K, [&] {
+        const LargeConfig c = choose_tile64(kind_class(kind), M, N, K);
+        return Tile64Plan{c.cost, c.split};
+    });
 }
 
 // Launch shapes that were timed faster than the cost model's choice, for the layer shapes of the

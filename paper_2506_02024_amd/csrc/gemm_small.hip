@@ -547,15 +547,19 @@ static const TunedSmall kTunedSmall[] = {
     {-1, 0, 0, 0, 0, 0},
 };
 
-// What a launch costs, in microseconds.  Least-squares fit to 34 000 timings (33 layer shapes of 1 to 470 Mi
-// weights x 1, 4, 16, 24, 32 and 64 tokens x three classes x every K split, slice length and tile count;
-// weights cold, replayed graphs), 4-5 % rms; on those the cheapest candidate is within 1-2.5 % of the
-// fastest launch on average.  What it says, and the rules it replaced did not: a K split costs 1.5 us and 0.5 us per slice
-// (the last workgroup's three trips to memory), more than it gives on small layers, where eight slices took
-// 10 us against 4.3 for one ((1560, 1040), 1 token); a CU takes in weights at 45 GB/s at most.
+// What a launch costs, in microseconds.  Fitted by fit_costs.py to 129 000 timings: 72 layer shapes of 0.3 to
+// 500 Mi weights x 1, 8, 16, 24, 32 and 64 tokens x both storage orders of the planes and FP16 weights x
+// every K split, slice length and tile count; weights cold, replayed graphs.  On those the cheapest candidate
+// is 1 % behind the fastest launch on average, 5-6 % at the 95th percentile.  What it says: a K split
+// costs about 1 us and 0.7 us per slice (the last workgroup's three trips to memory), more than it gives
+// on small layers, where eight slices took 10 us against 4.3 for one ((1560, 1040), 1 token); a CU takes in
+// weights at 40 GB/s at most, and at 27 if its workgroups have a single tile each, whose look-ahead then has
+// nothing to fetch: (2432, 7104) at 1 token 13.4 us on 152 workgroups of one tile, 10.6 on 228 of two.
 struct SmallCost {
     double base;            // launch, first load, reduction over the waves
     double chip_rate, cu_rate;      // bytes per microsecond of the weight stream: whole chip, one CU
+    double single;          // a CU's time with one tile per workgroup, against several
+    double four;            // a CU's time with four token tiles, against one or two
     double split, slice;    // K split: once, per slice
     double x_rate;          // bytes per microsecond at which a CU fetches activations
     double round;           // workgroups beyond what fits the chip at a time, per round
@@ -563,10 +567,9 @@ struct SmallCost {
     double pass;            // a further pass over K
 };
 static const SmallCost kSmallCost[2] = {
-    // FP16 mode; plain FP16 too (its own fit is within 3 % of this one), so that the same knobs give both
-    // the same launch shape
-    {3.75, 7.42e6, 45.6e3, 0.40, 0.52, 103e3, 2.03, 1.24e6, 0.86},
-    {3.49, 7.36e6, 45.6e3, 0.34, 0.58, 108e3, 1.51, 1.08e6, 0.91},      // E4M3
+    // FP16 mode; plain FP16 too (fitted together), so that the same knobs give both the same launch shape
+    {2.90, 8.08e6, 40.4e3, 1.47, 1.25, 0.57, 0.67, 110e3, 2.37, 1.11e6, 1.24},
+    {2.99, 8.01e6, 40.6e3, 1.48, 1.34, 0.35, 0.73, 137e3, 1.58, 0.98e6, 1.23},      // E4M3
 };
 
 static double price_small(int kind, const SmallConfig &c, int64_t M, int64_t N, int64_t K) {
@@ -581,7 +584,8 @@ static double price_small(int kind, const SmallConfig &c, int64_t M, int64_t N, 
     const double k_wg = (double)c.waves * c.passes * c.spw * (fp8 ? 128 : 64);      // columns of a workgroup
     const double wg_cu = (double)((wgs + 255) / 256);             // workgroups of the busiest CU
     const double chip = (double)N * (double)K * wb / k.chip_rate;
-    const double cu = wg_cu * c.tiles_per_wg * 16.0 * std::min(k_wg, (double)K) * wb / k.cu_rate;
+    const double cu = wg_cu * c.tiles_per_wg * 16.0 * std::min(k_wg, (double)K) * wb / k.cu_rate *
+                      (c.tiles_per_wg == 1 ? k.single : 1.0) * (c.mt == 4 ? k.four : 1.0);
     const double a = chip * chip, b = cu * cu;
     double t = k.base + std::sqrt(std::sqrt(a * a + b * b));
     t += wg_cu * (double)std::min<int64_t>(M, 16 * c.mt) * k_wg * wb / k.x_rate;

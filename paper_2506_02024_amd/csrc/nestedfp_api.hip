@@ -43,15 +43,22 @@ static bool route_small(int kind, int64_t M, int64_t N, int64_t K, int64_t ldw) 
     if (M <= 16) return true;
     // 17 ... 64 tokens: the streaming kernel (two or four token tiles per wave) against the 64-token tiles of
     // the tiled kernels, by their cost models.  The models were fitted apart; factor and offset line them
-    // up with timings of both kernels on 33 layer shapes (1 to 470 Mi weights) at 24, 32 and 64 tokens, where the
-    // rule's choice is within 1 % of the faster one on average.  With four token tiles the streaming
-    // kernel never wins on the largest layers ((35840, 5120) at 64 tokens: 95 against 88 us).
+    // up with timings of both kernels on 117 layer shapes (0.3 to 500 Mi weights) at ten batch sizes (found by
+    // fit_costs.py), on which the rule's choice is within 0.2-0.6 % of the faster one on average; all tiled would be
+    // 15-29 % behind, all streaming 0.6-1.9 %.  Up to 32 tokens the streaming kernel is the slower one in FP16 mode
+    // mainly where the 64-token tiles fill the chip unsplit ((28672, 5120) at 32 tokens: 56 against 51 us), hence an
+    // offset of its own.  With four token tiles it never wins on the largest layers ((35840, 5120) at 64
+    // tokens: 94 against 86 us).
     if (M > 32 && N * K >= ((int64_t)100 << 20)) return false;
     // Plain FP16 weights go where FP16 mode goes, so that the two can be pinned to one launch shape.
-    static const double kFactor[2][2] = {{1.20, 1.10}, {1.20, 1.20}};      // [FP16, E4M3][17 ... 32, 33 ... 64 tokens]
-    static const double kOffset[2][2] = {{5.0, 2.5}, {5.0, 5.0}};          // microseconds
-    const int f = kind_is_fp8(kind) ? 1 : 0, m = M > 32 ? 1 : 0, priced = f ? kE4M3 : kNestedF16;
-    return small_gemm_cost(priced, M, N, K) * kFactor[f][m] <= tile64_cost(priced, M, N, K) + kOffset[f][m];
+    struct Line { double factor, unsplit, split; };                       // offsets in microseconds
+    static const Line kLine[2][2] = {{{1.30, 8.5, 13.0}, {1.15, 5.5, 5.5}},        // FP16: 17 ... 32, 33 ... 64 tokens
+                                     {{1.40, 10.0, 10.0}, {1.10, 4.5, 4.5}}};      // E4M3
+    const bool fp8 = kind_is_fp8(kind);
+    const int priced = fp8 ? kE4M3 : kNestedF16;
+    const Line &line = kLine[fp8 ? 1 : 0][M > 32 ? 1 : 0];
+    const Tile64Plan tiles = tile64_plan(priced, M, N, K);
+    return small_gemm_cost(priced, M, N, K) * line.factor <= tiles.cost + (tiles.split > 1 ? line.split : line.unsplit);
 }
 
 static size_t partial_bytes_for(int kind, int64_t M, int64_t N, int64_t K) {

@@ -137,7 +137,8 @@ int launch_quantize_act(const uint16_t *X, int64_t M, int64_t K, int64_t ldx,
 // streaming (small-M) and tiled (large-M) GEMM families
 bool small_gemm_supports(int kind, int64_t M, int64_t N, int64_t K, int64_t ldw);
 double small_gemm_cost(int kind, int64_t M, int64_t N, int64_t K);     // priced microseconds of the chosen launch shape
-double tile64_cost(int kind, int64_t M, int64_t N, int64_t K);         // the same for the 64-token tiles
+struct Tile64Plan { double cost; int split; };
+Tile64Plan tile64_plan(int kind, int64_t M, int64_t N, int64_t K);     // the same for the 64-token tiles, and their K split
 bool small_gemm_fuses_quant(int64_t M, int64_t N, int64_t K);
 size_t small_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K);
 int launch_small_gemm(int kind, const GemmArgs &a, hipStream_t stream);
