@@ -557,7 +557,7 @@ struct BypassKernel {
     // no faster for the 64-token tiles)
     static constexpr int NST = DEEP ? 8 : 4;                   // LDS stages of the token tile
     static constexpr int XA = DEEP ? 6 : 3;                    // token loads run this many K-tiles ahead
-        static constexpr int NRAW = DEEP || PAIR ? 4 : 2;          // register sets of plane blocks, one K-tile each: loaded this many K-tiles ahead
+    static constexpr int NRAW = DEEP || PAIR ? 4 : 2;          // register sets of plane blocks, one K-tile each: loaded this many K-tiles ahead
     static_assert(XA >= 3 && XA < NST && (NRAW <= XA || PAIR) && NRAW >= 2, "the stage being filled is neither the one in use nor the next");
     static_assert(NST * TM * 128 <= 160 * 1024, "LDS stages");
     static constexpr int STAGE = TM * 128;
@@ -1350,16 +1350,36 @@ static void launch_large_k(const LargeParams &p, const LargeConfig &c, dim3 grid
     }
 }
 
-// Row-major planes on tiles of 128 weight rows: by pairs of K-tiles (see BypassKernel::PAIR; 1-38 % faster
-// over 140 problems of 37 layer shapes at 48 ... 300 tokens), unless the slices of a K split have an odd number
-// of K-tiles: every second slice then starts in the middle of a line, its pieces take two lines each, and
-// fetching K-tile by K-tile is 1-20 % faster.  (Rows that do not start on lines gain by pairs either way.)  Slices
-// of less than a dozen K-tiles are over before the longer look-ahead pays (3-8 % behind).
+// Row-major planes on tiles of 128 weight rows: by pairs of K-tiles (see BypassKernel::PAIR; up to 45 % faster)
+// where the longer look-ahead pays.  Timed both ways on 2760 launches (26 values of K from 512 to 17344, four N,
+// twelve batch sizes, every split): the rule is 0.4 % behind the faster way on average and at most 8 % behind
+// unpaired loads (the rule "12 K-tiles per slice" was 1.3 % and 23 %).
+//  - Rows that start on lines: a dozen K-tiles per slice (64 tokens per tile 1.07-1.12 x at 12 K-tiles and 1.2 x at
+//    24, 128 tokens 1.01 and 1.07); but not where the slices of a split have an odd number of K-tiles: every
+//    second slice then starts in the middle of a line, its pieces take two lines each, and K-tile by K-tile
+//    is 4-8 % faster.
+//  - Rows that start inside lines: 14 K-tiles per slice, 6 Mi weights (smaller planes stay in the caches: K = 2064
+//    at 100 tokens 0.97 x with N = 2048, 1.20 x with N = 5632), and longer rows the more token tiles read them
+//    ((12288, 1600) at 128 tokens per tile: 1.11 x with one, 0.90 x with three).
+//  - 256 tokens per tile gain little (1.0-1.1 x), lose up to 16 % where the last of several tiles is mostly empty
+//    ((5632, 6432) at 777 tokens 0.87 x), and have nothing to gain from rows that start in the middle of
+//    lines, of which unpaired loads take halves.
+bool rows_by_pairs(int tm, int64_t M, int64_t N, int64_t K, int64_t row_bytes, int split) {
+    const bool on_lines = (row_bytes & 127) == 0;
+    const int64_t kt = (K + 63) / 64, per = (kt + split - 1) / split, tiles_m = (M + tm - 1) / tm;
+    const int64_t weights = N * K, mi = (int64_t)1 << 20;
+    if (tm == 256 && tiles_m > 1 && 10 * M < 9 * 256 * tiles_m) return false;
+    if (on_lines) return per >= (tm == 256 ? 20 : 12) && (per >= kt || (per & 1) == 0);
+    if (per < 14) return false;
+    if (tm == 256) return kt >= 48 && (row_bytes & 63) != 0;
+    if (tiles_m == 1) return weights >= (kt >= 24 ? 6 : 10) * mi;
+    return weights >= 6 * mi && kt >= (tiles_m <= 4 ? 32 : 48);
+}
+
 template <int TM, bool DEEP = false>
 static void launch_rows128(const LargeParams &p, dim3 grid, hipStream_t stream) {
     const bool nt = streams_rows(p) && (TM == 64 || (TM == 128 && (int64_t)p.N * p.K >= ((int64_t)100 << 20)));
-    const bool pairs = p.ktiles_per_split >= 12 &&
-                       (grid.y == 1 || (p.ktiles_per_split & 1) == 0 || (p.w_row_bytes & 127) != 0);
+    const bool pairs = rows_by_pairs(TM, p.M, p.N, p.K, p.w_row_bytes, (int)grid.y);
     if (!pairs) launch_bypass<TM, 128, kNestedF16Row, DEEP>(p, grid, stream);
     else if (nt) launch_bypass<TM, 128, kNestedF16Row, DEEP, TM != 256, true>(p, grid, stream);
     else launch_bypass<TM, 128, kNestedF16Row, DEEP, false, true>(p, grid, stream);

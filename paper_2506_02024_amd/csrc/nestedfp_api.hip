@@ -37,7 +37,7 @@ struct Workspace {
     size_t partial_bytes;
 };
 
-static bool route_small(int kind, int64_t M, int64_t N, int64_t K, int64_t ldw) {
+bool route_small(int kind, int64_t M, int64_t N, int64_t K, int64_t ldw) {
     if (!use_small_gemm(M) || !small_gemm_supports(kind, M, N, K, ldw)) return false;
     if (tuning().small_max_m >= 0) return true;
     if (M <= 16) return true;

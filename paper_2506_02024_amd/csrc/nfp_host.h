@@ -142,6 +142,7 @@ Tile64Plan tile64_plan(int kind, int64_t M, int64_t N, int64_t K);     // the sa
 bool small_gemm_fuses_quant(int64_t M, int64_t N, int64_t K);
 size_t small_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K);
 int launch_small_gemm(int kind, const GemmArgs &a, hipStream_t stream);
+bool rows_by_pairs(int tm, int64_t M, int64_t N, int64_t K, int64_t row_bytes, int split);   // row-major planes, tiles of tm tokens x 128 rows
 size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K);
 int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream);
 
@@ -181,5 +182,6 @@ int launch_probe_mfma(const void *operands, int fp8, int iters, uint32_t *sink, 
                       hipStream_t stream);
 
 bool use_small_gemm(int64_t M);
+bool route_small(int kind, int64_t M, int64_t N, int64_t K, int64_t ldw);     // which of the two families a problem runs on
 
 }  // namespace nfp

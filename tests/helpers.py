@@ -124,3 +124,21 @@ def decompose_ref(W, workers=16):
     with ThreadPoolExecutor(max_workers=workers) as pool:
         parts = list(pool.map(lambda i: oracle.decompose(W[bounds[i]:bounds[i + 1]]), range(workers)))
     return (np.concatenate([p[0] for p in parts]), np.concatenate([p[1] for p in parts]), sum(p[2] for p in parts))
+
+
+def streaming_kernel_takes(nfp, mode, M, N, K):
+    """Whether the library sends the problem (row-major or packed planes) to the streaming kernel."""
+    import ctypes
+
+    f = nfp.lib()._ZN3nfp11route_smallEillll               # nfp::route_small
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] + 4 * [ctypes.c_int64]
+    return f(2 if mode == nfp.MODE_FP8 else 1, M, N, K, K)
+
+
+def fetched_by_pairs(nfp, tile_tokens, M, N, K, split):
+    """Whether tiles of that many tokens x 128 rows fetch row-major planes for two K-tiles at a time."""
+    import ctypes
+
+    f = nfp.lib()._ZN3nfp13rows_by_pairsEilllli            # nfp::rows_by_pairs
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] + 4 * [ctypes.c_int64] + [ctypes.c_int]
+    return f(tile_tokens, M, N, K, K, split)
