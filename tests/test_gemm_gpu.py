@@ -318,23 +318,52 @@ def test_random_shapes_and_launch_shapes(nfp, seed):
                 nfp.tune(k, -1)
 
 
+@pytest.mark.parametrize("split", [0, 1, 4])
 @pytest.mark.parametrize("M", [49, 57, 64])
-def test_tiled_route_of_49_to_64_tokens(nfp, M):
-    # from 49 tokens on, FP16 mode leaves the streaming kernel for 64-token tiles split along K
-    # (on all but the smallest layers): default routing, ragged N, against the oracle
+def test_tiles_of_64_tokens_at_49_to_64_tokens(nfp, M, split):
+    # 64-token tiles of the tiled kernels, ragged N and K, unsplit and split along K, against the oracle;
+    # split 0: the same problems by default routing, which sends layers as small as this to the streaming kernel
     N, K = 4100 + 24, 1024 + 48
     W = workloads.weight_host(N, K, seed=410)
     X = workloads.act_host(M, K, seed=411)
-    run_both_modes(nfp, X, W, "M=%d" % M, check_plain=False)
+    knobs = {"small_max_m": 0, "large_bm": 64, "large_bn": 128, "large_split": split} if split else {}
+    for k, v in knobs.items():
+        nfp.tune(k, v)
+    try:
+        assert all(streaming_kernel_takes(nfp, mode, M, N, K) == (split == 0) for mode in (nfp.MODE_FP16, nfp.MODE_FP8))
+        run_both_modes(nfp, X, W, "M=%d split %d" % (M, split), check_plain=False)
+    finally:
+        for k in knobs:
+            nfp.tune(k, -1)
 
 
+@pytest.mark.parametrize("split", [0, 1, 8])
 @pytest.mark.parametrize("M,N,K", [(50, 16384 + 40, 256 + 16), (35, 16384 + 8, 192), (64, 264, 14336 + 80)])
-def test_fp8_mode_tiled_route_of_33_to_64_tokens(nfp, M, N, K):
-    # FP8 mode takes 64-token tiles (E4M3 blocks through registers) on wide layers and on layers
-    # with a long K: default routing, ragged N and K, against the oracle
+def test_fp8_mode_tiles_of_64_tokens_at_33_to_64_tokens(nfp, M, N, K, split):
+    # E4M3 blocks through registers under 64-token tiles on wide layers and on layers with a long K (8 slices
+    # only there), ragged N and K, against the oracle; split 0: by default routing
+    if split > 1 and K < 1024:
+        split = 2
     W = workloads.weight_host(N, K, seed=420)
     X = workloads.act_host(M, K, seed=421)
-    run_both_modes(nfp, X, W, "M=%d N=%d K=%d" % (M, N, K), check_plain=False)
+    knobs = {"small_max_m": 0, "large_bm": 64, "large_bn": 128, "large_split": split} if split else {}
+    for k, v in knobs.items():
+        nfp.tune(k, v)
+    try:
+        assert streaming_kernel_takes(nfp, nfp.MODE_FP8, M, N, K) == (split == 0)
+        run_both_modes(nfp, X, W, "M=%d N=%d K=%d split %d" % (M, N, K, split), check_plain=False)
+    finally:
+        for k in knobs:
+            nfp.tune(k, -1)
+
+
+@pytest.mark.parametrize("mode,M,N,K,streaming", [("fp16", 40, 2048 + 8, 8192 + 16, True), ("fp16", 64, 2048 + 8, 8192 + 16, False),
+                                                  ("fp8", 48, 1024 + 8, 16384 + 16, True), ("fp8", 64, 1024 + 8, 16384 + 16, False)])
+def test_default_route_on_both_sides_of_its_line(nfp, mode, M, N, K, streaming):
+    # 17 ... 64 tokens go to the streaming kernel or to the 64-token tiles by price: both sides, against the oracle
+    assert streaming_kernel_takes(nfp, nfp.MODE_FP8 if mode == "fp8" else nfp.MODE_FP16, M, N, K) == streaming
+    run_both_modes(nfp, workloads.act_host(M, K, seed=431), workloads.weight_host(N, K, seed=430),
+                   "M=%d N=%d K=%d" % (M, N, K), check_plain=False)
 
 
 @pytest.mark.parametrize("M,N,K,bm,bn", [(300, 1100, 512, 128, 128), (300, 600, 256, 128, 128), (700, 2300, 384, 256, 256),

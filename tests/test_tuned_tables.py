@@ -46,3 +46,16 @@ def test_streaming_kernel_table_holds_legal_launch_shapes():
         assert 1 <= tiles <= 16
         assert (cls, N, K) not in seen
         seen.add((cls, N, K))
+
+
+def test_tiled_entries_of_at_most_64_tokens_are_asked_for():
+    # an entry serves the batches of more than half its size; the streaming kernel may not take all of them
+    from paper_2506_02024_amd import binding, build
+    import ctypes
+
+    if build.is_stale():
+        build.build_library()
+    route = binding.lib()._ZN3nfp11route_smallEillll         # nfp::route_small
+    route.restype, route.argtypes = ctypes.c_bool, [ctypes.c_int] + 4 * [ctypes.c_int64]
+    for cls, N, K, M, tm, tn, split, deep in rows("tuned_tiles.inc"):
+        assert M > 64 or not all(route(cls, m, N, K, K) for m in range(M // 2 + 1, M + 1)), (cls, N, K, M)
