@@ -8,9 +8,10 @@ then every linear is run in FP8 mode (per-token activation quantisation + upper 
 only).  The stack is 13.0 GiB of planes, so no weight is served from a cache between
 steps.  The decomposition is offline in the paper (Sec. 4.1) and is timed separately.
 
-Prints ONE JSON line: the whole-step algorithmic GB/s as `value`, the roofline of the
-dominant kernel (FP16-mode streaming GEMM), the CPU oracle timed on the host cores, and
-under `extra`: both plane layouts (row-major planes as the format defines them, and the
+Prints ONE JSON line of less than 2000 characters: the whole-step algorithmic GB/s as `value`, the
+roofline of the dominant kernel (FP16-mode streaming GEMM) and the CPU oracle timed on the host cores.
+Everything else goes to standard error as a second JSON line (or to the file given with --details): both
+plane layouts (row-major planes as the format defines them, and the
 library's optional packed pre-pack) next to plain FP16 / FP8 GEMMs of the same kernel
 family in both layouts, what the chip sustains for a pure read stream and a pure MFMA
 loop in the same run, the compute-bound (prefill) table, a subset of the Llama-3-70B
@@ -44,17 +45,18 @@ def parse():
     ap.add_argument("--bursts", type=int, default=7, help="repetitions per comparison (median is reported)")
     ap.add_argument("--no-prefill", action="store_true", help="skip the compute-bound extras")
     ap.add_argument("--no-vendor", action="store_true", help="leave the vendor library's GEMMs out of the compute-bound extras")
-    ap.add_argument("--no-70b", action="store_true", help="skip the Llama-3-70B subset (configs[3])")
-    ap.add_argument("--no-mode-switch", action="store_true", help="skip the mode-alternation run (configs[4])")
+    ap.add_argument("--no-70b", action="store_true", help="skip the Llama-3-70B subset")
+    ap.add_argument("--no-mode-switch", action="store_true", help="skip the mode-alternation run")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
     ap.add_argument("--no-graph", action="store_true", help="launch eagerly instead of replaying HIP graphs")
     ap.add_argument("--sweep-70b", action="store_true",
-                    help="extra: full roofline curve on the Llama-3-70B shapes, M = 1 ... 8192 (configs[3])")
+                    help="extra: full roofline curve on the Llama-3-70B shapes, M = 1 ... 8192")
     ap.add_argument("--paper-shapes", action="store_true",
                     help="extra: FP16-mode overhead over the plain FP16 GEMM on the shapes of the "
                          "paper's kernel benchmark, M = 32 ... 2048 step 32")
     ap.add_argument("--switch-demo", action="store_true",
                     help="extra: token-count threshold switching over a synthetic bursty arrival sequence")
+    ap.add_argument("--details", default=None, help="file for the details (JSON); default: standard error")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run a 1 GiB elementwise copy (known traffic) so that rocprofv3 "
                          "FETCH_SIZE / WRITE_SIZE readings can be scaled to bytes")
@@ -354,6 +356,26 @@ def main():
 
     cpu = None if args.no_cpu else cpu_baseline(workloads, M)
 
+    line, details = report(args, M, L, value, ms_per_step, roofline, cpu, extra)
+    if args.details:
+        with open(args.details, "w") as f:
+            f.write(details + "\n")
+    else:
+        print(details, file=sys.stderr, flush=True)
+    print(line, flush=True)
+
+
+def rounded(x):
+    """x with every float at five significant digits."""
+    if isinstance(x, dict):
+        return {k: rounded(v) for k, v in x.items()}
+    if isinstance(x, (list, tuple)):
+        return [rounded(v) for v in x]
+    return float("%.5g" % x) if isinstance(x, float) else x
+
+
+def report(args, M, L, value, ms_per_step, roofline, cpu, extra):
+    """The contract line and the details, as JSON texts."""
     line = {
         "metric": "NestedFP GEMM algorithmic GB/s over one decode step (FP16 mode + FP8 mode) "
                   "of a Llama-3-8B-shaped linear stack",
@@ -368,14 +390,14 @@ def main():
         "vs_baseline": None,
         "dtype": "f16/e4m3 operands, f32 accumulate",
         "data": "synthetic",
-        "config": {"workload": "configs[1]: Llama-3-8B-shaped linears qkv/o/gate_up/down x %d layers, "
+        "config": {"workload": "Llama-3-8B-shaped linears qkv/o/gate_up/down x %d layers, "
                                "decode M=%d, FP16 mode then FP8 mode per step, %s planes" % (args.layers, M, L),
                    "tokens": M, "layers": args.layers, "hip_graph": not args.no_graph, "plane_layout": L},
-        "roofline": roofline,
-        "cpu_baseline": cpu,
-        "extra": extra,
+        "roofline": rounded({k: roofline[k] for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic", "avg_launch_us")}),
+        "cpu_baseline": rounded({k: v for k, v in cpu.items() if isinstance(v, (int, float)) or len(v) < 40}) if cpu else None,
+        "legs_ms": rounded({k: v["ms"] for k, v in extra.get("legs_interleaved", {}).items()}),
     }
-    print(json.dumps(line))
+    return json.dumps(line), json.dumps(rounded({"roofline": roofline, "cpu_baseline": cpu, "extra": extra}))
 
 
 def read_traffic():
@@ -459,7 +481,7 @@ def achievable_rates(torch, nfp, workloads, stack, timer, dev):
 
 
 def prefill_extras(torch, nfp, workloads, stack, timer, dev, bursts, vendor=True):
-    """Compute-bound regime (configs[2]): the same four linears at M in {512, 2048, 8192}; both
+    """Compute-bound regime: the same four linears at M in {512, 2048, 8192}; both
     modes, both plane layouts and the plain baselines, interleaved; layers rotated so that the
     weights are cold.  With `vendor`, the vendor library's GEMMs (torch.mm and torch._scaled_mm,
     i.e. hipBLASLt) run in the same interleaving on the same operands, as context for what this
@@ -532,7 +554,7 @@ def _layer_copies(torch, nfp, workloads, N, K, sigma, dev, seed0):
 
 
 def sweep_extras(torch, nfp, workloads, timer, dev, shapes, sigma, Ms, bursts):
-    """Roofline curve (configs[3]): both modes over packed and row-major planes and the plain FP16
+    """Roofline curve: both modes over packed and row-major planes and the plain FP16
     baselines over M on each shape; the bound of a point is max(algorithmic bytes / 8 TB/s, flops /
     MFMA peak of the mode)."""
     out = {}
@@ -626,7 +648,7 @@ def _stack_buffers(torch, nfp, workloads, M, dev):
 
 
 def mode_switch_extras(torch, nfp, workloads, stack, layout, dev):
-    """Sec. 5.4: the mode is chosen per iteration (configs[4]).  64 steps over the whole stack, the
+    """Sec. 5.4: the mode is chosen per iteration.  64 steps over the whole stack, the
     mode flipping every 8 steps, at M = 64 and M = 2048: step time by mode, the first step after a
     flip against the steady state, allocated device memory before and after."""
     out = {"plane_layout": layout}

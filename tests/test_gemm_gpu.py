@@ -586,7 +586,7 @@ def _default_pins(M):
 
 @pytest.mark.parametrize("name", ["qkv", "o", "gate_up", "down"])
 def test_llama8b_shapes_structured_sample(nfp, name):
-    # configs[1] and configs[2]: decode and prefill batch sizes on the 8B linears
+    # decode and prefill batch sizes on the 8B linears
     N, K = workloads.LLAMA3_8B[name]
     _full_size_check(nfp, N, K, [1, 16, 64, 512, 2048, 8192], workloads.SIGMA_W_8B, "8B " + name, seed=N % 97,
                      pin_sets=_default_pins)
@@ -594,7 +594,7 @@ def test_llama8b_shapes_structured_sample(nfp, name):
 
 @pytest.mark.parametrize("name", ["qkv", "o", "gate_up", "down"])
 def test_llama70b_shapes_structured_sample(nfp, name):
-    # configs[3]: the unsharded 70B linears on one GPU, sigma 0.015, decode to prefill
+    # the unsharded 70B linears on one GPU, sigma 0.015, decode to prefill
     N, K = workloads.LLAMA3_70B[name]
     _full_size_check(nfp, N, K, [1, 2, 16, 64, 128, 512, 2048, 8192], workloads.SIGMA_W_70B, "70B " + name, seed=70 + N % 89,
                      pin_sets=_default_pins)

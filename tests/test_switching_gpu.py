@@ -55,7 +55,7 @@ class _Stack:
 
 @pytest.mark.parametrize("M,packed", [(64, True), (64, False), (2048, True), (2048, False)])
 def test_mode_alternation_on_8b_layer_shapes(nfp, M, packed):
-    # configs[4] on two layers of the stack: the mode flips every 8 steps; the steps next to each
+    # two layers of the stack: the mode flips every 8 steps; the steps next to each
     # flip are checked against the oracle, the planes and the allocator are not touched
     stack = _Stack(nfp, 2, packed)
     shapes = workloads.LLAMA3_8B
