@@ -1146,7 +1146,10 @@ static double split_cost(int64_t M, int64_t N, int slices, double launch_us, dou
 
 // At most 64 tokens: one 64 x 128 tile shape per weight kind and only the split to choose.  Such a
 // launch is bound by the weight stream, whose rate depends on how many workgroups pull on it.
-// Constants from timings of the four splits on six layer shapes at M = 64.
+// Constants from timings of the four splits on six layer shapes at M = 64, packed planes.  Row-major planes
+// share them, so that both storage orders launch alike and give the same bits, though by pairs of K-tiles
+// (BypassKernel::PAIR) they hold one workgroup per CU: over 72 layer shapes at 20 ... 64 tokens the choice is
+// 1.7 % (packed) and 2.3 % (row-major) behind the best split on average, 25 and 36 % at worst.
 struct Tile64Cost {
     double tk, tfix;        // microseconds per K-tile and per workgroup
     int slots;              // workgroups the chip holds at a time
@@ -1155,7 +1158,7 @@ struct Tile64Cost {
 };
 static const Tile64Cost kTile64Cost[3] = {
     {0.7, 0.4, 512, 4.5e6, 5.5e6, 0.5},       // plain FP16 (LDS kernel, three workgroups per CU)
-    {0.466, 0.4, 512, 5.25e6, 5.5e6, 0.5},    // NestedFP16 (register path, two per CU)
+    {0.466, 0.4, 512, 5.25e6, 5.5e6, 0.5},    // NestedFP16 (register path; packed planes: two per CU)
     {0.35, 0.4, 256, 5.5e6, 5.5e6, 0.3},      // E4M3 (register path, one per CU)
 };
 static LargeConfig choose_tile64(int cls, int64_t M, int64_t N, int64_t K, int max_split = 8) {

@@ -1,5 +1,6 @@
 // Streaming GEMM for decode-sized batches (M <= 64): Y = X * W^T with the weight stream
-// read exactly once from HBM and nothing staged in LDS (no weight reuse across waves).
+// read exactly once from HBM.  No weight is used by two waves, so nothing is staged for sharing; row-major
+// weights and the activations pass through 2 KB of LDS per wave on their way into operand order.
 // The paper's sweep starts at M = 32 with T_m >= 16 (Sec. 5.2, App. C); below that the
 // linear layer is bound by HBM bandwidth, so the kernel is built around 128-bit loads of
 // the byte planes with many loads in flight, K split across the waves of a workgroup,

@@ -70,7 +70,7 @@ constexpr size_t kCounterBytes = kMaxCounters * sizeof(uint32_t);
 struct Tuning {
     int64_t small_max_m;     // largest M routed to the streaming kernel
     int64_t small_split;     // grid-level split-K of the streaming kernel
-    int64_t small_spw;       // K-steps per wave (2 or 4)
+    int64_t small_spw;       // K-steps per wave (2, 4, or 8: row-major FP16 operands with a long K only)
     int64_t small_tiles;     // 16-row weight tiles per workgroup
     int64_t small_interleave;  // 1: a workgroup's tiles are strided by the grid size
     int64_t large_split;     // grid-level split-K of the tiled kernel
