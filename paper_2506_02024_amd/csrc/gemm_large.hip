@@ -1169,9 +1169,15 @@ static LargeConfig choose_tile64(int cls, int64_t M, int64_t N, int64_t K, int m
     c.tm = 64;  c.tn = 128;  c.split = 1;  c.deep = 0;
     const int64_t tiles = ((M + 63) / 64) * ((N + 127) / 128);
     double best = 1e30;
+    // A split stays inside the scratch of the entry point without a workspace wherever the problem does: the
+    // streaming kernel, which may run the same layer, never needs more.  It bars splits of very wide layers only, which
+    // fill the chip without: (57344, 8192) in FP16 mode at 64 tokens 199 us in the four slices the model
+    // would take, 159 unsplit.  (Plain FP16 weights have no such entry point.)
+    const bool bounded = cls != 0 && static_scratch_holds(1, M, N, K, cls == 2, partial_ld(N));
     for (int split : {1, 2, 3, 4, 6, 8}) {
         if (t.large_split > 0) split = (int)(t.large_split < kt ? t.large_split : kt);
         else if (split > 1 && (split > kt / 4 || split > max_split)) break;
+        else if (bounded && !static_scratch_holds(split, M, N, K, cls == 2, partial_ld(N))) break;
         const int per = (kt + split - 1) / split;
         const int slices = (kt + per - 1) / per;
         const int64_t wgs = tiles * slices;

@@ -160,16 +160,16 @@ constexpr size_t workspace_need(size_t partial_bytes, int64_t M, int64_t K, bool
     return b > 0 ? b + kCounterBytes : 0;
 }
 
-// The entry point without a workspace argument has a fixed scratch, and takes every problem whose split fits
-// it with rows of N floats.  A split that only the padding of the rows would push past it is not taken -- by
-// any entry point, so that all of them give the same bits: (1221, 167, 22112) in FP8 mode needs 33545472
-// bytes in three slices unpadded, 33584384 padded.
+// The entry point without a workspace argument has a fixed scratch, and takes every problem that fits it.
 constexpr size_t kStaticScratch = (size_t)32 << 20;
+constexpr bool static_scratch_holds(int split, int64_t M, int64_t N, int64_t K, bool quantize, int64_t ld) {
+    return workspace_need(split > 1 ? (size_t)split * (size_t)M * (size_t)ld * sizeof(float) : 0, M, K, quantize) <= kStaticScratch;
+}
+// A split that only the padding of the rows would push past that scratch is not taken -- by any entry point, so
+// that all of them give the same bits: (1221, 167, 22112) in FP8 mode needs 33545472 bytes in three slices
+// unpadded, 33584384 padded.
 constexpr bool padded_split_fits(int split, int64_t M, int64_t N, int64_t K, bool quantize) {
-    if (split <= 1) return true;
-    const size_t rows = (size_t)split * (size_t)M * sizeof(float);
-    return workspace_need(rows * (size_t)partial_ld(N), M, K, quantize) <= kStaticScratch ||
-           workspace_need(rows * (size_t)N, M, K, quantize) > kStaticScratch;
+    return static_scratch_holds(split, M, N, K, quantize, partial_ld(N)) || !static_scratch_holds(split, M, N, K, quantize, N);
 }
 
 int launch_splitk_reduce(const float *partials, int S, int64_t M, int64_t N, const float *scales,

@@ -74,6 +74,22 @@ def test_problems_that_just_fit_the_fixed_scratch_unpadded_are_taken(L, M, N, K,
     assert 0 < L.nestedfp_gemm_workspace_size(M, N, K, mode) <= 32 << 20
 
 
+@pytest.mark.parametrize("M,N,K,mode", [
+    (28, 103011, 7200, 0), (26, 68414, 9520, 0), (32, 32814, 26768, 0), (64, 57344, 8192, 0), (21, 65540, 14880, 0),
+    (23, 60320, 34672, 1), (25, 172284, 8896, 1), (17, 139021, 9104, 1), (29, 165544, 9264, 1), (64, 128256, 4096, 1),
+])
+def test_wide_layers_of_decode_batches_fit_the_fixed_scratch_on_either_route(L, M, N, K, mode):
+    # up to 64 tokens a problem that fits the 32 MiB unsplit fits them whichever kernel it is sent to
+    i64, kind = ctypes.c_int64, 5 if mode else 4               # row-major planes, as the entry point takes them
+    route, small, large = L._ZN3nfp11route_smallEillll, L._ZN3nfp24small_gemm_partial_bytesEilll, L._ZN3nfp24large_gemm_partial_bytesEilll
+    route.restype, route.argtypes = ctypes.c_bool, [ctypes.c_int] + 4 * [i64]
+    for f in (small, large):
+        f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int] + 3 * [i64]
+    rest = 16384 + (M * K + 4 * M + 512 if mode else 0)
+    assert rest + max(small(kind, M, N, K), large(kind, M, N, K)) <= 32 << 20
+    assert route(kind, M, N, K, K) in (True, False)
+
+
 def test_argument_errors_are_reported_before_any_launch(L):
     P = ctypes.c_void_p
     fake = P(0x1000)         # aligned, never dereferenced: every call below fails validation first
