@@ -867,6 +867,292 @@ nested_bypass_kernel(LargeParams p) {
     Kern::run(p, lds_raw, (typename Kern::lds_byte *)lds_raw);
 }
 
+// ---- NestedFP16 from row-major planes, by pairs of K-tiles ------------------------------------------
+// The same layout of work as nested_bypass_kernel, but the planes reach their wave through LDS: both planes
+// of two K-tiles are copied there directly, 128 bytes of 8 rows per instruction, into a part of the LDS that
+// only this wave uses (4 KB for 16 weight rows), and a lane reads its 16 bytes of each plane from there one
+// K-tile before they are merged.  Loaded straight into registers in operand order, 16 rows x 64 bytes per
+// instruction, every 128-byte line is requested twice: a load-only kernel takes in 38 bytes per nanosecond
+// and CU so, and 137 by whole lines.
+// A pair's copies are under way while the pair before it is multiplied from registers (1.7 K-tiles).  The
+// one barrier of a K-tile sits behind the last read of its token stage, in the last slots of the second
+// substep: the next K-tile's tokens have to be there by then, and the stage is free from then on, so that
+// three stages give the token copies two K-tiles.
+template <int TM, int TN, bool NT>
+struct RowsKernel {
+    typedef TileStore<kNestedF16, TM, TN, 1, 8> Store;
+    static constexpr int DW = 4;                               // waves that issue the token copies
+    static constexpr int WTN = TN / 8;
+    static constexpr int FMB = TM / 16, FNB = WTN / 16;
+    static constexpr int MF = FMB * FNB;                       // MFMAs per substep
+    static constexpr int NST = TM > 192 ? 3 : 4;               // LDS stages of the token tile
+    static constexpr int XA = NST - 1;                         // token copies run this many K-tiles ahead
+    static constexpr int STAGE = TM * 128;
+    static constexpr int OWN = FNB * 4096;                     // both planes of a pair of K-tiles of the wave's rows
+    static constexpr int RING_BYTES = NST * STAGE;
+    static constexpr int LDS_BYTES = RING_BYTES + 8 * OWN > TM * TN * 2 ? RING_BYTES + 8 * OWN : TM * TN * 2;
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+    static constexpr int POLICY = NT ? 2 : 0;                  // see BypassKernel
+    static constexpr int XG = TM / 8 / DW;                     // token copies per loading wave and K-tile
+    static constexpr int WG = 4 * FNB;                         // weight copies per wave and pair
+    static constexpr int LEAD = 2;                             // token fragments are read this many blocks ahead
+    static constexpr int NMQ = 2 * FNB;                        // merges of four weights per substep
+    static constexpr int MQS = MF / NMQ;                       // slots between them
+    static constexpr int DQS = MF / XG;                        // slots between token copies
+    static constexpr int QB = MF - 2;                          // slot that starts with the barrier
+    // Second substep of a pair's second K-tile: the next pair's bytes are read in slots 0 .. 2 FNB - 1, two per slot,
+    // and the copies of the pair after it are issued from slot QW on, all before the barrier and spread out: bunched in
+    // consecutive slots, where every wave waits for the address queue, they cost 1.5 % at 256 x 256.
+    static constexpr int QW = 2 * FNB + 2;
+    static constexpr int WPS = (WG + (QB - QW) - 1) / (QB - QW);         // copies per slot that issues any
+    static constexpr int WSTR = WG <= QB - QW ? (QB - QW) / WG : 1;      // slots between them
+    static_assert(FNB <= 2 && FMB > LEAD && MF % NMQ == 0 && MF % XG == 0 && MQS >= 2 && QW > 2 * FNB && QB > QW, "slot plan");
+    typedef __attribute__((address_space(3))) uint8_t lds_byte;
+
+    struct Raw { u32x4 u[FNB], l[FNB]; };                      // one K-tile of the wave's weights: 16 bytes of each plane
+
+    struct Ctx {
+        floatx4 (&acc)[FNB][FMB];
+        intx4 (&a)[2][FNB];                                    // merged weight fragments of substeps 0 / 1
+        intx4 (&b)[2][FMB];                                    // token fragments (a few are live at a time)
+        Raw (&raw)[2];                                         // first and second K-tile of a pair
+        __amdgpu_buffer_rsrc_t rx, rw0, rw1;
+        uint32_t x_off, x_step, x_kpos, x_lim;                 // offset of the wave's first token copy, step between its copies
+        uint32_t w_off, w_step, w_kpos, w_lim;                 // rows 0 .. 7; step to rows 8 .. 15; column; end of the slice
+        uint32_t own, get;                                     // LDS: the wave's part, the lane's chunk of the first K-tile
+        uint8_t *lds;
+        lds_byte *lds3;
+        int wave, lane;
+        int kt, st, fill;                                      // K-tile, its LDS stage, the stage that is filled
+    };
+
+    static __device__ __forceinline__ int next(int st) { return st + 1 == NST ? 0 : st + 1; }
+
+    template <int J>
+    static __device__ __forceinline__ void read_b(intx4 &dst, const uint8_t *stage, int lane, int s) {
+        dst = *reinterpret_cast<const intx4 *>(stage + swz(16 * J + (lane & 15), 4 * s + (lane >> 4)));
+    }
+
+    // piece D (row tile D / 2; upper plane, lower plane) of a pair's first (P = 0) or second K-tile: chunk g or 4 + g of
+    // the lane's row, whose place differs in one bit
+    template <int P, int D>
+    static __device__ __forceinline__ void read_raw(Raw &r, const Ctx &c) {
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(c.lds + (P == 0 ? c.get : c.get ^ 64u) + D * 2048);
+        if constexpr (D % 2 == 0) r.u[D / 2] = v;
+        else r.l[D / 2] = v;
+    }
+    template <int D>
+    static __device__ __forceinline__ void read_pair(const Ctx &c) {     // D of 4 FNB
+        if constexpr (D < 2 * FNB) read_raw<0, D>(c.raw[0], c);
+        else read_raw<1, D - 2 * FNB>(c.raw[1], c);
+    }
+    // the bytes read above have arrived: from here on their place may be written
+    static __device__ __forceinline__ void have_pair(const Ctx &c) {
+#pragma unroll
+        for (int i = 0; i < FNB; ++i) {
+            asm volatile("" : "+v"(c.raw[0].u[i]), "+v"(c.raw[0].l[i]) :: "memory");
+            asm volatile("" : "+v"(c.raw[1].u[i]), "+v"(c.raw[1].l[i]) :: "memory");
+        }
+    }
+
+    // copy D of a pair that starts with K-tile kt: row tile D / 4, plane D / 2 % 2, rows 0 .. 7 or 8 .. 15; a chunk past
+    // the slice is sent out of range and arrives as zeros
+    static __device__ __forceinline__ void dma_w(const Ctx &c, int d, int kt) {
+        const uint32_t flip = (uint32_t)(d & 1) << 6;          // rows 8 .. 15 swizzle with the top bit set
+        const uint32_t col = (uint32_t)kt * 64u + (c.w_kpos ^ flip);
+        const uint32_t kill = col < c.w_lim ? 0u : 0x80000000u;
+        const uint32_t off = (c.w_off + (uint32_t)(2 * (d >> 2) + (d & 1)) * c.w_step + col) | kill;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds((d & 2) ? c.rw1 : c.rw0,
+            (__attribute__((address_space(3))) void *)(c.lds3 + c.own + (uint32_t)((d >> 1) * 2048 + (d & 1) * 1024)), 16, off, 0, 0, POLICY);
+    }
+
+    static __device__ __forceinline__ void dma_x(const Ctx &c, int i, int kt, int stage) {
+        const uint32_t kb = (uint32_t)kt * 128u;
+        const uint32_t kill = (kb + c.x_kpos < c.x_lim) ? 0u : 0x80000000u;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(c.rx, (__attribute__((address_space(3))) void *)(c.lds3 + stage * STAGE + (i * DW + c.wave) * 1024),
+                                                 16, (c.x_off + (uint32_t)i * c.x_step + kb) | kill, 0, 0, 0);
+    }
+
+    // four weights of row tile I: dwords H (substep 0) or 2 + H (substep 1) of the lane's chunk of each plane
+    template <int S, int I, int H>
+    static __device__ __forceinline__ void merge_part(intx4 &dst, const Raw &r) {
+        uint32_t w01, w23;
+        merge4(r.u[I][2 * S + H], r.l[I][2 * S + H], w01, w23);
+        dst[2 * H] = (int)w01;
+        dst[2 * H + 1] = (int)w23;
+    }
+
+    // PAR: first or second K-tile of a pair.  OLDER: one of the DW waves that copy tokens.
+    template <bool OLDER, int S, int PAR, int Q>
+    static __device__ __forceinline__ void slot(Ctx &c) {
+        constexpr int j = Q / FNB, i = Q % FNB;
+        if constexpr (S == 1 && Q == QB) {
+            // the last fragments of this stage have arrived, and the next K-tile's tokens have landed.  Younger than
+            // those in a loading wave: the tokens of the XA - 1 K-tiles after it and the weights copied in the
+            // XA K-tiles since.
+            asm volatile("" : "+v"(c.b[1][FMB - 1]), "+v"(c.b[1][FMB - 2]));
+            if constexpr (OLDER) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((XA - 1) * XG + (XA + PAR) / 2 * WG) : "memory");
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (S == 1 && PAR == 1) {
+            if constexpr (Q == 0) {
+                // the next pair has landed (this wave's own copies; younger: the tokens of two K-tiles)
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(OLDER ? 2 * XG : 0) : "memory");
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (Q == QW) {
+                have_pair(c);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        {
+            union { intx4 v; half8 h; } a, b;
+            a.v = c.a[S][i];
+            b.v = c.b[S][j];
+            c.acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, b.h, c.acc[i][j], 0, 0, 0);
+        }
+        // token fragments LEAD blocks ahead: this substep, the next one; those of the next K-tile behind the barrier
+        if constexpr (i == 0) {
+            if constexpr (j + LEAD < FMB) read_b<j + LEAD>(c.b[S][j + LEAD], c.lds + c.st * STAGE, c.lane, S);
+            else if constexpr (S == 0) read_b<j + LEAD - FMB>(c.b[1][j + LEAD - FMB], c.lds + c.st * STAGE, c.lane, 1);
+        }
+        if constexpr (S == 1 && Q >= QB) read_b<Q - QB>(c.b[0][Q - QB], c.lds + next(c.st) * STAGE, c.lane, 0);
+        if constexpr (S == 1 && PAR == 1) {
+            if constexpr (Q < 2 * FNB) {
+                read_pair<2 * Q>(c);
+                read_pair<2 * Q + 1>(c);
+            }
+            if constexpr (Q >= QW && Q < QB && (Q - QW) % WSTR == 0) {
+#pragma unroll
+                for (int d = (Q - QW) / WSTR * WPS; d < ((Q - QW) / WSTR + 1) * WPS && d < WG; ++d) dma_w(c, d, c.kt + 3);
+            }
+        }
+        if constexpr (Q % MQS == MQS - 1) {
+            // substep 0 merges this K-tile's second half, substep 1 the next K-tile's first half
+            constexpr int m = Q / MQS;
+            if constexpr (S == 0) merge_part<1, m / 2, m % 2>(c.a[1][m / 2], c.raw[PAR]);
+            else merge_part<0, m / 2, m % 2>(c.a[0][m / 2], c.raw[PAR ^ 1]);
+        }
+        if constexpr (OLDER && S == 0 && Q % DQS == 0) dma_x(c, Q / DQS, c.kt + XA, c.fill);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (Q + 1 < MF) slot<OLDER, S, PAR, Q + 1>(c);
+    }
+
+    template <bool OLDER, int PAR>
+    static __device__ __forceinline__ void k_tile(Ctx &c, int kt) {
+        c.kt = kt;
+        __builtin_amdgcn_sched_barrier(0);
+        slot<OLDER, 0, PAR, 0>(c);
+        slot<OLDER, 1, PAR, 0>(c);
+        c.fill = c.st;
+        c.st = next(c.st);
+    }
+
+    // whole pairs: the second K-tile of the last one may lie past the slice, where tokens and weights are zero
+    template <bool OLDER>
+    static __device__ __forceinline__ void k_loop(Ctx &c, int kt_begin, int kt_end) {
+        for (int kt = kt_begin; kt < kt_end; kt += 2) {
+            k_tile<OLDER, 0>(c, kt);
+            k_tile<OLDER, 1>(c, kt + 1);
+        }
+    }
+
+    static __device__ __forceinline__ void run(const LargeParams &p, uint8_t *lds, lds_byte *lds3) {
+        const int lane = threadIdx.x & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        int tm, tn;
+        tile_of_block(p, blockIdx.x, tm, tn);
+        const int m0 = tm * TM, n0 = tn * TN;
+        const int split = blockIdx.y;
+        const int kt_begin = split * p.ktiles_per_split;
+        const int kt_end = min(kt_begin + p.ktiles_per_split, p.ktiles_total);
+
+        floatx4 acc[FNB][FMB];
+#pragma unroll
+        for (int i = 0; i < FNB; ++i)
+#pragma unroll
+            for (int j = 0; j < FMB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        intx4 a[2][FNB], b[2][FMB];
+        Raw raw[2];
+        const int w_rows = min(TN, p.N - n0);
+        const uint32_t own = (uint32_t)(RING_BYTES + wave * OWN);
+        const int r16 = lane & 15, g = lane >> 4;
+        const int xch = fp16_chunk_of_slot((lane & 7) ^ ((((wave & 1) << 2) + g) & 7));      // (row >> 1) & 7 for row = 8 (4 i + wave) + lane / 8
+        Ctx c{acc, a, b, raw,
+              tile_rsrc(p.X, m0, min(TM, p.M - m0), p.x_row_bytes, p.k_bytes),
+              tile_rsrc(p.W0, n0, w_rows, p.w_row_bytes, p.K), tile_rsrc(p.W1, n0, w_rows, p.w_row_bytes, p.K),
+              (uint32_t)(wave * 8 + (lane >> 3)) * (uint32_t)p.x_row_bytes + 16u * xch, (uint32_t)(DW * 8) * (uint32_t)p.x_row_bytes,
+              16u * xch, slice_end(p, kt_end),
+              (uint32_t)(FNB * wave * 16 + (lane >> 3)) * (uint32_t)p.w_row_bytes, 8u * (uint32_t)p.w_row_bytes,
+              16u * (uint32_t)((lane & 7) ^ g), slice_end(p, kt_end) >> 1,                  // (rows 0 .. 7: (row >> 1) & 7 = lane / 16)
+              own, own + (uint32_t)r16 * 128u + (uint32_t)((g ^ (r16 >> 1)) << 4),
+              lds, lds3, wave, lane, kt_begin, 0, XA};
+        // the first pair of the weights, the first XA K-tiles of the tokens
+#pragma unroll
+        for (int d = 0; d < WG; ++d) dma_w(c, d, kt_begin);
+        if (wave < DW) {
+#pragma unroll
+            for (int d = 0; d < XA; ++d)
+#pragma unroll
+                for (int i = 0; i < XG; ++i) dma_x(c, i, kt_begin + d, d);
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((XA - 1) * XG) : "memory");
+        } else {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read_pair<0>(c);
+        read_pair<1>(c);
+        read_pair<2>(c);
+        read_pair<3>(c);
+        if constexpr (FNB > 1) {
+            read_pair<4>(c);
+            read_pair<5>(c);
+            read_pair<6>(c);
+            read_pair<7>(c);
+        }
+        read_b<0>(b[0][0], lds, lane, 0);
+        read_b<1>(b[0][1], lds, lane, 0);
+        have_pair(c);
+        // (its copies are the youngest before the loop, as those of any later pair are when the next K-tile begins)
+#pragma unroll
+        for (int d = 0; d < WG; ++d) dma_w(c, d, kt_begin + 2);
+        merge_part<0, 0, 0>(a[0][0], raw[0]);
+        merge_part<0, 0, 1>(a[0][0], raw[0]);
+        if constexpr (FNB > 1) {
+            merge_part<0, FNB - 1, 0>(a[0][FNB - 1], raw[0]);
+            merge_part<0, FNB - 1, 1>(a[0][FNB - 1], raw[0]);
+        }
+        if (wave < DW) k_loop<true>(c, kt_begin, kt_end);
+        else k_loop<false>(c, kt_begin, kt_end);
+        // copies of K-tiles past the end are still in flight: they must have landed before the LDS is reused
+        // for the output tile or handed back
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // (keeps the epilogue's address arithmetic behind the loop, where registers are free)
+        int lane_out = lane;
+        asm volatile("" : "+v"(lane_out));
+        if (p.row_store && gridDim.y == 1) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the look-ahead fragment reads
+            __syncthreads();
+            Store::epilogue_lds(p, acc, m0, n0, 0, wave, lane_out, wave, lds);
+        } else {
+            Store::epilogue(p, acc, m0, n0, 0, wave, lane_out, split);
+        }
+    }
+};
+
+template <int TM, int TN, bool NT>
+__global__ void __launch_bounds__(512)
+nested_rows_kernel(LargeParams p) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
+    typedef RowsKernel<TM, TN, NT> Kern;
+    Kern::run(p, lds_raw, (typename Kern::lds_byte *)lds_raw);
+}
+
 // ---- FP8 mode on at most 64 tokens per tile: E4M3 weights through registers ---------------------
 // The same layout of work as nested_bypass_kernel (eight waves side by side along the weight rows,
 // packed 1 KB blocks loaded 16 bytes per lane, token tile in a ring of four LDS stages), for
@@ -1322,6 +1608,18 @@ static void launch_bypass(const LargeParams &p, dim3 grid, hipStream_t stream) {
     kern<<<grid, 512, lds, stream>>>(p);
 }
 
+template <int TM, int TN, bool NT = false>
+static void launch_rows(const LargeParams &p, dim3 grid, hipStream_t stream) {
+    auto kern = nested_rows_kernel<TM, TN, NT>;
+    constexpr int lds = RowsKernel<TM, TN, NT>::LDS_BYTES;
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set.load(std::memory_order_acquire)) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        attr_set.store(true, std::memory_order_release);
+    }
+    kern<<<grid, 512, lds, stream>>>(p);
+}
+
 template <int TM, int TN, bool ROWMAJOR, bool NT = false>
 static void launch_e4m3_bypass(const LargeParams &p, dim3 grid, hipStream_t stream) {
     if constexpr (ROWMAJOR && !NT) {
@@ -1359,8 +1657,9 @@ static void launch_large_k(const LargeParams &p, const LargeConfig &c, dim3 grid
     }
 }
 
-// Row-major planes on tiles of 128 weight rows: by pairs of K-tiles (see BypassKernel::PAIR; up to 45 % faster)
-// where the longer look-ahead pays.  Timed both ways on 2760 launches (26 values of K from 512 to 17344, four N,
+// Row-major planes on the 64-token tiles and in the deeper pipeline, 128 weight rows per tile: by pairs of K-tiles (see
+// BypassKernel::PAIR; up to 45 % faster) where the longer look-ahead pays.  Timed both ways on 2760 launches, tiles of
+// 128 and 256 tokens among them, which by now have a kernel of their own (26 values of K from 512 to 17344, four N,
 // twelve batch sizes, every split): the rule is 0.4 % behind the faster way on average and at most 8 % behind
 // unpaired loads (the rule "12 K-tiles per slice" was 1.3 % and 23 %).
 //  - Rows that start on lines: a dozen K-tiles per slice (64 tokens per tile 1.07-1.12 x at 12 K-tiles and 1.2 x at
@@ -1385,31 +1684,71 @@ bool rows_by_pairs(int tm, int64_t M, int64_t N, int64_t K, int64_t row_bytes, i
     return weights >= 6 * mi && kt >= (tiles_m <= 4 ? 32 : 48);
 }
 
-template <int TM, bool DEEP = false>
-static void launch_rows128(const LargeParams &p, dim3 grid, hipStream_t stream) {
-    const bool nt = streams_rows(p) && (TM == 64 || (TM == 128 && (int64_t)p.N * p.K >= ((int64_t)100 << 20)));
-    const bool pairs = rows_by_pairs(TM, p.M, p.N, p.K, p.w_row_bytes, (int)grid.y);
-    if (!pairs) launch_bypass<TM, 128, kNestedF16Row, DEEP>(p, grid, stream);
-    else if (nt) launch_bypass<TM, 128, kNestedF16Row, DEEP, TM != 256, true>(p, grid, stream);
+// Row-major planes on the other tiles: through LDS by pairs of K-tiles (RowsKernel), or straight into registers in operand
+// order, K-tile by K-tile.  Timed both ways on 14700 launches (22 values of K from 512 to 8192, six N, twelve batch
+// sizes, four tile shapes, splits of 1 ... 4): the rule is 0.5 % behind the faster way on average (everything straight
+// into registers: 5 %) and at most 10 % behind loads into registers.
+//  - Rows that start on lines: through LDS (1.01-1.06 x at less than a dozen K-tiles per slice, 1.15-1.24 x from three
+//    dozen on), but on 128 x 128 tiles from a dozen K-tiles on (0.99 x on average below, 0.81 x at worst).
+//  - Slices with an odd number of such K-tiles: every second one starts in the middle of a line, so that its pieces take
+//    two lines each, and the last pair is half empty: a dozen K-tiles, on 256 x 256 tiles four dozen.
+//  - Rows that start inside lines, where pieces share lines but unpaired loads take whole halves if the row is a multiple
+//    of 64 bytes: longer slices and rows, all the more where several token tiles read them from the caches.
+bool rows_through_lds(int tm, int tn, int64_t M, int64_t K, int64_t row_bytes, int split) {
+    const int64_t kt = (K + 63) / 64, per = (kt + split - 1) / split, tiles_m = (M + tm - 1) / tm;
+    if ((row_bytes & 127) == 0) {
+        if (per < kt && (per & 1)) return per >= (tm == 256 && tn == 256 ? 48 : 12);
+        return per >= 12 || tm > 128 || tn > 128;
+    }
+    if ((row_bytes & 63) == 0) return per >= 20 && kt >= (tiles_m == 1 ? 24 : 48);
+    return per >= 14 && kt >= (tiles_m == 1 ? 20 : 36);
+}
+
+template <int TM, bool DEEP>
+static void launch_rows_by_pairs(const LargeParams &p, dim3 grid, hipStream_t stream) {
+    const bool nt = streams_rows(p) && (TM == 64 || (int64_t)p.N * p.K >= ((int64_t)100 << 20));
+    if (!rows_by_pairs(TM, p.M, p.N, p.K, p.w_row_bytes, (int)grid.y)) launch_bypass<TM, 128, kNestedF16Row, DEEP>(p, grid, stream);
+    else if (nt) launch_bypass<TM, 128, kNestedF16Row, DEEP, true, true>(p, grid, stream);
     else launch_bypass<TM, 128, kNestedF16Row, DEEP, false, true>(p, grid, stream);
 }
 
-// weights through registers: NestedFP16 in either storage order, packed FP16
+template <int TM, int TN>
+static void launch_rows_tile(const LargeParams &p, dim3 grid, hipStream_t stream) {
+    if (!rows_through_lds(TM > 128 ? 256 : 128, TN, p.M, p.K, p.w_row_bytes, (int)grid.y)) {
+        launch_bypass<TM, TN, kNestedF16Row>(p, grid, stream);
+        return;
+    }
+    if constexpr (TM == 128 && TN == 128) {
+        if (streams_rows(p) && (int64_t)p.N * p.K >= ((int64_t)100 << 20)) { launch_rows<TM, TN, true>(p, grid, stream);  return; }
+    }
+    launch_rows<TM, TN>(p, grid, stream);
+}
+
+// weights through registers: NestedFP16 in either storage order, packed FP16.
+template <int WK, int TM>
+static void launch_nested_tm(const LargeParams &p, const LargeConfig &c, dim3 grid, hipStream_t stream) {
+    if constexpr (WK == kNestedF16Row) {
+        if (c.tn == 128) launch_rows_tile<TM, 128>(p, grid, stream);
+        else launch_rows_tile<TM, 256>(p, grid, stream);
+    } else {
+        if (c.tn == 128) launch_bypass<TM, 128, WK>(p, grid, stream);
+        else launch_bypass<TM, 256, WK>(p, grid, stream);
+    }
+}
+
 template <int WK>
 static void launch_nested(const LargeParams &p, const LargeConfig &c, dim3 grid, hipStream_t stream) {
+    if (c.tm == 256) { launch_nested_tm<WK, 256>(p, c, grid, stream);  return; }
     if constexpr (WK == kNestedF16Row) {
-        if (c.tn == 128) {
-            if (c.tm == 64) launch_rows128<64>(p, grid, stream);
-            else if (c.tm == 256) launch_rows128<256>(p, grid, stream);
-            else if (c.deep) launch_rows128<128, true>(p, grid, stream);
-            else launch_rows128<128>(p, grid, stream);
-            return;
-        }
+        if (c.tm == 64) launch_rows_by_pairs<64, false>(p, grid, stream);
+        else if (c.deep && c.tn == 128) launch_rows_by_pairs<128, true>(p, grid, stream);
+        else if (c.deep) launch_bypass<128, 256, WK, true>(p, grid, stream);
+        else launch_nested_tm<WK, 128>(p, c, grid, stream);
+        return;
     }
-    if (c.tm == 64) launch_bypass<64, 128, WK>(p, grid, stream);
-    else if (c.tm == 256 && c.tn == 256) launch_bypass<256, 256, WK>(p, grid, stream);
-    else if (c.tm == 256) launch_bypass<256, 128, WK>(p, grid, stream);
-    else {
+    if (c.tm == 64) {
+        launch_bypass<64, 128, WK>(p, grid, stream);
+    } else {
         // one token tile over a large packed layer: weights marked non-temporal (see BypassKernel)
         if constexpr (WK != kNestedF16Row) {
             if (p.tiles_m == 1 && (int64_t)p.N * p.K >= ((int64_t)100 << 20)) {
