@@ -1516,6 +1516,62 @@ static bool tuned_large(int cls, int64_t M, int64_t N, int64_t K, LargeConfig &c
     return false;
 }
 
+// Token tiles of 256 are cut down to the height that the batch needs: as many tiles as before, all of them the same
+// multiple of 32 tokens high.  777 tokens are four tiles of 224 instead of three of 256 and one of 9; what is left out
+// are rows that only padding would fill, the sums are the same.  Register-path kernels, (28672, 4096): 150 tokens
+// 83.6 -> 66.9 us (row-major planes), 300 tokens 120 -> 96 us.
+static int token_tile(int tm, int64_t M) {
+    if (tm != 256) return tm;
+    const int64_t tiles = (M + 255) / 256;
+    const int h = (int)(((M + tiles - 1) / tiles + 31) / 32 * 32);
+    return h < 160 ? 160 : h;
+}
+
+// 65 ... 256 tokens, operands through registers: every tile shape, the 64-token tiles included, priced by what was
+// found to add up -- the rounds of workgroups, the weights, what all workgroups take in from L2 (weights and
+// tokens) and what the busiest CU does.  Fitted to timings of every shape and split on 960 problems (layers of 0.8 to
+// 470 Mi weights, both storage orders): its choice is 1.7 % behind the fastest launch on average, where the model
+// below, which knows neither the 64-token tiles nor the kernels of the row-major planes, was 7 % behind (9 % up to 128 tokens).
+static LargeConfig choose_short(int64_t M, int64_t N, int64_t K) {
+    static const struct { int tm, tn; double tk, tfix; } kShape[5] = {
+        {256, 256, 0.725, 6.05}, {256, 128, 0.421, 2.63}, {128, 256, 0.500, 2.61}, {128, 128, 0.2785, 0.83}, {64, 128, 0.271, 0.51}};
+    const Tuning &t = tuning();
+    const int kt = (int)((K + 63) / 64);
+    LargeConfig c;
+    c.tm = 128;  c.tn = 128;  c.split = 1;  c.deep = 0;
+    double best = 1e30;
+    for (int sh = 0; sh < 5; ++sh) {
+        const int tm = kShape[sh].tm, tn = kShape[sh].tn;
+        if (t.large_bm > 0 && t.large_bm != tm) continue;
+        if (t.large_bn > 0 && t.large_bn != tn) continue;
+        const int height = token_tile(tm, M);
+        const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
+        double tk = kShape[sh].tk, tfix = kShape[sh].tfix;
+        if (tm == 256) {                               // between the tiles of 128 and of 256 tokens
+            const double f = (height - 128) / 128.0;
+            tk = kShape[sh + 2].tk + f * (tk - kShape[sh + 2].tk);
+            tfix = kShape[sh + 2].tfix + f * (tfix - kShape[sh + 2].tfix);
+        }
+        for (int split : kSplits) {
+            if (t.large_split > 0) split = (int)(t.large_split < kt ? t.large_split : kt);
+            // (a split's scratch fits the fixed one of nestedfp_gemm_static, which takes every problem unsplit)
+            else if (split > 1 && (split > kt / 4 || !static_scratch_holds(split, M, N, K, false, partial_ld(N)))) break;
+            const int per = (kt + split - 1) / split;
+            const int slices = (kt + per - 1) / per;
+            const double wgs = (double)(tiles * slices), rounds = (double)((tiles * slices + 255) / 256);
+            double time = rounds * (tfix + per * tk);
+            if (tn == 128 && tm <= 128 && rounds > 1) time /= 1.045;
+            time += 3.0 + 2.0 * (double)N * (double)K / 15.2e6 + wgs * per * (height + tn) * 128.0 / 219e6 +
+                    rounds * per * (double)(std::min<int64_t>(height, M) + tn) * 128.0 / 167e3;
+            if (slices > 1) time += split_cost(M, N, slices, 3.45, 5.28e6);
+            if (time < best) { best = time;  c.tm = tm;  c.tn = tn;  c.split = split; }
+            if (t.large_split > 0) break;
+        }
+    }
+    c.cost = best;
+    return c;
+}
+
 static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, int max_split = 8) {
     LargeConfig c;
     c.cost = 0.0;
@@ -1527,6 +1583,7 @@ static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, int m
         return c;
     if (t.large_bm == 64 || (M <= 64 && t.large_bm < 0 && t.large_bn < 0))
         return choose_tile64(cls, M, N, K);
+    if (cls == 1 && M <= 256 && t.large_deep <= 0) return choose_short(M, N, K);
     double best = 1e30;
     c.tm = c.tn = 256;
     c.split = 1;
@@ -1542,7 +1599,14 @@ static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, int m
         for (int deep = 0; deep < 2; ++deep) {
             if (deep && (kDeepTileCost[cls][sh].tk == 0.0 || t.large_deep == 0)) continue;
             if (!deep && t.large_deep > 0 && kDeepTileCost[cls][sh].tk != 0.0) continue;
-            const TileCost &tc = deep ? kDeepTileCost[cls][sh] : kTileCost[cls][sh];
+            TileCost tc = deep ? kDeepTileCost[cls][sh] : kTileCost[cls][sh];
+            if (cls == 1 && bm == 256) {
+                // a tile cut down to the batch lies between those of 128 and of 256 tokens
+                const double f = (token_tile(256, M) - 128) / 128.0;
+                const TileCost &low = kTileCost[cls][sh + 2];
+                tc.tk = low.tk + f * (tc.tk - low.tk);
+                tc.tfix = low.tfix + f * (tc.tfix - low.tfix);
+            }
             for (int split : kSplits) {
                 if (t.large_split > 0) split = (int)(t.large_split < kt ? t.large_split : kt);
                 else if (split > 1 && (split > kt / 4 || split > max_split)) break;
@@ -1724,7 +1788,8 @@ static void launch_rows_tile(const LargeParams &p, dim3 grid, hipStream_t stream
     launch_rows<TM, TN>(p, grid, stream);
 }
 
-// weights through registers: NestedFP16 in either storage order, packed FP16.
+// weights through registers: NestedFP16 in either storage order, packed FP16.  TM: c.tm, or the height the token
+// tiles are cut down to (see token_tile)
 template <int WK, int TM>
 static void launch_nested_tm(const LargeParams &p, const LargeConfig &c, dim3 grid, hipStream_t stream) {
     if constexpr (WK == kNestedF16Row) {
@@ -1737,8 +1802,11 @@ static void launch_nested_tm(const LargeParams &p, const LargeConfig &c, dim3 gr
 }
 
 template <int WK>
-static void launch_nested(const LargeParams &p, const LargeConfig &c, dim3 grid, hipStream_t stream) {
-    if (c.tm == 256) { launch_nested_tm<WK, 256>(p, c, grid, stream);  return; }
+static void launch_nested(const LargeParams &p, const LargeConfig &c, int height, dim3 grid, hipStream_t stream) {
+    if (height == 256) { launch_nested_tm<WK, 256>(p, c, grid, stream);  return; }
+    if (height == 224) { launch_nested_tm<WK, 224>(p, c, grid, stream);  return; }
+    if (height == 192) { launch_nested_tm<WK, 192>(p, c, grid, stream);  return; }
+    if (height == 160) { launch_nested_tm<WK, 160>(p, c, grid, stream);  return; }
     if constexpr (WK == kNestedF16Row) {
         if (c.tm == 64) launch_rows_by_pairs<64, false>(p, grid, stream);
         else if (c.deep && c.tn == 128) launch_rows_by_pairs<128, true>(p, grid, stream);
@@ -1806,7 +1874,8 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     p.Y = a.Y;  p.ldy = a.ldy;
     p.partials = a.partials;
     p.ldp = (int)partial_ld(a.N);
-    p.tiles_m = (int)((a.M + c.tm - 1) / c.tm);
+    const int height = kind_class(kind) == 1 ? token_tile(c.tm, a.M) : c.tm;
+    p.tiles_m = (int)((a.M + height - 1) / height);
     p.tiles_n = (int)((a.N + c.tn - 1) / c.tn);
     p.ktiles_total = (p.k_bytes + 127) / 128;
     p.ktiles_per_split = (p.ktiles_total + c.split - 1) / c.split;
@@ -1818,9 +1887,9 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)c.split);
     switch (kind) {
         case kPlainF16: launch_large_k<kPlainF16>(p, c, grid, stream); break;
-        case kNestedF16: launch_nested<kNestedF16>(p, c, grid, stream); break;
-        case kNestedF16Row: launch_nested<kNestedF16Row>(p, c, grid, stream); break;
-        case kPlainF16Packed: launch_nested<kPlainF16Packed>(p, c, grid, stream); break;
+        case kNestedF16: launch_nested<kNestedF16>(p, c, height, grid, stream); break;
+        case kNestedF16Row: launch_nested<kNestedF16Row>(p, c, height, grid, stream); break;
+        case kPlainF16Packed: launch_nested<kPlainF16Packed>(p, c, height, grid, stream); break;
         case kE4M3: launch_large_k<kE4M3>(p, c, grid, stream); break;
         case kE4M3Row: launch_large_k<kE4M3Row>(p, c, grid, stream); break;
         default: return kErrArg;

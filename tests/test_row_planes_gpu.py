@@ -1,9 +1,11 @@
-"""GPU parity of the tiled kernel that brings row-major planes through LDS (pairs of K-tiles)."""
+"""GPU parity of the tiled kernels: row-major planes through LDS, token tiles cut down to the batch."""
 import ctypes
 
+import numpy as np
 import pytest
 
 from paper_2506_02024_amd import workloads
+from helpers import bits, to_dev
 from test_gemm_gpu import run_both_modes
 
 pytestmark = pytest.mark.gpu
@@ -45,3 +47,32 @@ def test_row_planes_through_lds(nfp, M, N, K, bm, bn, split, lds):
     finally:
         for k in knobs:
             nfp.tune(k, -1)
+
+
+@pytest.mark.parametrize("M,N,K,bn,split", [
+    # token tiles of 256 cut down to 160, 192 and 224 tokens: first and last batch of each, several tiles, K-tails
+    (97, 260, 64 * 3 + 16, 256, 1), (160, 140, 64 * 5, 128, 1), (161, 140, 64 * 8, 128, 2), (192, 270, 64 * 4, 256, 1),
+    (193, 130, 64 * 21 + 32, 128, 1), (224, 520, 64 * 12, 256, 2), (225, 264, 64 * 4, 256, 1),
+    (257, 264, 64 * 6, 256, 1), (385, 264, 64 * 9 + 48, 256, 1), (449, 136, 64 * 4, 128, 1), (620, 264, 64 * 22, 128, 2), (777, 300, 64 * 2, 256, 1),
+])
+def test_token_tiles_cut_down_to_the_batch(nfp, M, N, K, bn, split):
+    knobs = {"small_max_m": 0, "large_bm": 256, "large_bn": bn, "large_split": split}
+    try:
+        for k, v in knobs.items():
+            nfp.tune(k, v)
+        X, W = workloads.act_host(M, K, seed=N), workloads.weight_host(N, K, seed=M)
+        run_both_modes(nfp, X, W, "%d x %d, M=%d %s" % (N, K, M, knobs), check_plain=False)
+        # the same tiles without the merge
+        Xd, Wd = to_dev(X), to_dev(W)
+        up, lo = nfp.decompose(Wd)
+        assert np.array_equal(bits(nfp.gemm(Xd, up, lo, nfp.MODE_FP16)), bits(nfp.plain_gemm_fp16(Xd, nfp.pack_fp16(Wd))))
+    finally:
+        for k in knobs:
+            nfp.tune(k, -1)
+
+
+@pytest.mark.parametrize("M,N,K", [(65, 4096, 1024), (66, 300, 640), (128, 1536, 2064), (129, 640, 4096), (200, 2056, 1040), (255, 130, 5120), (256, 3000, 768)])
+def test_short_batches_in_their_own_launch_shapes(nfp, M, N, K):
+    # 65 ... 256 tokens with no knob set: every shape the launch may take fits the fixed scratch
+    assert nfp.gemm_workspace_size(M, N, K, nfp.MODE_FP16) <= nfp.STATIC_SCRATCH_BYTES
+    run_both_modes(nfp, workloads.act_host(M, K, seed=N), workloads.weight_host(N, K, seed=M), "%d x %d, M=%d" % (N, K, M))
