@@ -118,7 +118,7 @@ struct TileStore {
     static constexpr int WAVES = WAVES_M * WAVES_N;
     static constexpr int WTM = TM / WAVES_M, WTN = TN / WAVES_N;
     static constexpr int MB = MB_;
-    static constexpr int FMB = WTM / MB, FNB = WTN / MB;
+    static constexpr int FMB = (WTM + MB - 1) / MB, FNB = WTN / MB;      // (WTM: on average, see LargeKernel::UNEVEN)
     typedef typename std::conditional<MB == 32, floatx16, floatx4>::type AccT;
 
     // Result tile through LDS: the MFMA layout leaves a lane with 4 consecutive outputs of one
@@ -131,12 +131,14 @@ struct TileStore {
     static __device__ __forceinline__ float scaled(float x, float s) { return kind_is_fp8(KIND) ? scale_f32(x, s) : x; }
     static __device__ __forceinline__ int acc_col(int lane, int v) { return MB == 32 ? 8 * v + 4 * (lane >> 5) : 4 * (lane >> 4); }
 
-    static __device__ __forceinline__ void epilogue_lds(const LargeParams &p, AccT (&acc)[FNB][FMB], int m0, int n0,
-                                                        int wm, int wn, int lane, int wave, uint8_t *lds) {
+    // row0: the wave's first token row within the tile, F: its token blocks
+    template <int F>
+    static __device__ __forceinline__ void to_lds(const LargeParams &p, AccT (&acc)[FNB][FMB], int m0, int row0, int wn, int lane,
+                                                  uint8_t *lds) {
         const int r = lane % MB;
 #pragma unroll
-        for (int j = 0; j < FMB; ++j) {
-            const int row = wm * WTM + MB * j + r;
+        for (int j = 0; j < F; ++j) {
+            const int row = row0 + MB * j + r;
             float s = 1.0f;
             if (kind_is_fp8(KIND)) {
                 const int m = m0 + row;
@@ -154,7 +156,14 @@ struct TileStore {
                     *reinterpret_cast<u32x2 *>(lds + row * (TN * 2) + ((chunk ^ (row & (OCH - 1))) << 4) + 8 * ((col >> 2) & 1)) = o;
                 }
         }
+    }
+    static __device__ __forceinline__ void epilogue_lds(const LargeParams &p, AccT (&acc)[FNB][FMB], int m0, int n0,
+                                                        int row0, int wn, int lane, int wave, uint8_t *lds) {
+        to_lds<FMB>(p, acc, m0, row0, wn, lane, lds);
         __syncthreads();
+        store_rows(p, m0, n0, lane, wave, lds);
+    }
+    static __device__ __forceinline__ void store_rows(const LargeParams &p, int m0, int n0, int lane, int wave, const uint8_t *lds) {
         constexpr int RPI = 64 / OCH;                  // rows per store instruction
         constexpr int ROWS = TM / WAVES;               // rows per wave
         const int chunk = lane % OCH;
@@ -168,12 +177,13 @@ struct TileStore {
         }
     }
 
+    template <int F = FMB>
     static __device__ __forceinline__ void epilogue(const LargeParams &p, AccT (&acc)[FNB][FMB], int m0, int n0,
-                                                    int wm, int wn, int lane, int split) {
+                                                    int row0, int wn, int lane, int split) {
         const int r = lane % MB;
 #pragma unroll
-        for (int j = 0; j < FMB; ++j) {
-            const int m = m0 + wm * WTM + MB * j + r;
+        for (int j = 0; j < F; ++j) {
+            const int m = m0 + row0 + MB * j + r;
             if (m >= p.M) continue;
             float s = 1.0f;
             if (kind_is_fp8(KIND) && gridDim.y == 1) s = p.scales[m] * p.w_scale;
@@ -209,7 +219,9 @@ struct TileStore {
 // NST: LDS stages.  Two are enough where a K-tile's MFMAs outlast the latency of the next K-tile's
 // loads (256 x 256 tiles) or two workgroups share a CU; a launch with at most one workgroup per CU
 // and smaller tiles takes three or four, so that loads run NST - 1 K-tiles ahead.
-template <int KIND, int TM, int TN, int WAVES_M, int WAVES_N, int NST = 2>
+// NSTW: stages of the weights.  On tiles of 256 weight rows, two stages of both and a third one of the weights alone
+// take the 160 KB: tokens come from L2, within a K-tile, weights from memory, in two.
+template <int KIND, int TM, int TN, int WAVES_M, int WAVES_N, int NST = 2, int NSTW = NST>
 struct LargeKernel {
     static_assert(KIND == kPlainF16 || KIND == kE4M3 || KIND == kE4M3Row, "NestedFP16 has a kernel of its own");
     static constexpr bool FP8 = kind_is_fp8(KIND);
@@ -218,9 +230,10 @@ struct LargeKernel {
     static_assert(WAVES == 8, "two waves per SIMD: one loading (older), one not");
     static constexpr int THREADS = 64 * WAVES;
     static constexpr int WTM = TM / WAVES_M, WTN = TN / WAVES_N;
-    static constexpr int STAGE = (TM + TN) * 128;      // bytes per LDS stage
-    static constexpr int LDS_BYTES = NST * STAGE;
-    static_assert(NST >= 2 && LDS_BYTES <= 160 * 1024, "LDS stages");
+    static constexpr int XSTAGE = TM * 128, WSTAGE = TN * 128;       // bytes per LDS stage
+    static constexpr int XBASE = NSTW * WSTAGE;        // the token stages follow the weights'
+    static constexpr int LDS_BYTES = XBASE + NST * XSTAGE;
+    static_assert(NST >= 2 && (NSTW == NST || NSTW == NST + 1) && LDS_BYTES <= 160 * 1024, "LDS stages");
     typedef TileStore<KIND, TM, TN, WAVES_M, WAVES_N> Store;
     static_assert(TM * TN * 2 <= LDS_BYTES, "output tile must fit into the operand stages");
 
@@ -236,8 +249,12 @@ struct LargeKernel {
     static constexpr int MB = FP8 ? 32 : 16;
     static constexpr int SUBS = 2;
     static constexpr int NCH = FP8 ? 2 : 1;
-    static constexpr int FMB = WTM / MB, FNB = WTN / MB;
-    static constexpr int MF = FMB * FNB;                             // MFMAs per substep
+    // UNEVEN: tiles of 160 and 224 tokens, an odd number of 32-token blocks for two waves: the older four waves,
+    // which issue the loads as well, take one block less than the younger four (two waves of a SIMD are one of each).
+    static constexpr bool UNEVEN = WTM % MB != 0;
+    static_assert(!UNEVEN || (WAVES_M == 2 && WAVES_N == 4), "one wave of each kind per SIMD");
+    static constexpr int FMB = (WTM + MB - 1) / MB, FNB = WTN / MB;
+    template <bool OLDER> static constexpr int blocks() { return UNEVEN && OLDER ? FMB - 1 : FMB; }
     typedef typename std::conditional<MB == 32, floatx16, floatx4>::type AccT;
     // Slot plan of a substep.  The MFMAs run token block by token block (the FNB weight
     // fragments stay, the token fragments stream).  The first NPRE fragments of a substep (all
@@ -246,16 +263,19 @@ struct LargeKernel {
     // their use.  The one barrier of a K-tile sits in its second substep behind the last read of
     // the current stage (slot QB): from there on the stage is free for K-tile kt+2; the loads of
     // kt+2 and the first reads of kt+1 follow it.
-    static constexpr int NB0 = FMB < 2 ? FMB : 2;
-    static constexpr int NPRE = FNB + NB0;
-    static constexpr int NREST = FMB - NB0;
-    static constexpr int RSTR = (3 * FNB) / 4 > 0 ? (3 * FNB) / 4 : 1;        // slots between the early token reads
-    static constexpr int QB = NREST > 0 ? (NREST - 1) * RSTR + (MB == 32 ? 2 : 3) : 0;   // slot that starts with the barrier
-    static constexpr int RPT = (NPRE + (MF - QB) - 1) / (MF - QB);            // look-ahead reads per tail slot
-    static constexpr int TSLOTS = (NPRE + RPT - 1) / RPT;                     // tail slots that read
-    static constexpr int TSTR = (MF - QB) / TSLOTS;                           // slots between them
-    static constexpr int TAIL0 = MF - TSLOTS * TSTR;
-    static_assert(QB < MF && TAIL0 >= QB && TSTR >= 1, "slot plan");
+    template <int F> struct Plan {                                   // F: token blocks of the wave
+        static constexpr int MF = F * FNB;                           // MFMAs per substep
+        static constexpr int NB0 = F < 2 ? F : 2;
+        static constexpr int NPRE = FNB + NB0;
+        static constexpr int NREST = F - NB0;
+        static constexpr int RSTR = (3 * FNB) / 4 > 0 ? (3 * FNB) / 4 : 1;        // slots between the early token reads
+        static constexpr int QB = NREST > 0 ? (NREST - 1) * RSTR + (MB == 32 ? 2 : 3) : 0;   // slot that starts with the barrier
+        static constexpr int RPT = (NPRE + (MF - QB) - 1) / (MF - QB);            // look-ahead reads per tail slot
+        static constexpr int TSLOTS = (NPRE + RPT - 1) / RPT;                     // tail slots that read
+        static constexpr int TSTR = (MF - QB) / TSLOTS;                           // slots between them
+        static constexpr int TAIL0 = MF - TSLOTS * TSTR;
+        static_assert(QB < MF && TAIL0 >= QB && TSTR >= 1, "slot plan");
+    };
 
     struct Frags { intx4 a[FNB][NCH]; intx4 b[FMB][NCH]; };
 
@@ -273,23 +293,23 @@ struct LargeKernel {
 
     // fragment R of substep s in the order of first use: weight blocks 0..FNB-1, token blocks 0..FMB-1
     template <int R>
-    static __device__ __forceinline__ void read_frag(Frags &f, const uint8_t *stage, int wm, int wn, int lane, int s) {
+    static __device__ __forceinline__ void read_frag(Frags &f, const uint8_t *wstage, const uint8_t *xstage, int row0, int wn, int lane, int s) {
         const int r = lane % MB, g = lane / MB;
 #pragma unroll
         for (int q = 0; q < NCH; ++q) {
             if constexpr (R < FNB)
-                f.a[R][q] = *reinterpret_cast<const intx4 *>(stage + w_addr(wn * WTN + MB * R + r, s, g, q));
+                f.a[R][q] = *reinterpret_cast<const intx4 *>(wstage + w_addr(wn * WTN + MB * R + r, s, g, q));
             else
                 f.b[R - FNB][q] = *reinterpret_cast<const intx4 *>(
-                    stage + TN * 128 + swz(wm * WTM + MB * (R - FNB) + r, k_chunk(s, g, q)));
+                    xstage + swz(row0 + MB * (R - FNB) + r, k_chunk(s, g, q)));
         }
     }
 
     template <int R, int END>
-    static __device__ __forceinline__ void read_frags(Frags &f, const uint8_t *stage, int wm, int wn, int lane, int s) {
+    static __device__ __forceinline__ void read_frags(Frags &f, const uint8_t *wstage, const uint8_t *xstage, int row0, int wn, int lane, int s) {
         if constexpr (R < END) {
-            read_frag<R>(f, stage, wm, wn, lane, s);
-            read_frags<R + 1, END>(f, stage, wm, wn, lane, s);
+            read_frag<R>(f, wstage, xstage, row0, wn, lane, s);
+            read_frags<R + 1, END>(f, wstage, xstage, row0, wn, lane, s);
         }
     }
 
@@ -322,7 +342,6 @@ struct LargeKernel {
     static constexpr int XG = TM / 8 / DW;             // 8-row groups per loading wave, token tile
     static constexpr int WG8 = TN / 8 / DW;            // 8-row groups per loading wave, weight tile
     static constexpr int DMAS = XG + WG8;              // loads per loading wave per K-tile
-    static constexpr int DPS = (DMAS + (MF - QB) - 1) / (MF - QB);     // loads per slot behind the barrier
 
     struct DmaOffsets {
         uint32_t x[XG], w[WG8];
@@ -353,23 +372,26 @@ struct LargeKernel {
 
     typedef __attribute__((address_space(3))) uint8_t lds_byte;
 
-    // the i-th of a wave's XG + WG8 direct-to-LDS loads of one K-tile (token rows first);
+    // the i-th of a wave's XG + WG8 direct-to-LDS loads of one K-tile (token rows first, of K-tile kt into stage xst, weights of
+    // ktw into wst);
     // i is a constant at every call site
     static __device__ __forceinline__ void dma_one(int i, const DmaOffsets &o, uint32_t x_lim, uint32_t w_lim,
                                                    __amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw,
-                                                   lds_byte *stage, int wave, int kt) {
-        const uint32_t kb = (uint32_t)kt * 128u;
+                                                   lds_byte *lds3, int xst, int wst, int wave, int kt, int ktw) {
         if (i < XG) {
+            const uint32_t kb = (uint32_t)kt * 128u;
             const uint32_t kill = (kb + o.kpos < x_lim) ? 0u : 0x80000000u;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void *)(stage + TN * 128 + (i * DW + wave) * 1024),
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void *)(lds3 + XBASE + xst * XSTAGE + (i * DW + wave) * 1024),
                                                      16, (o.x[i] + kb) | kill, 0, 0, 0);
         } else {
             const int j = i - XG;
+            const uint32_t kb = (uint32_t)ktw * 128u;
+            lds_byte *stage = lds3 + wst * WSTAGE;
             if (PACKED_W) {
                 // w_lim = block columns of the plane; past them the load is sent out of range
-                const uint32_t kill = ((uint32_t)(2 * kt + o.wbit) < w_lim) ? 0u : 0x80000000u;
+                const uint32_t kill = ((uint32_t)(2 * ktw + o.wbit) < w_lim) ? 0u : 0x80000000u;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void *)(stage + (j * DW + wave) * 1024),
-                                                         16, (o.w[j] + (uint32_t)kt * 2048u) | kill, 0, 0, 0);
+                                                         16, (o.w[j] + (uint32_t)ktw * 2048u) | kill, 0, 0, 0);
             } else {
                 const uint32_t kill = (kb + o.kpos < w_lim) ? 0u : 0x80000000u;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void *)(stage + (j * DW + wave) * 1024),
@@ -391,20 +413,23 @@ struct LargeKernel {
         uint8_t *lds;
         lds_byte *lds3;
         uint32_t x_lim, w_lim;
-        int wave, lane, wm, wn;
-        int kt, cur, nxt;                               // K-tile, its LDS stage, the next K-tile's
+        int wave, lane, row0, wn;                       // row0: the wave's first token row
+        int kt, cur, nxt, wcur, wnxt;                   // K-tile, its token and weight stages, the next K-tile's
     };
 
     template <bool OLDER, int S, int PAR, int Q>
     static __device__ __forceinline__ void slot(Ctx &c) {
+        typedef Plan<blocks<OLDER>()> P;
+        constexpr int MF = P::MF, QB = P::QB, RSTR = P::RSTR, NREST = P::NREST, NPRE = P::NPRE;
+        constexpr int DPS = (DMAS + (MF - QB) - 1) / (MF - QB);        // loads per slot behind the barrier
         constexpr bool last = (S == SUBS - 1);
         if constexpr (last && Q == QB) {
             // every read of the current stage has been issued; once all waves are here and their
-            // loads of the next K-tile have landed (those of the NST - 2 K-tiles after it may stay
-            // in flight), the stage is free and the next one complete
-            if constexpr (OLDER) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NST - 2) * DMAS) : "memory");
+            // loads of the next K-tile have landed (those of the NST - 2 K-tiles after it, and a further stage of
+            // weights, may stay in flight), the stage is free and the next one complete
+            if constexpr (OLDER) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NST - 2) * DMAS + (NSTW > NST ? WG8 : 0)) : "memory");
             else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if constexpr (NST == 2) {
+            if constexpr (NSTW == 2) {
                 __syncthreads();
             } else {
                 // a bare barrier: the fence of __syncthreads() would drain the loads in flight.  What
@@ -418,16 +443,17 @@ struct LargeKernel {
         }
         mfma_one<Q>(c.fr[PAR], c.acc);
         if constexpr (Q % RSTR == 0 && Q / RSTR < NREST)
-            read_frag<FNB + NB0 + Q / RSTR>(c.fr[PAR], c.lds + c.cur * STAGE, c.wm, c.wn, c.lane, S);
-        if constexpr (Q >= TAIL0 && (Q - TAIL0) % TSTR == 0 && (Q - TAIL0) / TSTR < TSLOTS) {
-            constexpr int r0 = (Q - TAIL0) / TSTR * RPT;
-            read_frags<r0, (r0 + RPT < NPRE ? r0 + RPT : NPRE)>(c.fr[PAR ^ 1], c.lds + (last ? c.nxt : c.cur) * STAGE, c.wm, c.wn,
+            read_frag<FNB + P::NB0 + Q / RSTR>(c.fr[PAR], c.lds + c.wcur * WSTAGE, c.lds + XBASE + c.cur * XSTAGE, c.row0, c.wn, c.lane, S);
+        if constexpr (Q >= P::TAIL0 && (Q - P::TAIL0) % P::TSTR == 0 && (Q - P::TAIL0) / P::TSTR < P::TSLOTS) {
+            constexpr int r0 = (Q - P::TAIL0) / P::TSTR * P::RPT;
+            read_frags<r0, (r0 + P::RPT < NPRE ? r0 + P::RPT : NPRE)>(c.fr[PAR ^ 1], c.lds + (last ? c.wnxt : c.wcur) * WSTAGE,
+                                                                c.lds + XBASE + (last ? c.nxt : c.cur) * XSTAGE, c.row0, c.wn,
                                                                 c.lane, last ? 0 : S + 1);
         }
         if constexpr (last && OLDER && Q >= QB) {
 #pragma unroll
             for (int d = (Q - QB) * DPS; d < (Q - QB + 1) * DPS && d < DMAS; ++d)
-                dma_one(d, c.dof, c.x_lim, c.w_lim, c.rx, c.rw, c.lds3 + c.cur * STAGE, c.wave, c.kt + NST);
+                dma_one(d, c.dof, c.x_lim, c.w_lim, c.rx, c.rw, c.lds3, c.cur, c.wcur, c.wave, c.kt + NST, c.kt + NSTW);
         }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (Q + 1 < MF) slot<OLDER, S, PAR, Q + 1>(c);
@@ -435,12 +461,15 @@ struct LargeKernel {
 
     template <bool OLDER>
     static __device__ __forceinline__ void k_loop(Ctx &c, int kt_begin, int kt_end) {
-        int cur = 0;
+        int cur = 0, wcur = 0;
         for (int kt = kt_begin; kt < kt_end; ++kt) {
             c.kt = kt;
             c.cur = cur;
             cur = cur + 1 == NST ? 0 : cur + 1;
             c.nxt = cur;
+            c.wcur = NSTW == NST ? c.cur : wcur;
+            wcur = wcur + 1 == NSTW ? 0 : wcur + 1;
+            c.wnxt = NSTW == NST ? c.nxt : wcur;
             __builtin_amdgcn_sched_barrier(0);
             slot<OLDER, 0, 0, 0>(c);
             slot<OLDER, 1, 1, 0>(c);
@@ -450,7 +479,8 @@ struct LargeKernel {
     static __device__ __forceinline__ void run(const LargeParams &p, uint8_t *lds, lds_byte *lds3) {
         const int lane = threadIdx.x & 63;
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const int wm = wave % WAVES_M, wn = wave / WAVES_M;
+        const int wm = UNEVEN ? wave / WAVES_N : wave % WAVES_M, wn = UNEVEN ? wave % WAVES_N : wave / WAVES_M;
+        const int row0 = UNEVEN ? wm * blocks<true>() * MB : wm * WTM;
         int tm, tn;
         tile_of_block(p, blockIdx.x, tm, tn);
         const int m0 = tm * TM, n0 = tn * TN;
@@ -468,17 +498,23 @@ struct LargeKernel {
         const uint32_t x_lim = slice_end(p, kt_end);
         const uint32_t w_lim = PACKED_W ? (uint32_t)min(p.kblocks, 2 * kt_end) : x_lim;
 
-        // NST LDS stages; tokens and weights go straight from global memory into LDS.
+        // Tokens and weights go straight from global memory into LDS.
         if (wave < DW) {
 #pragma unroll
-            for (int st = 0; st < NST; ++st)
+            for (int st = 0; st < NSTW; ++st)
 #pragma unroll
-                for (int i = 0; i < DMAS; ++i)
-                    dma_one(i, dof, x_lim, w_lim, rx, rw, lds3 + st * STAGE, wave, kt_begin + st);
+                for (int i = st < NST ? 0 : XG; i < DMAS; ++i)
+                    dma_one(i, dof, x_lim, w_lim, rx, rw, lds3, st, st, wave, kt_begin + st, kt_begin + st);
         }
         // the loads of K-tile kt_begin (a wave that issued none passes straight through)
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * DMAS) : "memory");
-        __syncthreads();
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * DMAS + (NSTW - NST) * WG8) : "memory");
+        if constexpr (NSTW == 2) {
+            __syncthreads();
+        } else {
+            asm volatile("" ::: "memory");                     // (a bare barrier, as in the loop)
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
 
         AccT acc[FNB][FMB];
 #pragma unroll
@@ -488,8 +524,9 @@ struct LargeKernel {
 #pragma unroll
                 for (int q = 0; q < (MB == 32 ? 16 : 4); ++q) acc[i][j][q] = 0.f;
         Frags fr[2];
-        Ctx c{acc, fr, dof, rx, rw, lds, lds3, x_lim, w_lim, wave, lane, wm, wn, kt_begin, 0, 0};
-        read_frags<0, NPRE>(fr[0], lds, wm, wn, lane, 0);
+        Ctx c{acc, fr, dof, rx, rw, lds, lds3, x_lim, w_lim, wave, lane, row0, wn, kt_begin, 0, 0, 0, 0};
+        static_assert(Plan<blocks<true>()>::NPRE == Plan<blocks<false>()>::NPRE, "the first fragments are read before the roles part");
+        read_frags<0, Plan<FMB>::NPRE>(fr[0], lds, lds + XBASE, row0, wn, lane, 0);
         if (wave < DW) k_loop<true>(c, kt_begin, kt_end);
         else k_loop<false>(c, kt_begin, kt_end);
         // the loads of the K-tiles past the end are still in flight: they must have landed
@@ -498,19 +535,23 @@ struct LargeKernel {
         if (p.row_store && gridDim.y == 1) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the look-ahead fragment reads
             __syncthreads();
-            Store::epilogue_lds(p, acc, m0, n0, wm, wn, lane, wave, lds);
+            if (UNEVEN && wave < DW) Store::template to_lds<blocks<true>()>(p, acc, m0, row0, wn, lane, lds);
+            else Store::template to_lds<FMB>(p, acc, m0, row0, wn, lane, lds);
+            __syncthreads();
+            Store::store_rows(p, m0, n0, lane, wave, lds);
+        } else if (UNEVEN && wave < DW) {
+            Store::template epilogue<blocks<true>()>(p, acc, m0, n0, row0, wn, lane, split);
         } else {
-            Store::epilogue(p, acc, m0, n0, wm, wn, lane, split);
+            Store::template epilogue<FMB>(p, acc, m0, n0, row0, wn, lane, split);
         }
     }
-
 };
 
-template <int KIND, int TM, int TN, int WAVES_M, int WAVES_N, int NST>
+template <int KIND, int TM, int TN, int WAVES_M, int WAVES_N, int NST, int NSTW>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
 large_gemm_kernel(LargeParams p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
-    typedef LargeKernel<KIND, TM, TN, WAVES_M, WAVES_N, NST> Kern;
+    typedef LargeKernel<KIND, TM, TN, WAVES_M, WAVES_N, NST, NSTW> Kern;
     Kern::run(p, lds_raw, (typename Kern::lds_byte *)lds_raw);
 }
 
@@ -1518,53 +1559,70 @@ static bool tuned_large(int cls, int64_t M, int64_t N, int64_t K, LargeConfig &c
 
 // Token tiles of 256 are cut down to the height that the batch needs: as many tiles as before, all of them the same
 // multiple of 32 tokens high.  777 tokens are four tiles of 224 instead of three of 256 and one of 9; what is left out
-// are rows that only padding would fill, the sums are the same.  Register-path kernels, (28672, 4096): 150 tokens
-// 83.6 -> 66.9 us (row-major planes), 300 tokens 120 -> 96 us.
+// are rows that only padding would fill, the sums are the same.  (28672, 4096), FP16 mode: 150 tokens
+// 83.6 -> 66.9 us (row-major planes), 300 tokens 120 -> 96 us; FP8 mode gains 1-8 %.
 static int token_tile(int tm, int64_t M) {
     if (tm != 256) return tm;
     const int64_t tiles = (M + 255) / 256;
     const int h = (int)(((M + tiles - 1) / tiles + 31) / 32 * 32);
     return h < 160 ? 160 : h;
 }
+// ... by the kernels that exist in these heights: register-path tiles, the 256 x 256 tile of E4M3
+static bool cuts_tiles(int cls, int tn) { return cls == 1 || (cls == 2 && tn == 256); }
 
-// 65 ... 256 tokens, operands through registers: every tile shape, the 64-token tiles included, priced by what was
-// found to add up -- the rounds of workgroups, the weights, what all workgroups take in from L2 (weights and
-// tokens) and what the busiest CU does.  Fitted to timings of every shape and split on 960 problems (layers of 0.8 to
-// 470 Mi weights, both storage orders): its choice is 1.7 % behind the fastest launch on average, where the model
-// below, which knows neither the 64-token tiles nor the kernels of the row-major planes, was 7 % behind (9 % up to 128 tokens).
-static LargeConfig choose_short(int64_t M, int64_t N, int64_t K) {
-    static const struct { int tm, tn; double tk, tfix; } kShape[5] = {
-        {256, 256, 0.725, 6.05}, {256, 128, 0.421, 2.63}, {128, 256, 0.500, 2.61}, {128, 128, 0.2785, 0.83}, {64, 128, 0.271, 0.51}};
+// 65 ... 256 tokens of the two classes whose tiles of 256 tokens are cut down: every tile shape, the 64-token tiles
+// included, priced by what was found to add up -- the rounds of workgroups, the weights, what all workgroups take in
+// from L2 (weights and tokens) and what the busiest CU does.  Fitted to timings of every shape and split (and both
+// pipeline depths of E4M3, of which the deeper one is all that is left) on 960 problems in FP16 mode and 1020 in FP8
+// mode, layers of 0.8 to 470 Mi weights, both storage orders: the choice is 1.7 % and 3.3 % behind the fastest launch on
+// average, where the model below, which knows neither the 64-token tiles nor the newer kernels, was 7 % and 10 % behind.
+struct ShortShape { int tm, tn, deep; double tk, tfix, tk160, tfix160; };      // microseconds per K-tile and per workgroup; at a height of 160
+struct ShortCost {
+    ShortShape shape[5];
+    double pair128, pair64;             // workgroups of a CU that run together
+    double base, w_rate, l2_rate, cu_rate, split, split_rate;
+};
+static const ShortCost kShortCost[2] = {
+    // FP16 operands through registers
+    {{{256, 256, 0, 0.725, 6.05, 0.556, 3.47}, {256, 128, 0, 0.421, 2.63, 0.314, 1.28}, {128, 256, 0, 0.500, 2.61, 0, 0},
+      {128, 128, 0, 0.2785, 0.83, 0, 0}, {64, 128, 0, 0.271, 0.51, 0, 0}}, 1.045, 1.045, 3.0, 15.2e6, 219e6, 167e3, 3.45, 5.28e6},
+    // E4M3
+    {{{256, 256, 0, 0.6255, 3.16, 0.378, 3.16}, {256, 128, 1, 0.319, 2.41, 0.319, 2.41}, {128, 256, 1, 0.334, 2.71, 0, 0},
+      {128, 128, 1, 0.2136, 1.73, 0, 0}, {64, 128, 0, 0.183, 1.54, 0, 0}}, 1.0, 1.10, 2.0, 10.4e6, 1e15, 144e3, 3.28, 4.68e6},
+};
+static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K) {
+    const bool fp8 = cls == 2;
+    const ShortCost &m = kShortCost[fp8 ? 1 : 0];
     const Tuning &t = tuning();
-    const int kt = (int)((K + 63) / 64);
+    const int kt = (int)(((fp8 ? K : 2 * K) + 127) / 128);
+    const bool bounded = static_scratch_holds(1, M, N, K, fp8, partial_ld(N));
     LargeConfig c;
     c.tm = 128;  c.tn = 128;  c.split = 1;  c.deep = 0;
     double best = 1e30;
-    for (int sh = 0; sh < 5; ++sh) {
-        const int tm = kShape[sh].tm, tn = kShape[sh].tn;
-        if (t.large_bm > 0 && t.large_bm != tm) continue;
-        if (t.large_bn > 0 && t.large_bn != tn) continue;
-        const int height = token_tile(tm, M);
-        const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
-        double tk = kShape[sh].tk, tfix = kShape[sh].tfix;
-        if (tm == 256) {                               // between the tiles of 128 and of 256 tokens
-            const double f = (height - 128) / 128.0;
-            tk = kShape[sh + 2].tk + f * (tk - kShape[sh + 2].tk);
-            tfix = kShape[sh + 2].tfix + f * (tfix - kShape[sh + 2].tfix);
+    for (const ShortShape &e : m.shape) {
+        if (t.large_bm > 0 && t.large_bm != e.tm) continue;
+        if (t.large_bn > 0 && t.large_bn != e.tn) continue;
+        const int height = cuts_tiles(cls, e.tn) ? token_tile(e.tm, M) : e.tm;
+        const int64_t tiles = ((M + e.tm - 1) / e.tm) * ((N + e.tn - 1) / e.tn);
+        double tk = e.tk, tfix = e.tfix;
+        if (e.tm == 256) {
+            const double f = (height - 160) / 96.0;
+            tk = e.tk160 + f * (e.tk - e.tk160);
+            tfix = e.tfix160 + f * (e.tfix - e.tfix160);
         }
         for (int split : kSplits) {
             if (t.large_split > 0) split = (int)(t.large_split < kt ? t.large_split : kt);
-            // (a split's scratch fits the fixed one of nestedfp_gemm_static, which takes every problem unsplit)
-            else if (split > 1 && (split > kt / 4 || !static_scratch_holds(split, M, N, K, false, partial_ld(N)))) break;
+            // (a split's scratch fits the fixed one of nestedfp_gemm_static wherever the problem does without)
+            else if (split > 1 && (split > kt / 4 || (bounded && !static_scratch_holds(split, M, N, K, fp8, partial_ld(N))))) break;
             const int per = (kt + split - 1) / split;
             const int slices = (kt + per - 1) / per;
             const double wgs = (double)(tiles * slices), rounds = (double)((tiles * slices + 255) / 256);
             double time = rounds * (tfix + per * tk);
-            if (tn == 128 && tm <= 128 && rounds > 1) time /= 1.045;
-            time += 3.0 + 2.0 * (double)N * (double)K / 15.2e6 + wgs * per * (height + tn) * 128.0 / 219e6 +
-                    rounds * per * (double)(std::min<int64_t>(height, M) + tn) * 128.0 / 167e3;
-            if (slices > 1) time += split_cost(M, N, slices, 3.45, 5.28e6);
-            if (time < best) { best = time;  c.tm = tm;  c.tn = tn;  c.split = split; }
+            if (rounds > 1 && e.tn == 128 && e.tm <= 128) time /= e.tm == 64 ? m.pair64 : m.pair128;
+            time += m.base + (double)N * (double)K * (fp8 ? 1.0 : 2.0) / m.w_rate + wgs * per * (height + e.tn) * 128.0 / m.l2_rate +
+                    rounds * per * (double)(std::min<int64_t>(height, M) + e.tn) * 128.0 / m.cu_rate;
+            if (slices > 1) time += split_cost(M, N, slices, m.split, m.split_rate);
+            if (time < best) { best = time;  c.tm = e.tm;  c.tn = e.tn;  c.split = split;  c.deep = e.deep; }
             if (t.large_split > 0) break;
         }
     }
@@ -1583,7 +1641,8 @@ static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, int m
         return c;
     if (t.large_bm == 64 || (M <= 64 && t.large_bm < 0 && t.large_bn < 0))
         return choose_tile64(cls, M, N, K);
-    if (cls == 1 && M <= 256 && t.large_deep <= 0) return choose_short(M, N, K);
+    const bool pinned = t.large_bm > 0 || t.large_bn > 0 || t.large_split > 0;
+    if (M <= 256 && ((cls == 1 && t.large_deep <= 0) || (cls == 2 && t.large_deep < 0 && !pinned))) return choose_short(cls, M, N, K);
     double best = 1e30;
     c.tm = c.tn = 256;
     c.split = 1;
@@ -1599,19 +1658,21 @@ static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, int m
         for (int deep = 0; deep < 2; ++deep) {
             if (deep && (kDeepTileCost[cls][sh].tk == 0.0 || t.large_deep == 0)) continue;
             if (!deep && t.large_deep > 0 && kDeepTileCost[cls][sh].tk != 0.0) continue;
-            TileCost tc = deep ? kDeepTileCost[cls][sh] : kTileCost[cls][sh];
-            if (cls == 1 && bm == 256) {
-                // a tile cut down to the batch lies between those of 128 and of 256 tokens
-                const double f = (token_tile(256, M) - 128) / 128.0;
-                const TileCost &low = kTileCost[cls][sh + 2];
-                tc.tk = low.tk + f * (tc.tk - low.tk);
-                tc.tfix = low.tfix + f * (tc.tfix - low.tfix);
-            }
+            const TileCost &whole = deep ? kDeepTileCost[cls][sh] : kTileCost[cls][sh];
             for (int split : kSplits) {
                 if (t.large_split > 0) split = (int)(t.large_split < kt ? t.large_split : kt);
                 else if (split > 1 && (split > kt / 4 || split > max_split)) break;
                 const int per = (kt + split - 1) / split;                     // K-tiles per workgroup
                 const int slices = (kt + per - 1) / per;
+                TileCost tc = whole;
+                if (cls == 1 && bm == 256 && static_scratch_holds(slices, M, N, K, false, partial_ld(N))) {
+                    // A tile cut down to the batch lies between those of 128 and of 256 tokens.  (Splits that outgrow the
+                    // fixed scratch are priced as whole tiles, as ever, so that none is taken in place of one that fits.)
+                    const double f = (token_tile(256, M) - 128) / 128.0;
+                    const TileCost &low = kTileCost[cls][sh + 2];
+                    tc.tk = low.tk + f * (tc.tk - low.tk);
+                    tc.tfix = low.tfix + f * (tc.tfix - low.tfix);
+                }
                 const int64_t rounds = (tiles * slices + 255) / 256;
                 double time = (double)rounds * (tc.tfix + per * tc.tk);
                 if (sh == 3 && rounds >= 2 && !deep) time /= kPairSpeedup[cls];
@@ -1640,10 +1701,10 @@ size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K) {
     return c.split > 1 ? (size_t)c.split * (size_t)M * (size_t)partial_ld(N) * sizeof(float) : 0;
 }
 
-template <int KIND, int TM, int TN, int WAVES_M, int WAVES_N, int NST = 2>
+template <int KIND, int TM, int TN, int WAVES_M, int WAVES_N, int NST = 2, int NSTW = NST>
 static void launch_large_t(const LargeParams &p, dim3 grid, hipStream_t stream) {
-    auto kern = large_gemm_kernel<KIND, TM, TN, WAVES_M, WAVES_N, NST>;
-    constexpr int lds = LargeKernel<KIND, TM, TN, WAVES_M, WAVES_N, NST>::LDS_BYTES;
+    auto kern = large_gemm_kernel<KIND, TM, TN, WAVES_M, WAVES_N, NST, NSTW>;
+    constexpr int lds = LargeKernel<KIND, TM, TN, WAVES_M, WAVES_N, NST, NSTW>::LDS_BYTES;
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -1702,13 +1763,18 @@ static void launch_e4m3_bypass(const LargeParams &p, dim3 grid, hipStream_t stre
     kern<<<grid, 512, lds, stream>>>(p);
 }
 
-// weights through LDS: plain row-major FP16, E4M3 in either storage order
+// weights through LDS: plain row-major FP16, E4M3 in either storage order (height: see token_tile)
 template <int KIND>
-static void launch_large_k(const LargeParams &p, const LargeConfig &c, dim3 grid, hipStream_t stream) {
+static void launch_large_k(const LargeParams &p, const LargeConfig &c, int height, dim3 grid, hipStream_t stream) {
+    if constexpr (kind_is_fp8(KIND)) {
+        if (height == 224) { launch_large_t<KIND, 224, 256, 2, 4, 2, 3>(p, grid, stream);  return; }
+        if (height == 192) { launch_large_t<KIND, 192, 256, 2, 4, 2, 3>(p, grid, stream);  return; }
+        if (height == 160) { launch_large_t<KIND, 160, 256, 2, 4, 3>(p, grid, stream);  return; }
+    }
     if (c.tm == 64) {
         if constexpr (KIND == kPlainF16) launch_large_t<KIND, 64, 128, 2, 4>(p, grid, stream);
         else launch_e4m3_bypass<64, 128, KIND == kE4M3Row>(p, grid, stream);
-    } else if (c.tm == 256 && c.tn == 256) launch_large_t<KIND, 256, 256, 2, 4>(p, grid, stream);
+    } else if (c.tm == 256 && c.tn == 256) launch_large_t<KIND, 256, 256, 2, 4, 2, 3>(p, grid, stream);
     else if (c.tm == 256) {
         if (c.deep) launch_large_t<KIND, 256, 128, 4, 2, 3>(p, grid, stream);
         else launch_large_t<KIND, 256, 128, 4, 2>(p, grid, stream);
@@ -1874,7 +1940,7 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     p.Y = a.Y;  p.ldy = a.ldy;
     p.partials = a.partials;
     p.ldp = (int)partial_ld(a.N);
-    const int height = kind_class(kind) == 1 ? token_tile(c.tm, a.M) : c.tm;
+    const int height = cuts_tiles(kind_class(kind), c.tn) ? token_tile(c.tm, a.M) : c.tm;
     p.tiles_m = (int)((a.M + height - 1) / height);
     p.tiles_n = (int)((a.N + c.tn - 1) / c.tn);
     p.ktiles_total = (p.k_bytes + 127) / 128;
@@ -1886,12 +1952,12 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     if (tuning().large_epilogue == 0) p.row_store = 0;
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)c.split);
     switch (kind) {
-        case kPlainF16: launch_large_k<kPlainF16>(p, c, grid, stream); break;
+        case kPlainF16: launch_large_k<kPlainF16>(p, c, height, grid, stream); break;
         case kNestedF16: launch_nested<kNestedF16>(p, c, height, grid, stream); break;
         case kNestedF16Row: launch_nested<kNestedF16Row>(p, c, height, grid, stream); break;
         case kPlainF16Packed: launch_nested<kPlainF16Packed>(p, c, height, grid, stream); break;
-        case kE4M3: launch_large_k<kE4M3>(p, c, grid, stream); break;
-        case kE4M3Row: launch_large_k<kE4M3Row>(p, c, grid, stream); break;
+        case kE4M3: launch_large_k<kE4M3>(p, c, height, grid, stream); break;
+        case kE4M3Row: launch_large_k<kE4M3Row>(p, c, height, grid, stream); break;
         default: return kErrArg;
     }
     if (hipGetLastError() != hipSuccess) return kErrHip;
