@@ -120,9 +120,10 @@ struct PlanCache {
 };
 
 int launch_decompose(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, uint8_t *upper,
-                     uint8_t *lower, uint64_t *counter, bool packed, hipStream_t stream);
-int launch_range_check(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, uint64_t *counter,
+                     uint8_t *lower, uint64_t *counter, bool clear, bool packed, hipStream_t stream);      // clear: the counter starts at zero
+int launch_range_check(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, uint64_t *counter, bool clear,
                        hipStream_t stream);
+int launch_hand_on_count(uint64_t *counter, uint64_t *dev, uint64_t *host, hipStream_t stream);
 int launch_zero_u64(uint64_t *p, hipStream_t stream);
 int launch_reconstruct(const uint8_t *upper, const uint8_t *lower, int64_t N, int64_t K,
                        uint16_t *W, int64_t ldw, bool packed, hipStream_t stream);

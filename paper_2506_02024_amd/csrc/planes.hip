@@ -206,6 +206,15 @@ repack_kernel(const uint8_t *__restrict__ src, uint8_t *__restrict__ dst, int64_
 
 __global__ void zero_u64_kernel(uint64_t *p) { *p = 0; }
 
+// Hands a finished count on to the caller's device word and to host memory, and clears the counter.  The counter is
+// taken by an atomic exchange, like the additions to it: every XCD has an L2 of its own, and a plain load may find
+// a line there from before they were made.
+__global__ void hand_on_count_kernel(uint64_t *counter, uint64_t *dev, uint64_t *host) {
+    const uint64_t n = __hip_atomic_exchange(counter, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *dev = n;
+    __hip_atomic_store(host, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __global__ void zero_words_kernel(uint32_t *p, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
@@ -222,6 +231,11 @@ int launch_zero_u64(uint64_t *p, hipStream_t stream) {
     return hip_ok(hipGetLastError());
 }
 
+int launch_hand_on_count(uint64_t *counter, uint64_t *dev, uint64_t *host, hipStream_t stream) {
+    hand_on_count_kernel<<<1, 1, 0, stream>>>(counter, dev, host);
+    return hip_ok(hipGetLastError());
+}
+
 static int plane_grid(int64_t total_chunks) {
     // one chunk per lane for small tensors; up to four per lane (grid-stride) for large ones
     int64_t blocks = (total_chunks + kPlaneThreads - 1) / kPlaneThreads;
@@ -235,8 +249,8 @@ size_t plane_bytes(int64_t N, int64_t K) {
 }
 
 int launch_decompose(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, uint8_t *upper,
-                     uint8_t *lower, uint64_t *counter, bool packed, hipStream_t stream) {
-    if (counter) zero_u64_kernel<<<1, 1, 0, stream>>>(counter);
+                     uint8_t *lower, uint64_t *counter, bool clear, bool packed, hipStream_t stream) {
+    if (counter && clear) zero_u64_kernel<<<1, 1, 0, stream>>>(counter);
     if (packed) {
         BlockMap map = block_map(N, K);
         decompose_kernel<<<plane_grid(map.blocks * 64), kPlaneThreads, 0, stream>>>(W, ldw, map, upper, lower,
@@ -249,10 +263,10 @@ int launch_decompose(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, uint8
     return hip_ok(hipGetLastError());
 }
 
-int launch_range_check(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, uint64_t *counter,
+int launch_range_check(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, uint64_t *counter, bool clear,
                        hipStream_t stream) {
     ChunkMap map{K / 16, N * (K / 16)};
-    zero_u64_kernel<<<1, 1, 0, stream>>>(counter);
+    if (clear) zero_u64_kernel<<<1, 1, 0, stream>>>(counter);
     range_check_kernel<<<plane_grid(map.total), kPlaneThreads, 0, stream>>>(W, ldw, map, counter);
     return hip_ok(hipGetLastError());
 }
