@@ -191,6 +191,13 @@ public:
     }
 };
 
+// One for all calls, whatever they count: the device's counters are one array.  (Never destroyed: calls may come until
+// the process ends.)
+static PinnedCounts &pinned_counts() {
+    static PinnedCounts *const counts = new PinnedCounts;
+    return *counts;
+}
+
 // Runs `count(counter, clear)`, which launches the kernels that add up out-of-range weights, and leaves the count in
 // *dev and, if host is given, there too after the stream has been waited for.  With host, the kernels add to a counter
 // of the library's own that is zero already, and a single thread behind them hands the count on to *dev and to pinned
@@ -199,8 +206,7 @@ public:
 template <typename Count>
 static int counted(uint64_t *dev, uint64_t *host, hipStream_t stream, Count count) {
     if (host == nullptr) return count(dev, dev != nullptr);
-    static PinnedCounts *const counts = new PinnedCounts;         // (never destroyed: calls may come until the process ends)
-    const PinnedCounts::Slot slot = counts->take();
+    const PinnedCounts::Slot slot = pinned_counts().take();
     if (slot.word == nullptr) {
         const int st = count(dev, true);
         if (st != kOk) return st;
@@ -214,7 +220,7 @@ static int counted(uint64_t *dev, uint64_t *host, hipStream_t stream, Count coun
     if (st == kOk) st = launch_hand_on_count(slot.counter, dev, slot.word, stream);
     if (st != kOk || hipStreamSynchronize(stream) != hipSuccess) return NESTEDFP_ERR_HIP;    // (what may still be written is kept)
     const uint64_t n = *static_cast<volatile uint64_t *>(slot.word);
-    counts->give_back(slot);
+    pinned_counts().give_back(slot);
     *host = n;
     return n == 0 ? NESTEDFP_OK : NESTEDFP_ERR_RANGE;
 }

@@ -206,9 +206,8 @@ repack_kernel(const uint8_t *__restrict__ src, uint8_t *__restrict__ dst, int64_
 
 __global__ void zero_u64_kernel(uint64_t *p) { *p = 0; }
 
-// Hands a finished count on to the caller's device word and to host memory, and clears the counter.  The counter is
-// taken by an atomic exchange, like the additions to it: every XCD has an L2 of its own, and a plain load may find
-// a line there from before they were made.
+// Hands a finished count on to the caller's device word and to host memory, and clears the counter, which is taken by an
+// atomic exchange like the additions to it.
 __global__ void hand_on_count_kernel(uint64_t *counter, uint64_t *dev, uint64_t *host) {
     const uint64_t n = __hip_atomic_exchange(counter, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *dev = n;
