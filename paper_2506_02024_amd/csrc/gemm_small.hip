@@ -299,8 +299,8 @@ small_gemm_kernel(SmallParams p) {
     };
 
     WItem buf0[SPW], buf1[SPW];
-    __shared__ uint32_t row_max[KIND == kE4M3Quant ? 16 * 16 : 1];   // per wave and token row
-    float row_scale = 1.0f;
+    __shared__ uint32_t row_max[kind_quantizes(KIND) ? 16 * 16 : 1];   // per wave and token row
+    __shared__ float row_scale[kind_quantizes(KIND) ? 16 : 1];
     const int passes = MULTIPASS ? p.k_passes : 1;
     for (int pass = 0; pass < passes; ++pass) {
         const int k_slice = ((slice * passes + pass) * waves + ks) * (SPW * KSTEP);
@@ -318,63 +318,77 @@ small_gemm_kernel(SmallParams p) {
 #pragma unroll
             for (int q = 0; q < SPW; ++q) va[q] = q < row_pieces<KIND, SPW>() && kb + 128 * q < p.K * L::EB;
         }
-        if (KIND == kE4M3Quant) {
-            // Fused activation quantisation (Sec. 2.2 per-token scaling; one token tile, the
-            // workgroup covers all of K): every wave loads the FP16 activations of its own slice,
-            // the row maxima are combined through LDS, and each lane converts what it holds --
-            // the same divisions and conversions as the stand-alone kernel, no Xq round trip.
-            u32x4 xr[SPW][4];
-            const bool row_ok = r16 < p.M;
+        if constexpr (kind_quantizes(KIND)) {
+            // Activations quantised here (Sec. 2.2 per-token scaling; one token tile, the workgroup covers all of K):
+            // every wave loads the FP16 activations of its own slice in load order (lane l: rows l / 8 and 8 + l / 8, 16
+            // columns), the row maxima are combined through LDS, each lane converts what it holds -- the
+            // quotients and codes of the stand-alone kernel -- and the bytes take the way of loaded ones.
+            const int row = lane >> 3;
+            constexpr int H = SPW == 2 ? 2 : 1;        // (four K-steps of 16 rows do not fit the registers: M <= 8, see the host)
+            const bool two = H == 2 && p.M > 8;
+            u32x4 xr[SPW][H][2];
 #pragma unroll
             for (int s = 0; s < SPW; ++s) {
-                const int k = k_wave + s * KSTEP;
-                const uint8_t *src = p.X + (int64_t)r16 * p.x_row_bytes + 2 * (int64_t)k;
-                const bool ok0 = row_ok && k < p.K, ok1 = row_ok && (k + 64) < p.K;
+                const int k = k_slice + s * KSTEP + 16 * (lane & 7);
+                const uint8_t *src = p.X + (int64_t)row * p.x_row_bytes + 2 * (int64_t)k;
                 const u32x4 zero = {0u, 0u, 0u, 0u};
-                xr[s][0] = ok0 ? *reinterpret_cast<const u32x4 *>(src) : zero;
-                xr[s][1] = ok0 ? *reinterpret_cast<const u32x4 *>(src + 16) : zero;
-                xr[s][2] = ok1 ? *reinterpret_cast<const u32x4 *>(src + 128) : zero;
-                xr[s][3] = ok1 ? *reinterpret_cast<const u32x4 *>(src + 144) : zero;
+                const bool ok = k < p.K && row < p.M, ok2 = k < p.K && row + 8 < p.M;
+                xr[s][0][0] = ok ? *reinterpret_cast<const u32x4 *>(src) : zero;
+                xr[s][0][1] = ok ? *reinterpret_cast<const u32x4 *>(src + 16) : zero;
+                if constexpr (H == 2) {
+                    xr[s][1][0] = ok2 ? *reinterpret_cast<const u32x4 *>(src + 8 * p.x_row_bytes) : zero;
+                    xr[s][1][1] = ok2 ? *reinterpret_cast<const u32x4 *>(src + 8 * p.x_row_bytes + 16) : zero;
+                }
             }
             fetch(buf0, 0);                            // the weights travel during the reduction
-            float sc;
-            if (p.static_scale) {
-                sc = *p.static_scale;
-            } else {
-                uint32_t amax_bits = 0;                // |x| as an integer compare on the magnitude bits
+            float sc[2], rc[2];
+            uint32_t largest[2] = {0u, 0u};            // |x| as an integer compare on the magnitude bits
+            if (!p.static_scale) {
 #pragma unroll
-                for (int s = 0; s < SPW; ++s)
+                for (int h = 0; h < H; ++h) {
+                    if (h == 1 && !two) break;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const uint32_t w[4] = {xr[s][q].x, xr[s][q].y, xr[s][q].z, xr[s][q].w};
+                    for (int s = 0; s < SPW; ++s)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            amax_bits = max(amax_bits, max(w[e] & 0x7fffu, (w[e] >> 16) & 0x7fffu));
-                    }
-                amax_bits = max(amax_bits, (uint32_t)__shfl_xor((int)amax_bits, 16, 64));
-                amax_bits = max(amax_bits, (uint32_t)__shfl_xor((int)amax_bits, 32, 64));
-                if (g == 0) row_max[wave * 16 + r16] = amax_bits;
+                        for (int q = 0; q < 2; ++q) {
+                            const uint32_t w[4] = {xr[s][h][q].x, xr[s][h][q].y, xr[s][h][q].z, xr[s][h][q].w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) largest[h] = max(largest[h], max(w[e] & 0x7fffu, (w[e] >> 16) & 0x7fffu));
+                        }
+#pragma unroll
+                    for (int off = 1; off < 8; off <<= 1) largest[h] = max(largest[h], (uint32_t)__shfl_xor((int)largest[h], off, 64));
+                    if ((lane & 7) == 0) row_max[wave * 16 + 8 * h + row] = largest[h];
+                }
                 __syncthreads();
-                uint32_t all = 0;
-                for (int w2 = 0; w2 < waves; ++w2) all = max(all, row_max[w2 * 16 + r16]);
-                const float amax = half_bits_to_float(all);
-                sc = (amax == 0.0f) ? 1.0f : amax / 448.0f;
+                for (int w2 = 0; w2 < waves; ++w2) {
+                    largest[0] = max(largest[0], row_max[w2 * 16 + row]);
+                    if (two) largest[1] = max(largest[1], row_max[w2 * 16 + 8 + row]);
+                }
             }
-            row_scale = sc;
-            const float rc = 1.0f / sc;                // correctly rounded; see div_by_scale
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float amax = half_bits_to_float(largest[h]);
+                sc[h] = p.static_scale ? *p.static_scale : (amax == 0.0f ? 1.0f : amax / 448.0f);
+                rc[h] = 1.0f / sc[h];                  // correctly rounded; see div_by_scale
+                if (wave == 0 && (lane & 7) == 0) row_scale[8 * h + row] = sc[h];
+            }
+            // (a row with an infinity or a NaN, a scale given by the caller: codes that need clamping)
+            const bool plain = p.quant_hw && !p.static_scale && !__any(largest[0] >= 0x7c00u || largest[1] >= 0x7c00u);
 #pragma unroll
             for (int s = 0; s < SPW; ++s) {
-                if (p.quant_hw) {
-                    xa[s][0] = u32x4{quant4<true>(xr[s][0].x, xr[s][0].y, sc, rc), quant4<true>(xr[s][0].z, xr[s][0].w, sc, rc),
-                                     quant4<true>(xr[s][1].x, xr[s][1].y, sc, rc), quant4<true>(xr[s][1].z, xr[s][1].w, sc, rc)};
-                    xb[s][0] = u32x4{quant4<true>(xr[s][2].x, xr[s][2].y, sc, rc), quant4<true>(xr[s][2].z, xr[s][2].w, sc, rc),
-                                     quant4<true>(xr[s][3].x, xr[s][3].y, sc, rc), quant4<true>(xr[s][3].z, xr[s][3].w, sc, rc)};
-                } else {
-                    xa[s][0] = u32x4{quant4<false>(xr[s][0].x, xr[s][0].y, sc, rc), quant4<false>(xr[s][0].z, xr[s][0].w, sc, rc),
-                                     quant4<false>(xr[s][1].x, xr[s][1].y, sc, rc), quant4<false>(xr[s][1].z, xr[s][1].w, sc, rc)};
-                    xb[s][0] = u32x4{quant4<false>(xr[s][2].x, xr[s][2].y, sc, rc), quant4<false>(xr[s][2].z, xr[s][2].w, sc, rc),
-                                     quant4<false>(xr[s][3].x, xr[s][3].y, sc, rc), quant4<false>(xr[s][3].z, xr[s][3].w, sc, rc)};
-                }
+                auto convert = [&](u32x4 &to, const u32x4 (&x)[2], float sc_, float rc_) {
+                    if (plain) to = u32x4{quant4_own_scale(x[0].x, x[0].y, sc_, rc_), quant4_own_scale(x[0].z, x[0].w, sc_, rc_),
+                                          quant4_own_scale(x[1].x, x[1].y, sc_, rc_), quant4_own_scale(x[1].z, x[1].w, sc_, rc_)};
+                    else if (p.quant_hw) to = u32x4{quant4<true>(x[0].x, x[0].y, sc_, rc_), quant4<true>(x[0].z, x[0].w, sc_, rc_),
+                                                    quant4<true>(x[1].x, x[1].y, sc_, rc_), quant4<true>(x[1].z, x[1].w, sc_, rc_)};
+                    else to = u32x4{quant4<false>(x[0].x, x[0].y, sc_, rc_), quant4<false>(x[0].z, x[0].w, sc_, rc_),
+                                    quant4<false>(x[1].x, x[1].y, sc_, rc_), quant4<false>(x[1].z, x[1].w, sc_, rc_)};
+                };
+                convert(xa[s][0], xr[s][0], sc[0], rc[0]);
+                xb[s][0] = u32x4{0u, 0u, 0u, 0u};
+                if constexpr (H == 2)
+                    if (two) convert(xb[s][0], xr[s][1], sc[1], rc[1]);
+                rx.run(xa[s][0], xb[s][0]);
             }
         } else {
             // (the first weights travel while the activations are regrouped)
@@ -409,7 +423,7 @@ small_gemm_kernel(SmallParams p) {
     // ---- fixed-order reduction over the waves of the workgroup -----------------------------
     auto store_y = [&](floatx4 sum, int m, int n) {
         if (kind_is_fp8(KIND)) {
-            float sc = (KIND == kE4M3Quant ? row_scale : p.scales[m]) * p.w_scale;
+            float sc = (kind_quantizes(KIND) ? row_scale[m] : p.scales[m]) * p.w_scale;
             sum.x = scale_f32(sum.x, sc); sum.y = scale_f32(sum.y, sc); sum.z = scale_f32(sum.z, sc); sum.w = scale_f32(sum.w, sc);
         }
         uint16_t *dst = p.Y + (int64_t)m * p.ldy + n;
@@ -672,6 +686,12 @@ size_t small_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K) {
     return c.split > 1 ? (size_t)c.split * (size_t)M * (size_t)partial_ld(N) * sizeof(float) : 0;
 }
 
+// dynamic LDS of a launch: a kilobyte per tile, token tile and wave (an even number of tiles), 2 KB per wave to regroup in
+static size_t small_lds(const SmallConfig &c) {
+    return (size_t)((c.tiles_per_wg + 1) & ~1) * c.waves * c.mt * 1024 + (size_t)c.waves * 2048;
+}
+constexpr int kQuantLds = 158 * 1024;                            // (the row maxima and scales are static)
+
 template <int KIND, int MT, int SPW, int POL = kStream>
 static void launch_small_t(const SmallParams &p, const SmallConfig &c, dim3 grid, hipStream_t stream) {
     if constexpr (!kind_is_packed(KIND) && POL == kStream) {      // rows that do not start on lines (see kStream)
@@ -681,50 +701,46 @@ static void launch_small_t(const SmallParams &p, const SmallConfig &c, dim3 grid
             return;
         }
     }
-    size_t lds = (size_t)((c.tiles_per_wg + 1) & ~1) * c.waves * MT * 64 * sizeof(floatx4) +
-                 (size_t)c.waves * 2048;
+    const size_t lds = small_lds(c);
+    constexpr bool passes = !kind_quantizes(KIND);               // (quantising kinds have one pass)
     auto kern1 = small_gemm_kernel<KIND, MT, SPW, false, POL>;
-    auto kernp = small_gemm_kernel<KIND, MT, SPW, true, POL>;
+    auto kernp = small_gemm_kernel<KIND, MT, SPW, passes, POL>;
     static std::atomic<bool> attr_set{false};                    // once per instantiation
     if (!attr_set.load(std::memory_order_acquire)) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern1),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernp),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, passes ? 160 * 1024 : kQuantLds);
+        if (passes) (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernp),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         attr_set.store(true, std::memory_order_release);
     }
     if (c.passes > 1) kernp<<<grid, c.waves * 64, lds, stream>>>(p);
     else kern1<<<grid, c.waves * 64, lds, stream>>>(p);
 }
 
-// The fused-quantisation kind exists for one token tile, one K pass and no grid split only.
-static void launch_small_quant(const SmallParams &p, const SmallConfig &c, dim3 grid, hipStream_t stream) {
-    size_t lds = (size_t)((c.tiles_per_wg + 1) & ~1) * c.waves * 64 * sizeof(floatx4);
-    auto k2 = small_gemm_kernel<kE4M3Quant, 1, 2, false, kStream>;
-    auto k4 = small_gemm_kernel<kE4M3Quant, 1, 4, false, kStream>;
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set.load(std::memory_order_acquire)) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k2), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k4), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-        attr_set.store(true, std::memory_order_release);
-    }
-    if (c.spw == 2) k2<<<grid, c.waves * 64, lds, stream>>>(p);
-    else k4<<<grid, c.waves * 64, lds, stream>>>(p);
-}
-
+// Whether the streaming kernel quantises the activations itself: one token tile, all of K in the workgroup.  What it saves
+// is a launch (1.3 us in a graph, 3 us of host time outside one); what it costs is that every workgroup waits for
+// its M x K activations, their row maxima and 4 VALU instructions per value before it multiplies, while two weight
+// tiles are on their way.  Up to 8 tokens (half the lanes' rows) that pays where a workgroup has further tiles or the
+// rows are short: (1024, 1024) 5.5 -> 4.1 us, (11008, 3072) 10.9 -> 10.0, (7680, 5120) 11.9 -> 11.1, (10240, 8192) 19.5 -> 18.6; with
+// one tile (4096, 4096) takes 8.6 against 8.9 and (3072, 7168) 10.8 against 11.3.  With 16 rows to convert it pays
+// on short rows only: 16 tokens on (1024, 1024) 5.8 -> 5.2 us, on (2048, 2048) 6.8 -> 7.3, on (4096, 4096) 9.2 -> 11.5.
 bool small_gemm_fuses_quant(int64_t M, int64_t N, int64_t K) {
-    // Off unless asked for: every workgroup has to convert all of its 16 x K activations
-    // itself, which costs more VALU time per CU (measured 3-6 us per call at K = 4096) than
-    // the separate quantisation launch it saves.
-    if (tuning().small_fuse_quant <= 0) return false;
-    SmallConfig c = choose_small(kE4M3, M, N, K);
-    return c.mt == 1 && c.split == 1 && c.passes == 1;
+    const int64_t knob = tuning().small_fuse_quant;
+    if (knob == 0) return false;
+    const SmallConfig c = choose_small(kE4M3, M, N, K);
+    if (c.mt != 1 || c.split != 1 || c.passes != 1 || (c.spw != 2 && M > 8) || small_lds(c) > (size_t)kQuantLds) return false;
+    return knob > 0 || (M <= 8 ? (c.tiles_per_wg > 1 || K <= 3072) : K <= 1280);
 }
 
 template <int KIND>
 static void launch_small_k(const SmallParams &p, const SmallConfig &c, dim3 grid, hipStream_t stream) {
     if constexpr (KIND == kPlainF16 || KIND == kNestedF16Row) {
         if (c.mt == 1 && c.spw == 8) { launch_small_t<KIND, 1, 8>(p, c, grid, stream);  return; }
+    }
+    if constexpr (kind_quantizes(KIND)) {
+        if (c.spw == 4) launch_small_t<KIND, 1, 4>(p, c, grid, stream);
+        else launch_small_t<KIND, 1, 2>(p, c, grid, stream);
+        return;
     }
     switch (c.mt * 10 + c.spw) {
         case 14: launch_small_t<KIND, 1, 4>(p, c, grid, stream); break;
@@ -780,13 +796,14 @@ int launch_small_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
                         a.partial_bytes < (size_t)c.split * a.M * partial_ld(a.N) * sizeof(float)))
         return kErrWorkspace;
     dim3 grid(grid_x, (unsigned)c.split);
-    if (kind == kE4M3Quant && !(c.mt == 1 && c.split == 1 && c.passes == 1)) return kErrArg;   // caller checks first
+    if (kind_quantizes(kind) && !(c.mt == 1 && c.split == 1 && c.passes == 1)) return kErrArg;   // caller checks first
     switch (kind) {
         case kPlainF16: launch_small_k<kPlainF16>(p, c, grid, stream); break;
         case kPlainF16Packed: launch_small_k<kPlainF16Packed>(p, c, grid, stream); break;
         case kNestedF16: launch_small_k<kNestedF16>(p, c, grid, stream); break;
         case kNestedF16Row: launch_small_k<kNestedF16Row>(p, c, grid, stream); break;
-        case kE4M3Quant: launch_small_quant(p, c, grid, stream); break;
+        case kE4M3Quant: launch_small_k<kE4M3Quant>(p, c, grid, stream); break;
+        case kE4M3QuantRow: launch_small_k<kE4M3QuantRow>(p, c, grid, stream); break;
         case kE4M3Row: launch_small_k<kE4M3Row>(p, c, grid, stream); break;
         case kE4M3: launch_small_k<kE4M3>(p, c, grid, stream); break;
         default: return kErrArg;

@@ -119,17 +119,17 @@ static bool valid_mode(int mode) { return mode == NESTEDFP_MODE_FP16 || mode == 
 static bool valid_layout(int layout) { return layout == NESTEDFP_LAYOUT_ROWMAJOR || layout == NESTEDFP_LAYOUT_PACKED; }
 
 // FP8-mode GEMM straight from FP16 activations where the streaming kernel can quantise them
-// itself (decode batches whose K fits one workgroup pass, packed planes); returns -1 if it cannot.
+// itself (decode batches whose K fits one workgroup pass); returns -1 if it does not.
 static int fp8_gemm_fused(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, const float *act_scale,
                           const uint8_t *Wq, int64_t N, int w_kind, float w_scale, uint16_t *Y, int64_t ldy,
                           hipStream_t stream) {
-    if (w_kind != kE4M3 || !route_small(kE4M3, M, N, K, K) || !small_gemm_fuses_quant(M, N, K)) return -1;
+    if (!route_small(w_kind, M, N, K, K) || !small_gemm_fuses_quant(M, N, K)) return -1;
     GemmArgs a;
     memset(&a, 0, sizeof(a));
     a.X = X;  a.ldx = ldx;  a.static_scale = act_scale;  a.w_scale = w_scale;
     a.W0 = Wq;  a.W1 = nullptr;  a.ldw = K;
     a.M = M;  a.N = N;  a.K = K;  a.Y = Y;  a.ldy = ldy;
-    return launch_small_gemm(kE4M3Quant, a, stream);
+    return launch_small_gemm(w_kind == kE4M3 ? kE4M3Quant : kE4M3QuantRow, a, stream);
 }
 
 static int fp8_gemm(const uint8_t *Xq, const float *scales, int64_t M, int64_t K, const uint8_t *Wq,

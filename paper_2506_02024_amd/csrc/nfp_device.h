@@ -172,6 +172,21 @@ __device__ __forceinline__ uint32_t quant4(uint32_t w01, uint32_t w23, float s, 
            (e4m3_from_float_sw(d) << 24);
 }
 
+// The same for finite activations of a row and its own scale, amax / 448: no quotient exceeds 448 by more than its own
+// rounding, which converts to 448, so nothing is clamped; the sign, which a quotient of zero would lose, is put back for
+// four codes at once.
+__device__ __forceinline__ uint32_t quant4_own_scale(uint32_t w01, uint32_t w23, float s, float y) {
+    const uint32_t w[4] = {w01 & 0xffffu, w01 >> 16, w23 & 0xffffu, w23 >> 16};
+    float q[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = half_bits_to_float(w[i]);
+        const float q0 = a * y;
+        q[i] = __builtin_fmaf(__builtin_fmaf(-q0, s, a), y, q0);
+    }
+    return e4m3x4_from_float_hw(q[0], q[1], q[2], q[3]) | (byte_perm(w23, w01, 0x07050301u) & 0x80808080u);
+}
+
 // FP8-mode outputs are the FP32 sum times the FP32 scale, rounded to FP32, then converted to FP16,
 // in every kernel: the empty asm keeps the compiler from fusing product and conversion into a single
 // rounding in some kernels and not in others, so that every launch shape gives the same bits.

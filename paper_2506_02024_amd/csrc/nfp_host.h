@@ -17,14 +17,15 @@ inline int hip_ok(hipError_t e) { return e == hipSuccess ? kOk : kErrHip; }
 //   kPlainF16      : FP16 weights, row-major [N,K] (row stride ldw)
 //   kNestedF16     : the two byte planes in packed 1 KB blocks
 //   kE4M3          : E4M3 bytes (the upper plane) in packed 1 KB blocks
-//   kE4M3Quant     : as kE4M3, FP16 activations quantised per token inside the kernel
+//   kE4M3Quant, kE4M3QuantRow: as kE4M3, kE4M3Row, FP16 activations quantised per token inside the kernel
 //   kNestedF16Row  : the two byte planes row-major [N,K], regrouped into operand order in flight
 //   kE4M3Row       : E4M3 bytes row-major [N,K]
 //   kPlainF16Packed: FP16 weights in packed 2 KB blocks (the like-for-like partner of kNestedF16)
 enum WeightKind { kPlainF16 = 0, kNestedF16 = 1, kE4M3 = 2, kE4M3Quant = 3,
-                  kNestedF16Row = 4, kE4M3Row = 5, kPlainF16Packed = 6, kNumKinds = 7 };
+                  kNestedF16Row = 4, kE4M3Row = 5, kPlainF16Packed = 6, kE4M3QuantRow = 7, kNumKinds = 8 };
 
-constexpr bool kind_is_fp8(int k) { return k == kE4M3 || k == kE4M3Quant || k == kE4M3Row; }
+constexpr bool kind_quantizes(int k) { return k == kE4M3Quant || k == kE4M3QuantRow; }
+constexpr bool kind_is_fp8(int k) { return k == kE4M3 || k == kE4M3Row || kind_quantizes(k); }
 constexpr bool kind_is_nested(int k) { return k == kNestedF16 || k == kNestedF16Row; }
 // weights stored in blocks of 16 rows x 64 columns, lane order inside
 constexpr bool kind_is_packed(int k) { return k == kNestedF16 || k == kE4M3 || k == kE4M3Quant || k == kPlainF16Packed; }

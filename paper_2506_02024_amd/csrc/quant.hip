@@ -122,9 +122,12 @@ int launch_quantize_act(const uint16_t *X, int64_t M, int64_t K, int64_t ldx,
     bool hw = tuning().quant_hw != 0;
     const int64_t chunks = K / 8;
     const int64_t onepass = tuning().quant_onepass;
-    // one pass for decode-sized batches (latency) and for long rows at any batch (measured at 8192
-    // tokens: 5.1-5.4 TB/s against 3.9 for K = 14336 / 28672, equal at K = 8192, 4 % behind at 4096)
-    if (chunks <= 4096 && (onepass > 0 || (onepass < 0 && (M <= 256 || chunks >= 1024)))) {
+    // one pass for decode-sized batches (latency; at 300 to 500 tokens still 3.8 against 4.1 us for K = 4096, 5.0 against
+    // 5.5 for 7168, and 4.8 against 5.2 at 1000 tokens for 4096, where 7168 takes 8.0 against 7.4) and for long
+    // rows at any batch (measured at 8192 tokens: 5.1-5.4 TB/s against 3.9 for K = 14336 / 28672, equal at
+    // K = 8192, 4 % behind at 4096)
+    const bool few = M <= 512 || (M <= 1024 && chunks <= 512);
+    if (chunks <= 4096 && (onepass > 0 || (onepass < 0 && (few || chunks >= 1024)))) {
         // as many lanes as the row has chunks (up to 1024, 4 chunks each)
         int cpt = chunks <= 1024 ? 1 : (chunks <= 2048 ? 2 : 4);
         int threads = (int)(((chunks + cpt - 1) / cpt + 63) / 64 * 64);
