@@ -1,14 +1,15 @@
 // LDS-tiled MFMA GEMMs for prefill-sized batches: Y = X * W^T, compute-bound.
 //
-// Three kernels.  large_gemm_kernel multiplies plain FP16 weights or E4M3 weights (FP8 mode: the
+// Four kernels.  large_gemm_kernel multiplies plain FP16 weights or E4M3 weights (FP8 mode: the
 // upper plane as it is, row-major or in packed blocks): TM tokens x TN weight rows x 128 bytes of K
-// per row (64 halves or 128 E4M3 bytes) per stage, two LDS stages, 8 waves.  nested_bypass_kernel is FP16 mode: Sec. 4.2
+// per row (64 halves or 128 E4M3 bytes) per stage, two or more LDS stages, 8 waves.  nested_bypass_kernel is FP16 mode: Sec. 4.2
 // puts the FP16 reconstruction between the shared-memory-to-register copy and the tensor-core
 // instruction of every warp and hides it with a third pipeline stage; here every weight belongs
 // to exactly one wave, which loads its 16 bytes of each plane per lane (from row-major planes or
 // from packed blocks) into registers, merges them there (Alg. 1) and feeds them to the MFMA -- the
 // weights never pass through LDS; the same kernel without the merge multiplies FP16 weights stored
-// in packed blocks, the like-for-like baseline of Sec. 5.2.  e4m3_bypass_kernel
+// in packed blocks, the like-for-like baseline of Sec. 5.2.  nested_rows_kernel is FP16 mode on row-major planes, which
+// come by whole lines through a part of the LDS that belongs to the wave.  e4m3_bypass_kernel
 // is the same register path for E4M3 weights, used for batches of 49 .. 64 tokens, where the
 // weight stream is the bound.
 //
@@ -216,11 +217,12 @@ struct TileStore {
     }
 };
 
-// NST: LDS stages.  Two are enough where a K-tile's MFMAs outlast the latency of the next K-tile's
-// loads (256 x 256 tiles) or two workgroups share a CU; a launch with at most one workgroup per CU
-// and smaller tiles takes three or four, so that loads run NST - 1 K-tiles ahead.
-// NSTW: stages of the weights.  On tiles of 256 weight rows, two stages of both and a third one of the weights alone
-// take the 160 KB: tokens come from L2, within a K-tile, weights from memory, in two.
+// NST: LDS stages.  Two are enough where two workgroups share a CU; a launch with at most one workgroup per CU takes
+// three or four on tiles below 256 x 256, so that loads run NST - 1 K-tiles ahead.
+// NSTW: stages of the weights.  On 256 x 256 tiles two stages of both and a third one of the weights alone take the
+// 160 KB: tokens come from L2, within a K-tile, weights from memory, in two.  With two of both, a K-tile took at least the
+// latency of a weight load: FP8 mode, (28672, 4096) at 777 tokens 107 -> 98 us, at 8192 tokens 787 -> 754, (4096, 14336) at
+// 300 tokens unsplit 148 -> 107; plain FP16 (4096, 14336) at 2048 tokens unsplit 283 -> 238.
 template <int KIND, int TM, int TN, int WAVES_M, int WAVES_N, int NST = 2, int NSTW = NST>
 struct LargeKernel {
     static_assert(KIND == kPlainF16 || KIND == kE4M3 || KIND == kE4M3Row, "NestedFP16 has a kernel of its own");
@@ -915,6 +917,8 @@ nested_bypass_kernel(LargeParams p) {
 // K-tile before they are merged.  Loaded straight into registers in operand order, 16 rows x 64 bytes per
 // instruction, every 128-byte line is requested twice: a load-only kernel takes in 38 bytes per nanosecond
 // and CU so, and 137 by whole lines.
+// (28672, 4096): 100 tokens 61.8 us with pairs regrouped in registers, 56.5 so; 2048 tokens 452 us in operand order, 435 so;
+// 128 x 256 tiles gain 12-28 %.
 // A pair's copies are under way while the pair before it is multiplied from registers (1.7 K-tiles).  The
 // one barrier of a K-tile sits behind the last read of its token stage, in the last slots of the second
 // substep: the next K-tile's tokens have to be there by then, and the stage is free from then on, so that
@@ -1596,12 +1600,14 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K) {
     const Tuning &t = tuning();
     const int kt = (int)(((fp8 ? K : 2 * K) + 127) / 128);
     const bool bounded = static_scratch_holds(1, M, N, K, fp8, partial_ld(N));
+    const int want_m = (t.large_bm == 128 || t.large_bm == 256) ? (int)t.large_bm : 0;
+    const int want_n = (t.large_bn == 128 || t.large_bn == 256) ? (int)t.large_bn : want_m;
     LargeConfig c;
     c.tm = 128;  c.tn = 128;  c.split = 1;  c.deep = 0;
     double best = 1e30;
     for (const ShortShape &e : m.shape) {
-        if (t.large_bm > 0 && t.large_bm != e.tm) continue;
-        if (t.large_bn > 0 && t.large_bn != e.tn) continue;
+        if (want_m && want_m != e.tm) continue;
+        if (want_n && want_n != e.tn) continue;
         const int height = cuts_tiles(cls, e.tn) ? token_tile(e.tm, M) : e.tm;
         const int64_t tiles = ((M + e.tm - 1) / e.tm) * ((N + e.tn - 1) / e.tn);
         double tk = e.tk, tfix = e.tfix;
