@@ -154,8 +154,33 @@ namespace nfp {
 
 constexpr int kMaxDevices = 64;
 
+// The device that `stream` launches on, which need not be the current one; -1 if that cannot be said.
+static int device_of(hipStream_t stream) {
+    int dev = -1;
+    const bool own = stream == nullptr || stream == hipStreamLegacy || stream == hipStreamPerThread;   // (the current device's)
+    const hipError_t e = own ? hipGetDevice(&dev) : hipStreamGetDevice(stream, &dev);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return -1;
+    }
+    return dev >= 0 && dev < kMaxDevices ? dev : -1;
+}
+
+// The address of a variable of the library on a device; nullptr if it has none.
+static void *symbol_address(const void *symbol, int dev) {
+    int before = -1;
+    void *p = nullptr;
+    if (hipGetDevice(&before) != hipSuccess || (before != dev && hipSetDevice(dev) != hipSuccess) ||
+        hipGetSymbolAddress(&p, symbol) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+    }
+    if (before >= 0 && before != dev) (void)hipSetDevice(before);
+    return p;
+}
+
 // Where counts land on the host: 64 words of pinned memory, allocated by the first call that wants a count and
-// kept until the process ends.  A call holds a word, and the device's counter of the same number, while it waits;
+// kept until the process ends.  A call holds a word, and the counter of the same number on its stream's device, while it waits;
 // one that finds none free clears and copies the caller's device word instead.  Nothing is freed when a host thread
 // ends: the runtime refuses that, as an error of the capture, while another thread captures a graph.
 class PinnedCounts {
@@ -164,20 +189,16 @@ class PinnedCounts {
     uint64_t *counters[kMaxDevices] = {};
 public:
     struct Slot { uint64_t *word = nullptr, *counter = nullptr; };
-    Slot take() {
+    Slot take(hipStream_t stream) {
         Slot s;
-        int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return s;
+        const int dev = device_of(stream);
+        if (dev < 0) return s;
         std::lock_guard<std::mutex> lock(mutex);
         if (words == nullptr && hipHostMalloc(reinterpret_cast<void **>(&words), 64 * sizeof(uint64_t), hipHostMallocPortable) != hipSuccess) {
             words = nullptr;
             (void)hipGetLastError();
         }
-        if (counters[dev] == nullptr) {
-            void *p = nullptr;
-            if (hipGetSymbolAddress(&p, HIP_SYMBOL(waited_counts)) == hipSuccess) counters[dev] = static_cast<uint64_t *>(p);
-            else (void)hipGetLastError();
-        }
+        if (counters[dev] == nullptr) counters[dev] = static_cast<uint64_t *>(symbol_address(HIP_SYMBOL(waited_counts), dev));
         if (words == nullptr || counters[dev] == nullptr || ~taken == 0) return s;
         const int i = __builtin_ctzll(~taken);
         taken |= (uint64_t)1 << i;
@@ -206,7 +227,7 @@ static PinnedCounts &pinned_counts() {
 template <typename Count>
 static int counted(uint64_t *dev, uint64_t *host, hipStream_t stream, Count count) {
     if (host == nullptr) return count(dev, dev != nullptr);
-    const PinnedCounts::Slot slot = pinned_counts().take();
+    const PinnedCounts::Slot slot = pinned_counts().take(stream);
     if (slot.word == nullptr) {
         const int st = count(dev, true);
         if (st != kOk) return st;
