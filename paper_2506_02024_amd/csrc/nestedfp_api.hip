@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <mutex>
+#include <new>
 
 namespace nfp {
 
@@ -231,11 +232,14 @@ static int counted(uint64_t *dev, uint64_t *host, hipStream_t stream, Count coun
     if (slot.word == nullptr) {
         const int st = count(dev, true);
         if (st != kOk) return st;
-        uint64_t n = 0;
-        if (hipMemcpyAsync(&n, dev, sizeof(n), hipMemcpyDeviceToHost, stream) != hipSuccess ||
-            hipStreamSynchronize(stream) != hipSuccess) return NESTEDFP_ERR_HIP;
-        *host = n;
-        return n == 0 ? NESTEDFP_OK : NESTEDFP_ERR_RANGE;
+        uint64_t *const n = new (std::nothrow) uint64_t(0);
+        if (n == nullptr) return NESTEDFP_ERR_HIP;
+        const bool queued = hipMemcpyAsync(n, dev, sizeof(*n), hipMemcpyDeviceToHost, stream) == hipSuccess;
+        if (queued && hipStreamSynchronize(stream) != hipSuccess) return NESTEDFP_ERR_HIP;    // (*n may still be written: kept)
+        if (queued) *host = *n;
+        delete n;
+        if (!queued) return NESTEDFP_ERR_HIP;
+        return *host == 0 ? NESTEDFP_OK : NESTEDFP_ERR_RANGE;
     }
     int st = count(slot.counter, false);
     if (st == kOk) st = launch_hand_on_count(slot.counter, dev, slot.word, stream);

@@ -169,6 +169,31 @@ static void streams_of_two_devices() {
     CHECK(current == 1 && wrong_device == 0 && copies == 0);
 }
 
+// no pinned memory: the count takes the way through the caller's device word; where the wait fails the copy may come later
+static void without_pinned_words() {
+    fail_pinned = true;
+    for (int dev : {0, 1}) all_right(stream_of(dev));
+    CHECK(copies > 0);
+    uint64_t dev = 99, host = 98;
+    Layer layer;
+    bad_weights = 7;
+    for (int call = 0; call < 3; ++call) {
+        fail_wait = true;
+        last_copy = {};
+        CHECK((call == 0 ? decompose(W, 4, 32, 32, up, lo, &dev, &host, stream_of(0)) :
+               call == 1 ? range_check(W, 4, 32, 32, &dev, &host, stream_of(0)) :
+                           prepare(W, 4, 32, 32, 0, up, lo, &dev, &layer, stream_of(0))) == ERR_HIP);
+        CHECK(last_copy.first != nullptr && !on_stack(last_copy.first));
+        if (on_stack(last_copy.first)) queued.clear();
+        fail_wait = false;
+        run_queued();
+    }
+    fail_copy = true;
+    CHECK(decompose(W, 4, 32, 32, up, lo, &dev, &host, stream_of(0)) == ERR_HIP);
+    fail_copy = false;
+    all_right(stream_of(1));
+}
+
 int main(int argc, char **argv) {
     void *h = argc > 2 ? dlopen(argv[1], RTLD_NOW) : nullptr;
     if (h == nullptr) { fprintf(stderr, "%s\n", dlerror());  return 2; }
@@ -177,6 +202,7 @@ int main(int argc, char **argv) {
     *(void **)&prepare = dlsym(h, "nestedfp_layer_prepare");
     const std::string what = argv[2];
     if (what == "streams_of_two_devices") streams_of_two_devices();
+    else if (what == "without_pinned_words") without_pinned_words();
     else return 2;
     if (launches == 0) return 2;                               // (the library bound to the real runtime)
     return failures ? 1 : 0;
@@ -199,7 +225,7 @@ def program(tmp_path_factory):
     return [str(exe), os.environ.get("NESTEDFP_LIB") or build.lib_path()]
 
 
-@pytest.mark.parametrize("what", ["streams_of_two_devices"])
+@pytest.mark.parametrize("what", ["streams_of_two_devices", "without_pinned_words"])
 def test_waited_counts(program, what):
     res = subprocess.run(program + [what], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0, res.stdout + res.stderr
