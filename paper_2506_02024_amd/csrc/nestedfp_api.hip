@@ -147,7 +147,8 @@ static int fp8_gemm(const uint8_t *Xq, const float *scales, int64_t M, int64_t K
 
 }  // namespace nfp
 
-// Counters of the calls that wait for their count, one per word below and each on a line of its own: zero between calls.
+// Counters of the calls that wait for their count, one per word below and each on a line of its own: zero between calls, but
+// for those behind which a launch failed.
 constexpr int kCountStride = 16;
 static __device__ __align__(128) unsigned long long waited_counts[64 * kCountStride];
 
@@ -183,13 +184,14 @@ static void *symbol_address(const void *symbol, int dev) {
 // Where counts land on the host: 64 words of pinned memory, allocated by the first call that wants a count and
 // kept until the process ends.  A call holds a word, and the counter of the same number on its stream's device, while it waits;
 // one that finds none free clears and copies the caller's device word instead.  Nothing is freed when a host thread
-// ends: the runtime refuses that, as an error of the capture, while another thread captures a graph.
+// ends: the runtime refuses that, as an error of the capture, while another thread captures a graph.  A word is given back as
+// soon as nothing can write to it any more, so that calls whose launches fail do not use the words up.
 class PinnedCounts {
     std::mutex mutex;
     uint64_t *words = nullptr, taken = 0;
-    uint64_t *counters[kMaxDevices] = {};
+    uint64_t *counters[kMaxDevices] = {}, used[kMaxDevices] = {};       // (used: counters that may not be zero)
 public:
-    struct Slot { uint64_t *word = nullptr, *counter = nullptr; };
+    struct Slot { uint64_t *word = nullptr, *counter = nullptr;  int dev = -1;  bool clear = false; };
     Slot take(hipStream_t stream) {
         Slot s;
         const int dev = device_of(stream);
@@ -205,11 +207,16 @@ public:
         taken |= (uint64_t)1 << i;
         s.word = words + i;
         s.counter = counters[dev] + i * kCountStride;
+        s.dev = dev;
+        s.clear = (used[dev] >> i & 1) != 0;
         return s;
     }
-    void give_back(const Slot &s) {
+    // zero: the call left its counter so
+    void give_back(const Slot &s, bool zero) {
         std::lock_guard<std::mutex> lock(mutex);
-        taken &= ~((uint64_t)1 << (s.word - words));
+        const uint64_t bit = (uint64_t)1 << (s.word - words);
+        taken &= ~bit;
+        used[s.dev] = zero ? used[s.dev] & ~bit : used[s.dev] | bit;
     }
 };
 
@@ -241,11 +248,13 @@ static int counted(uint64_t *dev, uint64_t *host, hipStream_t stream, Count coun
         if (!queued) return NESTEDFP_ERR_HIP;
         return *host == 0 ? NESTEDFP_OK : NESTEDFP_ERR_RANGE;
     }
-    int st = count(slot.counter, false);
+    int st = count(slot.counter, slot.clear);
     if (st == kOk) st = launch_hand_on_count(slot.counter, dev, slot.word, stream);
-    if (st != kOk || hipStreamSynchronize(stream) != hipSuccess) return NESTEDFP_ERR_HIP;    // (what may still be written is kept)
+    // (behind a launch that failed too: once the stream has been waited for, nothing writes to the slot any more)
+    if (hipStreamSynchronize(stream) != hipSuccess) return NESTEDFP_ERR_HIP;       // (what may still be written is kept)
     const uint64_t n = *static_cast<volatile uint64_t *>(slot.word);
-    pinned_counts().give_back(slot);
+    pinned_counts().give_back(slot, st == kOk);
+    if (st != kOk) return st;
     *host = n;
     return n == 0 ? NESTEDFP_OK : NESTEDFP_ERR_RANGE;
 }

@@ -194,6 +194,53 @@ static void without_pinned_words() {
     all_right(stream_of(1));
 }
 
+// A launch that fails costs no word, however often: neither one that was refused nor one behind an earlier call's error, whose
+// kernels run and leave a counter that is not zero.  A wait that fails keeps its word, to which a count may still come.
+static void failing_calls() {
+    uint64_t dev = 99, host = 99;
+    Layer layer;
+    for (int kind : {1, 2})
+        for (int i = 0; i < 200; ++i) {
+            bad_weights = 5;
+            fail_launch = kind;
+            void *const stream = stream_of(i % 2);
+            CHECK((i % 3 == 0 ? decompose(W, 4, 32, 32, up, lo, &dev, &host, stream) :
+                   i % 3 == 1 ? range_check(W, 4, 32, 32, &dev, &host, stream) :
+                                prepare(W, 4, 32, 32, 1, up, lo, &dev, &layer, stream)) == ERR_HIP);
+            fail_launch = 0;
+            last_error = 0;
+            if (i % 50 == 0) all_right(stream_of(i / 50 % 2));
+        }
+    all_right(stream_of(0));
+    all_right(stream_of(1));
+    CHECK(copies == 0);
+    // (a launch behind an earlier error whose wait fails as well: its kernels are still to come)
+    fail_wait = true;
+    fail_launch = 2;
+    CHECK(decompose(W, 4, 32, 32, up, lo, &dev, &host, stream_of(0)) == ERR_HIP);
+    fail_launch = last_error = 0;
+    for (int i = 0; i < 20; ++i) CHECK(decompose(W, 4, 32, 32, up, lo, &dev, &host, stream_of(0)) == ERR_HIP);
+    fail_wait = false;
+    auto late = queued;
+    queued.clear();
+    for (uint64_t n : {(uint64_t)3, (uint64_t)0}) {
+        bad_weights = n;
+        dev = host = 99;
+        CHECK(decompose(W, 4, 32, 32, up, lo, &dev, &host, stream_of(0)) == (n ? ERR_RANGE : OK) && dev == n && host == n);
+        for (auto &f : late) f();
+    }
+    all_right(stream_of(0));
+    CHECK(copies == 0);
+    // ... until there is none left, and the counts take the other way
+    fail_wait = true;
+    for (int i = 0; i < 100; ++i) CHECK(decompose(W, 4, 32, 32, up, lo, &dev, &host, stream_of(0)) == ERR_HIP);
+    fail_wait = false;
+    CHECK(copies > 0);
+    run_queued();
+    all_right(stream_of(0));
+    all_right(stream_of(1));
+}
+
 int main(int argc, char **argv) {
     void *h = argc > 2 ? dlopen(argv[1], RTLD_NOW) : nullptr;
     if (h == nullptr) { fprintf(stderr, "%s\n", dlerror());  return 2; }
@@ -203,6 +250,7 @@ int main(int argc, char **argv) {
     const std::string what = argv[2];
     if (what == "streams_of_two_devices") streams_of_two_devices();
     else if (what == "without_pinned_words") without_pinned_words();
+    else if (what == "failing_calls") failing_calls();
     else return 2;
     if (launches == 0) return 2;                               // (the library bound to the real runtime)
     return failures ? 1 : 0;
@@ -225,7 +273,7 @@ def program(tmp_path_factory):
     return [str(exe), os.environ.get("NESTEDFP_LIB") or build.lib_path()]
 
 
-@pytest.mark.parametrize("what", ["streams_of_two_devices", "without_pinned_words"])
+@pytest.mark.parametrize("what", ["streams_of_two_devices", "without_pinned_words", "failing_calls"])
 def test_waited_counts(program, what):
     res = subprocess.run(program + [what], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0, res.stdout + res.stderr
