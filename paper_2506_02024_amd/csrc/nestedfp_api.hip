@@ -408,15 +408,15 @@ namespace nfp {
 static void *g_scratch_ptr[kMaxDevices];               // device address of `scratch`, per device
 static std::mutex g_scratch_mutex;
 
-// Address of this device's scratch array; on first use its arrival counters are cleared (the image
+// Address of the scratch array of the stream's device; on first use its arrival counters are cleared (the image
 // starts zeroed and every call leaves them zero; the fill makes that independent of the loader).
 static int static_scratch(void **out, hipStream_t stream) {
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return kErrHip;
+    const int dev = device_of(stream);
+    if (dev < 0) return kErrHip;
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
     if (g_scratch_ptr[dev] == nullptr) {
-        void *ptr = nullptr;
-        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || ptr == nullptr) return kErrHip;
+        void *const ptr = symbol_address(HIP_SYMBOL(scratch), dev);
+        if (ptr == nullptr) return kErrHip;
         if (launch_zero_words(static_cast<uint32_t *>(ptr), kMaxCounters, stream) != kOk) return kErrHip;
         g_scratch_ptr[dev] = ptr;
     }

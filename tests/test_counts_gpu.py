@@ -60,3 +60,30 @@ def test_device_word_holds_the_count_with_and_without_a_wait():
     # an empty layer clears the word
     assert nfp.lib().nestedfp_decompose(None, 0, 256, 256, None, None, cnt.data_ptr(), ctypes.byref(host), nfp._stream()) == nfp.OK
     assert cnt.item() == 0 and host.value == 0
+
+
+def test_library_memory_on_side_streams_and_in_a_graph():
+    # the library asks a stream for its device: streams of their own, and one that a graph is captured on
+    from paper_2506_02024_amd import binding as nfp
+
+    M, N, K = 40, 520, 14336
+    Wd, X = to_dev(workloads.weight_host(N, K, seed=3)), to_dev(workloads.act_host(M, K, seed=4))
+    up, lo = nfp.decompose(Wd)
+    for mode in (nfp.MODE_FP16, nfp.MODE_FP8):
+        ref = nfp.gemm(X, up, lo, mode)
+        out = torch.zeros_like(ref)
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            assert nfp.range_check(Wd) == 0
+            nfp.gemm_static(X, up, lo, mode, out)
+        side.synchronize()
+        assert torch.equal(out, ref)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            nfp.gemm_static(X, up, lo, mode, out)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref)

@@ -1,4 +1,4 @@
-"""Host side of the calls that wait for a count of out-of-range weights, against a stand-in for the HIP runtime: two
+"""Host side of the calls that use memory of the library's own (waited counts, the fixed scratch), against a stand-in for the HIP runtime: two
 devices, kernels that run on the CPU when their stream is waited for, calls that can be made to fail.  Needs no GPU."""
 import os
 import shutil
@@ -25,7 +25,7 @@ static const int kFail = 1;
 static int current = 0;                                        // current device
 static bool fail_wait, fail_pinned, fail_copy;
 static int fail_launch;                                        // 1: refused; 2: an earlier error is reported, the kernel is queued
-static int last_error, copies, launches, wrong_device;
+static int last_error, copies, launches, wrong_device, scratch_uses;
 static uint64_t bad_weights;                                   // what a counting kernel finds
 static std::deque<std::function<void()>> queued;
 static std::map<const void *, std::string> kernels;
@@ -113,6 +113,18 @@ int hipLaunchKernel(const void *f, Dim3, Dim3, void **args, size_t, void *stream
         look(counter);
         const uint64_t n = bad_weights;
         if (counter) queued.push_back([=] { *counter += n; });
+    } else if (name.find("quantize_act") != std::string::npos || name.find("splitk_reduce") != std::string::npos) {
+        for (int i : {0, 3, 4, 5}) {
+            if (i > 0 && name.find("splitk_reduce") != std::string::npos) break;
+            look(arg(i));
+        }
+    } else if (name.find("gemm_kernel") != std::string::npos || name.find("bypass") != std::string::npos ||
+               name.find("nested_rows") != std::string::npos) {
+        for (int i = 0; i < 15; ++i) {                         // the pointers among the first 120 bytes of its parameters
+            void *const p = static_cast<void **>(args[0])[i];
+            look(p);
+            scratch_uses += owner(p) >= 0;
+        }
     } else {
         fprintf(stderr, "unknown kernel %s\n", name.c_str());
         exit(3);
@@ -126,6 +138,7 @@ struct Layer { int64_t N, K; int32_t is_exception, layout; const void *upper, *l
 static int (*range_check)(const void *, int64_t, int64_t, int64_t, uint64_t *, uint64_t *, void *);
 static int (*decompose)(const void *, int64_t, int64_t, int64_t, void *, void *, uint64_t *, uint64_t *, void *);
 static int (*prepare)(const void *, int64_t, int64_t, int64_t, int, void *, void *, uint64_t *, Layer *, void *);
+static int (*gemm_static)(const void *, int64_t, int64_t, int64_t, const void *, const void *, int64_t, int, const float *, void *, int64_t, void *);
 static char W[4096] __attribute__((aligned(16))), up[4096] __attribute__((aligned(16))), lo[4096] __attribute__((aligned(16)));
 
 static int failures;
@@ -241,16 +254,32 @@ static void failing_calls() {
     all_right(stream_of(1));
 }
 
+// the call without a workspace: its scratch is the stream's device's
+static void fixed_scratch_on_two_devices() {
+    static char X[1 << 20] __attribute__((aligned(16))), Y[1 << 20] __attribute__((aligned(16)));
+    for (void *stream : {stream_of(1), stream_of(0), stream_of(1), (void *)nullptr})
+        for (int mode : {0, 1})
+            for (int64_t M : {1, 16, 40, 300}) {
+                const int before = scratch_uses;
+                CHECK(gemm_static(X, M, 14336, 14336, W, W, 4096, mode, nullptr, Y, 4096, stream) == OK);
+                CHECK(scratch_uses > before || (mode == 0 && M != 40));
+                CHECK(current == 0);
+            }
+    CHECK(wrong_device == 0 && scratch_uses > 0);
+}
+
 int main(int argc, char **argv) {
     void *h = argc > 2 ? dlopen(argv[1], RTLD_NOW) : nullptr;
     if (h == nullptr) { fprintf(stderr, "%s\n", dlerror());  return 2; }
     *(void **)&range_check = dlsym(h, "nestedfp_range_check");
     *(void **)&decompose = dlsym(h, "nestedfp_decompose");
     *(void **)&prepare = dlsym(h, "nestedfp_layer_prepare");
+    *(void **)&gemm_static = dlsym(h, "nestedfp_gemm_static");
     const std::string what = argv[2];
     if (what == "streams_of_two_devices") streams_of_two_devices();
     else if (what == "without_pinned_words") without_pinned_words();
     else if (what == "failing_calls") failing_calls();
+    else if (what == "fixed_scratch_on_two_devices") fixed_scratch_on_two_devices();
     else return 2;
     if (launches == 0) return 2;                               // (the library bound to the real runtime)
     return failures ? 1 : 0;
@@ -273,7 +302,7 @@ def program(tmp_path_factory):
     return [str(exe), os.environ.get("NESTEDFP_LIB") or build.lib_path()]
 
 
-@pytest.mark.parametrize("what", ["streams_of_two_devices", "without_pinned_words", "failing_calls"])
-def test_waited_counts(program, what):
+@pytest.mark.parametrize("what", ["streams_of_two_devices", "without_pinned_words", "failing_calls", "fixed_scratch_on_two_devices"])
+def test_memory_of_the_library(program, what):
     res = subprocess.run(program + [what], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0, res.stdout + res.stderr
