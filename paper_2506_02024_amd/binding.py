@@ -428,19 +428,24 @@ class Layer:
 
     def __init__(self, W, packed=False):
         N, K, ldw = _rowmajor(W, "W")
-        self.c = _LayerStruct()
+        c = _LayerStruct()
         upper, lower = _new_planes(N, K, W.device, packed)
         cnt = torch.empty(1, dtype=torch.int64, device=W.device)
         st = lib().nestedfp_layer_prepare(_ptr(W), N, K, ldw, LAYOUT_PACKED if packed else LAYOUT_ROWMAJOR,
-                                          _ptr(upper), _ptr(lower), _ptr(cnt), ctypes.byref(self.c), _stream())
+                                          _ptr(upper), _ptr(lower), _ptr(cnt), ctypes.byref(c), _stream())
         _check(st, "nestedfp_layer_prepare")
-        self.shape = (N, K)
-        self._ref = ctypes.byref(self.c)
-        if self.c.is_exception:
+        self.c = c
+        if c.is_exception:
             self.W, self.upper, self.lower = W, None, None     # planes released
         else:
             self.W, self.upper, self.lower = None, upper, lower
 
+    def _describe(self, c):
+        # what linear() needs of it, taken out once (two field reads and a reference cost 0.3 us)
+        self._c, self._ref, self._dims = c, ctypes.byref(c), (int(c.N), int(c.K))
+
+    c = property(lambda self: self._c, _describe)              # the struct that the library reads
+    shape = property(lambda self: self._dims)
     is_exception = property(lambda self: bool(self.c.is_exception))
     out_of_range = property(lambda self: int(self.c.out_of_range))
 
@@ -448,7 +453,7 @@ class Layer:
 def linear(X, layer, mode, act_scale=None, out=None, workspace=None):
     """Y = X @ W^T for a Layer in the given mode (exception layers always run in FP16)."""
     M, K, ldx = _rowmajor(X, "X")
-    N, layer_K = layer.shape
+    N, layer_K = layer._dims
     if layer_K != K:
         raise ValueError("K of X and of the layer differ")
     if out is None:

@@ -179,3 +179,13 @@ def test_layer_entry_points_reject_missing_descriptors(L):
     assert L.nestedfp_layer_prepare(fake, 4, 32, 32, 1, fake, fake, P(0), fake, P(0)) == 1
     assert L.nestedfp_layer_prepare(fake, 4, 32, 32, 9, fake, fake, fake, fake, P(0)) == 1
 
+
+
+def test_a_layer_follows_its_description():
+    from paper_2506_02024_amd import binding
+
+    layer = binding.Layer.__new__(binding.Layer)
+    for n, k in ((48, 128), (80, 256)):
+        layer.c = binding._LayerStruct(N=n, K=k, is_exception=1, out_of_range=n)
+        assert layer.shape == (n, k) and layer.is_exception and layer.out_of_range == n
+        assert layer._ref._obj is layer.c                  # what linear() hands to the library

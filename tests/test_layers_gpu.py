@@ -138,3 +138,19 @@ def test_counts_of_many_threads_at_once(nfp):
     with ThreadPoolExecutor(max_workers=80) as pool:
         counts = list(pool.map(lambda j: nfp.range_check(mats[j % 8]), range(800)))
     assert counts == [3 * (j % 8) for j in range(800)]
+
+
+def test_a_replaced_description_is_the_one_that_counts():
+    # Layer.c, the struct that the library reads, may be exchanged: shape and linear() follow it
+    from paper_2506_02024_amd import binding as nfp
+
+    a, b = (nfp.Layer(to_dev(workloads.weight_host(N, K, seed=N))) for N, K in ((48, 128), (80, 256)))
+    X = to_dev(workloads.act_host(3, 256, seed=1))
+    want = nfp.linear(X, b, nfp.MODE_FP16)
+    a.c = b.c
+    assert a.shape == (80, 256) and torch.equal(nfp.linear(X, a, nfp.MODE_FP16), want)
+    bare = nfp.Layer.__new__(nfp.Layer)
+    bare.c = b.c
+    assert bare.shape == (80, 256) and torch.equal(nfp.linear(X, bare, nfp.MODE_FP16), want)
+    with pytest.raises(AttributeError):
+        a.shape = (1, 2)
