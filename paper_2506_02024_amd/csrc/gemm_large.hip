@@ -1827,13 +1827,15 @@ bool rows_by_pairs(int tm, int64_t M, int64_t N, int64_t K, int64_t row_bytes, i
 //  - Rows that start on lines: through LDS (1.01-1.06 x at less than a dozen K-tiles per slice, 1.15-1.24 x from three
 //    dozen on), but on 128 x 128 tiles from a dozen K-tiles on (0.99 x on average below, 0.81 x at worst).
 //  - Slices with an odd number of such K-tiles: every second one starts in the middle of a line, so that its pieces take
-//    two lines each, and the last pair is half empty: a dozen K-tiles, on 256 x 256 tiles four dozen.
+//    two lines each, and the last pair is half empty: a dozen K-tiles, but never on 256 x 256 tiles, whose two row tiles
+//    per wave copy twice as much (1.02-1.07 x the time whatever the length; (5120, 14336) at 1024 tokens in slices of 75
+//    K-tiles 170.7 us against 158.7).
 //  - Rows that start inside lines, where pieces share lines but unpaired loads take whole halves if the row is a multiple
 //    of 64 bytes: longer slices and rows, all the more where several token tiles read them from the caches.
 bool rows_through_lds(int tm, int tn, int64_t M, int64_t K, int64_t row_bytes, int split) {
     const int64_t kt = (K + 63) / 64, per = (kt + split - 1) / split, tiles_m = (M + tm - 1) / tm;
     if ((row_bytes & 127) == 0) {
-        if (per < kt && (per & 1)) return per >= (tm == 256 && tn == 256 ? 48 : 12);
+        if (per < kt && (per & 1)) return per >= 12 && !(tm == 256 && tn == 256);
         return per >= 12 || tm > 128 || tn > 128;
     }
     if ((row_bytes & 63) == 0) return per >= 20 && kt >= (tiles_m == 1 ? 24 : 48);
