@@ -578,10 +578,11 @@ struct BypassKernel {
     static constexpr bool MERGE = kind_is_nested(WK);
     static constexpr bool ROWMAJOR = WK == kNestedF16Row;
     // NT: the launch has one token tile, so every weight is read once; packed blocks (whole lines per
-    // instruction) are then marked non-temporal, as in the streaming kernel.  The 64-token tiles always
-    // are; the 128-token tiles on the large layers (timed: 6-10 % faster from about 100 Mi weights on at
+    // instruction) are then marked non-temporal, as in the streaming kernel.  The 64-token tiles of such a launch always
+    // are (and some of several token tiles: see streams_tiles64); the 128-token
+    // tiles on the large layers (timed: 6-10 % faster from about 100 Mi weights on at
     // M = 96 and 128, a few per cent slower on the small ones).
-    static constexpr int POLICY = (NT || (!ROWMAJOR && TM == 64)) ? 2 : 0;
+    static constexpr int POLICY = NT ? 2 : 0;
     // PAIR: row-major planes are fetched for two K-tiles at a time, 128 bytes of 8 rows per instruction, and
     // regrouped through 2 KB of LDS per wave one K-tile before the first of the two is merged.  Fetched
     // for one K-tile, 64 bytes of 16 rows per instruction, every line is requested twice: (28672, 5120) at 48
@@ -1226,7 +1227,7 @@ struct E4m3BypassKernel {
     static_assert(XA >= 3 && XA < NST && NRAW <= XA, "the stage being filled is neither the one in use nor the next");
     typedef __attribute__((address_space(3))) uint8_t lds_byte;
 
-    static constexpr int POLICY = (NT || (!ROWMAJOR && TM == 64)) ? 2 : 0;   // whole lines, read once per launch: non-temporal
+    static constexpr int POLICY = NT ? 2 : 0;                  // whole lines, read once per launch: non-temporal
     struct Raw { intx4 u[FNB][2]; };                           // one K-tile of the wave's plane blocks
     struct Tok { intx4 q[FMB][2]; };                           // one K-tile of token fragments
 
@@ -1727,6 +1728,16 @@ static bool streams_rows(const LargeParams &p) {
            (reinterpret_cast<uintptr_t>(p.W1) & 127) == 0;
 }
 
+// Packed weights on 64-token tiles are marked non-temporal with one token tile, which reads them once, and with several
+// where all token tiles of a weight tile follow each other on one XCD (1.01-1.09 x faster so).  The weight tiles past a multiple of eight are
+// read on several XCDs (see tile_of_block): on layers of 4 Mi weights and more, unmarked weights, which the memory-side cache keeps, are 2-13 %
+// faster with two to four token tiles, and on FP16 layers of 64 Mi and more they are with any (6-8 %).  Timed both ways, weights cold,
+// on 72 layers at 80, 128, 192 and 256 tokens in one to three slices.
+static bool streams_tiles64(const LargeParams &p, bool fp8) {
+    const int64_t weights = (int64_t)p.N * p.K, mi = (int64_t)1 << 20;
+    return p.tiles_m == 1 || weights < 4 * mi || ((p.tiles_n & 7) == 0 && (fp8 || weights < 64 * mi));
+}
+
 template <int TM, int TN, int WK, bool DEEP = false, bool NT = false, bool PAIRS = false>
 static void launch_bypass(const LargeParams &p, dim3 grid, hipStream_t stream) {
     auto kern = nested_bypass_kernel<TM, TN, WK, DEEP, NT, PAIRS>;
@@ -1753,8 +1764,8 @@ static void launch_rows(const LargeParams &p, dim3 grid, hipStream_t stream) {
 
 template <int TM, int TN, bool ROWMAJOR, bool NT = false>
 static void launch_e4m3_bypass(const LargeParams &p, dim3 grid, hipStream_t stream) {
-    if constexpr (ROWMAJOR && !NT) {
-        if (streams_rows(p)) {
+    if constexpr (!NT) {
+        if (ROWMAJOR ? streams_rows(p) : streams_tiles64(p, true)) {
             launch_e4m3_bypass<TM, TN, ROWMAJOR, true>(p, grid, stream);
             return;
         }
@@ -1889,7 +1900,8 @@ static void launch_nested(const LargeParams &p, const LargeConfig &c, int height
         return;
     }
     if (c.tm == 64) {
-        launch_bypass<64, 128, WK>(p, grid, stream);
+        if (streams_tiles64(p, false)) launch_bypass<64, 128, WK, false, true>(p, grid, stream);
+        else launch_bypass<64, 128, WK>(p, grid, stream);
     } else {
         // one token tile over a large packed layer: weights marked non-temporal (see BypassKernel)
         if constexpr (WK != kNestedF16Row) {

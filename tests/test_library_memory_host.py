@@ -1,5 +1,6 @@
-"""Host side of the calls that use memory of the library's own (waited counts, the fixed scratch), against a stand-in for the HIP runtime: two
-devices, kernels that run on the CPU when their stream is waited for, calls that can be made to fail.  Needs no GPU."""
+"""Host side of the library against a stand-in for the HIP runtime (two devices, kernels that run on the CPU when their
+stream is waited for, calls that can be made to fail): memory of the library's own, and which kernels are launched.
+Needs no GPU."""
 import os
 import shutil
 import subprocess
@@ -31,6 +32,7 @@ static std::deque<std::function<void()>> queued;
 static std::map<const void *, std::string> kernels;
 static std::map<const void *, size_t> variables;
 static std::map<std::pair<int, const void *>, char *> images;  // a variable's copy on a device
+static std::string last_gemm;                                  // name of the last GEMM kernel
 static std::pair<void *, void *> last_copy;                    // where, from where
 
 static void *stream_of(int dev) { return reinterpret_cast<void *>((intptr_t)0x1000 + dev); }
@@ -120,6 +122,7 @@ int hipLaunchKernel(const void *f, Dim3, Dim3, void **args, size_t, void *stream
         }
     } else if (name.find("gemm_kernel") != std::string::npos || name.find("bypass") != std::string::npos ||
                name.find("nested_rows") != std::string::npos) {
+        last_gemm = name;
         for (int i = 0; i < 15; ++i) {                         // the pointers among the first 120 bytes of its parameters
             void *const p = static_cast<void **>(args[0])[i];
             look(p);
@@ -139,6 +142,8 @@ static int (*range_check)(const void *, int64_t, int64_t, int64_t, uint64_t *, u
 static int (*decompose)(const void *, int64_t, int64_t, int64_t, void *, void *, uint64_t *, uint64_t *, void *);
 static int (*prepare)(const void *, int64_t, int64_t, int64_t, int, void *, void *, uint64_t *, Layer *, void *);
 static int (*gemm_static)(const void *, int64_t, int64_t, int64_t, const void *, const void *, int64_t, int, const float *, void *, int64_t, void *);
+static int (*gemm_packed)(const void *, int64_t, int64_t, int64_t, const void *, const void *, int64_t, int, const float *, void *, int64_t, void *, size_t, void *);
+static int (*tune)(const char *, int64_t);
 static char W[4096] __attribute__((aligned(16))), up[4096] __attribute__((aligned(16))), lo[4096] __attribute__((aligned(16)));
 
 static int failures;
@@ -268,6 +273,28 @@ static void fixed_scratch_on_two_devices() {
     CHECK(wrong_device == 0 && scratch_uses > 0);
 }
 
+// Packed weights on 64-token tiles: marked non-temporal with one token tile, on small layers, and where the weight tiles are a
+// multiple of eight (FP16 mode: below 64 Mi weights).
+static void non_temporal_weights() {
+    static char ws[8 << 20] __attribute__((aligned(16))), X[16 << 20] __attribute__((aligned(16)));
+    tune("small_max_m", 0);
+    tune("large_bm", 64);
+    tune("large_split", 1);
+    struct { int64_t M, N, K;  bool fp16, fp8; } const cases[] = {
+        {33, 5696, 5696, true, true}, {64, 5696, 5696, true, true}, {65, 5696, 5696, false, false}, {256, 5696, 5696, false, false},
+        {200, 2000, 1024, true, true}, {200, 2944, 1536, false, false},       // 1.95 and 4.3 Mi weights in 16 and 23 tiles
+        {200, 2049, 1024, true, true}, {256, 8192, 4096, true, true}, {256, 8192, 8192, false, true}};
+    for (const auto &c : cases) {
+        CHECK(gemm_packed(X, c.M, c.K, c.K, W, W, c.N, 0, nullptr, X, (c.N + 3) & ~3, ws, sizeof(ws), nullptr) == OK);
+        CHECK(last_gemm.find(c.fp16 ? "nested_bypass_kernelILi64ELi128ELi1ELb0ELb1ELb0E" : "nested_bypass_kernelILi64ELi128ELi1ELb0ELb0ELb0E") != std::string::npos);
+        CHECK(gemm_packed(X, c.M, c.K, c.K, W, W, c.N, 1, nullptr, X, (c.N + 3) & ~3, ws, sizeof(ws), nullptr) == OK);
+        CHECK(last_gemm.find(c.fp8 ? "e4m3_bypass_kernelILi64ELi128ELb0ELb1E" : "e4m3_bypass_kernelILi64ELi128ELb0ELb0E") != std::string::npos);
+    }
+    tune("small_max_m", -1);
+    tune("large_bm", -1);
+    tune("large_split", -1);
+}
+
 int main(int argc, char **argv) {
     void *h = argc > 2 ? dlopen(argv[1], RTLD_NOW) : nullptr;
     if (h == nullptr) { fprintf(stderr, "%s\n", dlerror());  return 2; }
@@ -275,11 +302,14 @@ int main(int argc, char **argv) {
     *(void **)&decompose = dlsym(h, "nestedfp_decompose");
     *(void **)&prepare = dlsym(h, "nestedfp_layer_prepare");
     *(void **)&gemm_static = dlsym(h, "nestedfp_gemm_static");
+    *(void **)&gemm_packed = dlsym(h, "nestedfp_gemm_packed");
+    *(void **)&tune = dlsym(h, "nestedfp_tune");
     const std::string what = argv[2];
     if (what == "streams_of_two_devices") streams_of_two_devices();
     else if (what == "without_pinned_words") without_pinned_words();
     else if (what == "failing_calls") failing_calls();
     else if (what == "fixed_scratch_on_two_devices") fixed_scratch_on_two_devices();
+    else if (what == "non_temporal_weights") non_temporal_weights();
     else return 2;
     if (launches == 0) return 2;                               // (the library bound to the real runtime)
     return failures ? 1 : 0;
@@ -302,7 +332,7 @@ def program(tmp_path_factory):
     return [str(exe), os.environ.get("NESTEDFP_LIB") or build.lib_path()]
 
 
-@pytest.mark.parametrize("what", ["streams_of_two_devices", "without_pinned_words", "failing_calls", "fixed_scratch_on_two_devices"])
-def test_memory_of_the_library(program, what):
+@pytest.mark.parametrize("what", ["streams_of_two_devices", "without_pinned_words", "failing_calls", "fixed_scratch_on_two_devices", "non_temporal_weights"])
+def test_host_side(program, what):
     res = subprocess.run(program + [what], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0, res.stdout + res.stderr

@@ -76,3 +76,20 @@ def test_short_batches_in_their_own_launch_shapes(nfp, M, N, K):
     # 65 ... 256 tokens with no knob set: every shape the launch may take fits the fixed scratch
     assert nfp.gemm_workspace_size(M, N, K, nfp.MODE_FP16) <= nfp.STATIC_SCRATCH_BYTES
     run_both_modes(nfp, workloads.act_host(M, K, seed=N), workloads.weight_host(N, K, seed=M), "%d x %d, M=%d" % (N, K, M))
+
+
+@pytest.mark.parametrize("M,N,K,split", [(65, 130, 64 * 3 + 16, 1), (130, 264, 64 * 9, 2), (192, 560, 64 * 20 + 48, 1), (200, 136, 64 * 16, 3), (256, 1040, 64 * 5, 1)])
+def test_several_token_tiles_of_64(nfp, M, N, K, split):
+    # packed weights that are not marked non-temporal: against the oracle, the row-major planes and packed FP16 weights
+    knobs = {"large_bm": 64, "large_split": split}
+    try:
+        for k, v in knobs.items():
+            nfp.tune(k, v)
+        X, W = workloads.act_host(M, K, seed=N), workloads.weight_host(N, K, seed=M)
+        run_both_modes(nfp, X, W, "%d x %d, M=%d %s" % (N, K, M, knobs), check_plain=False)
+        Xd, Wd = to_dev(X), to_dev(W)
+        up, lo = nfp.decompose(Wd)
+        assert np.array_equal(bits(nfp.gemm(Xd, up, lo, nfp.MODE_FP16)), bits(nfp.plain_gemm_fp16(Xd, nfp.pack_fp16(Wd))))
+    finally:
+        for k in knobs:
+            nfp.tune(k, -1)
