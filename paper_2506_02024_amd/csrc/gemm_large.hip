@@ -1595,6 +1595,9 @@ static const ShortCost kShortCost[2] = {
     {{{256, 256, 0, 0.6255, 3.16, 0.378, 3.16}, {256, 128, 1, 0.319, 2.41, 0.319, 2.41}, {128, 256, 1, 0.334, 2.71, 0, 0},
       {128, 128, 1, 0.2136, 1.73, 0, 0}, {64, 128, 0, 0.183, 1.54, 0, 0}}, 1.0, 1.10, 2.0, 10.4e6, 1e15, 144e3, 3.28, 4.68e6},
 };
+// E4M3 weights on 64-token tiles: the weight tiles past a multiple of eight (see tile_of_block) are fetched by each token tile on
+// another XCD, from memory once the plane is larger than the L2s: with three and four token tiles such launches take 10-30 % longer than
+// priced ((5840, 5840) at 144 tokens 29 us against 20.6 in two slices of 128 x 128), the others what they are priced at.
 static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K) {
     const bool fp8 = cls == 2;
     const ShortCost &m = kShortCost[fp8 ? 1 : 0];
@@ -1629,6 +1632,7 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K) {
             time += m.base + (double)N * (double)K * (fp8 ? 1.0 : 2.0) / m.w_rate + wgs * per * (height + e.tn) * 128.0 / m.l2_rate +
                     rounds * per * (double)(std::min<int64_t>(height, M) + e.tn) * 128.0 / m.cu_rate;
             if (slices > 1) time += split_cost(M, N, slices, m.split, m.split_rate);
+            if (fp8 && e.tm == 64 && M > 128 && (((N + 127) / 128) & 7) != 0 && N * K >= ((int64_t)24 << 20)) time *= 1.1;
             if (time < best) { best = time;  c.tm = e.tm;  c.tn = e.tn;  c.split = split;  c.deep = e.deep; }
             if (t.large_split > 0) break;
         }

@@ -27,3 +27,20 @@ def through_lds(L, bm, bn, M, K, split):
 ])
 def test_how_row_major_planes_reach_a_tile(L, bm, bn, M, K, split, lds):
     assert through_lds(L, bm, bn, M, K, split) == lds
+
+
+def partial_bytes(L, kind, M, N, K, which="24large_gemm_partial_bytes"):
+    f = getattr(L, "_ZN3nfp%sEilll" % which)
+    f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int] + 3 * [ctypes.c_int64]
+    return f(kind, M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K,split", [
+    # E4M3 weights, 45 to 46 weight tiles of 128 rows (a tail past a multiple of eight), 31 Mi and more, three and four token tiles: two
+    # slices of 128 x 128 20.6, 19.9 and 22.4 us, 64-token tiles unsplit 29.6, 27.1 and 29.7
+    (144, 5840, 5840, True), (160, 5696, 5696, True), (176, 5840, 5840, True),
+    # no tail, or a plane that stays in the L2s: unsplit
+    (160, 6144, 4096, False), (208, 4480, 4480, False),
+])
+def test_e4m3_weights_on_64_token_tiles_with_a_tail(L, M, N, K, split):
+    assert (partial_bytes(L, 2, M, N, K) > 0) == split
