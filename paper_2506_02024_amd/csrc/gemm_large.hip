@@ -1595,15 +1595,19 @@ static const ShortCost kShortCost[2] = {
     {{{256, 256, 0, 0.6255, 3.16, 0.378, 3.16}, {256, 128, 1, 0.319, 2.41, 0.319, 2.41}, {128, 256, 1, 0.334, 2.71, 0, 0},
       {128, 128, 1, 0.2136, 1.73, 0, 0}, {64, 128, 0, 0.183, 1.54, 0, 0}}, 1.0, 1.10, 2.0, 10.4e6, 1e15, 144e3, 3.28, 4.68e6},
 };
+// Splits whose partial sums outgrow the fixed scratch of nestedfp_gemm_static are left to FP16 mode, where they are priced 4 %
+// cheaper than what fits: (17616, 5872) at 256 tokens in three slices of 18 MB 81 us (packed) and 93 (row-major), unsplit 103 and 111.
+// (At 1-3 % they gain and lose by 10 %; in FP8 mode (8192, 28672) would gain 5-13 %, (5120, 32768) lose 12-21 %.)  That entry
+// point takes what fits (bounded).
 // E4M3 weights on 64-token tiles: the weight tiles past a multiple of eight (see tile_of_block) are fetched by each token tile on
 // another XCD, from memory once the plane is larger than the L2s: with three and four token tiles such launches take 10-30 % longer than
 // priced ((5840, 5840) at 144 tokens 29 us against 20.6 in two slices of 128 x 128), the others what they are priced at.
-static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K) {
+static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K, bool bounded) {
     const bool fp8 = cls == 2;
     const ShortCost &m = kShortCost[fp8 ? 1 : 0];
     const Tuning &t = tuning();
     const int kt = (int)(((fp8 ? K : 2 * K) + 127) / 128);
-    const bool bounded = static_scratch_holds(1, M, N, K, fp8, partial_ld(N));
+    const bool limited = static_scratch_holds(1, M, N, K, fp8, partial_ld(N));
     const int want_m = (t.large_bm == 128 || t.large_bm == 256) ? (int)t.large_bm : 0;
     const int want_n = (t.large_bn == 128 || t.large_bn == 256) ? (int)t.large_bn : want_m;
     LargeConfig c;
@@ -1622,8 +1626,9 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K) {
         }
         for (int split : kSplits) {
             if (t.large_split > 0) split = (int)(t.large_split < kt ? t.large_split : kt);
-            // (a split's scratch fits the fixed one of nestedfp_gemm_static wherever the problem does without)
-            else if (split > 1 && (split > kt / 4 || (bounded && !static_scratch_holds(split, M, N, K, fp8, partial_ld(N))))) break;
+            else if (split > 1 && split > kt / 4) break;
+            const bool fits = t.large_split > 0 || !limited || static_scratch_holds(split, M, N, K, fp8, partial_ld(N));
+            if (!fits && (fp8 || bounded || !padded_split_fits(split, M, N, K, fp8))) break;
             const int per = (kt + split - 1) / split;
             const int slices = (kt + per - 1) / per;
             const double wgs = (double)(tiles * slices), rounds = (double)((tiles * slices + 255) / 256);
@@ -1632,6 +1637,7 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K) {
             time += m.base + (double)N * (double)K * (fp8 ? 1.0 : 2.0) / m.w_rate + wgs * per * (height + e.tn) * 128.0 / m.l2_rate +
                     rounds * per * (double)(std::min<int64_t>(height, M) + e.tn) * 128.0 / m.cu_rate;
             if (slices > 1) time += split_cost(M, N, slices, m.split, m.split_rate);
+            if (!fits) time /= 0.96;
             if (fp8 && e.tm == 64 && M > 128 && (((N + 127) / 128) & 7) != 0 && N * K >= ((int64_t)24 << 20)) time *= 1.1;
             if (time < best) { best = time;  c.tm = e.tm;  c.tn = e.tn;  c.split = split;  c.deep = e.deep; }
             if (t.large_split > 0) break;
@@ -1641,7 +1647,7 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K) {
     return c;
 }
 
-static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, int max_split = 8) {
+static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, bool bounded, int max_split = 8) {
     LargeConfig c;
     c.cost = 0.0;
     const Tuning &t = tuning();
@@ -1653,7 +1659,7 @@ static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, int m
     if (t.large_bm == 64 || (M <= 64 && t.large_bm < 0 && t.large_bn < 0))
         return choose_tile64(cls, M, N, K);
     const bool pinned = t.large_bm > 0 || t.large_bn > 0 || t.large_split > 0;
-    if (M <= 256 && ((cls == 1 && t.large_deep <= 0) || (cls == 2 && t.large_deep < 0 && !pinned))) return choose_short(cls, M, N, K);
+    if (M <= 256 && ((cls == 1 && t.large_deep <= 0) || (cls == 2 && t.large_deep < 0 && !pinned))) return choose_short(cls, M, N, K, bounded);
     double best = 1e30;
     c.tm = c.tn = 256;
     c.split = 1;
@@ -1698,19 +1704,20 @@ static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, int m
             }
         }
     }
-    if (t.large_split <= 0 && !padded_split_fits(c.split, M, N, K, fp8)) return compute_large(cls, M, N, K, c.split - 1);
+    if (t.large_split <= 0 && !padded_split_fits(c.split, M, N, K, fp8)) return compute_large(cls, M, N, K, bounded, c.split - 1);
     return c;
 }
 
-static LargeConfig choose_large(int kind, int64_t M, int64_t N, int64_t K) {
+static LargeConfig choose_large(int kind, int64_t M, int64_t N, int64_t K, bool bounded) {
     static thread_local PlanCache<LargeConfig> cache;
-    return cache.get(kind_class(kind), M, N, K, [&] { return compute_large(kind_class(kind), M, N, K); });
+    return cache.get(kind_class(kind) + (bounded ? 3 : 0), M, N, K, [&] { return compute_large(kind_class(kind), M, N, K, bounded); });
 }
 
-size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K) {
-    LargeConfig c = choose_large(kind, M, N, K);
+static size_t partial_bytes(const LargeConfig &c, int64_t M, int64_t N) {
     return c.split > 1 ? (size_t)c.split * (size_t)M * (size_t)partial_ld(N) * sizeof(float) : 0;
 }
+size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K) { return partial_bytes(choose_large(kind, M, N, K, false), M, N); }
+size_t large_gemm_bounded_bytes(int kind, int64_t M, int64_t N, int64_t K) { return partial_bytes(choose_large(kind, M, N, K, true), M, N); }
 
 template <int KIND, int TM, int TN, int WAVES_M, int WAVES_N, int NST = 2, int NSTW = NST>
 static void launch_large_t(const LargeParams &p, dim3 grid, hipStream_t stream) {
@@ -1941,7 +1948,7 @@ bool large_gemm_supports(int kind, int64_t K, int64_t ldx, int64_t ldw) {
 
 int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     if (!large_gemm_supports(kind, a.K, a.ldx, a.ldw)) return kErrShape;
-    LargeConfig c = choose_large(kind, a.M, a.N, a.K);
+    LargeConfig c = choose_large(kind, a.M, a.N, a.K, a.bounded);
     // the register-path kernels take the deeper pipeline only where it is asked for (knob) or was
     // timed faster (table), and only on the tiles of 128 tokens
     if (kind_class(kind) == 1) c.deep = (tuning().large_deep > 0 || (c.deep && tuning().large_deep != 0)) && c.tm == 128;

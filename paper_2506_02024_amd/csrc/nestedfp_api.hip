@@ -62,18 +62,18 @@ bool route_small(int kind, int64_t M, int64_t N, int64_t K, int64_t ldw) {
     return small_gemm_cost(priced, M, N, K) * line.factor <= tiles.cost + (tiles.split > 1 ? line.split : line.unsplit);
 }
 
-static size_t partial_bytes_for(int kind, int64_t M, int64_t N, int64_t K) {
-    return route_small(kind, M, N, K, K) ? small_gemm_partial_bytes(kind, M, N, K)
-                                   : large_gemm_partial_bytes(kind, M, N, K);
+static size_t partial_bytes_for(int kind, int64_t M, int64_t N, int64_t K, bool bounded) {
+    if (route_small(kind, M, N, K, K)) return small_gemm_partial_bytes(kind, M, N, K);
+    return bounded ? large_gemm_bounded_bytes(kind, M, N, K) : large_gemm_partial_bytes(kind, M, N, K);
 }
 
-static size_t workspace_bytes_for(int kind, int64_t M, int64_t N, int64_t K, bool quantize) {
-    return workspace_need(partial_bytes_for(kind, M, N, K), M, K, quantize);
+static size_t workspace_bytes_for(int kind, int64_t M, int64_t N, int64_t K, bool quantize, bool bounded = false) {
+    return workspace_need(partial_bytes_for(kind, M, N, K, bounded), M, K, quantize);
 }
 
 static bool carve(void *ws, size_t ws_bytes, int kind, int64_t M, int64_t N, int64_t K, bool quantize,
-                  Workspace &out) {
-    size_t need = workspace_bytes_for(kind, M, N, K, quantize);
+                  Workspace &out, bool bounded = false) {
+    size_t need = workspace_bytes_for(kind, M, N, K, quantize, bounded);
     if (need > 0 && (ws == nullptr || ws_bytes < need || !aligned(ws, 16))) return false;
     out.counters = nullptr;
     out.xq = nullptr;
@@ -135,9 +135,10 @@ static int fp8_gemm_fused(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, 
 
 static int fp8_gemm(const uint8_t *Xq, const float *scales, int64_t M, int64_t K, const uint8_t *Wq,
                     int64_t N, int w_kind, float w_scale, uint16_t *Y, int64_t ldy, const Workspace &ws,
-                    hipStream_t stream) {
+                    hipStream_t stream, bool bounded = false) {
     GemmArgs a;
     memset(&a, 0, sizeof(a));
+    a.bounded = bounded;
     a.X = Xq;  a.ldx = K;  a.scales = scales;  a.w_scale = w_scale;
     a.W0 = Wq;  a.W1 = nullptr;  a.ldw = K;
     a.M = M;  a.N = N;  a.K = K;  a.Y = Y;  a.ldy = ldy;
@@ -313,7 +314,7 @@ static size_t gemm_workspace_size(int64_t M, int64_t N, int64_t K, int mode) {
 
 static int gemm_impl(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, const uint8_t *upper,
                      const uint8_t *lower, int64_t N, int layout, int mode, const float *act_scale, uint16_t *Y,
-                     int64_t ldy, void *workspace, size_t workspace_bytes, void *stream) {
+                     int64_t ldy, void *workspace, size_t workspace_bytes, void *stream, bool bounded = false) {
     if (!valid_mode(mode) || !valid_layout(layout)) return NESTEDFP_ERR_ARG;
     int st = check_dims(M, N, K);
     if (st != kOk) return st;
@@ -330,22 +331,23 @@ static int gemm_impl(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, const
     Workspace ws;
     if (mode == NESTEDFP_MODE_FP16) {
         const int kind = packed ? kNestedF16 : kNestedF16Row;
-        if (!carve(workspace, workspace_bytes, kind, M, N, K, false, ws)) return NESTEDFP_ERR_WORKSPACE;
+        if (!carve(workspace, workspace_bytes, kind, M, N, K, false, ws, bounded)) return NESTEDFP_ERR_WORKSPACE;
         GemmArgs a;
         memset(&a, 0, sizeof(a));
+        a.bounded = bounded;
         a.X = X;  a.ldx = ldx;  a.W0 = upper;  a.W1 = lower;  a.ldw = K;
         a.M = M;  a.N = N;  a.K = K;  a.Y = Y;  a.ldy = ldy;
         a.partials = ws.partials;  a.partial_bytes = ws.partial_bytes;  a.counters = ws.counters;
         return run_gemm(kind, a, s);
     }
     const int kind = packed ? kE4M3 : kE4M3Row;
-    if (!carve(workspace, workspace_bytes, kind, M, N, K, true, ws)) return NESTEDFP_ERR_WORKSPACE;
+    if (!carve(workspace, workspace_bytes, kind, M, N, K, true, ws, bounded)) return NESTEDFP_ERR_WORKSPACE;
     // Sec. 4.1: the upper plane read as E4M3 is the weight times 2^8
     st = fp8_gemm_fused(X, M, K, ldx, act_scale, upper, N, kind, 0.00390625f, Y, ldy, s);
     if (st >= 0) return st;
     st = launch_quantize_act(X, M, K, ldx, act_scale, ws.xq, ws.scales, s);
     if (st != kOk) return st;
-    return fp8_gemm(ws.xq, ws.scales, M, K, upper, N, kind, 0.00390625f, Y, ldy, ws, s);
+    return fp8_gemm(ws.xq, ws.scales, M, K, upper, N, kind, 0.00390625f, Y, ldy, ws, s, bounded);
 }
 
 static int plain_fp16_impl(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, const void *W, int64_t N,
@@ -565,7 +567,10 @@ int nestedfp_gemm_static(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, c
     if (M == 0 || N == 0) return NESTEDFP_OK;
     // the scratch this problem needs in this plane layout and mode, against the fixed array
     const int kind = mode == NESTEDFP_MODE_FP16 ? kNestedF16Row : kE4M3Row;
-    const size_t need = workspace_bytes_for(kind, M, N, K, mode == NESTEDFP_MODE_FP8);
+    size_t need = workspace_bytes_for(kind, M, N, K, mode == NESTEDFP_MODE_FP8);
+    // (a K split of 65 ... 256 tokens that outgrows it: one that does not)
+    const bool bounded = need > (size_t)NESTEDFP_STATIC_SCRATCH_BYTES;
+    if (bounded) need = workspace_bytes_for(kind, M, N, K, mode == NESTEDFP_MODE_FP8, true);
     if (need > (size_t)NESTEDFP_STATIC_SCRATCH_BYTES) return NESTEDFP_ERR_WORKSPACE;
     void *ws = nullptr;
     if (need > 0) {
@@ -573,7 +578,7 @@ int nestedfp_gemm_static(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, c
         if (st != kOk) return st;
     }
     return gemm_impl(X, M, K, ldx, upper, lower, N, NESTEDFP_LAYOUT_ROWMAJOR, mode, act_scale, Y, ldy, ws,
-                     need > 0 ? (size_t)NESTEDFP_STATIC_SCRATCH_BYTES : 0, stream);
+                     need > 0 ? (size_t)NESTEDFP_STATIC_SCRATCH_BYTES : 0, stream, bounded);
 }
 
 int nestedfp_plain_gemm_fp16(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, const uint16_t *W,

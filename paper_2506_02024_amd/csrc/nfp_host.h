@@ -61,6 +61,7 @@ struct GemmArgs {
     float *partials;      // split-K scratch (may be NULL if split == 1)
     size_t partial_bytes;
     uint32_t *counters;   // kMaxCounters arrival counters, all zero between calls (NULL: reduce in a second launch)
+    bool bounded;         // K splits of 65 ... 256 tokens that fit the fixed scratch only (see nestedfp_gemm_static)
 };
 
 // arrival counters at the start of every workspace: one per output tile of a split launch
@@ -147,6 +148,7 @@ int launch_small_gemm(int kind, const GemmArgs &a, hipStream_t stream);
 bool rows_by_pairs(int tm, int64_t M, int64_t N, int64_t K, int64_t row_bytes, int split);   // row-major planes, tiles of tm tokens x 128 rows
 bool rows_through_lds(int tm, int tn, int64_t M, int64_t K, int64_t row_bytes, int split);           // the other tiles
 size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K);
+size_t large_gemm_bounded_bytes(int kind, int64_t M, int64_t N, int64_t K);      // with GemmArgs::bounded
 int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream);
 
 // Row stride of the split-K partial sums [slice][token][ld]: whole groups of four columns, so that they are

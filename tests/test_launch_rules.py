@@ -44,3 +44,25 @@ def partial_bytes(L, kind, M, N, K, which="24large_gemm_partial_bytes"):
 ])
 def test_e4m3_weights_on_64_token_tiles_with_a_tail(L, M, N, K, split):
     assert (partial_bytes(L, 2, M, N, K) > 0) == split
+
+
+@pytest.mark.parametrize("M,N,K", [(160, 17616, 5872), (200, 17616, 5872), (256, 17616, 5872)])
+def test_fp16_splits_beyond_the_fixed_scratch(L, M, N, K):
+    # three slices of 256 x 256: 61, 72 and 81 us on packed planes, unsplit 78, 86 and 103; the entry point without a workspace takes
+    # a split that fits
+    for kind in (1, 4, 6):
+        assert partial_bytes(L, kind, M, N, K) == 3 * M * N * 4 > 32 << 20
+        assert 16384 + partial_bytes(L, kind, M, N, K, "24large_gemm_bounded_bytes") <= 32 << 20
+    # FP8 mode: what fits
+    assert partial_bytes(L, 2, 256, 5120, 32768) + 256 * 32768 + 16384 + 2048 <= 32 << 20
+
+
+def test_fp16_splits_beyond_the_fixed_scratch_are_never_chosen_without_a_workspace(L):
+    import random
+
+    rng = random.Random(3)
+    for _ in range(3000):
+        M, N, K = rng.randrange(65, 257), rng.randrange(1, 70000), 16 * rng.randrange(1, 2000)
+        for kind in (1, 4):
+            free, bounded = (partial_bytes(L, kind, M, N, K, w) for w in ("24large_gemm_partial_bytes", "24large_gemm_bounded_bytes"))
+            assert bounded <= free and (bounded == free or free > (32 << 20) - 16384)

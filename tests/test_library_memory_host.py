@@ -270,6 +270,8 @@ static void fixed_scratch_on_two_devices() {
                 CHECK(scratch_uses > before || (mode == 0 && M != 40));
                 CHECK(current == 0);
             }
+    // a split that does not fit is not taken: the call is
+    CHECK(gemm_static(X, 256, 5872, 5872, W, W, 17616, 0, nullptr, Y, 17616, stream_of(0)) == OK);
     CHECK(wrong_device == 0 && scratch_uses > 0);
 }
 

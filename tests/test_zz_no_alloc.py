@@ -61,3 +61,22 @@ def test_problems_beyond_the_fixed_scratch_are_refused(nfp):
         nfp.gemm_static(X, up, None, nfp.MODE_FP8, out)
     assert e.value.status == nfp.ERR_WORKSPACE
     assert int(out.count_nonzero()) == 0
+
+
+def test_split_that_outgrows_the_fixed_scratch(nfp):
+    # nestedfp_gemm takes three slices of 18 MB here; without a workspace a split that fits is taken: the same products, summed in
+    # another order
+    from helpers import assert_gemm_close
+
+    M, N, K = 256, 17616, 5872
+    assert nfp.gemm_workspace_size(M, N, K, nfp.MODE_FP16) > nfp.STATIC_SCRATCH_BYTES
+    W = to_dev(workloads.weight_host(N, K, seed=5))
+    X = to_dev(workloads.act_host(M, K, seed=6))
+    up, lo = nfp.decompose(W)
+    want = nfp.gemm(X, up, lo, nfp.MODE_FP16).float().cpu().numpy()
+    out = torch.zeros((M, N), dtype=torch.float16, device="cuda:0")
+    before = torch.cuda.memory_allocated()
+    nfp.gemm_static(X, up, lo, nfp.MODE_FP16, out)
+    torch.cuda.synchronize()
+    assert torch.cuda.memory_allocated() == before
+    assert_gemm_close(out.cpu().numpy(), want, "bounded split")
