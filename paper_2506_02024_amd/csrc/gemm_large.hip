@@ -1577,10 +1577,12 @@ static bool cuts_tiles(int cls, int tn) { return cls == 1 || (cls == 2 && tn == 
 
 // 65 ... 256 tokens of the two classes whose tiles of 256 tokens are cut down: every tile shape, the 64-token tiles
 // included, priced by what was found to add up -- the rounds of workgroups, the weights, what all workgroups take in
-// from L2 (weights and tokens) and what the busiest CU does.  Fitted to timings of every shape and split (and both
-// pipeline depths of E4M3, of which the deeper one is all that is left) on 960 problems in FP16 mode and 1020 in FP8
-// mode, layers of 0.8 to 470 Mi weights, both storage orders: the choice is 1.7 % and 3.3 % behind the fastest launch on
-// average, where the model below, which knows neither the 64-token tiles nor the newer kernels, was 7 % and 10 % behind.
+// from L2 (weights and tokens) and what the busiest CU does.  Taken from timings of every shape and split (and both
+// pipeline depths of E4M3, of which the deeper one is all that is left).  On the 82 000 launches that fit_costs.py times for them (weights
+// cold, 70 layers of 0.8 to 500 Mi weights, twelve batch sizes, both storage orders) the choice is 2.2 % (FP16 mode) and 2.0 % (FP8
+// mode) behind the fastest launch on average, 12-13 % at the 95th percentile; the model below, which knows neither the 64-token
+// tiles nor the newer kernels, was 7-10 % behind.  Constants fitted to these timings are at 1.7 and 1.6 %, but take 40 to 90
+// launches that lose more than 6 %; one launch timed twice differs by up to as much.
 struct ShortShape { int tm, tn, deep; double tk, tfix, tk160, tfix160; };      // microseconds per K-tile and per workgroup; at a height of 160
 struct ShortCost {
     ShortShape shape[5];
@@ -1843,9 +1845,9 @@ bool rows_by_pairs(int tm, int64_t M, int64_t N, int64_t K, int64_t row_bytes, i
 }
 
 // Row-major planes on the other tiles: through LDS by pairs of K-tiles (RowsKernel), or straight into registers in operand
-// order, K-tile by K-tile.  Timed both ways on 14700 launches (22 values of K from 512 to 8192, six N, twelve batch
-// sizes, four tile shapes, splits of 1 ... 4): the rule is 0.5 % behind the faster way on average (everything straight
-// into registers: 5 %) and at most 10 % behind loads into registers.
+// order, K-tile by K-tile.  Timed both ways by fit_costs.py on 17600 launches at 65 ... 256 tokens (70 layers, every tile shape
+// and split, weights cold): the rule is 0.6 % behind the faster way on average, 5 % at the 95th percentile (everything
+// straight into registers: 12 and 32 %); on 7200 launches of 300 ... 2048 tokens 0.3 and 2 % (8 %).
 //  - Rows that start on lines: through LDS (1.01-1.06 x at less than a dozen K-tiles per slice, 1.15-1.24 x from three
 //    dozen on), but on 128 x 128 tiles from a dozen K-tiles on (0.99 x on average below, 0.81 x at worst).
 //  - Slices with an odd number of such K-tiles: every second one starts in the middle of a line, so that its pieces take
@@ -1874,7 +1876,9 @@ static void launch_rows_by_pairs(const LargeParams &p, dim3 grid, hipStream_t st
 
 template <int TM, int TN>
 static void launch_rows_tile(const LargeParams &p, dim3 grid, hipStream_t stream) {
-    if (!rows_through_lds(TM > 128 ? 256 : 128, TN, p.M, p.K, p.w_row_bytes, (int)grid.y)) {
+    const int64_t knob = tuning().large_rows;
+    const bool lds = knob >= 0 ? knob != 0 : rows_through_lds(TM > 128 ? 256 : 128, TN, p.M, p.K, p.w_row_bytes, (int)grid.y);
+    if (!lds) {
         launch_bypass<TM, TN, kNestedF16Row>(p, grid, stream);
         return;
     }

@@ -12,7 +12,7 @@
 namespace nfp {
 
 Tuning &tuning() {
-    static Tuning t = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, 1, -1, -1, -1, -1, -1};
+    static Tuning t = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, 1, -1, -1, -1, -1, -1, -1};
     return t;
 }
 
@@ -686,7 +686,7 @@ int nestedfp_probe_mfma(const void *operands, int fp8, int iters, uint32_t *sink
 
 static const char *const kKnobs[] = {"small_max_m", "small_split", "small_spw", "small_tiles", "small_interleave",
                                      "large_split", "large_bm", "large_bn", "large_epilogue", "small_fuse_quant", "quant_hw", "large_xcd_map",
-                                     "fused_reduce", "large_deep", "tuned_table", "quant_onepass", nullptr};
+                                     "fused_reduce", "large_deep", "large_rows", "tuned_table", "quant_onepass", nullptr};
 
 const char *nestedfp_tune_name(int index) {
     if (index < 0 || index >= (int)(sizeof(kKnobs) / sizeof(kKnobs[0]))) return nullptr;
@@ -711,6 +711,7 @@ int nestedfp_tune(const char *knob, int64_t value) {
     else if (!strcmp(knob, "large_xcd_map")) t.large_xcd_map = value;
     else if (!strcmp(knob, "fused_reduce")) t.fused_reduce = value;
     else if (!strcmp(knob, "large_deep")) t.large_deep = value;
+    else if (!strcmp(knob, "large_rows")) t.large_rows = value;
     else if (!strcmp(knob, "tuned_table")) t.tuned_table = value;
     else if (!strcmp(knob, "quant_onepass")) t.quant_onepass = value;
     else return NESTEDFP_ERR_ARG;

@@ -1,14 +1,20 @@
-"""Times the launch shapes of the streaming kernel over many layers and fits the constants that the
-library compiles in: kSmallCost (csrc/gemm_small.hip) and the lines between the streaming kernel and the
-64-token tiles at 17 ... 64 tokens (kLine in csrc/nestedfp_api.hip).
+"""Times the launch shapes of the kernels over many layers and fits the constants that the library compiles in:
+kSmallCost (csrc/gemm_small.hip), the lines between the streaming kernel and the 64-token tiles at 17 ... 64 tokens
+(kLine in csrc/nestedfp_api.hip), kShortCost (65 ... 256 tokens, csrc/gemm_large.hip); and says how far the
+choices that the library makes are behind the fastest launch, rows_through_lds among them.
 
     python -m paper_2506_02024_amd.fit_costs time candidates.jsonl routes.jsonl     # on the GPU, about 7 minutes
     python -m paper_2506_02024_amd.fit_costs fit candidates.jsonl routes.jsonl      # prints the constants
+    python -m paper_2506_02024_amd.fit_costs time-tiles tiles.jsonl [--tokens ...]  # on the GPU, about 10 minutes
+    python -m paper_2506_02024_amd.fit_costs fit-tiles tiles.jsonl
 
 `time` writes one line per timing: [N, K, tokens, storage, [K-steps per wave, K split, tiles per workgroup],
 us] and [N, K, tokens, storage, us of the tiled kernel, us of the streaming kernel].  Weights are cold (copies
 taken in turn) and the calls are replayed as one graph.  storage: 16p / 16r the planes in FP16 mode, packed and
-row-major, 8p / 8r the upper plane in FP8 mode on quantised activations, pr plain row-major FP16.
+row-major, 8p / 8r the upper plane in FP8 mode on quantised activations, pr plain row-major FP16.  `time-tiles`: [N, K,
+tokens, storage, launch, us], launch = null for the built-in choice or [tile tokens, tile weight rows, K split, deeper
+pipeline, way of row-major planes].  The layers taken in turn hold 700 MB: what the 256 MB memory-side cache keeps
+from one pass to the next makes non-temporal loads look slow and the others fast.
 `fit` mirrors price_small() and choose_tile64() of the library.  The constants minimise the time lost to the
 fastest candidate by a soft choice of the cheapest one, plus the error of the prices; the lines are searched on
 a grid for the time lost to the faster kernel, prices as the library has them compiled in.
@@ -58,31 +64,36 @@ def geometry(N, K, M, storage, spw, split, per):
 
 # ---- on the GPU -------------------------------------------------------------------------------------
 
+def graph_of(call, reps):
+    import torch
+
+    call(0)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for r in range(reps):
+            call(r)
+    g.replay()
+    return g
+
+
+def microseconds(g, reps):
+    import torch
+
+    a, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record()
+    g.replay()
+    e.record()
+    e.synchronize()
+    return a.elapsed_time(e) * 1e3 / reps
+
+
 def time_all(candidates_path, routes_path, shapes):
     import torch
 
     from . import binding as nfp, workloads
 
     dev = torch.device("cuda:0")
-
-    def graph_of(call, reps):
-        call(0)
-        torch.cuda.synchronize()
-        g = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(g):
-            for r in range(reps):
-                call(r)
-        g.replay()
-        return g
-
-    def microseconds(g, reps):
-        a, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        a.record()
-        g.replay()
-        e.record()
-        e.synchronize()
-        return a.elapsed_time(e) * 1e3 / reps
-
     t0 = time.time()
     with open(candidates_path, "w") as cand, open(routes_path, "w") as routes:
         for N, K in shapes:
@@ -138,6 +149,73 @@ def time_all(candidates_path, routes_path, shapes):
                                         nfp.tune(k, -1)
                                 us = float(np.median([microseconds(graph, reps) for _ in range(5)]))
                                 cand.write(json.dumps([N, K, M, storage, [spw, split, per], round(us, 2)]) + "\n")
+                del layers
+                torch.cuda.empty_cache()
+            print("N=%d K=%d  %.0f s" % (N, K, time.time() - t0), flush=True)
+
+
+TILE_TOKENS = (65, 80, 96, 112, 128, 144, 160, 176, 192, 208, 224, 256)
+TILE_SHAPES = ((256, 256), (256, 128), (128, 256), (128, 128), (64, 128))        # tokens x weight rows
+
+
+def tile_launches(N, K, M, storage):
+    """Every launch shape of the tiled kernels that is worth a timing: tile, K split, deeper pipeline (E4M3), way of the
+    row-major planes (FP16 mode: straight into registers, through LDS; -1: there is one way)."""
+    kt = -(-K // (128 if storage[0] == "8" else 64))
+    for tm, tn in TILE_SHAPES:
+        for split in SPLITS:
+            wgs = -(-M // tm) * -(-N // tn) * split
+            if split > 1 and (split > kt // 4 or wgs > 1280):
+                break
+            for deep in ((0, 1) if storage[0] == "8" and tm * tn < 256 * 256 and tm > 64 else (0,)):
+                for way in ((0, 1) if storage == "16r" and tm > 64 else (-1,)):
+                    yield tm, tn, split, deep, way
+
+
+def time_tiles(path, shapes, tokens):
+    import torch
+
+    from . import binding as nfp, workloads
+
+    dev = torch.device("cuda:0")
+    t0 = time.time()
+    with open(path, "w") as out:
+        for N, K in shapes:
+            for storage in STORAGES[:4]:
+                fp8 = storage[0] == "8"
+                copies = max(2, min(64, int(700e6 / (N * K * (1 if fp8 else 2))) + 1))
+                layers = [nfp.decompose(workloads.weight_device(N, K, 0.02, seed=i), check=False, packed=storage[-1] == "p")
+                          for i in range(copies)]
+                for M in tokens:
+                    X = workloads.act_device(M, K, seed=2)
+                    Xq, sc = nfp.quantize_act(X)
+                    Y = torch.empty((M, N), dtype=torch.float16, device=dev)
+                    ws = nfp.new_workspace(8 * M * (N + 4) * 4 + M * K + 4 * M + (1 << 20), dev)
+
+                    def call(i):
+                        up, lo = layers[i % copies]
+                        if fp8:
+                            nfp.gemm_fp8_prequantized(Xq, sc, up, out=Y, workspace=ws)
+                        else:
+                            nfp.gemm(X, up, lo, nfp.MODE_FP16, out=Y, workspace=ws)
+
+                    def timed(launch):
+                        pins = {} if launch is None else dict(zip(("large_bm", "large_bn", "large_split", "large_deep", "large_rows"), launch))
+                        if not fp8:
+                            pins.pop("large_deep", None)
+                        for k, v in pins.items():
+                            nfp.tune(k, v)
+                        try:
+                            graph = graph_of(call, copies)
+                        finally:
+                            for k in pins:
+                                nfp.tune(k, -1)
+                        us = float(np.median([microseconds(graph, copies) for _ in range(5)]))
+                        out.write(json.dumps([N, K, M, storage, launch, round(us, 2)]) + "\n")
+
+                    timed(None)                                # the built-in choice
+                    for launch in tile_launches(N, K, M, storage):
+                        timed(launch)
                 del layers
                 torch.cuda.empty_cache()
             print("N=%d K=%d  %.0f s" % (N, K, time.time() - t0), flush=True)
@@ -234,22 +312,134 @@ def fit_lines(path):
               % (key + (a, unsplit, split, 100 * mean, 100 * most, 100 * np.log(t / best).mean(), 100 * np.log(s / best).mean())))
 
 
+# kShortCost: per tile shape microseconds per K-tile and per workgroup (tiles of 256 tokens: also at a height of 160), then the rest
+SHORT_PARAMS = ("pair128", "pair64", "base", "w_rate", "l2_rate", "cu_rate", "split", "split_rate")
+SHORT_START = {False: (0.725, 6.05, 0.556, 3.47, 0.421, 2.63, 0.314, 1.28, 0.5, 2.61, 0.2785, 0.83, 0.271, 0.51, 1.045, 1.045, 3.0, 15.2, 219, 167, 3.45, 5.28),
+               True: (0.6255, 3.16, 0.378, 3.16, 0.319, 2.41, 0.319, 2.41, 0.334, 2.71, 0.2136, 1.73, 0.183, 1.54, 1.0, 1.10, 2.0, 10.4, 1e9, 144, 3.28, 4.68)}
+
+
+def price_short(p, f, fp8):
+    """What choose_short() prices a launch at; rates in 1e6 (cu_rate: 1e3) bytes per microsecond."""
+    pair128, pair64, base, w, l2, cu, split, split_rate = p[14:]
+    at = (f["height"] - 160) / 96
+    shape = [f["shape"] == i for i in range(5)]
+    tk = np.select(shape, [p[2] + at * (p[0] - p[2]), p[6] + at * (p[4] - p[6]), p[8], p[10], p[12]])
+    tfix = np.select(shape, [p[3] + at * (p[1] - p[3]), p[7] + at * (p[5] - p[7]), p[9], p[11], p[13]])
+    rounds = np.ceil(f["wgs"] / 256)
+    t = rounds * (tfix + f["per"] * tk)
+    t = t / np.where(rounds > 1, np.select([shape[3], shape[4]], [pair128, pair64], 1.0), 1.0)
+    t = t + base + f["N"] * f["K"] * f["bytes"] / (w * 1e6) + f["wgs"] * f["per"] * (f["height"] + f["tn"]) * 128 / (l2 * 1e6)
+    t = t + rounds * f["per"] * (np.minimum(f["height"], f["M"]) + f["tn"]) * 128 / (cu * 1e3)
+    t = t + np.where(f["slices"] > 1, split + 8 * f["M"] * f["N"] * f["slices"] / (split_rate * 1e6), 0.0)
+    tail = (f["shape"] == 4) & (f["M"] > 128) & (np.ceil(f["N"] / 128) % 8 != 0) & (f["N"] * f["K"] >= 24 << 20)
+    return t * np.where(tail & fp8, 1.1, 1.0)
+
+
+def fit_tiles(path):
+    from scipy.optimize import minimize
+
+    from . import binding
+
+    through = binding.lib()._ZN3nfp16rows_through_ldsEiillli                      # nfp::rows_through_lds
+    through.restype, through.argtypes = ctypes.c_bool, [ctypes.c_int] * 2 + [ctypes.c_int64] * 3 + [ctypes.c_int]
+    problems = {}
+    for line in open(path):
+        N, K, M, storage, launch, us = json.loads(line)
+        problems.setdefault((N, K, M, storage), {})[None if launch is None else tuple(launch)] = us
+
+    def behind(v):
+        v = np.array(v)
+        return "%.1f %% behind on average, 95th percentile %.0f %%, at most %.0f %%" % (
+            100 * (np.exp(np.log(v).mean()) - 1), 100 * (np.percentile(v, 95) - 1), 100 * (v.max() - 1))
+
+    for storage in STORAGES[:4]:
+        v = [d[None] / min(us for launch, us in d.items() if launch) for key, d in problems.items() if key[3] == storage]
+        if v:
+            print("// %s: built-in choice against the fastest of its %d launches on %d problems: %s" % (
+                storage, sum(len(d) - 1 for key, d in problems.items() if key[3] == storage), len(v), behind(v)))
+    rule, regs = [], []
+    for (N, K, M, storage), d in problems.items():
+        for launch, us in d.items():
+            if storage == "16r" and launch and launch[4] == 1 and launch[:4] + (0,) in d:
+                both = (d[launch[:4] + (0,)], us)
+                rule.append(both[through(launch[0], launch[1], M, K, K, launch[2])] / min(both))
+                regs.append(both[0] / min(both))
+    if rule:
+        print("// row-major planes, %d launches both ways: the rule %s; all into registers %s" % (len(rule), behind(rule), behind(regs)))
+    for fp8 in (False, True):
+        geo, us, group, groups = [], [], [], {}
+        for (N, K, M, storage), d in problems.items():
+            if M > 256 or (storage[0] == "8") != fp8:
+                continue
+            kt = -(-K // (128 if fp8 else 64))
+            for launch, t in d.items():
+                if launch is None:
+                    continue
+                tm, tn, split, deep, way = launch
+                if fp8 and tm > 64 and tm * tn < 256 * 256 and not deep:
+                    continue                               # (the deeper pipeline where there is one)
+                if way >= 0 and way != through(tm, tn, M, K, K, split):
+                    continue
+                per = -(-kt // split)
+                slices = -(-kt // per)
+                height = max(160, -(-M // 32) * 32) if tm == 256 and (tn == 256 or not fp8) else tm
+                geo.append(dict(N=N, K=K, M=M, shape=TILE_SHAPES.index((tm, tn)), tn=tn, height=height, per=per, slices=slices,
+                                wgs=-(-M // tm) * -(-N // tn) * slices, bytes=1 if fp8 else 2))
+                us.append(t)
+                group.append(groups.setdefault((N, K, M, storage), len(groups)))
+        if not geo:
+            continue
+        f = {k: np.array([g[k] for g in geo], float) for k in geo[0]}
+        us, group = np.array(us), np.array(group)
+        best = np.full(len(groups), 1e30)
+        np.minimum.at(best, group, us)
+        lost = np.log(us / best[group])
+        weight = np.exp(-4 * lost)
+        weight /= weight.sum()
+
+        def objective(logp):
+            lp = np.log(price_short(np.exp(logp), f, fp8))
+            low = np.full(len(groups), 1e30)
+            np.minimum.at(low, group, lp)
+            e = np.exp(-(lp - low[group]) / 0.02)
+            soft = np.bincount(group, e * (lost + 3 * np.maximum(lost - 0.04, 0))) / np.bincount(group, e)
+            return soft.mean() + 0.3 * np.sqrt((weight * (lp - np.log(us)) ** 2).sum())
+
+        def regret(p):
+            order = np.lexsort((price_short(p, f, fp8), group))
+            first = order[np.unique(group[order], return_index=True)[1]]
+            return behind(us[first] / best[group[first]])
+
+        start = np.array(SHORT_START[fp8])
+        p = np.exp(minimize(objective, np.log(start), method="L-BFGS-B", options=dict(maxiter=150)).x)
+        print("// %s: %d timings; constants as they are: %s; fitted: %s" % ("E4M3" if fp8 else "FP16", len(us), regret(start), regret(p)))
+        print("tiles {%s}, %s" % (", ".join("%.3g" % v for v in p[:14]), ", ".join("%s %.4g" % v for v in zip(SHORT_PARAMS, p[14:]))))
+
+
 def main():
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
-    ap.add_argument("do", choices=("time", "fit"))
-    ap.add_argument("candidates")
-    ap.add_argument("routes")
+    ap.add_argument("do", choices=("time", "fit", "time-tiles", "fit-tiles"))
+    ap.add_argument("files", nargs="+", help="candidates.jsonl routes.jsonl, or tiles.jsonl")
     ap.add_argument("--shapes", nargs="*", default=None, help="N,K pairs instead of the built-in layer shapes")
+    ap.add_argument("--tokens", nargs="*", type=int, default=TILE_TOKENS, help="batch sizes of time-tiles")
     args = ap.parse_args()
+    shapes = [tuple(int(v) for v in s.split(",")) for s in args.shapes] if args.shapes else \
+        sorted({s for v in MODEL_SHAPES.values() for s in v} | set(OTHER_SHAPES))
+    if len(args.files) != (1 if "tiles" in args.do else 2):
+        ap.error("%s takes %s" % (args.do, "one file" if "tiles" in args.do else "two files"))
     if args.do == "time":
-        shapes = [tuple(int(v) for v in s.split(",")) for s in args.shapes] if args.shapes else \
-            sorted({s for v in MODEL_SHAPES.values() for s in v} | set(OTHER_SHAPES))
-        time_all(args.candidates, args.routes, shapes)
+        time_all(args.files[0], args.files[1], shapes)
+        return
+    if args.do == "time-tiles":
+        time_tiles(args.files[0], shapes, args.tokens)
+        return
+    if args.do == "fit-tiles":
+        fit_tiles(args.files[0])
         return
     print("// kSmallCost: " + ", ".join(PARAMS))
     for storages in (("16p", "16r", "pr"), ("8p", "8r")):
-        fit_small(args.candidates, storages)
-    fit_lines(args.routes)
+        fit_small(args.files[0], storages)
+    fit_lines(args.files[1])
 
 
 if __name__ == "__main__":
