@@ -737,16 +737,16 @@ static void launch_small_k(const SmallParams &p, const SmallConfig &c, dim3 grid
     if constexpr (KIND == kPlainF16 || KIND == kNestedF16Row) {
         if (c.mt == 1 && c.spw == 8) { launch_small_t<KIND, 1, 8>(p, c, grid, stream);  return; }
     }
-    if constexpr (kind_quantizes(KIND)) {
+    if constexpr (kind_quantizes(KIND)) {                        // (one token tile)
         if (c.spw == 4) launch_small_t<KIND, 1, 4>(p, c, grid, stream);
         else launch_small_t<KIND, 1, 2>(p, c, grid, stream);
-        return;
-    }
-    switch (c.mt * 10 + c.spw) {
-        case 14: launch_small_t<KIND, 1, 4>(p, c, grid, stream); break;
-        case 12: launch_small_t<KIND, 1, 2>(p, c, grid, stream); break;
-        case 22: launch_small_t<KIND, 2, 2>(p, c, grid, stream); break;
-        default: launch_small_t<KIND, 4, 2>(p, c, grid, stream); break;
+    } else {
+        switch (c.mt * 10 + c.spw) {
+            case 14: launch_small_t<KIND, 1, 4>(p, c, grid, stream); break;
+            case 12: launch_small_t<KIND, 1, 2>(p, c, grid, stream); break;
+            case 22: launch_small_t<KIND, 2, 2>(p, c, grid, stream); break;
+            default: launch_small_t<KIND, 4, 2>(p, c, grid, stream); break;
+        }
     }
 }
 
