@@ -1817,11 +1817,10 @@ static void launch_large_k(const LargeParams &p, const LargeConfig &c, int heigh
     }
 }
 
-// Row-major planes on the 64-token tiles and in the deeper pipeline, 128 weight rows per tile: by pairs of K-tiles (see
-// BypassKernel::PAIR; up to 45 % faster) where the longer look-ahead pays.  Timed both ways on 2760 launches, tiles of
-// 128 and 256 tokens among them, which by now have a kernel of their own (26 values of K from 512 to 17344, four N,
-// twelve batch sizes, every split): the rule is 0.4 % behind the faster way on average and at most 8 % behind
-// unpaired loads (the rule "12 K-tiles per slice" was 1.3 % and 23 %).
+// Row-major planes on the 64-token tiles and in the deeper pipeline of 128 tokens, 128 weight rows per tile: by pairs of K-tiles
+// (see BypassKernel::PAIR; up to 45 % faster) where the longer look-ahead pays.  Timed both ways on 2760 launches (26 values
+// of K from 512 to 17344, four N, twelve batch sizes, every split; tiles of 256 tokens among them): the rule was 0.4 % behind
+// the faster way on average and at most 8 % behind unpaired loads (the rule "12 K-tiles per slice" 1.3 % and 23 %).
 //  - Rows that start on lines: a dozen K-tiles per slice (64 tokens per tile 1.07-1.12 x at 12 K-tiles and 1.2 x at
 //    24, 128 tokens 1.01 and 1.07); but not where the slices of a split have an odd number of K-tiles: every
 //    second slice then starts in the middle of a line, its pieces take two lines each, and K-tile by K-tile
@@ -1829,17 +1828,11 @@ static void launch_large_k(const LargeParams &p, const LargeConfig &c, int heigh
 //  - Rows that start inside lines: 14 K-tiles per slice, 6 Mi weights (smaller planes stay in the caches: K = 2064
 //    at 100 tokens 0.97 x with N = 2048, 1.20 x with N = 5632), and longer rows the more token tiles read them
 //    ((12288, 1600) at 128 tokens per tile: 1.11 x with one, 0.90 x with three).
-//  - 256 tokens per tile gain little (1.0-1.1 x), lose up to 16 % where the last of several tiles is mostly empty
-//    ((5632, 6432) at 777 tokens 0.87 x), and have nothing to gain from rows that start in the middle of
-//    lines, of which unpaired loads take halves.
 bool rows_by_pairs(int tm, int64_t M, int64_t N, int64_t K, int64_t row_bytes, int split) {
-    const bool on_lines = (row_bytes & 127) == 0;
     const int64_t kt = (K + 63) / 64, per = (kt + split - 1) / split, tiles_m = (M + tm - 1) / tm;
     const int64_t weights = N * K, mi = (int64_t)1 << 20;
-    if (tm == 256 && tiles_m > 1 && 10 * M < 9 * 256 * tiles_m) return false;
-    if (on_lines) return per >= (tm == 256 ? 20 : 12) && (per >= kt || (per & 1) == 0);
+    if ((row_bytes & 127) == 0) return per >= 12 && (per >= kt || (per & 1) == 0);
     if (per < 14) return false;
-    if (tm == 256) return kt >= 48 && (row_bytes & 63) != 0;
     if (tiles_m == 1) return weights >= (kt >= 24 ? 6 : 10) * mi;
     return weights >= 6 * mi && kt >= (tiles_m <= 4 ? 32 : 48);
 }
@@ -1912,32 +1905,24 @@ static void launch_nested(const LargeParams &p, const LargeConfig &c, int height
         else if (c.deep && c.tn == 128) launch_rows_by_pairs<128, true>(p, grid, stream);
         else if (c.deep) launch_bypass<128, 256, WK, true>(p, grid, stream);
         else launch_nested_tm<WK, 128>(p, c, grid, stream);
-        return;
-    }
-    if (c.tm == 64) {
+    } else if (c.tm == 64) {
         if (streams_tiles64(p, false)) launch_bypass<64, 128, WK, false, true>(p, grid, stream);
         else launch_bypass<64, 128, WK>(p, grid, stream);
-    } else {
+    } else if (p.tiles_m == 1 && (int64_t)p.N * p.K >= ((int64_t)100 << 20)) {
         // one token tile over a large packed layer: weights marked non-temporal (see BypassKernel)
-        if constexpr (WK != kNestedF16Row) {
-            if (p.tiles_m == 1 && (int64_t)p.N * p.K >= ((int64_t)100 << 20)) {
-                if (c.tn == 256) {
-                    if (c.deep) launch_bypass<128, 256, WK, true, true>(p, grid, stream);
-                    else launch_bypass<128, 256, WK, false, true>(p, grid, stream);
-                } else {
-                    if (c.deep) launch_bypass<128, 128, WK, true, true>(p, grid, stream);
-                    else launch_bypass<128, 128, WK, false, true>(p, grid, stream);
-                }
-                return;
-            }
-        }
         if (c.tn == 256) {
-            if (c.deep) launch_bypass<128, 256, WK, true>(p, grid, stream);
-            else launch_bypass<128, 256, WK>(p, grid, stream);
+            if (c.deep) launch_bypass<128, 256, WK, true, true>(p, grid, stream);
+            else launch_bypass<128, 256, WK, false, true>(p, grid, stream);
         } else {
-            if (c.deep) launch_bypass<128, 128, WK, true>(p, grid, stream);
-            else launch_bypass<128, 128, WK>(p, grid, stream);
+            if (c.deep) launch_bypass<128, 128, WK, true, true>(p, grid, stream);
+            else launch_bypass<128, 128, WK, false, true>(p, grid, stream);
         }
+    } else if (c.tn == 256) {
+        if (c.deep) launch_bypass<128, 256, WK, true>(p, grid, stream);
+        else launch_bypass<128, 256, WK>(p, grid, stream);
+    } else {
+        if (c.deep) launch_bypass<128, 128, WK, true>(p, grid, stream);
+        else launch_bypass<128, 128, WK>(p, grid, stream);
     }
 }
 

@@ -146,7 +146,7 @@ Tile64Plan tile64_plan(int kind, int64_t M, int64_t N, int64_t K);     // the sa
 bool small_gemm_fuses_quant(int64_t M, int64_t N, int64_t K);
 size_t small_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K);
 int launch_small_gemm(int kind, const GemmArgs &a, hipStream_t stream);
-bool rows_by_pairs(int tm, int64_t M, int64_t N, int64_t K, int64_t row_bytes, int split);   // row-major planes, tiles of tm tokens x 128 rows
+bool rows_by_pairs(int tm, int64_t M, int64_t N, int64_t K, int64_t row_bytes, int split);   // row-major planes, 64-token tiles and the deeper pipeline
 bool rows_through_lds(int tm, int tn, int64_t M, int64_t K, int64_t row_bytes, int split);           // the other tiles
 size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K);
 size_t large_gemm_bounded_bytes(int kind, int64_t M, int64_t N, int64_t K);      // with GemmArgs::bounded

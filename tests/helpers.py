@@ -135,10 +135,15 @@ def streaming_kernel_takes(nfp, mode, M, N, K):
     return f(2 if mode == nfp.MODE_FP8 else 1, M, N, K, K)
 
 
-def fetched_by_pairs(nfp, tile_tokens, M, N, K, split):
-    """Whether tiles of that many tokens x 128 rows fetch row-major planes for two K-tiles at a time."""
+def fetched_by_pairs(nfp, bm, bn, M, N, K, split, deep):
+    """Whether a launch fetches row-major planes for two K-tiles at a time: into registers (64-token tiles, the deeper
+    pipeline on 128 weight rows) or through LDS (the other tiles)."""
     import ctypes
 
-    f = nfp.lib()._ZN3nfp13rows_by_pairsEilllli            # nfp::rows_by_pairs
-    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] + 4 * [ctypes.c_int64] + [ctypes.c_int]
-    return f(tile_tokens, M, N, K, K, split)
+    if bm == 64 or deep > 0:
+        f = nfp.lib()._ZN3nfp13rows_by_pairsEilllli        # nfp::rows_by_pairs
+        f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] + 4 * [ctypes.c_int64] + [ctypes.c_int]
+        return f(bm, M, N, K, K, split)
+    f = nfp.lib()._ZN3nfp16rows_through_ldsEiillli         # nfp::rows_through_lds
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] * 2 + [ctypes.c_int64] * 3 + [ctypes.c_int]
+    return f(bm, bn, M, K, K, split)

@@ -734,18 +734,21 @@ def test_streaming_kernel_on_row_pieces(nfp, M, N, K, knobs):
     (64, 250, 3 * 64 + 48, 64, 128, 1, -1, False), (60, 130, 9 * 64, 64, 128, 3, -1, False), (20, 264, 11 * 64 + 16, 64, 128, 2, -1, False),
     (100, 200, 5 * 64, 128, 128, 1, -1, False), (130, 264, 7 * 128 + 32, 128, 128, 3, -1, False), (70, 136, 13 * 64, 128, 128, 2, 1, False),
     (200, 140, 6 * 64 + 16, 256, 128, 1, -1, False), (257, 264, 11 * 64, 256, 128, 4, -1, False),
-    (130, 300, 7 * 128 + 32, 128, 256, 3, -1, None), (257, 264, 11 * 64, 256, 256, 2, -1, None),      # tiles of 256 rows have no pairs
+    (130, 300, 7 * 128 + 32, 128, 256, 3, -1, False), (257, 264, 11 * 64, 256, 256, 2, -1, False),
     # rows on lines (an even count of K-tiles): 12 unsplit, slices of 12 and of 14, 14, 12; odd slices: no pairs
     (33, 136, 12 * 64, 64, 128, 1, -1, True), (64, 250, 24 * 64, 64, 128, 2, -1, True), (7, 130, 40 * 64, 64, 128, 3, -1, True),
     (20, 130, 26 * 64, 64, 128, 2, -1, False), (100, 200, 12 * 64, 128, 128, 1, -1, True), (130, 264, 40 * 64, 128, 128, 3, -1, True),
-    (200, 264, 20 * 64, 256, 128, 1, -1, True), (500, 136, 42 * 64, 256, 128, 2, -1, False), (490, 136, 40 * 64, 256, 128, 2, -1, True),
-    (300, 136, 40 * 64, 256, 128, 1, -1, False),                  # the last of several tiles of 256 tokens is mostly empty
+    (200, 264, 20 * 64, 256, 128, 1, -1, True), (490, 136, 40 * 64, 256, 128, 2, -1, True), (300, 136, 40 * 64, 256, 128, 1, -1, True),
+    # odd slices through LDS: from a dozen K-tiles on, never on tiles of 256 x 256
+    (500, 136, 42 * 64, 256, 128, 2, -1, True), (150, 264, 22 * 64, 128, 256, 2, -1, False), (300, 264, 102 * 64, 256, 256, 2, -1, False),
     # rows that start inside lines: odd counts of K-tiles, a last piece that K ends in, slices that start
     # and end inside a pair and inside a line
     (20, 10264, 16 * 64 + 16, 64, 128, 1, -1, True), (60, 3944, 25 * 64, 64, 128, 1, -1, True), (64, 3496, 28 * 64 + 16, 64, 128, 2, -1, True),
     (33, 3496, 44 * 64 + 48, 64, 128, 3, -1, True), (70, 3056, 32 * 64 + 16, 64, 128, 2, -1, True), (64, 2000, 28 * 64 + 16, 64, 128, 2, -1, False),
-    (100, 3496, 28 * 64 + 16, 128, 128, 1, -1, True), (128, 3496, 28 * 64 + 16, 128, 128, 2, -1, True), (130, 3056, 32 * 64 + 16, 128, 128, 2, -1, True),
-    (250, 140, 48 * 64 + 16, 256, 128, 1, -1, True), (200, 264, 48 * 64 + 16, 256, 128, 3, -1, True), (200, 264, 49 * 64, 256, 128, 1, -1, False),
+    (100, 3496, 28 * 64 + 16, 128, 128, 1, -1, True), (128, 3496, 28 * 64 + 16, 128, 128, 2, -1, True), (130, 3056, 32 * 64 + 16, 128, 128, 2, -1, False),
+    (130, 3056, 40 * 64 + 16, 128, 128, 2, -1, True), (129, 264, 40 * 64 + 16, 128, 256, 4, -1, False), (257, 264, 34 * 64 + 16, 256, 256, 2, -1, False),
+    (250, 140, 48 * 64 + 16, 256, 128, 1, -1, True), (200, 264, 48 * 64 + 16, 256, 128, 3, -1, True), (200, 264, 49 * 64, 256, 128, 1, -1, True),
+    (200, 264, 49 * 64, 256, 256, 3, -1, False),
     # the deeper pipeline by pairs: unsplit, even slices on lines, odd and even slices off them
     (100, 200, 24 * 64, 128, 128, 1, 1, True), (130, 264, 28 * 64, 128, 128, 2, 1, True), (77, 136, 40 * 64, 128, 128, 3, 1, True),
     (100, 3496, 28 * 64 + 16, 128, 128, 1, 1, True), (128, 3496, 28 * 64 + 16, 128, 128, 2, 1, True), (130, 3056, 44 * 64 + 16, 128, 128, 3, 1, True),
@@ -755,8 +758,7 @@ def test_tiled_kernels_on_row_pieces_and_slice_ends(nfp, M, N, K, bm, bn, split,
     # mode: one of 128 columns): odd counts of K-tiles, slices of a split that start and end inside a pair,
     # K inside a piece; and no kernel's look-ahead takes anything from the next slice (both plane
     # layouts, LDS kernels included)
-    if pairs is not None:
-        assert fetched_by_pairs(nfp, bm, M, N, K, split) == pairs
+    assert fetched_by_pairs(nfp, bm, bn, M, N, K, split, deep) == pairs
     knobs = {"small_max_m": 0, "large_bm": bm, "large_bn": bn, "large_split": split, "large_deep": deep}
     try:
         for k, v in knobs.items():
@@ -774,7 +776,7 @@ def test_deeper_pipeline_by_pairs_on_a_layer_read_once(nfp):
     # the table of timed launch shapes gives this layer the deeper pipeline in six slices at 97 to 128 tokens; its
     # row-major planes are then read by pairs of K-tiles and marked non-temporal
     N, K, M = 5120, 32768, 100
-    assert fetched_by_pairs(nfp, 128, M, N, K, 6)
+    assert fetched_by_pairs(nfp, 128, 128, M, N, K, 6, 1)
     _full_size_check(nfp, N, K, [M], workloads.SIGMA_W_8B, "N=%d K=%d" % (N, K), seed=77, pin_sets=_default_pins)
 
 
