@@ -773,11 +773,17 @@ def test_tiled_kernels_on_row_pieces_and_slice_ends(nfp, M, N, K, bm, bn, split,
 
 
 def test_deeper_pipeline_by_pairs_on_a_layer_read_once(nfp):
-    # the table of timed launch shapes gives this layer the deeper pipeline in six slices at 97 to 128 tokens; its
-    # row-major planes are then read by pairs of K-tiles and marked non-temporal
+    # the deeper pipeline in six slices: row-major planes read by pairs of K-tiles and marked non-temporal
     N, K, M = 5120, 32768, 100
+    knobs = {"large_bm": 128, "large_bn": 128, "large_split": 6, "large_deep": 1}
     assert fetched_by_pairs(nfp, 128, 128, M, N, K, 6, 1)
-    _full_size_check(nfp, N, K, [M], workloads.SIGMA_W_8B, "N=%d K=%d" % (N, K), seed=77, pin_sets=_default_pins)
+    try:
+        for k, v in knobs.items():
+            nfp.tune(k, v)
+        _full_size_check(nfp, N, K, [M], workloads.SIGMA_W_8B, "N=%d K=%d" % (N, K), seed=77, pin_sets=lambda M: [{}])
+    finally:
+        for k in knobs:
+            nfp.tune(k, -1)
 
 
 @pytest.mark.parametrize("M,N,K,knobs", [(16, 4096 + 8, 14336, {}), (4, 300, 28672, {}),
