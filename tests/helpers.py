@@ -147,3 +147,12 @@ def fetched_by_pairs(nfp, bm, bn, M, N, K, split, deep):
     f = nfp.lib()._ZN3nfp16rows_through_ldsEiillli         # nfp::rows_through_lds
     f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] * 2 + [ctypes.c_int64] * 3 + [ctypes.c_int]
     return f(bm, bn, M, K, K, split)
+
+
+def quantises_itself(nfp, M, N, K):
+    """Whether the streaming kernel quantises the activations of the problem itself, under the knobs as they are."""
+    import ctypes
+
+    f = nfp.lib()._ZN3nfp22small_gemm_fuses_quantElll      # nfp::small_gemm_fuses_quant
+    f.restype, f.argtypes = ctypes.c_bool, 3 * [ctypes.c_int64]
+    return f(M, N, K)

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 from paper_2506_02024_amd import workloads
-from helpers import bits, to_dev
+from helpers import bits, quantises_itself, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -43,6 +43,7 @@ def test_fused_quantisation_gives_the_same_bits(M, N, K, packed):
             for knob in (0, 1, -1):
                 nfp.tune("small_fuse_quant", knob)
                 try:
+                    assert quantises_itself(nfp, M, N, K) == (knob != 0)          # (by default too at these sizes)
                     got[knob] = bits(nfp.gemm(xd, up, None, nfp.MODE_FP8, act_scale=scale))
                 finally:
                     nfp.tune("small_fuse_quant", -1)

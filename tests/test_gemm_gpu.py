@@ -5,7 +5,7 @@ import torch
 
 import oracle
 from paper_2506_02024_amd import workloads
-from helpers import (assert_gemm_close, assert_plane_equal, bits, decompose_ref, fetched_by_pairs, streaming_kernel_takes,
+from helpers import (assert_gemm_close, assert_plane_equal, bits, decompose_ref, fetched_by_pairs, quantises_itself, streaming_kernel_takes,
                      structured_sample, to_dev)
 
 pytestmark = pytest.mark.gpu
@@ -629,22 +629,25 @@ def test_paper_kernel_benchmark_shapes_sampled(nfp, N, K, Ms):
 
 
 @pytest.mark.parametrize("M,N,K,split", [(16, 4096, 4096, -1), (1, 6144, 4096, -1), (5, 304, 2048 + 64, 1),
-                                         (16, 520, 528, 1), (13, 272, 4096 + 16, 1)])
+                                         (16, 520, 528, 1), (7, 272, 4096 + 16, 1), (13, 272, 2048 + 16, 1)])
 def test_fused_activation_quantisation_equals_the_two_kernel_path(nfp, M, N, K, split):
-    # decode batches whose K fits one workgroup pass can quantise the activations inside the GEMM
-    # kernel (knob small_fuse_quant); the result must be bit-identical to quantise-then-multiply and match the oracle
+    # decode batches whose K fits one workgroup pass can quantise the activations inside the GEMM kernel (knob
+    # small_fuse_quant); the result must be bit-identical to quantise-then-multiply and match the oracle (packed planes;
+    # row-major ones in test_fused_quant_gpu.py)
     W = workloads.weight_host(N, K, seed=N + K)
     X = workloads.act_host(M, K, seed=M + K)
     X[0, :] = 0                                        # an all-zero token: scale 1
     Xd = to_dev(X)
-    up, _ = nfp.decompose(to_dev(W), packed=True)      # the fused kind exists for packed planes
+    up, _ = nfp.decompose(to_dev(W), packed=True)
     sc = torch.tensor([0.0123], dtype=torch.float32, device="cuda:0")
     nfp.tune("small_split", split)
     nfp.tune("small_fuse_quant", 1)
     try:
+        assert quantises_itself(nfp, M, N, K)
         fused = bits(nfp.gemm(Xd, up, None, nfp.MODE_FP8))
         fused_static = bits(nfp.gemm(Xd, up, None, nfp.MODE_FP8, act_scale=sc))
         nfp.tune("small_fuse_quant", 0)
+        assert not quantises_itself(nfp, M, N, K)
         plain = bits(nfp.gemm(Xd, up, None, nfp.MODE_FP8))
         plain_static = bits(nfp.gemm(Xd, up, None, nfp.MODE_FP8, act_scale=sc))
         Xq_d, s_d = nfp.quantize_act(Xd)

@@ -66,3 +66,17 @@ def test_fp16_splits_beyond_the_fixed_scratch_are_never_chosen_without_a_workspa
         for kind in (1, 4):
             free, bounded = (partial_bytes(L, kind, M, N, K, w) for w in ("24large_gemm_partial_bytes", "24large_gemm_bounded_bytes"))
             assert bounded <= free and (bounded == free or free > (32 << 20) - 16384)
+
+
+@pytest.mark.parametrize("M,N,K,fused", [
+    # up to 8 tokens: several weight tiles per workgroup, or rows of up to 3072 columns (microseconds fused / not: 10.0 / 10.9,
+    # 11.1 / 11.9, 18.6 / 19.5, 4.1 / 5.5; 8.9 / 8.6, 11.3 / 10.8)
+    (8, 11008, 3072, True), (8, 7680, 5120, True), (8, 10240, 8192, True), (8, 1024, 1024, True), (8, 1024, 3072, True),
+    (8, 4096, 4096, False), (8, 3072, 7168, False), (8, 1024, 3088, False),
+    # 9 to 16 tokens: up to 1280 columns (5.2 / 5.8; 7.3 / 6.8, 11.5 / 9.2)
+    (16, 1024, 1024, True), (9, 1024, 1280, True), (9, 1024, 1296, False), (16, 2048, 2048, False), (16, 4096, 4096, False),
+])
+def test_which_batches_are_quantised_in_the_streaming_kernel(L, M, N, K, fused):
+    f = L._ZN3nfp22small_gemm_fuses_quantElll                 # nfp::small_gemm_fuses_quant
+    f.restype, f.argtypes = ctypes.c_bool, 3 * [ctypes.c_int64]
+    assert f(M, N, K) == fused
