@@ -1450,7 +1450,10 @@ struct LargeConfig { int tm, tn, split, deep; double cost; };
 // one after the other; a layer cannot finish before its weights have crossed the memory bus
 // once; a split adds a reduction launch plus the traffic of the fp32 partials.  The constants
 // are a least-squares fit (microseconds) to sweeps of every shape and split over M = 128 ...
-// 4096 on the four Llama-3-8B layer shapes and a square 8192 layer.
+// 4096 on the four Llama-3-8B layer shapes and a square 8192 layer.  They are older than the third weight stage of the
+// 256x256 tiles of plain FP16 and E4M3, and know tiles cut to the batch (token_tile) on the register path only: above 256 tokens,
+// where they decide, constants fitted to the present kernels were 1-2 % better on average, but kept within the fixed scratch
+// some launches lost 30 %.
 struct TileCost { double tk, tfix; };                  // per K-tile, per workgroup
 static const int kTileShapes[4][2] = {{256, 256}, {256, 128}, {128, 256}, {128, 128}};   // tokens x weight rows
 static const TileCost kTileCost[3][4] = {
