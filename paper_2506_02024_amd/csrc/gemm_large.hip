@@ -43,7 +43,7 @@ struct LargeParams {
     int tiles_m, tiles_n;
     int ktiles_total, ktiles_per_split;
     int vec_store;
-    int row_store;          // Y rows can be written 16 bytes per lane (N, ldy multiples of 8, Y 16-byte aligned)
+    int row_store;          // tiles leave through LDS by rows: 1 rows start on 16 bytes (N, ldy multiples of 8, Y 16-byte aligned), 2 anywhere; 0 straight from the MFMA layout
     int xcd_map;            // group the token tiles of a weight tile on one XCD (see tile_of_block)
 };
 
@@ -168,6 +168,10 @@ struct TileStore {
         constexpr int RPI = 64 / OCH;                  // rows per store instruction
         constexpr int ROWS = TM / WAVES;               // rows per wave
         const int chunk = lane % OCH;
+        if (p.row_store == 2) {
+            store_rows_shifted(p, m0, n0, lane, wave, lds);
+            return;
+        }
         const int n = n0 + chunk * 8;
 #pragma unroll
         for (int it = 0; it < ROWS / RPI; ++it) {
@@ -176,6 +180,57 @@ struct TileStore {
             const int m = m0 + row;
             if (m < p.M && n < p.N) *reinterpret_cast<u32x4 *>(p.Y + (int64_t)m * p.ldy + n) = v;
         }
+    }
+
+    // Output rows that start anywhere (N or ldy no multiple of 8): a row's first 16-byte boundary lies `skip` columns
+    // into the tile, and the 16 bytes that a lane stores are put together from two chunks of the LDS.  The columns
+    // before the first boundary and behind the last go out two bytes at a time, those of 8 rows per instruction.
+    // Straight from the MFMA layout, in two-byte pieces, a lane needs four stores for what is one here: FP8 mode
+    // (7955, 1280) at 1768 tokens 62.7 us so, 32.0 through LDS; (28689, 4096) at 777 tokens 154 and 101, at 200 tokens 51.7 and
+    // 42.2; FP16 mode (12479, 2304) at 2048 tokens 155 and 125, at 100 tokens 24.7 and 23.1.  N = 28676, whose rows took
+    // 8-byte pieces: level at 2048 tokens (432 us packed).
+    static __device__ __forceinline__ void store_rows_shifted(const LargeParams &p, int m0, int n0, int lane, int wave, const uint8_t *lds) {
+        constexpr int RPI = 64 / OCH, ROWS = TM / WAVES;
+        const int chunk = lane % OCH;
+        const int n_end = min(p.N, n0 + TN);
+#pragma unroll
+        for (int it = 0; it < ROWS / RPI; ++it) {
+            const int row = wave * ROWS + it * RPI + lane / OCH, m = m0 + row;
+            uint16_t *const dst = p.Y + (int64_t)m * p.ldy + n0;
+            const int skip = (int)(0u - (uint32_t)(reinterpret_cast<uintptr_t>(dst) >> 1)) & 7;
+            const uint8_t *const src = lds + row * (TN * 2);
+            const u32x4 a = *reinterpret_cast<const u32x4 *>(src + ((chunk ^ (row & (OCH - 1))) << 4));
+            const u32x4 b = *reinterpret_cast<const u32x4 *>(src + (((chunk + 1) & (OCH - 1)) ^ (row & (OCH - 1))) * 16);
+            // eight dwords, moved down by four bytes times skip / 2, then by two more if skip is odd
+            const bool four = (skip & 4) != 0, two = (skip & 2) != 0;
+            const uint32_t t0 = four ? a.z : a.x, t1 = four ? a.w : a.y, t2 = four ? b.x : a.z, t3 = four ? b.y : a.w,
+                           t4 = four ? b.z : b.x, t5 = four ? b.w : b.y;
+            const uint32_t u0 = two ? t1 : t0, u1 = two ? t2 : t1, u2 = two ? t3 : t2, u3 = two ? t4 : t3, u4 = two ? t5 : t4;
+            const uint32_t half = (uint32_t)(skip & 1) * 16u;
+            const u32x4 v = {__builtin_amdgcn_alignbit(u1, u0, half), __builtin_amdgcn_alignbit(u2, u1, half),
+                             __builtin_amdgcn_alignbit(u3, u2, half), __builtin_amdgcn_alignbit(u4, u3, half)};
+            const int c = skip + 8 * chunk, n = n0 + c;
+            if (m < p.M && c + 8 <= TN) {
+                if (n + 8 <= n_end) *reinterpret_cast<u32x4 *>(dst + c) = v;
+                else if (n < n_end) store_some(dst + c, v, n_end - n);
+            }
+        }
+        // (skip = 0: the row is whole 16-byte pieces)
+#pragma unroll
+        for (int it = 0; it < (ROWS + 7) / 8; ++it) {
+            const int r = it * 8 + (lane >> 3), row = wave * ROWS + r, m = m0 + row;
+            uint16_t *const dst = p.Y + (int64_t)m * p.ldy + n0;
+            const int skip = (int)(0u - (uint32_t)(reinterpret_cast<uintptr_t>(dst) >> 1)) & 7;
+            const int c = (lane & 7) < skip ? lane & 7 : TN - 8 + (lane & 7);
+            if (r < ROWS && m < p.M && skip != 0 && n0 + c < n_end)
+                dst[c] = *reinterpret_cast<const uint16_t *>(lds + row * (TN * 2) + (((c >> 3) ^ (row & (OCH - 1))) << 4) + 2 * (c & 7));
+        }
+    }
+    // the first `count` < 8 of eight halves
+    static __device__ __forceinline__ void store_some(uint16_t *dst, const u32x4 &v, int count) {
+#pragma unroll
+        for (int q = 0; q < 7; ++q)
+            if (q < count) dst[q] = (uint16_t)(v[q >> 1] >> (16 * (q & 1)));
     }
 
     template <int F = FMB>
@@ -1971,7 +2026,7 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     c.split = (p.ktiles_total + p.ktiles_per_split - 1) / p.ktiles_per_split;   // no empty slices
     p.xcd_map = (tuning().large_xcd_map != 0 && p.tiles_m >= 2 && p.tiles_m <= 8) ? 1 : 0;
     p.vec_store = ((a.N & 3) == 0 && (a.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 7) == 0) ? 1 : 0;
-    p.row_store = ((a.N & 7) == 0 && (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) ? 1 : 0;
+    p.row_store = ((a.N & 7) == 0 && (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) ? 1 : 2;
     if (tuning().large_epilogue == 0) p.row_store = 0;
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)c.split);
     switch (kind) {
