@@ -45,17 +45,33 @@ struct LargeParams {
     int vec_store;
     int row_store;          // tiles leave through LDS by rows: 1 rows start on 16 bytes (N, ldy multiples of 8, Y 16-byte aligned), 2 anywhere; 0 straight from the MFMA layout
     int xcd_map;            // group the token tiles of a weight tile on one XCD (see tile_of_block)
+    int xcd_group;          // token tiles per group of an XCD's part; 0: another order
 };
 
 // Which tile a workgroup takes.  The hardware deals consecutive workgroups to the 8 XCDs in turn,
-// and every XCD has an L2 of its own.  With few token tiles per weight tile (batches of up to about
-// 1000 tokens) the launch order "token tile fastest" puts the token tiles of one weight tile on
-// different XCDs, so each of them fetches those weights from memory again; instead, workgroup
-// b of XCD b % 8 takes token tile (b / 8) % tiles_m of weight tile 8 * ((b / 8) / tiles_m) + b % 8:
-// all token tiles of a weight tile follow each other on one XCD.  The last tiles_n % 8 weight tiles
-// keep the launch order.  With many token tiles per weight tile the launch order already gives
-// every XCD a near-square block of tiles (tiles_m / 8 token tiles x 8 weight tiles at a time).
+// and every XCD has an L2 of its own.  In launch order "token tile fastest" the token tiles of one weight tile land on
+// different XCDs, and each of those fetches the weights from memory again.
+// Up to seven token tiles: workgroup b of XCD b % 8 takes token tile (b / 8) % tiles_m of weight tile
+// 8 * ((b / 8) / tiles_m) + b % 8, so that all token tiles of a weight tile follow each other on one XCD.  The last
+// tiles_n % 8 weight tiles keep the launch order.
+// From eight on (p.xcd_group): every XCD takes an eighth of the tiles, in an order that runs through groups of up to
+// six token tiles, all weight tiles of a group before the next: the 32 tiles that an XCD has under way are about six by
+// six, 12 operand tiles to fetch.  In launch order they are that only where tiles_m is a multiple of 8; else every XCD
+// has all token tiles under way, and with 9 or more of them it fetches up to three times as much.  Timed in turn on 26 000 launches
+// (150 layers, 80 to 8192 tokens, weights cold), time against the launch order, FP16 mode and FP8 mode: 9 to 15 token
+// tiles 0.96 and 0.92, 16 0.98 and 0.96, 17 to 23 0.97 and 0.95, 24 1.0, 25 to 31 0.90 and 0.89, 32 0.99 and 0.96, 33 and
+// more 0.93 and 0.90; 8 against the order of fewer 0.99.  Groups of 8 or 16 are 1-4 % behind groups of 6; fewer than eight
+// token tiles as one group: level.
 __device__ __forceinline__ void tile_of_block(const LargeParams &p, int b, int &tm, int &tn) {
+    if (p.xcd_group) {
+        const int total = p.tiles_m * p.tiles_n, x = b & 7;
+        const int v = x * (total >> 3) + min(x, total & 7) + (b >> 3);       // the first total % 8 XCDs have one tile more
+        const int g = v / (p.xcd_group * p.tiles_n), u = v - g * (p.xcd_group * p.tiles_n);
+        const int rows = min(p.xcd_group, p.tiles_m - g * p.xcd_group);
+        tn = u / rows;
+        tm = g * p.xcd_group + u - tn * rows;
+        return;
+    }
     const int grouped = 8 * p.tiles_m * (p.tiles_n >> 3);
     if (p.xcd_map && b < grouped) {
         const int j = b >> 3;
@@ -2024,7 +2040,12 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     p.ktiles_total = (p.k_bytes + 127) / 128;
     p.ktiles_per_split = (p.ktiles_total + c.split - 1) / c.split;
     c.split = (p.ktiles_total + p.ktiles_per_split - 1) / p.ktiles_per_split;   // no empty slices
-    p.xcd_map = (tuning().large_xcd_map != 0 && p.tiles_m >= 2 && p.tiles_m <= 8) ? 1 : 0;
+    p.xcd_map = (tuning().large_xcd_map != 0 && p.tiles_m >= 2 && p.tiles_m < 8) ? 1 : 0;
+    p.xcd_group = 0;
+    if (tuning().large_xcd_map != 0 && p.tiles_m >= 8) {
+        const int groups = (p.tiles_m + 5) / 6;
+        p.xcd_group = (p.tiles_m + groups - 1) / groups;
+    }
     p.vec_store = ((a.N & 3) == 0 && (a.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 7) == 0) ? 1 : 0;
     p.row_store = ((a.N & 7) == 0 && (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) ? 1 : 2;
     if (tuning().large_epilogue == 0) p.row_store = 0;
