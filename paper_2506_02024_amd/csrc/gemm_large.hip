@@ -1513,36 +1513,8 @@ e4m3_bypass_kernel(LargeParams p) {
     Kern::run(p, lds_raw, (typename Kern::lds_byte *)lds_raw);
 }
 
-struct LargeConfig { int tm, tn, split, deep; double cost; };
+struct LargeConfig { int tm, tn, split, deep; double cost; int height; };     // height of the token tiles: tm or less (see cuts_tiles)
 
-// Tile shape and K split from a small cost model.  The workgroups are dealt round-robin to the
-// 256 CUs; a workgroup costs a fixed part plus a time per K-tile that depends on the tile shape
-// and the weight kind; two 128x128 workgroups share a CU and together run s2 times faster than
-// one after the other; a layer cannot finish before its weights have crossed the memory bus
-// once; a split adds a reduction launch plus the traffic of the fp32 partials.  The constants
-// are a least-squares fit (microseconds) to sweeps of every shape and split over M = 128 ...
-// 4096 on the four Llama-3-8B layer shapes and a square 8192 layer.  They are older than the third weight stage of the
-// 256x256 tiles of plain FP16 and E4M3, and know tiles cut to the batch (token_tile) on the register path only: above 256 tokens,
-// where they decide, constants fitted to the present kernels were 1-2 % better on average, but kept within the fixed scratch
-// some launches lost 30 %.
-struct TileCost { double tk, tfix; };                  // per K-tile, per workgroup
-static const int kTileShapes[4][2] = {{256, 256}, {256, 128}, {128, 256}, {128, 128}};   // tokens x weight rows
-static const TileCost kTileCost[3][4] = {
-    {{1.353, 0.0}, {1.053, 0.07}, {1.098, 0.0}, {0.848, 0.0}},      // plain FP16
-    {{1.242, 2.30}, {0.873, 0.75}, {0.887, 0.17}, {0.542, 0.0}},    // NestedFP16
-    {{1.317, 4.39}, {1.061, 2.10}, {1.089, 2.28}, {0.864, 1.01}},   // E4M3
-};
-static const double kPairSpeedup[3] = {1.58, 1.02, 1.51};
-// The same tile shapes with the deeper load pipeline (three or four LDS stages, one workgroup per
-// CU, no pair speed-up): per K-tile about a quarter cheaper for the kernels whose weights go through
-// LDS, at a higher fixed cost; nothing gained on the register path (NestedFP16), which does not use it.
-// Least-squares fit to a sweep of every shape, split and pipeline depth over M = 128 ... 2048 on six
-// Llama-3 8B / 70B layer shapes.
-static const TileCost kDeepTileCost[3][4] = {
-    {{0, 0}, {0.863, 1.56}, {0.900, 1.71}, {0.585, 2.50}},         // plain FP16
-    {{0, 0}, {0, 0}, {0, 0}, {0, 0}},                               // NestedFP16: not used
-    {{0, 0}, {0.978, 2.96}, {0.938, 2.77}, {0.606, 2.61}},         // E4M3
-};
 static const int kSplits[] = {1, 2, 3, 4, 6, 8};
 
 // split-K cost: the reduction kernel's launch plus its traffic
@@ -1572,7 +1544,7 @@ static LargeConfig choose_tile64(int cls, int64_t M, int64_t N, int64_t K, int m
     const Tuning &t = tuning();
     const Tile64Cost &tc = kTile64Cost[cls];
     LargeConfig c;
-    c.tm = 64;  c.tn = 128;  c.split = 1;  c.deep = 0;
+    c.tm = 64;  c.tn = 128;  c.split = 1;  c.deep = 0;  c.height = 64;
     const int64_t tiles = ((M + 63) / 64) * ((N + 127) / 128);
     double best = 1e30;
     // A split stays inside the scratch of the entry point without a workspace wherever the problem does: the
@@ -1614,6 +1586,24 @@ Tile64Plan tile64_plan(int kind, int64_t M, int64_t N, int64_t K) {
     });
 }
 
+// Token tiles of 256 exist cut down to 160, 192 and 224 tokens as well, all of a launch alike: register-path tiles and the
+// 256 x 256 tiles of plain FP16 and E4M3.  The sums are the same at every height.
+static bool cuts_tiles(int cls, int tn) { return cls == 1 || tn == 256; }
+// Up to 256 tokens, and for timed launch shapes: the height that the batch needs, as many tiles as of 256 without the
+// rows that only padding would fill.  777 tokens are four tiles of 224 instead of three of 256 and one of 9.  (28672, 4096),
+// FP16 mode: 150 tokens 83.6 -> 66.9 us (row-major planes), 300 tokens 120 -> 96 us; FP8 mode gains 1-8 %.
+static int token_tile(int cls, int tm, int tn, int64_t M) {
+    if (tm != 256 || !cuts_tiles(cls, tn)) return tm;
+    const int64_t tiles = (M + 255) / 256;
+    const int h = (int)(((M + tiles - 1) / tiles + 31) / 32 * 32);
+    return h < 160 ? 160 : h;
+}
+// the knob large_height instead, where there are such tiles
+static int knob_height(int cls, int tm, int tn) {
+    const int64_t want = tuning().large_height;
+    return tm == 256 && cuts_tiles(cls, tn) && want >= 160 && want <= 256 && want % 32 == 0 ? (int)want : 0;
+}
+
 // Launch shapes that were timed faster than the cost model's choice, for the layer shapes of the
 // models the paper evaluates (Sec. 5.1).  An entry tuned at M tokens serves the batches of more than
 // 3 M / 4 (M / 2 up to 64 tokens) and at most M tokens that give the same number of token tiles.
@@ -1630,24 +1620,11 @@ static bool tuned_large(int cls, int64_t M, int64_t N, int64_t K, LargeConfig &c
         // at M tokens is trusted down to three quarters of M)
         if (M > e.M || (e.M <= 64 ? 2 * M <= e.M : 4 * M <= 3 * e.M)) continue;
         if ((M + e.tm - 1) / e.tm != (e.M + e.tm - 1) / e.tm) continue;
-        c.tm = e.tm;  c.tn = e.tn;  c.split = e.split;  c.deep = e.deep;
+        c.tm = e.tm;  c.tn = e.tn;  c.split = e.split;  c.deep = e.deep;  c.height = token_tile(cls, e.tm, e.tn, M);
         return true;
     }
     return false;
 }
-
-// Token tiles of 256 are cut down to the height that the batch needs: as many tiles as before, all of them the same
-// multiple of 32 tokens high.  777 tokens are four tiles of 224 instead of three of 256 and one of 9; what is left out
-// are rows that only padding would fill, the sums are the same.  (28672, 4096), FP16 mode: 150 tokens
-// 83.6 -> 66.9 us (row-major planes), 300 tokens 120 -> 96 us; FP8 mode gains 1-8 %.
-static int token_tile(int tm, int64_t M) {
-    if (tm != 256) return tm;
-    const int64_t tiles = (M + 255) / 256;
-    const int h = (int)(((M + tiles - 1) / tiles + 31) / 32 * 32);
-    return h < 160 ? 160 : h;
-}
-// ... by the kernels that exist in these heights: register-path tiles, the 256 x 256 tile of E4M3
-static bool cuts_tiles(int cls, int tn) { return cls == 1 || (cls == 2 && tn == 256); }
 
 // 65 ... 256 tokens of the two classes whose tiles of 256 tokens are cut down: every tile shape, the 64-token tiles
 // included, priced by what was found to add up -- the rounds of workgroups, the weights, what all workgroups take in
@@ -1687,12 +1664,12 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K, bool b
     const int want_m = (t.large_bm == 128 || t.large_bm == 256) ? (int)t.large_bm : 0;
     const int want_n = (t.large_bn == 128 || t.large_bn == 256) ? (int)t.large_bn : want_m;
     LargeConfig c;
-    c.tm = 128;  c.tn = 128;  c.split = 1;  c.deep = 0;
+    c.tm = 128;  c.tn = 128;  c.split = 1;  c.deep = 0;  c.height = 128;
     double best = 1e30;
     for (const ShortShape &e : m.shape) {
         if (want_m && want_m != e.tm) continue;
         if (want_n && want_n != e.tn) continue;
-        const int height = cuts_tiles(cls, e.tn) ? token_tile(e.tm, M) : e.tm;
+        const int height = token_tile(cls, e.tm, e.tn, M);
         const int64_t tiles = ((M + e.tm - 1) / e.tm) * ((N + e.tn - 1) / e.tn);
         double tk = e.tk, tfix = e.tfix;
         if (e.tm == 256) {
@@ -1715,7 +1692,7 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K, bool b
             if (slices > 1) time += split_cost(M, N, slices, m.split, m.split_rate);
             if (!fits) time /= 0.96;
             if (fp8 && e.tm == 64 && M > 128 && (((N + 127) / 128) & 7) != 0 && N * K >= ((int64_t)24 << 20)) time *= 1.1;
-            if (time < best) { best = time;  c.tm = e.tm;  c.tn = e.tn;  c.split = split;  c.deep = e.deep; }
+            if (time < best) { best = time;  c.tm = e.tm;  c.tn = e.tn;  c.split = split;  c.deep = e.deep;  c.height = height; }
             if (t.large_split > 0) break;
         }
     }
@@ -1723,65 +1700,111 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K, bool b
     return c;
 }
 
-static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, bool bounded, int max_split = 8) {
-    LargeConfig c;
-    c.cost = 0.0;
+// More than 256 tokens: tile shape, height of the token tiles and K split by the rounds of
+// workgroups over 256 CUs, each a fixed time and a time per K-tile, the operands that all workgroups take in from L2,
+// and what a split costs.  What is won over tiles of 256 tokens is the last round: (5888, 5888) at 1645 tokens is 161 tiles of 256 or 253 of 160, (6144,
+// 4096) at 2048 tokens 192 or 240 of 224.  The constants were fitted, as those above,
+// to 112 000 timings of every shape, height and split worth one on 150 layers of 1 to 300 Mi weights at 272 to
+// 8192 tokens, both storage orders.  The choice is 0.5 % (FP16 mode), 0.6 % (E4M3) and
+// 0.7 % (plain FP16) behind the fastest launch on average, 3.6 to 4.2 % at the 95th percentile, and as
+// much on layers that were left out of the fit; the model before it, which knew no heights, 3.3, 4.1 and 4.3 %, 15 to 20 %.
+// That model still serves plain FP16 weights at 65 to 256 tokens, with the weights' one pass over the memory bus as a floor.
+struct TallShape { int tm, tn, deep; double tk, tfix, tk160, tfix160; };       // as ShortShape
+struct TallCost {
+    int shapes;
+    TallShape shape[7];
+    double pair;                        // 128 x 128 workgroups of a CU that run together, from the second round on
+    double l2_rate, split, split_rate;
+    double odd;                         // register path, rows on lines: slices of an odd number of K-tiles (see rows_through_lds)
+    double floor_rate;                  // of the memory bus, slower while the chip is not full
+};
+static const TallCost kTallCost[4] = {
+    // plain FP16 of up to 256 tokens
+    {7, {{256, 256, 0, 1.353, 0, 1.353, 0}, {256, 128, 0, 1.053, 0.07, 0, 0}, {256, 128, 1, 0.863, 1.56, 0, 0}, {128, 256, 0, 1.098, 0, 0, 0},
+         {128, 256, 1, 0.900, 1.71, 0, 0}, {128, 128, 0, 0.848, 0, 0, 0}, {128, 128, 1, 0.585, 2.50, 0, 0}}, 1.58, 1e15, 3.18, 4.44e6, 1.0, 4.57e6},
+    // FP16 operands through registers
+    {4, {{256, 256, 0, 1.09, 8.73, 0.755, 6.53}, {256, 128, 0, 0.595, 5.43, 0.380, 4.79}, {128, 256, 0, 0.631, 6.15, 0, 0},
+         {128, 128, 0, 0.328, 3.33, 0, 0}}, 1.0, 27.2e6, 3.40, 7.16e6, 1.04, 0},
+    // E4M3
+    {5, {{256, 256, 0, 0.892, 9.10, 0.581, 6.73}, {256, 128, 1, 0.406, 6.42, 0, 0}, {128, 256, 1, 0.490, 5.23, 0, 0},
+         {128, 128, 0, 0.498, 4.23, 0, 0}, {128, 128, 1, 0.267, 4.50, 0, 0}}, 1.78, 30.2e6, 3.05, 6.63e6, 1.0, 0},
+    // plain FP16 above
+    {5, {{256, 256, 0, 1.01, 7.85, 0.691, 5.53}, {256, 128, 1, 0.487, 5.98, 0, 0}, {128, 256, 1, 0.571, 4.19, 0, 0},
+         {128, 128, 0, 0.528, 3.21, 0, 0}, {128, 128, 1, 0.316, 2.84, 0, 0}}, 1.67, 31.7e6, 3.37, 6.41e6, 1.0, 0},
+};
+// A split whose partial sums outgrow the fixed scratch of nestedfp_gemm_static is taken where it is priced 4 % below what fits,
+// and by that entry point (bounded) nowhere: FP16 mode is 0.5 % behind the fastest launch so, 0.9 % if nothing beyond
+// the scratch is taken.
+static LargeConfig choose_tall(int cls, int64_t M, int64_t N, int64_t K, bool bounded) {
+    const bool fp8 = cls == 2;
+    const TallCost &m = kTallCost[cls == 0 && M > 256 ? 3 : cls];
     const Tuning &t = tuning();
-    const bool fp8 = cls == 2;                         // cls: cost tables of plain FP16 through LDS, FP16 through registers, E4M3
     const int kt = (int)(((fp8 ? K : 2 * K) + 127) / 128);
-    if (t.tuned_table != 0 && t.large_bm < 0 && t.large_bn < 0 && t.large_split <= 0 && t.large_deep < 0 &&
-        tuned_large(cls, M, N, K, c))
-        return c;
-    if (t.large_bm == 64 || (M <= 64 && t.large_bm < 0 && t.large_bn < 0))
-        return choose_tile64(cls, M, N, K);
-    const bool pinned = t.large_bm > 0 || t.large_bn > 0 || t.large_split > 0;
-    if (M <= 256 && ((cls == 1 && t.large_deep <= 0) || (cls == 2 && t.large_deep < 0 && !pinned))) return choose_short(cls, M, N, K, bounded);
-    double best = 1e30;
-    c.tm = c.tn = 256;
-    c.split = 1;
-    c.deep = 0;
+    const bool limited = cls != 0 && static_scratch_holds(1, M, N, K, fp8, partial_ld(N));
     const int want_m = (t.large_bm == 128 || t.large_bm == 256) ? (int)t.large_bm : 0;
     const int want_n = (t.large_bn == 128 || t.large_bn == 256) ? (int)t.large_bn : want_m;
-    const double w_bytes = (double)N * (double)K * (fp8 ? 1.0 : 2.0);
-    for (int sh = 0; sh < 4; ++sh) {
-        const int bm = kTileShapes[sh][0], bn = kTileShapes[sh][1];
-        if (want_m && bm != want_m) continue;
-        if (want_n && bn != want_n) continue;
-        const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-        for (int deep = 0; deep < 2; ++deep) {
-            if (deep && (kDeepTileCost[cls][sh].tk == 0.0 || t.large_deep == 0)) continue;
-            if (!deep && t.large_deep > 0 && kDeepTileCost[cls][sh].tk != 0.0) continue;
-            const TileCost &whole = deep ? kDeepTileCost[cls][sh] : kTileCost[cls][sh];
+    LargeConfig c;
+    c.tm = 128;  c.tn = 128;  c.split = 1;  c.deep = 0;  c.height = 128;
+    double best = 1e30;
+    for (int i = 0; i < m.shapes; ++i) {
+        const TallShape &e = m.shape[i];
+        if (want_m && want_m != e.tm) continue;
+        if (want_n && want_n != e.tn) continue;
+        int deep = e.deep;
+        if (t.large_deep >= 0 && cls != 1 && !(e.tm == 256 && e.tn == 256)) {
+            deep = t.large_deep > 0 ? 1 : 0;
+            if (((e.tm == 128 && e.tn == 128) || m.shapes == 7) && deep != e.deep) continue;
+        }
+        const int pinned = knob_height(cls, e.tm, e.tn);
+        const bool cut = e.tm == 256 && cuts_tiles(cls, e.tn);
+        const int least = pinned ? pinned : (M <= 256 ? token_tile(cls, e.tm, e.tn, M) : (cut ? 160 : e.tm));
+        const int most = pinned || M <= 256 ? least : e.tm;
+        for (int height = least; height <= most; height += 32) {
+            const double f = cut ? (height - 160) / 96.0 : 1.0;
+            const double tk = e.tk160 + f * (e.tk - e.tk160), tfix = e.tfix160 + f * (e.tfix - e.tfix160);
+            const int64_t tiles = ((M + height - 1) / height) * ((N + e.tn - 1) / e.tn);
             for (int split : kSplits) {
                 if (t.large_split > 0) split = (int)(t.large_split < kt ? t.large_split : kt);
-                else if (split > 1 && (split > kt / 4 || split > max_split)) break;
+                else if (split > 1 && split > kt / 4) break;
+                const bool fits = t.large_split > 0 || !limited || static_scratch_holds(split, M, N, K, fp8, partial_ld(N));
+                if ((!fits && bounded) || (t.large_split <= 0 && !padded_split_fits(split, M, N, K, fp8))) break;
                 const int per = (kt + split - 1) / split;                     // K-tiles per workgroup
                 const int slices = (kt + per - 1) / per;
-                TileCost tc = whole;
-                if (cls == 1 && bm == 256 && static_scratch_holds(slices, M, N, K, false, partial_ld(N))) {
-                    // A tile cut down to the batch lies between those of 128 and of 256 tokens.  (Splits that outgrow the
-                    // fixed scratch are priced as whole tiles, as ever, so that none is taken in place of one that fits.)
-                    const double f = (token_tile(256, M) - 128) / 128.0;
-                    const TileCost &low = kTileCost[cls][sh + 2];
-                    tc.tk = low.tk + f * (tc.tk - low.tk);
-                    tc.tfix = low.tfix + f * (tc.tfix - low.tfix);
+                const int64_t wgs = tiles * slices, rounds = (wgs + 255) / 256;
+                double time = (double)rounds * (tfix + per * tk);
+                if (rounds > 1 && e.tm == 128 && e.tn == 128 && !deep) time /= m.pair;
+                if (M <= 256 && cls == 0) {
+                    double floor_t = (double)N * (double)K * 2.0 / m.floor_rate;
+                    if (wgs < 256) floor_t *= std::sqrt(256.0 / (double)wgs);
+                    if (time < floor_t) time = floor_t;
                 }
-                const int64_t rounds = (tiles * slices + 255) / 256;
-                double time = (double)rounds * (tc.tfix + per * tc.tk);
-                if (sh == 3 && rounds >= 2 && !deep) time /= kPairSpeedup[cls];
-                // the weights' one pass over the memory bus (slower while the chip is not full)
-                const int64_t wgs = tiles * slices;
-                double mem_floor = w_bytes / (wgs < 512 ? 4.57e6 : 4.44e6);
-                if (wgs < 256) mem_floor *= std::sqrt(256.0 / (double)wgs);
-                if (time < mem_floor) time = mem_floor;
-                if (slices > 1) time += split_cost(M, N, slices, 3.18, 4.44e6);
-                if (time < best) { best = time;  c.tm = bm;  c.tn = bn;  c.split = split;  c.deep = deep; }
+                time += (double)wgs * per * (height + e.tn) * 128.0 / m.l2_rate;
+                if (slices > 1) {
+                    time += split_cost(M, N, slices, m.split, m.split_rate);
+                    if ((per & 1) && (K & 127) == 0) time *= m.odd;
+                }
+                if (!fits) time /= 0.96;
+                if (time < best) { best = time;  c.tm = e.tm;  c.tn = e.tn;  c.split = split;  c.deep = deep;  c.height = height; }
                 if (t.large_split > 0) break;
             }
         }
     }
-    if (t.large_split <= 0 && !padded_split_fits(c.split, M, N, K, fp8)) return compute_large(cls, M, N, K, bounded, c.split - 1);
+    c.cost = best;
     return c;
+}
+
+static LargeConfig compute_large(int cls, int64_t M, int64_t N, int64_t K, bool bounded) {
+    LargeConfig c;
+    c.cost = 0.0;
+    const Tuning &t = tuning();
+    if (t.tuned_table != 0 && t.large_bm < 0 && t.large_bn < 0 && t.large_split <= 0 && t.large_deep < 0 && t.large_height < 0 &&
+        tuned_large(cls, M, N, K, c))
+        return c;
+    if (t.large_bm == 64 || (M <= 64 && t.large_bm < 0 && t.large_bn < 0)) return choose_tile64(cls, M, N, K);
+    const bool pinned = t.large_bm > 0 || t.large_bn > 0 || t.large_split > 0;
+    if (M <= 256 && t.large_height < 0 && ((cls == 1 && t.large_deep <= 0) || (cls == 2 && t.large_deep < 0 && !pinned)))
+        return choose_short(cls, M, N, K, bounded);
+    return choose_tall(cls, M, N, K, bounded);
 }
 
 static LargeConfig choose_large(int kind, int64_t M, int64_t N, int64_t K, bool bounded) {
@@ -1867,14 +1890,12 @@ static void launch_e4m3_bypass(const LargeParams &p, dim3 grid, hipStream_t stre
     kern<<<grid, 512, lds, stream>>>(p);
 }
 
-// weights through LDS: plain row-major FP16, E4M3 in either storage order (height: see token_tile)
+// weights through LDS: plain row-major FP16, E4M3 in either storage order
 template <int KIND>
-static void launch_large_k(const LargeParams &p, const LargeConfig &c, int height, dim3 grid, hipStream_t stream) {
-    if constexpr (kind_is_fp8(KIND)) {
-        if (height == 224) { launch_large_t<KIND, 224, 256, 2, 4, 2, 3>(p, grid, stream);  return; }
-        if (height == 192) { launch_large_t<KIND, 192, 256, 2, 4, 2, 3>(p, grid, stream);  return; }
-        if (height == 160) { launch_large_t<KIND, 160, 256, 2, 4, 3>(p, grid, stream);  return; }
-    }
+static void launch_large_k(const LargeParams &p, const LargeConfig &c, dim3 grid, hipStream_t stream) {
+    if (c.height == 224) { launch_large_t<KIND, 224, 256, 2, 4, 2, 3>(p, grid, stream);  return; }
+    if (c.height == 192) { launch_large_t<KIND, 192, 256, 2, 4, 2, 3>(p, grid, stream);  return; }
+    if (c.height == 160) { launch_large_t<KIND, 160, 256, 2, 4, 3>(p, grid, stream);  return; }
     if (c.tm == 64) {
         if constexpr (KIND == kPlainF16) launch_large_t<KIND, 64, 128, 2, 4>(p, grid, stream);
         else launch_e4m3_bypass<64, 128, KIND == kE4M3Row>(p, grid, stream);
@@ -1955,8 +1976,7 @@ static void launch_rows_tile(const LargeParams &p, dim3 grid, hipStream_t stream
     launch_rows<TM, TN>(p, grid, stream);
 }
 
-// weights through registers: NestedFP16 in either storage order, packed FP16.  TM: c.tm, or the height the token
-// tiles are cut down to (see token_tile)
+// weights through registers: NestedFP16 in either storage order, packed FP16.  TM: the height of the token tiles
 template <int WK, int TM>
 static void launch_nested_tm(const LargeParams &p, const LargeConfig &c, dim3 grid, hipStream_t stream) {
     if constexpr (WK == kNestedF16Row) {
@@ -1969,11 +1989,11 @@ static void launch_nested_tm(const LargeParams &p, const LargeConfig &c, dim3 gr
 }
 
 template <int WK>
-static void launch_nested(const LargeParams &p, const LargeConfig &c, int height, dim3 grid, hipStream_t stream) {
-    if (height == 256) { launch_nested_tm<WK, 256>(p, c, grid, stream);  return; }
-    if (height == 224) { launch_nested_tm<WK, 224>(p, c, grid, stream);  return; }
-    if (height == 192) { launch_nested_tm<WK, 192>(p, c, grid, stream);  return; }
-    if (height == 160) { launch_nested_tm<WK, 160>(p, c, grid, stream);  return; }
+static void launch_nested(const LargeParams &p, const LargeConfig &c, dim3 grid, hipStream_t stream) {
+    if (c.height == 256) { launch_nested_tm<WK, 256>(p, c, grid, stream);  return; }
+    if (c.height == 224) { launch_nested_tm<WK, 224>(p, c, grid, stream);  return; }
+    if (c.height == 192) { launch_nested_tm<WK, 192>(p, c, grid, stream);  return; }
+    if (c.height == 160) { launch_nested_tm<WK, 160>(p, c, grid, stream);  return; }
     if constexpr (WK == kNestedF16Row) {
         if (c.tm == 64) launch_rows_by_pairs<64, false>(p, grid, stream);
         else if (c.deep && c.tn == 128) launch_rows_by_pairs<128, true>(p, grid, stream);
@@ -2034,8 +2054,7 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     p.Y = a.Y;  p.ldy = a.ldy;
     p.partials = a.partials;
     p.ldp = (int)partial_ld(a.N);
-    const int height = cuts_tiles(kind_class(kind), c.tn) ? token_tile(c.tm, a.M) : c.tm;
-    p.tiles_m = (int)((a.M + height - 1) / height);
+    p.tiles_m = (int)((a.M + c.height - 1) / c.height);
     p.tiles_n = (int)((a.N + c.tn - 1) / c.tn);
     p.ktiles_total = (p.k_bytes + 127) / 128;
     p.ktiles_per_split = (p.ktiles_total + c.split - 1) / c.split;
@@ -2051,12 +2070,12 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
     if (tuning().large_epilogue == 0) p.row_store = 0;
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)c.split);
     switch (kind) {
-        case kPlainF16: launch_large_k<kPlainF16>(p, c, height, grid, stream); break;
-        case kNestedF16: launch_nested<kNestedF16>(p, c, height, grid, stream); break;
-        case kNestedF16Row: launch_nested<kNestedF16Row>(p, c, height, grid, stream); break;
-        case kPlainF16Packed: launch_nested<kPlainF16Packed>(p, c, height, grid, stream); break;
-        case kE4M3: launch_large_k<kE4M3>(p, c, height, grid, stream); break;
-        case kE4M3Row: launch_large_k<kE4M3Row>(p, c, height, grid, stream); break;
+        case kPlainF16: launch_large_k<kPlainF16>(p, c, grid, stream); break;
+        case kNestedF16: launch_nested<kNestedF16>(p, c, grid, stream); break;
+        case kNestedF16Row: launch_nested<kNestedF16Row>(p, c, grid, stream); break;
+        case kPlainF16Packed: launch_nested<kPlainF16Packed>(p, c, grid, stream); break;
+        case kE4M3: launch_large_k<kE4M3>(p, c, grid, stream); break;
+        case kE4M3Row: launch_large_k<kE4M3Row>(p, c, grid, stream); break;
         default: return kErrArg;
     }
     if (hipGetLastError() != hipSuccess) return kErrHip;

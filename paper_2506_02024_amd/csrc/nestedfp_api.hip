@@ -12,7 +12,7 @@
 namespace nfp {
 
 Tuning &tuning() {
-    static Tuning t = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, 1, -1, -1, -1, -1, -1, -1};
+    static Tuning t = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, 1, -1, -1, -1, -1, -1, -1, -1};
     return t;
 }
 
@@ -568,7 +568,7 @@ int nestedfp_gemm_static(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, c
     // the scratch this problem needs in this plane layout and mode, against the fixed array
     const int kind = mode == NESTEDFP_MODE_FP16 ? kNestedF16Row : kE4M3Row;
     size_t need = workspace_bytes_for(kind, M, N, K, mode == NESTEDFP_MODE_FP8);
-    // (a K split of 65 ... 256 tokens that outgrows it: one that does not)
+    // (a K split of more than 64 tokens that outgrows it: one that does not)
     const bool bounded = need > (size_t)NESTEDFP_STATIC_SCRATCH_BYTES;
     if (bounded) need = workspace_bytes_for(kind, M, N, K, mode == NESTEDFP_MODE_FP8, true);
     if (need > (size_t)NESTEDFP_STATIC_SCRATCH_BYTES) return NESTEDFP_ERR_WORKSPACE;
@@ -686,7 +686,7 @@ int nestedfp_probe_mfma(const void *operands, int fp8, int iters, uint32_t *sink
 
 static const char *const kKnobs[] = {"small_max_m", "small_split", "small_spw", "small_tiles", "small_interleave",
                                      "large_split", "large_bm", "large_bn", "large_epilogue", "small_fuse_quant", "quant_hw", "large_xcd_map",
-                                     "fused_reduce", "large_deep", "large_rows", "tuned_table", "quant_onepass", nullptr};
+                                     "fused_reduce", "large_deep", "large_height", "large_rows", "tuned_table", "quant_onepass", nullptr};
 
 const char *nestedfp_tune_name(int index) {
     if (index < 0 || index >= (int)(sizeof(kKnobs) / sizeof(kKnobs[0]))) return nullptr;
@@ -711,6 +711,7 @@ int nestedfp_tune(const char *knob, int64_t value) {
     else if (!strcmp(knob, "large_xcd_map")) t.large_xcd_map = value;
     else if (!strcmp(knob, "fused_reduce")) t.fused_reduce = value;
     else if (!strcmp(knob, "large_deep")) t.large_deep = value;
+    else if (!strcmp(knob, "large_height")) t.large_height = value;
     else if (!strcmp(knob, "large_rows")) t.large_rows = value;
     else if (!strcmp(knob, "tuned_table")) t.tuned_table = value;
     else if (!strcmp(knob, "quant_onepass")) t.quant_onepass = value;

@@ -61,7 +61,7 @@ struct GemmArgs {
     float *partials;      // split-K scratch (may be NULL if split == 1)
     size_t partial_bytes;
     uint32_t *counters;   // kMaxCounters arrival counters, all zero between calls (NULL: reduce in a second launch)
-    bool bounded;         // K splits of 65 ... 256 tokens that fit the fixed scratch only (see nestedfp_gemm_static)
+    bool bounded;         // K splits of more than 64 tokens that fit the fixed scratch only (see nestedfp_gemm_static)
 };
 
 // arrival counters at the start of every workspace: one per output tile of a split launch
@@ -84,6 +84,7 @@ struct Tuning {
     int64_t large_xcd_map;   // 0: tiles in launch order instead of grouped by XCD (tiled kernels)
     int64_t fused_reduce;    // 0: split-K partials are summed by a second launch instead of the last workgroup
     int64_t large_deep;      // 1 / 0: force / forbid the deeper load pipelines of the tiled kernels (tiles below 256 x 256)
+    int64_t large_height;    // height of token tiles of 256 where they exist cut down: 160, 192, 224 or 256
     int64_t large_rows;      // 1 / 0: row-major planes reach tiles above 64 tokens through LDS / straight into registers
     int64_t tuned_table;     // 0: the tiled kernels' launch shape always comes from the cost model, never from the table of timed shapes
     int64_t quant_onepass;   // 1 / 0: force / forbid the single-pass activation quantisation (rows kept in registers) where it fits

@@ -80,3 +80,21 @@ def test_which_batches_are_quantised_in_the_streaming_kernel(L, M, N, K, fused):
     f = L._ZN3nfp22small_gemm_fuses_quantElll                 # nfp::small_gemm_fuses_quant
     f.restype, f.argtypes = ctypes.c_bool, 3 * [ctypes.c_int64]
     assert f(M, N, K) == fused
+
+
+def test_splits_of_more_than_256_tokens_and_the_fixed_scratch(L):
+    # what fits the scratch unsplit gets a split that fits where there is no workspace, and the same one with a workspace unless
+    # that outgrows the scratch
+    import random
+
+    rng = random.Random(4)
+    for _ in range(3000):
+        M, N, K = int(257 * 40 ** rng.random()), rng.randrange(1, 40000), 16 * rng.randrange(1, 2000)
+        for kind in (1, 2, 4, 5):
+            fp8 = kind in (2, 5)
+            room = (32 << 20) - 16384 - (M * K + 4 * M + 512 if fp8 else 0)
+            free, bounded = (partial_bytes(L, kind, M, N, K, w) for w in ("24large_gemm_partial_bytes", "24large_gemm_bounded_bytes"))
+            if room >= 0:
+                assert bounded <= room and (bounded == free or free > room - 512)
+            else:
+                assert bounded == free
