@@ -341,7 +341,7 @@ small_gemm_kernel(SmallParams p) {
                 }
             }
             fetch(buf0, 0);                            // the weights travel during the reduction
-            float sc[2], rc[2];
+            float sc[2], rc[2], rest[2];
             uint32_t largest[2] = {0u, 0u};            // |x| as an integer compare on the magnitude bits
             if (!p.static_scale) {
 #pragma unroll
@@ -355,39 +355,39 @@ small_gemm_kernel(SmallParams p) {
 #pragma unroll
                             for (int e = 0; e < 4; ++e) largest[h] = max(largest[h], max(w[e] & 0x7fffu, (w[e] >> 16) & 0x7fffu));
                         }
-#pragma unroll
-                    for (int off = 1; off < 8; off <<= 1) largest[h] = max(largest[h], (uint32_t)__shfl_xor((int)largest[h], off, 64));
+                    largest[h] = max_of_8_lanes(largest[h]);
                     if ((lane & 7) == 0) row_max[wave * 16 + 8 * h + row] = largest[h];
                 }
                 __syncthreads();
-                for (int w2 = 0; w2 < waves; ++w2) {
-                    largest[0] = max(largest[0], row_max[w2 * 16 + row]);
-                    if (two) largest[1] = max(largest[1], row_max[w2 * 16 + 8 + row]);
-                }
+                // (16 waves at most: two words per lane, the maxima of a row's eight lanes)
+                const int w0 = min(lane & 7, waves - 1) * 16 + row, w1 = min((lane & 7) + 8, waves - 1) * 16 + row;
+                largest[0] = max_of_8_lanes(max(row_max[w0], row_max[w1]));
+                if (two) largest[1] = max_of_8_lanes(max(row_max[w0 + 8], row_max[w1 + 8]));
             }
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const float amax = half_bits_to_float(largest[h]);
                 sc[h] = p.static_scale ? *p.static_scale : (amax == 0.0f ? 1.0f : amax / 448.0f);
                 rc[h] = 1.0f / sc[h];                  // correctly rounded; see div_by_scale
+                rest[h] = rest_of_reciprocal(sc[h], rc[h]);
                 if (wave == 0 && (lane & 7) == 0) row_scale[8 * h + row] = sc[h];
             }
             // (a row with an infinity or a NaN, a scale given by the caller: codes that need clamping)
             const bool plain = p.quant_hw && !p.static_scale && !__any(largest[0] >= 0x7c00u || largest[1] >= 0x7c00u);
 #pragma unroll
             for (int s = 0; s < SPW; ++s) {
-                auto convert = [&](u32x4 &to, const u32x4 (&x)[2], float sc_, float rc_) {
-                    if (plain) to = u32x4{quant4_own_scale(x[0].x, x[0].y, sc_, rc_), quant4_own_scale(x[0].z, x[0].w, sc_, rc_),
-                                          quant4_own_scale(x[1].x, x[1].y, sc_, rc_), quant4_own_scale(x[1].z, x[1].w, sc_, rc_)};
+                auto convert = [&](u32x4 &to, const u32x4 (&x)[2], float sc_, float rc_, float rest_) {
+                    if (plain) to = u32x4{quant4_own_scale(x[0].x, x[0].y, rc_, rest_), quant4_own_scale(x[0].z, x[0].w, rc_, rest_),
+                                          quant4_own_scale(x[1].x, x[1].y, rc_, rest_), quant4_own_scale(x[1].z, x[1].w, rc_, rest_)};
                     else if (p.quant_hw) to = u32x4{quant4<true>(x[0].x, x[0].y, sc_, rc_), quant4<true>(x[0].z, x[0].w, sc_, rc_),
                                                     quant4<true>(x[1].x, x[1].y, sc_, rc_), quant4<true>(x[1].z, x[1].w, sc_, rc_)};
                     else to = u32x4{quant4<false>(x[0].x, x[0].y, sc_, rc_), quant4<false>(x[0].z, x[0].w, sc_, rc_),
                                     quant4<false>(x[1].x, x[1].y, sc_, rc_), quant4<false>(x[1].z, x[1].w, sc_, rc_)};
                 };
-                convert(xa[s][0], xr[s][0], sc[0], rc[0]);
+                convert(xa[s][0], xr[s][0], sc[0], rc[0], rest[0]);
                 xb[s][0] = u32x4{0u, 0u, 0u, 0u};
                 if constexpr (H == 2)
-                    if (two) convert(xb[s][0], xr[s][1], sc[1], rc[1]);
+                    if (two) convert(xb[s][0], xr[s][1], sc[1], rc[1], rest[1]);
                 rx.run(xa[s][0], xb[s][0]);
             }
         } else {
@@ -719,17 +719,18 @@ static void launch_small_t(const SmallParams &p, const SmallConfig &c, dim3 grid
 
 // Whether the streaming kernel quantises the activations itself: one token tile, all of K in the workgroup.  What it saves
 // is a launch (1.3 us in a graph, 3 us of host time outside one); what it costs is that every workgroup waits for
-// its M x K activations, their row maxima and 4 VALU instructions per value before it multiplies, while two weight
+// its M x K activations, their row maxima and 3 VALU instructions per value before it multiplies, while two weight
 // tiles are on their way.  Up to 8 tokens (half the lanes' rows) that pays where a workgroup has further tiles or the
-// rows are short: (1024, 1024) 5.5 -> 4.1 us, (11008, 3072) 10.9 -> 10.0, (7680, 5120) 11.9 -> 11.1, (10240, 8192) 19.5 -> 18.6; with
-// one tile (4096, 4096) takes 8.6 against 8.9 and (3072, 7168) 10.8 against 11.3.  With 16 rows to convert it pays
-// on short rows only: 16 tokens on (1024, 1024) 5.8 -> 5.2 us, on (2048, 2048) 6.8 -> 7.3, on (4096, 4096) 9.2 -> 11.5.
+// rows are short (us with the launch of its own / fused): (1024, 1024) 5.2 / 4.0, (12288, 3072) 10.9 / 9.8, (8192, 5120) 11.6 / 11.0,
+// (8192, 8192) 15.7 / 14.9; with one tile (4096, 4096) takes 8.5 / 8.5 and (3072, 7168) 10.5 / 11.3.  With 16 rows to convert it pays
+// on short rows, 16 tokens on (1024, 1280) 5.8 / 5.5, and up to 3584 columns from three tiles on: (12288, 2048) 9.6 / 9.0,
+// (32768, 2048) 15.2 / 14.7, (16384, 3584) 14.2 / 13.7 at 9 tokens and level at 16, (6144, 2560) with two 8.0 / 8.4, (4096, 4096) 8.7 / 10.5.
 bool small_gemm_fuses_quant(int64_t M, int64_t N, int64_t K) {
     const int64_t knob = tuning().small_fuse_quant;
     if (knob == 0) return false;
     const SmallConfig c = choose_small(kE4M3, M, N, K);
     if (c.mt != 1 || c.split != 1 || c.passes != 1 || (c.spw != 2 && M > 8) || small_lds(c) > (size_t)kQuantLds) return false;
-    return knob > 0 || (M <= 8 ? (c.tiles_per_wg > 1 || K <= 3072) : K <= 1280);
+    return knob > 0 || (M <= 8 ? (c.tiles_per_wg > 1 || K <= 3072) : (K <= 1280 || (K <= 3584 && c.tiles_per_wg > 2)));
 }
 
 template <int KIND>

@@ -172,19 +172,38 @@ __device__ __forceinline__ uint32_t quant4(uint32_t w01, uint32_t w23, float s, 
            (e4m3_from_float_sw(d) << 24);
 }
 
-// The same for finite activations of a row and its own scale, amax / 448: no quotient exceeds 448 by more than its own
+// The same for finite activations of a row and its own scale, s = amax / 448, from y = RN(1 / s) and rest_of_reciprocal(s, y):
+// a * y + RN(a * rest) in one FMA is the correctly rounded quotient of every finite activation and every finite
+// maximum not below it (all 504 million pairs compared with the division), two instructions with the activation's
+// conversion in them where the division takes four.  No quotient exceeds 448 by more than its own
 // rounding, which converts to 448, so nothing is clamped; the sign, which a quotient of zero would lose, is put back for
 // four codes at once.
-__device__ __forceinline__ uint32_t quant4_own_scale(uint32_t w01, uint32_t w23, float s, float y) {
+__device__ __forceinline__ float rest_of_reciprocal(float s, float y) { return __builtin_fmaf(-s, y, 1.0f) * y; }
+__device__ __forceinline__ uint32_t quant4_own_scale(uint32_t w01, uint32_t w23, float y, float rest) {
     const uint32_t w[4] = {w01 & 0xffffu, w01 >> 16, w23 & 0xffffu, w23 >> 16};
     float q[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const float a = half_bits_to_float(w[i]);
-        const float q0 = a * y;
-        q[i] = __builtin_fmaf(__builtin_fmaf(-q0, s, a), y, q0);
+        q[i] = __builtin_fmaf(a, y, a * rest);
     }
     return e4m3x4_from_float_hw(q[0], q[1], q[2], q[3]) | (byte_perm(w23, w01, 0x07050301u) & 0x80808080u);
+}
+
+// Largest value of 8, 16 or 64 consecutive lanes in all of them, by DPP moves, which cost a few cycles each where a
+// shuffle makes a trip through LDS.  All lanes of the wave take part.
+template <int CTRL>
+__device__ __forceinline__ uint32_t max_with_lane(uint32_t v) {
+    return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ uint32_t max_of_8_lanes(uint32_t v) {
+    return max_with_lane<0x141>(max_with_lane<0x4e>(max_with_lane<0xb1>(v)));    // lane ^ 1, lane ^ 2, 7 - lane
+}
+__device__ __forceinline__ uint32_t max_of_16_lanes(uint32_t v) { return max_with_lane<0x140>(max_of_8_lanes(v)); }      // 15 - lane
+__device__ __forceinline__ uint32_t max_of_wave(uint32_t v) {
+    v = max_of_16_lanes(v);
+    return max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
+               max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
 }
 
 // FP8-mode outputs are the FP32 sum times the FP32 scale, rounded to FP32, then converted to FP16,

@@ -9,6 +9,33 @@ namespace nfp {
 
 constexpr int kQuantThreads = 256;
 
+// Decode-sized batches wait for one chain: launch, load, maximum, conversion, store.  Maxima go by DPP, those of the waves are
+// read in one LDS access, and rows of finite activations take the short conversion.  Replayed in a graph, before and now: 16 tokens of
+// 4096 columns 2.63 -> 2.33 us, of 14336 3.90 -> 2.99; 777 tokens 4.2 -> 3.8 and 10.4 -> 8.0; 8192 tokens 19.5 -> 18.6 and 73 -> 63.
+struct RowScale { float s, y, rest;  bool plain; };
+template <bool HW>
+__device__ __forceinline__ RowScale scale_of(const float *static_scale, uint32_t amax_bits) {
+    RowScale r;
+    const float amax = half_bits_to_float(amax_bits);
+    r.s = static_scale ? *static_scale : (amax == 0.0f ? 1.0f : amax / 448.0f);
+    r.y = 1.0f / r.s;                                // correctly rounded; see div_by_scale
+    r.rest = rest_of_reciprocal(r.s, r.y);
+    r.plain = HW && !static_scale && amax_bits < 0x7c00u;     // (an infinity or a NaN, a scale given by the caller: codes that need clamping)
+    return r;
+}
+// the maximum of a workgroup of `waves` waves, red: a word for each
+__device__ __forceinline__ uint32_t max_of_workgroup(uint32_t v, uint32_t *red, int waves) {
+    v = max_of_wave(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)max_of_16_lanes(red[min((int)(threadIdx.x & 15), waves - 1)]));
+}
+template <bool HW>
+__device__ __forceinline__ u32x2 quant8(const u32x4 &v, const RowScale &r) {
+    if (r.plain) return u32x2{quant4_own_scale(v.x, v.y, r.y, r.rest), quant4_own_scale(v.z, v.w, r.y, r.rest)};
+    return u32x2{quant4<HW>(v.x, v.y, r.s, r.y), quant4<HW>(v.z, v.w, r.s, r.y)};
+}
+
 template <bool HW>
 __global__ void __launch_bounds__(kQuantThreads)
 quantize_act_kernel(const uint16_t *__restrict__ X, int64_t K, int64_t ldx,
@@ -18,12 +45,9 @@ quantize_act_kernel(const uint16_t *__restrict__ X, int64_t K, int64_t ldx,
     const u32x4 *row = reinterpret_cast<const u32x4 *>(X + m * ldx);
     const int chunks = (int)(K / 8);                 // 8 halves per 16-byte chunk
     __shared__ uint32_t red[kQuantThreads / 64];
-    float s;
-    if (static_scale) {
-        s = *static_scale;
-    } else {
+    uint32_t amax_bits = 0;
+    if (!static_scale) {
         // |x| as an integer compare on the magnitude bits: monotone for finite halves
-        uint32_t amax_bits = 0;
         for (int c = threadIdx.x; c < chunks; c += kQuantThreads) {
             u32x4 v = row[c];
             uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -33,26 +57,12 @@ quantize_act_kernel(const uint16_t *__restrict__ X, int64_t K, int64_t ldx,
                 amax_bits = max(amax_bits, max(lo, hi));
             }
         }
-        for (int off = 32; off > 0; off >>= 1)
-            amax_bits = max(amax_bits, (uint32_t)__shfl_xor((int)amax_bits, off, 64));
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = amax_bits;
-        __syncthreads();
-        uint32_t all = 0;
-#pragma unroll
-        for (int i = 0; i < kQuantThreads / 64; ++i) all = max(all, red[i]);
-        float amax = half_bits_to_float(all);
-        s = (amax == 0.0f) ? 1.0f : amax / 448.0f;
+        amax_bits = max_of_workgroup(amax_bits, red, kQuantThreads / 64);
     }
-    if (threadIdx.x == 0) scales[m] = s;
-    const float y = 1.0f / s;                        // correctly rounded; see div_by_scale
+    const RowScale r = scale_of<HW>(static_scale, amax_bits);
+    if (threadIdx.x == 0) scales[m] = r.s;
     u32x2 *out = reinterpret_cast<u32x2 *>(Xq + m * K);
-    for (int c = threadIdx.x; c < chunks; c += kQuantThreads) {
-        u32x4 v = row[c];
-        u32x2 q;
-        q.x = quant4<HW>(v.x, v.y, s, y);
-        q.y = quant4<HW>(v.z, v.w, s, y);
-        out[c] = q;
-    }
+    for (int c = threadIdx.x; c < chunks; c += kQuantThreads) out[c] = quant8<HW>(row[c], r);
 }
 
 // Single-pass variant for rows that fit in registers (K <= 32768): every lane keeps its
@@ -78,32 +88,14 @@ quantize_act_onepass_kernel(const uint16_t *__restrict__ X, int64_t K, int64_t l
 #pragma unroll
         for (int q = 0; q < 4; ++q) amax_bits = max(amax_bits, max(w[q] & 0x7fffu, (w[q] >> 16) & 0x7fffu));
     }
-    float s;
-    if (static_scale) {
-        s = *static_scale;
-    } else {
-        for (int off = 32; off > 0; off >>= 1)
-            amax_bits = max(amax_bits, (uint32_t)__shfl_xor((int)amax_bits, off, 64));
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = amax_bits;
-        __syncthreads();
-        uint32_t all = 0;
-        const int waves = blockDim.x >> 6;
-        for (int i = 0; i < waves; ++i) all = max(all, red[i]);
-        float amax = half_bits_to_float(all);
-        s = (amax == 0.0f) ? 1.0f : amax / 448.0f;
-    }
-    if (threadIdx.x == 0) scales[m] = s;
-    const float y = 1.0f / s;                        // correctly rounded; see div_by_scale
+    if (!static_scale) amax_bits = max_of_workgroup(amax_bits, red, blockDim.x >> 6);
+    const RowScale r = scale_of<HW>(static_scale, amax_bits);
+    if (threadIdx.x == 0) scales[m] = r.s;
     u32x2 *out = reinterpret_cast<u32x2 *>(Xq + m * K);
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
         int c = threadIdx.x + i * blockDim.x;
-        if (c < chunks) {
-            u32x2 q;
-            q.x = quant4<HW>(v[i].x, v[i].y, s, y);
-            q.y = quant4<HW>(v[i].z, v[i].w, s, y);
-            out[c] = q;
-        }
+        if (c < chunks) out[c] = quant8<HW>(v[i], r);
     }
 }
 

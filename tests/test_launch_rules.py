@@ -98,3 +98,14 @@ def test_splits_of_more_than_256_tokens_and_the_fixed_scratch(L):
                 assert bounded <= room and (bounded == free or free > room - 512)
             else:
                 assert bounded == free
+
+
+@pytest.mark.parametrize("M,N,K,fused", [
+    # 9 to 16 tokens, three weight tiles per workgroup and up to 3584 columns (us with a launch of its own and fused: 9.6 / 9.0, 14.2 / 13.7,
+    # 8.3 / 8.7 with two tiles, 15.0 / 15.0)
+    (16, 12288, 2048, True), (9, 16384, 3584, True), (9, 6144, 3072, False), (12, 16384, 4096, False),
+])
+def test_which_wide_layers_are_quantised_in_the_streaming_kernel(L, M, N, K, fused):
+    f = L._ZN3nfp22small_gemm_fuses_quantElll                 # nfp::small_gemm_fuses_quant
+    f.restype, f.argtypes = ctypes.c_bool, 3 * [ctypes.c_int64]
+    assert f(M, N, K) == fused
