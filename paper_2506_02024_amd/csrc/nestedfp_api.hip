@@ -33,6 +33,7 @@ constexpr int64_t kMaxK = (int64_t)1 << 21;            // K and leading dimensio
 struct Workspace {
     uint32_t *counters;
     uint8_t *xq;
+    int64_t xq_ld;                                     // bytes from row to row (see xq_row)
     float *scales;
     float *partials;
     size_t partial_bytes;
@@ -77,6 +78,7 @@ static bool carve(void *ws, size_t ws_bytes, int kind, int64_t M, int64_t N, int
     if (need > 0 && (ws == nullptr || ws_bytes < need || !aligned(ws, 16))) return false;
     out.counters = nullptr;
     out.xq = nullptr;
+    out.xq_ld = K;
     out.scales = nullptr;
     out.partials = nullptr;
     out.partial_bytes = 0;
@@ -84,7 +86,8 @@ static bool carve(void *ws, size_t ws_bytes, int kind, int64_t M, int64_t N, int
     uint8_t *p = static_cast<uint8_t *>(ws);
     out.counters = reinterpret_cast<uint32_t *>(p);  p += kCounterBytes;
     if (quantize) {
-        out.xq = p;  p += round256((size_t)M * (size_t)K);
+        if (ws_bytes - need >= xq_padding(M, K)) out.xq_ld = xq_row(K);
+        out.xq = p;  p += round256((size_t)M * (size_t)out.xq_ld);
         out.scales = reinterpret_cast<float *>(p);  p += round256((size_t)M * sizeof(float));
     }
     out.partials = reinterpret_cast<float *>(p);
@@ -133,13 +136,13 @@ static int fp8_gemm_fused(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, 
     return launch_small_gemm(w_kind == kE4M3 ? kE4M3Quant : kE4M3QuantRow, a, stream);
 }
 
-static int fp8_gemm(const uint8_t *Xq, const float *scales, int64_t M, int64_t K, const uint8_t *Wq,
+static int fp8_gemm(const uint8_t *Xq, int64_t ldx, const float *scales, int64_t M, int64_t K, const uint8_t *Wq,
                     int64_t N, int w_kind, float w_scale, uint16_t *Y, int64_t ldy, const Workspace &ws,
                     hipStream_t stream, bool bounded = false) {
     GemmArgs a;
     memset(&a, 0, sizeof(a));
     a.bounded = bounded;
-    a.X = Xq;  a.ldx = K;  a.scales = scales;  a.w_scale = w_scale;
+    a.X = Xq;  a.ldx = ldx;  a.scales = scales;  a.w_scale = w_scale;
     a.W0 = Wq;  a.W1 = nullptr;  a.ldw = K;
     a.M = M;  a.N = N;  a.K = K;  a.Y = Y;  a.ldy = ldy;
     a.partials = ws.partials;  a.partial_bytes = ws.partial_bytes;  a.counters = ws.counters;
@@ -308,6 +311,8 @@ static size_t gemm_workspace_size(int64_t M, int64_t N, int64_t K, int mode) {
             const size_t b = workspace_bytes_for(kind, M, N, K, true);
             if (b > need) need = b;
         }
+        const size_t padded = need + xq_padding(M, K);
+        if (padded <= kStaticScratch || need > kStaticScratch) need = padded;
     }
     return need;
 }
@@ -345,9 +350,9 @@ static int gemm_impl(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, const
     // Sec. 4.1: the upper plane read as E4M3 is the weight times 2^8
     st = fp8_gemm_fused(X, M, K, ldx, act_scale, upper, N, kind, 0.00390625f, Y, ldy, s);
     if (st >= 0) return st;
-    st = launch_quantize_act(X, M, K, ldx, act_scale, ws.xq, ws.scales, s);
+    st = launch_quantize_act(X, M, K, ldx, act_scale, ws.xq, ws.xq_ld, ws.scales, s);
     if (st != kOk) return st;
-    return fp8_gemm(ws.xq, ws.scales, M, K, upper, N, kind, 0.00390625f, Y, ldy, ws, s, bounded);
+    return fp8_gemm(ws.xq, ws.xq_ld, ws.scales, M, K, upper, N, kind, 0.00390625f, Y, ldy, ws, s, bounded);
 }
 
 static int plain_fp16_impl(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, const void *W, int64_t N,
@@ -391,9 +396,9 @@ static int plain_fp8_impl(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, 
     if (!carve(workspace, workspace_bytes, kind, M, N, K, true, ws)) return NESTEDFP_ERR_WORKSPACE;
     st = fp8_gemm_fused(X, M, K, ldx, act_scale, Wq, N, kind, w_scale, Y, ldy, s);
     if (st >= 0) return st;
-    st = launch_quantize_act(X, M, K, ldx, act_scale, ws.xq, ws.scales, s);
+    st = launch_quantize_act(X, M, K, ldx, act_scale, ws.xq, ws.xq_ld, ws.scales, s);
     if (st != kOk) return st;
-    return fp8_gemm(ws.xq, ws.scales, M, K, Wq, N, kind, w_scale, Y, ldy, ws, s);
+    return fp8_gemm(ws.xq, ws.xq_ld, ws.scales, M, K, Wq, N, kind, w_scale, Y, ldy, ws, s);
 }
 
 }  // namespace nfp
@@ -530,7 +535,7 @@ int nestedfp_quantize_act(const uint16_t *X, int64_t M, int64_t K, int64_t ldx, 
     if (st != kOk) return st;
     if (!aligned(Xq, 16) || !aligned(scales, 4)) return NESTEDFP_ERR_SHAPE;
     if (M == 0) return NESTEDFP_OK;
-    return launch_quantize_act(X, M, K, ldx, static_scale, Xq, scales, static_cast<hipStream_t>(stream));
+    return launch_quantize_act(X, M, K, ldx, static_scale, Xq, K, scales, static_cast<hipStream_t>(stream));
 }
 
 size_t nestedfp_gemm_workspace_size(int64_t M, int64_t N, int64_t K, int mode) {
@@ -619,7 +624,7 @@ int nestedfp_gemm_fp8_prequantized(const uint8_t *Xq, const float *scales, int64
     const int kind = layout == NESTEDFP_LAYOUT_PACKED ? kE4M3 : kE4M3Row;
     Workspace ws;
     if (!carve(workspace, workspace_bytes, kind, M, N, K, false, ws)) return NESTEDFP_ERR_WORKSPACE;
-    return fp8_gemm(Xq, scales, M, K, upper, N, kind, w_scale, Y, ldy, ws, static_cast<hipStream_t>(stream));
+    return fp8_gemm(Xq, K, scales, M, K, upper, N, kind, w_scale, Y, ldy, ws, static_cast<hipStream_t>(stream));
 }
 
 int nestedfp_layer_prepare(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, int layout, uint8_t *upper,

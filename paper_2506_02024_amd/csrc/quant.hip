@@ -40,7 +40,7 @@ template <bool HW>
 __global__ void __launch_bounds__(kQuantThreads)
 quantize_act_kernel(const uint16_t *__restrict__ X, int64_t K, int64_t ldx,
                     const float *__restrict__ static_scale, uint8_t *__restrict__ Xq,
-                    float *__restrict__ scales) {
+                    float *__restrict__ scales, int64_t ldq) {
     const int64_t m = blockIdx.x;
     const u32x4 *row = reinterpret_cast<const u32x4 *>(X + m * ldx);
     const int chunks = (int)(K / 8);                 // 8 halves per 16-byte chunk
@@ -61,7 +61,7 @@ quantize_act_kernel(const uint16_t *__restrict__ X, int64_t K, int64_t ldx,
     }
     const RowScale r = scale_of<HW>(static_scale, amax_bits);
     if (threadIdx.x == 0) scales[m] = r.s;
-    u32x2 *out = reinterpret_cast<u32x2 *>(Xq + m * K);
+    u32x2 *out = reinterpret_cast<u32x2 *>(Xq + m * ldq);
     for (int c = threadIdx.x; c < chunks; c += kQuantThreads) out[c] = quant8<HW>(row[c], r);
 }
 
@@ -73,7 +73,7 @@ template <int CPT, bool HW>
 __global__ void __launch_bounds__(1024)
 quantize_act_onepass_kernel(const uint16_t *__restrict__ X, int64_t K, int64_t ldx,
                             const float *__restrict__ static_scale, uint8_t *__restrict__ Xq,
-                            float *__restrict__ scales) {
+                            float *__restrict__ scales, int64_t ldq) {
     const int64_t m = blockIdx.x;
     const u32x4 *row = reinterpret_cast<const u32x4 *>(X + m * ldx);
     const int chunks = (int)(K / 8);
@@ -91,7 +91,7 @@ quantize_act_onepass_kernel(const uint16_t *__restrict__ X, int64_t K, int64_t l
     if (!static_scale) amax_bits = max_of_workgroup(amax_bits, red, blockDim.x >> 6);
     const RowScale r = scale_of<HW>(static_scale, amax_bits);
     if (threadIdx.x == 0) scales[m] = r.s;
-    u32x2 *out = reinterpret_cast<u32x2 *>(Xq + m * K);
+    u32x2 *out = reinterpret_cast<u32x2 *>(Xq + m * ldq);
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
         int c = threadIdx.x + i * blockDim.x;
@@ -101,16 +101,16 @@ quantize_act_onepass_kernel(const uint16_t *__restrict__ X, int64_t K, int64_t l
 
 template <int CPT>
 static void launch_onepass(bool hw, int threads, const uint16_t *X, int64_t M, int64_t K, int64_t ldx,
-                           const float *static_scale, uint8_t *Xq, float *scales, hipStream_t stream) {
+                           const float *static_scale, uint8_t *Xq, int64_t ldq, float *scales, hipStream_t stream) {
     dim3 grid((unsigned)M);
     if (hw)
-        quantize_act_onepass_kernel<CPT, true><<<grid, threads, 0, stream>>>(X, K, ldx, static_scale, Xq, scales);
+        quantize_act_onepass_kernel<CPT, true><<<grid, threads, 0, stream>>>(X, K, ldx, static_scale, Xq, scales, ldq);
     else
-        quantize_act_onepass_kernel<CPT, false><<<grid, threads, 0, stream>>>(X, K, ldx, static_scale, Xq, scales);
+        quantize_act_onepass_kernel<CPT, false><<<grid, threads, 0, stream>>>(X, K, ldx, static_scale, Xq, scales, ldq);
 }
 
 int launch_quantize_act(const uint16_t *X, int64_t M, int64_t K, int64_t ldx,
-                        const float *static_scale, uint8_t *Xq, float *scales, hipStream_t stream) {
+                        const float *static_scale, uint8_t *Xq, int64_t ldq, float *scales, hipStream_t stream) {
     bool hw = tuning().quant_hw != 0;
     const int64_t chunks = K / 8;
     const int64_t onepass = tuning().quant_onepass;
@@ -123,16 +123,16 @@ int launch_quantize_act(const uint16_t *X, int64_t M, int64_t K, int64_t ldx,
         // as many lanes as the row has chunks (up to 1024, 4 chunks each)
         int cpt = chunks <= 1024 ? 1 : (chunks <= 2048 ? 2 : 4);
         int threads = (int)(((chunks + cpt - 1) / cpt + 63) / 64 * 64);
-        if (cpt == 1) launch_onepass<1>(hw, threads, X, M, K, ldx, static_scale, Xq, scales, stream);
-        else if (cpt == 2) launch_onepass<2>(hw, threads, X, M, K, ldx, static_scale, Xq, scales, stream);
-        else launch_onepass<4>(hw, threads, X, M, K, ldx, static_scale, Xq, scales, stream);
+        if (cpt == 1) launch_onepass<1>(hw, threads, X, M, K, ldx, static_scale, Xq, ldq, scales, stream);
+        else if (cpt == 2) launch_onepass<2>(hw, threads, X, M, K, ldx, static_scale, Xq, ldq, scales, stream);
+        else launch_onepass<4>(hw, threads, X, M, K, ldx, static_scale, Xq, ldq, scales, stream);
         return hip_ok(hipGetLastError());
     }
     dim3 grid((unsigned)M);
     if (hw)
-        quantize_act_kernel<true><<<grid, kQuantThreads, 0, stream>>>(X, K, ldx, static_scale, Xq, scales);
+        quantize_act_kernel<true><<<grid, kQuantThreads, 0, stream>>>(X, K, ldx, static_scale, Xq, scales, ldq);
     else
-        quantize_act_kernel<false><<<grid, kQuantThreads, 0, stream>>>(X, K, ldx, static_scale, Xq, scales);
+        quantize_act_kernel<false><<<grid, kQuantThreads, 0, stream>>>(X, K, ldx, static_scale, Xq, scales, ldq);
     return hip_ok(hipGetLastError());
 }
 

@@ -109,3 +109,21 @@ def test_which_wide_layers_are_quantised_in_the_streaming_kernel(L, M, N, K, fus
     f = L._ZN3nfp22small_gemm_fuses_quantElll                 # nfp::small_gemm_fuses_quant
     f.restype, f.argtypes = ctypes.c_bool, 3 * [ctypes.c_int64]
     assert f(M, N, K) == fused
+
+
+def test_room_for_padded_codes_stays_inside_the_fixed_scratch(L):
+    # the query asks for rows of codes on 128-byte lines, but never takes a problem past the scratch of the entry point without a workspace
+    import random
+
+    rng = random.Random(5)
+    size = L.nestedfp_gemm_workspace_size
+    size.restype, size.argtypes = ctypes.c_size_t, 3 * [ctypes.c_int64] + [ctypes.c_int]
+    for _ in range(3000):
+        M, K = int(9000 ** rng.random()), 16 * rng.randrange(1, 2500)
+        N = rng.randrange(1, 3000)
+        dense = 16384 + (M * K + 255) // 256 * 256 + (4 * M + 255) // 256 * 256
+        pad = (M * ((K + 127) // 128 * 128) + 255) // 256 * 256 - (M * K + 255) // 256 * 256
+        most = max(partial_bytes(L, kind, M, N, K) if M > 64 else 0 for kind in (2, 5))
+        need = dense + (most + 255) // 256 * 256
+        if M > 64:
+            assert size(M, N, K, 1) == (need + pad if need + pad <= 32 << 20 or need > 32 << 20 else need)
