@@ -21,6 +21,8 @@
 #include <algorithm>
 #include <cmath>
 
+#include <type_traits>
+
 #include "nfp_device.h"
 #include "nfp_host.h"
 
@@ -453,11 +455,21 @@ small_gemm_kernel(SmallParams p) {
         p.partials, 0, fused ? (uint32_t)(gridDim.y * slice_elems * 4) : 0u, 0x00020000);
     for (int item = wave; item < T * MT; item += waves) {
         const int tile = item / MT, i = item - tile * MT;
+        // (eight, four, two reads under way at a time: read one by one, the last seven of 8 or 16 waves cost as many trips to LDS)
         floatx4 sum = slots[((tile * waves) * MT + i) * 64 + lane];
-        for (int w2 = 1; w2 < waves; ++w2) {
-            floatx4 v = slots[((tile * waves + w2) * MT + i) * 64 + lane];
-            sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
-        }
+        int w2 = 1;
+        auto add = [&](auto count) {
+            floatx4 v[decltype(count)::value];
+#pragma unroll
+            for (int q = 0; q < decltype(count)::value; ++q) v[q] = slots[((tile * waves + w2 + q) * MT + i) * 64 + lane];
+#pragma unroll
+            for (int q = 0; q < decltype(count)::value; ++q) { sum.x += v[q].x; sum.y += v[q].y; sum.z += v[q].z; sum.w += v[q].w; }
+            w2 += decltype(count)::value;
+        };
+        if (waves - w2 >= 8) add(std::integral_constant<int, 8>{});
+        if (waves - w2 >= 4) add(std::integral_constant<int, 4>{});
+        if (waves - w2 >= 2) add(std::integral_constant<int, 2>{});
+        if (waves - w2 >= 1) add(std::integral_constant<int, 1>{});
         const int m = 16 * i + r16;
         const int n = (tile0 + tile * tstride) * 16 + 4 * g;
         if (m >= p.M || n >= p.N) continue;
@@ -494,12 +506,20 @@ small_gemm_kernel(SmallParams p) {
         if (m >= p.M || n >= p.N) continue;
         const uint32_t off = (uint32_t)(((int64_t)m * p.ldp + n) * 4);
         const uint32_t sstep = (uint32_t)(slice_elems * 4);
-        u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rpart, off, 0, kThrough);
-        floatx4 sum = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
-        for (int s2 = 1; s2 < (int)gridDim.y; ++s2) {
-            v = __builtin_amdgcn_raw_buffer_load_b128(rpart, off + s2 * sstep, 0, kThrough);
-            sum.x += __uint_as_float(v.x); sum.y += __uint_as_float(v.y);
-            sum.z += __uint_as_float(v.z); sum.w += __uint_as_float(v.w);
+        // (four slices under way at a time; loads past the last one are sent out of range)
+        const int slices = (int)gridDim.y;
+        floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+        for (int s2 = 0; s2 < slices; s2 += 4) {
+            u32x4 v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                v[q] = __builtin_amdgcn_raw_buffer_load_b128(rpart, s2 + q < slices ? off + (uint32_t)(s2 + q) * sstep : 0x80000000u, 0, kThrough);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const floatx4 u = {__uint_as_float(v[q].x), __uint_as_float(v[q].y), __uint_as_float(v[q].z), __uint_as_float(v[q].w)};
+                if (s2 + q == 0) sum = u;
+                else if (s2 + q < slices) { sum.x += u.x; sum.y += u.y; sum.z += u.z; sum.w += u.w; }
+            }
         }
         store_y(sum, m, n);
     }
