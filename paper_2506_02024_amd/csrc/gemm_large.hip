@@ -1705,11 +1705,12 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K, bool b
 // and what a split costs.  What is won over tiles of 256 tokens is the last round: (5888, 5888) at 1645 tokens is 161 tiles of 256 or 253 of 160, (6144,
 // 4096) at 2048 tokens 192 or 240 of 224.  The constants were fitted, as those above,
 // to 112 000 timings of every shape, height and split worth one on 150 layers of 1 to 300 Mi weights at 272 to
-// 8192 tokens, both storage orders.  The choice is 0.5 % (FP16 mode), 0.6 % (E4M3) and
-// 0.7 % (plain FP16) behind the fastest launch on average, 3.6 to 4.2 % at the 95th percentile, and as
+// 8192 tokens, both storage orders.  Long K loops of the smaller tiles take more than their share (tk2): E4M3 on 128 x 128 tiles 13 %
+// more at 100 K-tiles; (4096, 12208) at 589 tokens 73 us so, 64 in three slices of 256 x 256.  The choice is 0.5 % (FP16 mode) and
+// 0.6 % (E4M3, plain FP16) behind the fastest launch on average, 3.3 to 4.4 % at the 95th percentile, and as
 // much on layers that were left out of the fit; the model before it, which knew no heights, 3.3, 4.1 and 4.3 %, 15 to 20 %.
 // That model still serves plain FP16 weights at 65 to 256 tokens, with the weights' one pass over the memory bus as a floor.
-struct TallShape { int tm, tn, deep; double tk, tfix, tk160, tfix160; };       // as ShortShape
+struct TallShape { int tm, tn, deep; double tk, tfix, tk160, tfix160, tk2; };       // as ShortShape; tk2: per K-tile squared
 struct TallCost {
     int shapes;
     TallShape shape[7];
@@ -1720,17 +1721,17 @@ struct TallCost {
 };
 static const TallCost kTallCost[4] = {
     // plain FP16 of up to 256 tokens
-    {7, {{256, 256, 0, 1.353, 0, 1.353, 0}, {256, 128, 0, 1.053, 0.07, 0, 0}, {256, 128, 1, 0.863, 1.56, 0, 0}, {128, 256, 0, 1.098, 0, 0, 0},
-         {128, 256, 1, 0.900, 1.71, 0, 0}, {128, 128, 0, 0.848, 0, 0, 0}, {128, 128, 1, 0.585, 2.50, 0, 0}}, 1.58, 1e15, 3.18, 4.44e6, 1.0, 4.57e6},
+    {7, {{256, 256, 0, 1.353, 0, 1.353, 0, 0}, {256, 128, 0, 1.053, 0.07, 0, 0, 0}, {256, 128, 1, 0.863, 1.56, 0, 0, 0}, {128, 256, 0, 1.098, 0, 0, 0, 0},
+         {128, 256, 1, 0.900, 1.71, 0, 0, 0}, {128, 128, 0, 0.848, 0, 0, 0, 0}, {128, 128, 1, 0.585, 2.50, 0, 0, 0}}, 1.58, 1e15, 3.18, 4.44e6, 1.0, 4.57e6},
     // FP16 operands through registers
-    {4, {{256, 256, 0, 1.09, 8.73, 0.755, 6.53}, {256, 128, 0, 0.595, 5.43, 0.380, 4.79}, {128, 256, 0, 0.631, 6.15, 0, 0},
-         {128, 128, 0, 0.328, 3.33, 0, 0}}, 1.0, 27.2e6, 3.40, 7.16e6, 1.04, 0},
+    {4, {{256, 256, 0, 1.11, 8.54, 0.773, 6.36, 0}, {256, 128, 0, 0.573, 6.03, 0.351, 5.53, 0.309e-3}, {128, 256, 0, 0.634, 6.39, 0, 0, 0.103e-3},
+         {128, 128, 0, 0.285, 4.28, 0, 0, 0.466e-3}}, 1.0, 28.3e6, 2.98, 6.93e6, 1.05, 0},
     // E4M3
-    {5, {{256, 256, 0, 0.892, 9.10, 0.581, 6.73}, {256, 128, 1, 0.406, 6.42, 0, 0}, {128, 256, 1, 0.490, 5.23, 0, 0},
-         {128, 128, 0, 0.498, 4.23, 0, 0}, {128, 128, 1, 0.267, 4.50, 0, 0}}, 1.78, 30.2e6, 3.05, 6.63e6, 1.0, 0},
+    {5, {{256, 256, 0, 0.951, 9.83, 0.653, 7.57, 0}, {256, 128, 1, 0.445, 7.46, 0, 0, 0.502e-3}, {128, 256, 1, 0.598, 5.27, 0, 0, 0.026e-3},
+         {128, 128, 0, 0.515, 4.75, 0, 0, 1.88e-3}, {128, 128, 1, 0.247, 5.41, 0, 0, 1.19e-3}}, 1.83, 50.5e6, 2.14, 5.55e6, 1.0, 0},
     // plain FP16 above
-    {5, {{256, 256, 0, 1.01, 7.85, 0.691, 5.53}, {256, 128, 1, 0.487, 5.98, 0, 0}, {128, 256, 1, 0.571, 4.19, 0, 0},
-         {128, 128, 0, 0.528, 3.21, 0, 0}, {128, 128, 1, 0.316, 2.84, 0, 0}}, 1.67, 31.7e6, 3.37, 6.41e6, 1.0, 0},
+    {5, {{256, 256, 0, 1.04, 7.72, 0.716, 5.68, 0}, {256, 128, 1, 0.466, 7.05, 0, 0, 0.286e-3}, {128, 256, 1, 0.578, 4.71, 0, 0, 0.168e-3},
+         {128, 128, 0, 0.432, 4.88, 0, 0, 1.34e-3}, {128, 128, 1, 0.223, 4.69, 0, 0, 1.00e-3}}, 1.70, 34.3e6, 2.61, 6.13e6, 1.0, 0},
 };
 // A split whose partial sums outgrow the fixed scratch of nestedfp_gemm_static is taken where it is priced 4 % below what fits,
 // and by that entry point (bounded) nowhere: FP16 mode is 0.5 % behind the fastest launch so, 0.9 % if nothing beyond
@@ -1773,6 +1774,7 @@ static LargeConfig choose_tall(int cls, int64_t M, int64_t N, int64_t K, bool bo
                 const int64_t wgs = tiles * slices, rounds = (wgs + 255) / 256;
                 double time = (double)rounds * (tfix + per * tk);
                 if (rounds > 1 && e.tm == 128 && e.tn == 128 && !deep) time /= m.pair;
+                time += (double)rounds * per * per * e.tk2;
                 if (M <= 256 && cls == 0) {
                     double floor_t = (double)N * (double)K * 2.0 / m.floor_rate;
                     if (wgs < 256) floor_t *= std::sqrt(256.0 / (double)wgs);
