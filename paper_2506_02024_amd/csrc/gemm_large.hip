@@ -1706,7 +1706,7 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K, bool b
 // 4096) at 2048 tokens 192 or 240 of 224.  The constants were fitted, as those above,
 // to 112 000 timings of every shape, height and split worth one on 150 layers of 1 to 300 Mi weights at 272 to
 // 8192 tokens, both storage orders.  Long K loops of the smaller tiles take more than their share (tk2): E4M3 on 128 x 128 tiles 13 %
-// more at 100 K-tiles; (4096, 12208) at 589 tokens 73 us so, 64 in three slices of 256 x 256.  The choice is 0.5 % (FP16 mode) and
+// more at 100 K-tiles; (4064, 12208) at 589 tokens 73 us so, 60 in slices.  The choice is 0.5 % (FP16 mode) and
 // 0.6 % (E4M3, plain FP16) behind the fastest launch on average, 3.3 to 4.4 % at the 95th percentile, and as
 // much on layers that were left out of the fit; the model before it, which knew no heights, 3.3, 4.1 and 4.3 %, 15 to 20 %.
 // That model still serves plain FP16 weights at 65 to 256 tokens, with the weights' one pass over the memory bus as a floor.
