@@ -42,8 +42,7 @@ struct LargeParams {
     int ldp;
     int tiles_m, tiles_n;
     int ktiles_total, ktiles_per_split;
-    int vec_store;
-    int row_store;          // tiles leave through LDS by rows: 1 rows start on 16 bytes (N, ldy multiples of 8, Y 16-byte aligned), 2 anywhere; 0 straight from the MFMA layout
+    int rows_anywhere;      // output rows need not start on 16 bytes (N or ldy no multiple of 8, or Y not 16-byte aligned)
     int xcd_map;            // group the token tiles of a weight tile on one XCD (see tile_of_block)
     int xcd_group;          // token tiles per group of an XCD's part; 0: another order
 };
@@ -144,7 +143,7 @@ struct TileStore {
     // whole rows, 16 bytes per lane, every store instruction covering complete 128-byte lines.
     // The caller guarantees that no wave still reads the operand stages.
     static constexpr int OCH = TN * 2 / 16;            // 16-byte chunks per output row
-        static constexpr int NV = MB == 32 ? 4 : 1;
+    static constexpr int NV = MB == 32 ? 4 : 1;
     static __device__ __forceinline__ float scaled(float x, float s) { return kind_is_fp8(KIND) ? scale_f32(x, s) : x; }
     static __device__ __forceinline__ int acc_col(int lane, int v) { return MB == 32 ? 8 * v + 4 * (lane >> 5) : 4 * (lane >> 4); }
 
@@ -184,7 +183,7 @@ struct TileStore {
         constexpr int RPI = 64 / OCH;                  // rows per store instruction
         constexpr int ROWS = TM / WAVES;               // rows per wave
         const int chunk = lane % OCH;
-        if (p.row_store == 2) {
+        if (p.rows_anywhere) {
             store_rows_shifted(p, m0, n0, lane, wave, lds);
             return;
         }
@@ -249,40 +248,25 @@ struct TileStore {
             if (q < count) dst[q] = (uint16_t)(v[q >> 1] >> (16 * (q & 1)));
     }
 
+    // A slice's sums of a K split, straight from the MFMA layout: 16 bytes per lane.  (Outputs have the one way through LDS only: a
+    // second one straight from here, though never taken, cost a quarter of the tiled kernels' code and the row-major 256 x 256 kernel
+    // of FP16 mode four more spilled registers; 2048 tokens of a Llama-3 8B layer 844 us with it, 838 without.)
     template <int F = FMB>
-    static __device__ __forceinline__ void epilogue(const LargeParams &p, AccT (&acc)[FNB][FMB], int m0, int n0,
-                                                    int row0, int wn, int lane, int split) {
+    static __device__ __forceinline__ void store_partials(const LargeParams &p, AccT (&acc)[FNB][FMB], int m0, int n0,
+                                                          int row0, int wn, int lane, int split) {
         const int r = lane % MB;
 #pragma unroll
         for (int j = 0; j < F; ++j) {
             const int m = m0 + row0 + MB * j + r;
             if (m >= p.M) continue;
-            float s = 1.0f;
-            if (kind_is_fp8(KIND) && gridDim.y == 1) s = p.scales[m] * p.w_scale;
 #pragma unroll
             for (int i = 0; i < FNB; ++i)
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
                     const int n = n0 + wn * WTN + MB * i + acc_col(lane, v);
-                    if (n >= p.N) continue;
-                    const float x[4] = {acc[i][j][4 * v], acc[i][j][4 * v + 1], acc[i][j][4 * v + 2], acc[i][j][4 * v + 3]};
-                    if (gridDim.y > 1) {
-                        *reinterpret_cast<floatx4 *>(p.partials + ((int64_t)split * p.M + m) * p.ldp + n) = floatx4{x[0], x[1], x[2], x[3]};
-                    } else {
-                        uint16_t *dst = p.Y + (int64_t)m * p.ldy + n;
-                        if (p.vec_store) {
-                            u32x2 o;
-                            o.x = float2_to_half2_bits(scaled(x[0], s), scaled(x[1], s));
-                            o.y = float2_to_half2_bits(scaled(x[2], s), scaled(x[3], s));
-                            *reinterpret_cast<u32x2 *>(dst) = o;
-                        } else {
-                            for (int e = 0; e < 4 && n + e < p.N; ++e) {
-                                union { _Float16 f; uint16_t u; } cv;
-                                cv.f = (_Float16)scaled(x[e], s);
-                                dst[e] = cv.u;
-                            }
-                        }
-                    }
+                    if (n < p.N)
+                        *reinterpret_cast<floatx4 *>(p.partials + ((int64_t)split * p.M + m) * p.ldp + n) =
+                            floatx4{acc[i][j][4 * v], acc[i][j][4 * v + 1], acc[i][j][4 * v + 2], acc[i][j][4 * v + 3]};
                 }
         }
     }
@@ -605,7 +589,7 @@ struct LargeKernel {
         // the loads of the K-tiles past the end are still in flight: they must have landed
         // before the LDS is reused for the output tile or handed back
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (p.row_store && gridDim.y == 1) {
+        if (gridDim.y == 1) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the look-ahead fragment reads
             __syncthreads();
             if (UNEVEN && wave < DW) Store::template to_lds<blocks<true>()>(p, acc, m0, row0, wn, lane, lds);
@@ -613,9 +597,9 @@ struct LargeKernel {
             __syncthreads();
             Store::store_rows(p, m0, n0, lane, wave, lds);
         } else if (UNEVEN && wave < DW) {
-            Store::template epilogue<blocks<true>()>(p, acc, m0, n0, row0, wn, lane, split);
+            Store::template store_partials<blocks<true>()>(p, acc, m0, n0, row0, wn, lane, split);
         } else {
-            Store::template epilogue<FMB>(p, acc, m0, n0, row0, wn, lane, split);
+            Store::template store_partials<FMB>(p, acc, m0, n0, row0, wn, lane, split);
         }
     }
 };
@@ -964,12 +948,12 @@ struct BypassKernel {
         // (keeps the epilogue's address arithmetic behind the loop, where registers are free)
         int lane_out = lane;
         asm volatile("" : "+v"(lane_out));
-        if (p.row_store && gridDim.y == 1) {
+        if (gridDim.y == 1) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the look-ahead fragment reads
             __syncthreads();
             Store::epilogue_lds(p, acc, m0, n0, 0, wave, lane_out, wave, lds);
         } else {
-            Store::epilogue(p, acc, m0, n0, 0, wave, lane_out, split);
+            Store::store_partials(p, acc, m0, n0, 0, wave, lane_out, split);
         }
     }
 };
@@ -1252,12 +1236,12 @@ struct RowsKernel {
         // (keeps the epilogue's address arithmetic behind the loop, where registers are free)
         int lane_out = lane;
         asm volatile("" : "+v"(lane_out));
-        if (p.row_store && gridDim.y == 1) {
+        if (gridDim.y == 1) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the look-ahead fragment reads
             __syncthreads();
             Store::epilogue_lds(p, acc, m0, n0, 0, wave, lane_out, wave, lds);
         } else {
-            Store::epilogue(p, acc, m0, n0, 0, wave, lane_out, split);
+            Store::store_partials(p, acc, m0, n0, 0, wave, lane_out, split);
         }
     }
 };
@@ -1495,12 +1479,12 @@ struct E4m3BypassKernel {
         // token loads of K-tiles past the end are still in flight: they must have landed before the
         // LDS is reused for the output tile or handed back
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (p.row_store && gridDim.y == 1) {
+        if (gridDim.y == 1) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the look-ahead fragment reads
             __syncthreads();
             Store::epilogue_lds(p, acc, m0, n0, 0, wave, lane, wave, lds);
         } else {
-            Store::epilogue(p, acc, m0, n0, 0, wave, lane, split);
+            Store::store_partials(p, acc, m0, n0, 0, wave, lane, split);
         }
     }
 };
@@ -2067,9 +2051,7 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream) {
         const int groups = (p.tiles_m + 5) / 6;
         p.xcd_group = (p.tiles_m + groups - 1) / groups;
     }
-    p.vec_store = ((a.N & 3) == 0 && (a.ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 7) == 0) ? 1 : 0;
-    p.row_store = ((a.N & 7) == 0 && (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) ? 1 : 2;
-    if (tuning().large_epilogue == 0) p.row_store = 0;
+    p.rows_anywhere = ((a.N & 7) == 0 && (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0) ? 0 : 1;
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)c.split);
     switch (kind) {
         case kPlainF16: launch_large_k<kPlainF16>(p, c, grid, stream); break;

@@ -12,7 +12,7 @@
 namespace nfp {
 
 Tuning &tuning() {
-    static Tuning t = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, 1, -1, -1, -1, -1, -1, -1, -1};
+    static Tuning t = {-1, -1, -1, -1, -1, -1, -1, -1, -1, 1, -1, -1, -1, -1, -1, -1, -1};
     return t;
 }
 
@@ -690,7 +690,7 @@ int nestedfp_probe_mfma(const void *operands, int fp8, int iters, uint32_t *sink
 }
 
 static const char *const kKnobs[] = {"small_max_m", "small_split", "small_spw", "small_tiles", "small_interleave",
-                                     "large_split", "large_bm", "large_bn", "large_epilogue", "small_fuse_quant", "quant_hw", "large_xcd_map",
+                                     "large_split", "large_bm", "large_bn", "small_fuse_quant", "quant_hw", "large_xcd_map",
                                      "fused_reduce", "large_deep", "large_height", "large_rows", "tuned_table", "quant_onepass", nullptr};
 
 const char *nestedfp_tune_name(int index) {
@@ -710,7 +710,6 @@ int nestedfp_tune(const char *knob, int64_t value) {
     else if (!strcmp(knob, "large_split")) t.large_split = value;
     else if (!strcmp(knob, "large_bm")) t.large_bm = value;
     else if (!strcmp(knob, "large_bn")) t.large_bn = value;
-    else if (!strcmp(knob, "large_epilogue")) t.large_epilogue = value;
     else if (!strcmp(knob, "small_fuse_quant")) t.small_fuse_quant = value;
     else if (!strcmp(knob, "quant_hw")) t.quant_hw = value < 0 ? 1 : value;
     else if (!strcmp(knob, "large_xcd_map")) t.large_xcd_map = value;

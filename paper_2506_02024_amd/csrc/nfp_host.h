@@ -78,7 +78,6 @@ struct Tuning {
     int64_t large_split;     // grid-level split-K of the tiled kernel
     int64_t large_bm;        // tokens per tile of the tiled kernel (64, 128 or 256)
     int64_t large_bn;        // weight rows per tile (128 or 256; unset: same as large_bm)
-    int64_t large_epilogue;  // 0: store results straight from the MFMA layout instead of row-wise through LDS
     int64_t small_fuse_quant;  // 1 / 0: quantise activations inside the streaming kernel wherever it can / nowhere
     int64_t quant_hw;        // 1: hardware E4M3 convert, 0: integer rounding
     int64_t large_xcd_map;   // 0: tiles in launch order instead of grouped by XCD (tiled kernels)
