@@ -1591,11 +1591,19 @@ static int knob_height(int cls, int tm, int tn) {
 // Launch shapes that were timed faster than the cost model's choice, for the layer shapes of the
 // models the paper evaluates (Sec. 5.1).  An entry tuned at M tokens serves the batches of more than
 // 3 M / 4 (M / 2 up to 64 tokens) and at most M tokens that give the same number of token tiles.
+// An entry holds no height of the token tiles: up to 256 tokens that is token_tile's, with the tile pinned for a timing as
+// in the launch it stands for; above, the model would choose it, and the entry would be launched at another one than it was timed at.
 struct TunedTile { int cls, N, K, M, tm, tn, split, deep; };
-static const TunedTile kTunedTiles[] = {
+static constexpr TunedTile kTunedTiles[] = {
 #include "tuned_tiles.inc"
     {-1, 0, 0, 0, 0, 0, 0, 0},
 };
+static constexpr bool tuned_up_to(int tokens) {
+    for (const TunedTile &e : kTunedTiles)
+        if (e.M > tokens) return false;
+    return true;
+}
+static_assert(tuned_up_to(256), "timed launch shapes of more than 256 tokens need their height");
 
 static bool tuned_large(int cls, int64_t M, int64_t N, int64_t K, LargeConfig &c) {
     for (const TunedTile &e : kTunedTiles) {

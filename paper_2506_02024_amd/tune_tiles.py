@@ -6,13 +6,14 @@ csrc/tuned_small.inc for the streaming kernel).
 
 The tiled kernels pick tile shape, K split and pipeline depth from a small cost model.  The model is
 within a few per cent of the best choice on average, but off by 10-30 % at some points of the
-ridge between the memory-bound and the compute-bound regime (M = 128 ... 512).  This script times
+ridge between the memory-bound and the compute-bound regime.  This script times
 every legal choice through the tuning knobs -- on the layer shapes of the models the paper evaluates
-(Sec. 5.1: Llama 3.1 8B / 70B, Mistral Nemo, Phi-4, Mistral Small), at M = 32 ... 8192, for the three
+(Sec. 5.1: Llama 3.1 8B / 70B, Mistral Nemo, Phi-4, Mistral Small), at M = 32 ... 256, for the three
 classes of weights (FP16 row-major, FP16 through registers = NestedFP planes, E4M3) -- and records a
 choice only where it beats the model's by more than the margin.  At M = 32 and 64 the layers that
 the library routes to its 64-token tiles are timed over the K split alone (on the others the knobs
-change nothing and nothing is recorded).  Other shapes keep the model.
+change nothing and nothing is recorded).  Other shapes keep the model, and so do all larger batches: there the
+height of the token tiles is chosen too, which an entry does not hold (fit_costs.py times and fits that choice).
 The streaming kernel (decode batches) is timed at 1, 4 and 16 tokens over its K-steps per wave, grid-level
 K split and tiles per workgroup, as graph replays over the rotated copies, the planes in both storage orders
 (an entry serves both, and batches of up to 16 tokens).  A shape is recorded if it beats the cost model's
@@ -34,8 +35,7 @@ MODEL_SHAPES = {
     "phi-4-14b": [(7680, 5120), (5120, 5120), (35840, 5120), (5120, 17920)],
     "mistral-small-24b": [(6144, 5120), (5120, 4096), (65536, 5120), (5120, 32768)],
 }
-M_POINTS = (32, 64, 96, 128, 192, 256, 384, 512, 768, 1024, 1536, 2048, 4096, 8192)  # 32, 64: the 64-token tiles, where only the K split is open;
-# 4096, 8192: no K split (the chip is full)
+M_POINTS = (32, 64, 96, 128, 192, 256)     # 32, 64: the 64-token tiles, where only the K split is open
 SMALL_TOKENS = (1, 4, 16)       # batch sizes of the streaming section
 TILES = ((256, 256), (256, 128), (128, 256), (128, 128))
 SPLITS = (1, 2, 3, 4, 6, 8)
@@ -55,6 +55,8 @@ def main():
                     help="batch sizes of the tiled section instead of the built-in list (to re-time a part of the table)")
     ap.add_argument("--log", default=None, help="write every timing as JSON lines")
     args = ap.parse_args()
+    if max(args.m_points or M_POINTS) > 256:
+        ap.error("an entry holds no height of the token tiles, which is open above 256 tokens")
 
     import torch
     from . import binding as nfp, workloads
@@ -186,8 +188,7 @@ def main():
         for M in (args.m_points or M_POINTS):
             X = workloads.act_device(M, K, seed=2)
             Y = torch.empty((M, N), dtype=torch.float16, device=dev)
-            # room for any split that is tried (up to 8 below 4096 tokens, the built-in choice above)
-            need = (8 if M < 4096 else 0) * M * N * 4 + M * K + 4 * M
+            need = 8 * M * N * 4 + M * K + 4 * M        # room for any split that is tried
             for table in (-1, 0):                       # with and without the table that is compiled in now
                 nfp.tune("tuned_table", table)
                 need = max(need, max(nfp.gemm_workspace_size(M, N, K, m) for m in (0, 1)))
@@ -206,7 +207,7 @@ def main():
                     kt = (K if cls == 2 else 2 * K) // 128
                     # (the 64-token tiles also compete at 128 and 256 tokens, as two and four token tiles)
                     for bm, bn in (((64, 128),) if M <= 64 else (TILES + ((64, 128),) if M <= 256 else TILES)):
-                        for sp in (SPLITS if M < 4096 else (1,)):
+                        for sp in SPLITS:
                             if sp > 1 and sp > kt // 4:
                                 continue
                             for deep in ((0,) if (bm, bn) == (256, 256) or bm == 64 or (cls == 1 and bm != 128) else (0, 1)):
@@ -249,7 +250,8 @@ def main():
         return 0
     with open(args.out, "w") as f:
         f.write("// Launch shapes of the tiled GEMM kernels that beat the cost model's choice by more than %.0f %% when\n" % (100 * args.margin))
-        f.write("// timed on an MI355X; written by paper_2506_02024_amd/tune_tiles.py, which says how.\n")
+        f.write("// timed on an MI355X; written by paper_2506_02024_amd/tune_tiles.py, which says how.  Up to 256 tokens: above, the\n")
+        f.write("// height of the token tiles is open as well, and an entry does not hold it.\n")
         f.write("// weight class (0 FP16 row-major, 1 FP16 through registers, 2 E4M3), N, K, tokens tuned at,\n")
         f.write("// tile tokens, tile weight rows, K split, deeper pipeline   // microseconds: tuned, model's choice\n")
         for r in sorted(rows):

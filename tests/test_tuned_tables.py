@@ -2,6 +2,10 @@
 kernels exist for (they are generated files: paper_2506_02024_amd/tune_tiles.py)."""
 import os
 import re
+import subprocess
+import sys
+
+from paper_2506_02024_amd.tune_tiles import M_POINTS
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_02024_amd", "csrc")
 ROW = re.compile(r"^\{([-0-9, ]+)\},")
@@ -21,7 +25,7 @@ def test_tiled_kernel_table_holds_legal_launch_shapes():
     for cls, N, K, M, tm, tn, split, deep in rows("tuned_tiles.inc"):
         assert cls in (0, 1, 2)
         assert N > 0 and K > 0 and K % 16 == 0 and N % 4 == 0   # (rows of partial sums without padding)
-        assert M in (32, 64, 96, 128, 192, 256, 384, 512, 768, 1024, 1536, 2048, 4096, 8192)
+        assert M in M_POINTS
         assert (tm, tn) in ((64, 128), (128, 128), (128, 256), (256, 128), (256, 256))
         assert split in (1, 2, 3, 4, 6, 8)
         if tm == 64:
@@ -34,6 +38,14 @@ def test_tiled_kernel_table_holds_legal_launch_shapes():
         assert split == 1 or split <= kt // 4
         assert (cls, N, K, M) not in seen                 # one entry per problem
         seen.add((cls, N, K, M))
+
+
+def test_no_entry_is_taken_where_the_height_of_the_tiles_is_open():
+    # above 256 tokens a pinned tile is timed at the height that the model picks, and an entry holds none
+    assert max(M_POINTS) <= 256
+    args = [sys.executable, "-m", "paper_2506_02024_amd.tune_tiles", "--skip-small", "--skip-tiled", "--m-points", "256", "384"]
+    done = subprocess.run(args, cwd=os.path.dirname(os.path.dirname(CSRC)), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert done.returncode == 2 and "height" in done.stdout
 
 
 def test_streaming_kernel_table_holds_legal_launch_shapes():
