@@ -1811,6 +1811,7 @@ static size_t partial_bytes(const LargeConfig &c, int64_t M, int64_t N) {
 }
 size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K) { return partial_bytes(choose_large(kind, M, N, K, false), M, N); }
 size_t large_gemm_bounded_bytes(int kind, int64_t M, int64_t N, int64_t K) { return partial_bytes(choose_large(kind, M, N, K, true), M, N); }
+int large_gemm_height(int kind, int64_t M, int64_t N, int64_t K) { return choose_large(kind, M, N, K, false).height; }
 
 template <int KIND, int TM, int TN, int WAVES_M, int WAVES_N, int NST = 2, int NSTW = NST>
 static void launch_large_t(const LargeParams &p, dim3 grid, hipStream_t stream) {

@@ -150,6 +150,7 @@ bool rows_by_pairs(int tm, int64_t M, int64_t N, int64_t K, int64_t row_bytes, i
 bool rows_through_lds(int tm, int tn, int64_t M, int64_t K, int64_t row_bytes, int split);           // the other tiles
 size_t large_gemm_partial_bytes(int kind, int64_t M, int64_t N, int64_t K);
 size_t large_gemm_bounded_bytes(int kind, int64_t M, int64_t N, int64_t K);      // with GemmArgs::bounded
+int large_gemm_height(int kind, int64_t M, int64_t N, int64_t K);                // tokens per tile
 int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream);
 
 // Row stride of the split-K partial sums [slice][token][ld]: whole groups of four columns, so that they are

@@ -1,6 +1,7 @@
 """Shared helpers for the GPU parity tests (comparison rule and host<->device glue)."""
 import numpy as np
 
+NESTED, NESTED_ROWS = 1, 4       # weight kinds of the tiled kernels: planes in packed blocks, row-major ones
 REL_TOL = 1e-2   # the build's stated GEMM tolerance: relative, fp16 output, fp32 accumulation
 
 
@@ -156,3 +157,12 @@ def quantises_itself(nfp, M, N, K):
     f = nfp.lib()._ZN3nfp22small_gemm_fuses_quantElll      # nfp::small_gemm_fuses_quant
     f.restype, f.argtypes = ctypes.c_bool, 3 * [ctypes.c_int64]
     return f(M, N, K)
+
+
+def tile_height(nfp, kind, M, N, K):
+    """Tokens per tile that the tiled kernels launch with under the present knobs."""
+    import ctypes
+
+    f = nfp.lib()._ZN3nfp17large_gemm_heightEilll            # nfp::large_gemm_height
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] + 3 * [ctypes.c_int64]
+    return f(kind, M, N, K)

@@ -5,7 +5,7 @@ import torch
 
 import oracle
 from paper_2506_02024_amd import workloads
-from helpers import (assert_gemm_close, assert_plane_equal, bits, decompose_ref, fetched_by_pairs, quantises_itself, streaming_kernel_takes,
+from helpers import (NESTED, assert_gemm_close, assert_plane_equal, bits, decompose_ref, fetched_by_pairs, quantises_itself, streaming_kernel_takes, tile_height,
                      structured_sample, to_dev)
 
 pytestmark = pytest.mark.gpu
@@ -376,13 +376,14 @@ def test_xcd_grouped_tile_order_changes_nothing(nfp, M, N, K, bm, bn):
     X = workloads.act_host(M, K, seed=431)
     Xd, Wd = to_dev(X), to_dev(W)
     up, lo = nfp.decompose(Wd, packed=(bm == 256))
-    pins = {"large_bm": bm, "large_bn": bn, "large_split": 1}
+    pins = {"large_bm": bm, "large_bn": bn, "large_split": 1, "large_height": 256}
     outs = {}
     for order in (0, -1):
         for k, v in pins.items():
             nfp.tune(k, v)
         nfp.tune("large_xcd_map", order)
         try:
+            assert tile_height(nfp, NESTED, M, N, K) == bm
             outs[order] = (bits(nfp.gemm(Xd, up, lo, nfp.MODE_FP16)), bits(nfp.plain_gemm_fp16(Xd, Wd)),
                            bits(nfp.gemm(Xd, up, None, nfp.MODE_FP8)))
         finally:

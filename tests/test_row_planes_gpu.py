@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2506_02024_amd import workloads
-from helpers import bits, to_dev
+from helpers import NESTED_ROWS, bits, tile_height, to_dev
 from test_gemm_gpu import run_both_modes
 
 pytestmark = pytest.mark.gpu
@@ -38,10 +38,11 @@ def through_lds(nfp, bm, bn, M, K, split):
 def test_row_planes_through_lds(nfp, M, N, K, bm, bn, split, lds):
     # against the oracle, and bit for bit against packed planes, which no kernel of this kind reads
     assert through_lds(nfp, bm, bn, M, K, split) == lds
-    knobs = {"small_max_m": 0, "large_bm": bm, "large_bn": bn, "large_split": split}
+    knobs = {"small_max_m": 0, "large_bm": bm, "large_bn": bn, "large_split": split, "large_height": 256 if M > 256 else -1}
     try:
         for k, v in knobs.items():
             nfp.tune(k, v)
+        assert M <= 256 or tile_height(nfp, NESTED_ROWS, M, N, K) == bm
         run_both_modes(nfp, workloads.act_host(M, K, seed=N), workloads.weight_host(N, K, seed=M),
                        "%d x %d, M=%d %s" % (N, K, M, knobs), check_plain=False)
     finally:
@@ -49,17 +50,19 @@ def test_row_planes_through_lds(nfp, M, N, K, bm, bn, split, lds):
             nfp.tune(k, -1)
 
 
-@pytest.mark.parametrize("M,N,K,bn,split", [
+@pytest.mark.parametrize("M,N,K,bn,split,height", [
     # token tiles of 256 cut down to 160, 192 and 224 tokens: first and last batch of each, several tiles, K-tails
-    (97, 260, 64 * 3 + 16, 256, 1), (160, 140, 64 * 5, 128, 1), (161, 140, 64 * 8, 128, 2), (192, 270, 64 * 4, 256, 1),
-    (193, 130, 64 * 21 + 32, 128, 1), (224, 520, 64 * 12, 256, 2), (225, 264, 64 * 4, 256, 1),
-    (257, 264, 64 * 6, 256, 1), (385, 264, 64 * 9 + 48, 256, 1), (449, 136, 64 * 4, 128, 1), (620, 264, 64 * 22, 128, 2), (777, 300, 64 * 2, 256, 1),
+    (97, 260, 64 * 3 + 16, 256, 1, 160), (160, 140, 64 * 5, 128, 1, 160), (161, 140, 64 * 8, 128, 2, 192), (192, 270, 64 * 4, 256, 1, 192),
+    (193, 130, 64 * 21 + 32, 128, 1, 224), (224, 520, 64 * 12, 256, 2, 224), (225, 264, 64 * 4, 256, 1, 256),
+    (257, 264, 64 * 6, 256, 1, 160), (385, 264, 64 * 9 + 48, 256, 1, 224), (449, 136, 64 * 4, 128, 1, 256), (620, 264, 64 * 22, 128, 2, 224), (777, 300, 64 * 2, 256, 1, 224),
 ])
-def test_token_tiles_cut_down_to_the_batch(nfp, M, N, K, bn, split):
-    knobs = {"small_max_m": 0, "large_bm": 256, "large_bn": bn, "large_split": split}
+def test_token_tiles_cut_down_to_the_batch(nfp, M, N, K, bn, split, height):
+    # (up to 256 tokens by themselves, above pinned: there the height is the one that is priced lowest)
+    knobs = {"small_max_m": 0, "large_bm": 256, "large_bn": bn, "large_split": split, "large_height": height if M > 256 else -1}
     try:
         for k, v in knobs.items():
             nfp.tune(k, v)
+        assert tile_height(nfp, NESTED_ROWS, M, N, K) == height
         X, W = workloads.act_host(M, K, seed=N), workloads.weight_host(N, K, seed=M)
         run_both_modes(nfp, X, W, "%d x %d, M=%d %s" % (N, K, M, knobs), check_plain=False)
         # the same tiles without the merge

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 from paper_2506_02024_amd import workloads
-from helpers import assert_gemm_close, bits, to_dev
+from helpers import NESTED_ROWS, assert_gemm_close, bits, tile_height, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -35,10 +35,11 @@ def test_rows_that_start_anywhere(nfp, M, N, bm, bn, mode):
         ref = oracle.gemm_fp8(Xq, s, up)
     else:
         ref = oracle.gemm_fp16(X, W)
-    knobs = {"small_max_m": 0, "large_bm": bm, "large_bn": bn, "large_split": 1}
+    knobs = {"small_max_m": 0, "large_bm": bm, "large_bn": bn, "large_split": 1, "large_height": 256 if M > 256 else -1}
     try:
         for k, v in knobs.items():
             nfp.tune(k, v)
+        assert M <= 256 or tile_height(nfp, NESTED_ROWS, M, N, K) == bm
         first = None
         for offset in (0, 1, 2, 4, 7):
             for ld in (N, (N + 7) // 8 * 8, N + 3):
