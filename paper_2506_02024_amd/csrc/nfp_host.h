@@ -158,8 +158,9 @@ int launch_large_gemm(int kind, const GemmArgs &a, hipStream_t stream);
 // each: (2903, 9168) in FP16 mode at 40 tokens 29.6 us against 21).
 constexpr int64_t partial_ld(int64_t N) { return (N + 3) & ~(int64_t)3; }
 
-// Workspace layout: [arrival counters : kCounterBytes][Xq : M*K bytes][scales : M floats][split-K partials],
-// each part rounded up to 256 bytes; 0 if nothing but the counters would be in it.
+// Workspace layout: [arrival counters : kCounterBytes][Xq : M rows of K bytes, or of xq_row(K) where there is room][scales :
+// M floats][split-K partials], each part rounded up to 256 bytes; 0 if nothing but the counters would be in it.  What follows
+// is the least, with dense rows.
 constexpr size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 constexpr size_t workspace_need(size_t partial_bytes, int64_t M, int64_t K, bool quantize) {
     const size_t b = round256(partial_bytes) +

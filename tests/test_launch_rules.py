@@ -112,18 +112,38 @@ def test_which_wide_layers_are_quantised_in_the_streaming_kernel(L, M, N, K, fus
 
 
 def test_room_for_padded_codes_stays_inside_the_fixed_scratch(L):
-    # the query asks for rows of codes on 128-byte lines, but never takes a problem past the scratch of the entry point without a workspace
+    # The query of FP8 mode asks for rows of codes on 128-byte lines, decode batches included, but never takes a problem past the
+    # scratch of the entry point without a workspace that would fit it with dense rows.
     import random
 
     rng = random.Random(5)
-    size = L.nestedfp_gemm_workspace_size
+    size, scratch = L.nestedfp_gemm_workspace_size, 32 << 20
     size.restype, size.argtypes = ctypes.c_size_t, 3 * [ctypes.c_int64] + [ctypes.c_int]
-    for _ in range(3000):
+    route = L._ZN3nfp11route_smallEillll                        # nfp::route_small
+    route.restype, route.argtypes = ctypes.c_bool, [ctypes.c_int] + 4 * [ctypes.c_int64]
+
+    def round256(n):
+        return (n + 255) // 256 * 256
+
+    padded = held_back = decode = 0
+    for _ in range(6000):
         M, K = int(9000 ** rng.random()), 16 * rng.randrange(1, 2500)
-        N = rng.randrange(1, 3000)
-        dense = 16384 + (M * K + 255) // 256 * 256 + (4 * M + 255) // 256 * 256
-        pad = (M * ((K + 127) // 128 * 128) + 255) // 256 * 256 - (M * K + 255) // 256 * 256
-        most = max(partial_bytes(L, kind, M, N, K) if M > 64 else 0 for kind in (2, 5))
-        need = dense + (most + 255) // 256 * 256
-        if M > 64:
-            assert size(M, N, K, 1) == (need + pad if need + pad <= 32 << 20 or need > 32 << 20 else need)
+        N = int(40000 ** rng.random())
+        if rng.random() < 0.2:                                  # near the limit
+            M, N = max(1, (scratch - rng.randrange(1 << 16)) // (K + 4)), rng.randrange(1, 64)
+        sums = max(partial_bytes(L, kind, M, N, K, "24small_gemm_partial_bytes" if route(kind, M, N, K, K) else "24large_gemm_partial_bytes")
+                   for kind in (2, 5))
+        rest = 16384 + round256(4 * M) + round256(sums)
+        dense, lines = rest + round256(M * K), rest + round256(M * ((K + 127) // 128 * 128))
+        got = size(M, N, K, 1)
+        assert got >= dense
+        if dense <= scratch:
+            assert got <= scratch
+        if lines <= scratch or dense > scratch:
+            assert got >= lines
+            padded += lines > dense
+            decode += lines > dense and M <= 64
+        else:
+            held_back += 1
+        assert got in (dense, lines)                            # and for no other room
+    assert padded > 1000 and decode > 500 and held_back > 5, (padded, decode, held_back)
