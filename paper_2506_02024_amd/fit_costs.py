@@ -1,20 +1,25 @@
 """Times the launch shapes of the kernels over many layers and fits the constants that the library compiles in:
 kSmallCost (csrc/gemm_small.hip), the lines between the streaming kernel and the 64-token tiles at 17 ... 64 tokens
-(kLine in csrc/nestedfp_api.hip), kShortCost (65 ... 256 tokens, csrc/gemm_large.hip); and says how far the
-choices that the library makes are behind the fastest launch, rows_through_lds among them.
+(kLine in csrc/nestedfp_api.hip), kShortCost (65 ... 256 tokens, csrc/gemm_large.hip), kTallCost (more than 256 tokens, there
+too); and says how far the choices that the library makes are behind the fastest launch, rows_through_lds among them.
 
     python -m paper_2506_02024_amd.fit_costs time candidates.jsonl routes.jsonl     # on the GPU, about 7 minutes
     python -m paper_2506_02024_amd.fit_costs fit candidates.jsonl routes.jsonl      # prints the constants
     python -m paper_2506_02024_amd.fit_costs time-tiles tiles.jsonl [--tokens ...]  # on the GPU, about 10 minutes
     python -m paper_2506_02024_amd.fit_costs fit-tiles tiles.jsonl
+    python -m paper_2506_02024_amd.fit_costs time-tall tall.jsonl [--tokens ...]    # on the GPU, about 10 s a layer
+    python -m paper_2506_02024_amd.fit_costs fit-tall tall.jsonl
 
 `time` writes one line per timing: [N, K, tokens, storage, [K-steps per wave, K split, tiles per workgroup],
 us] and [N, K, tokens, storage, us of the tiled kernel, us of the streaming kernel].  Weights are cold (copies
 taken in turn) and the calls are replayed as one graph.  storage: 16p / 16r the planes in FP16 mode, packed and
 row-major, 8p / 8r the upper plane in FP8 mode on quantised activations, pr plain row-major FP16.  `time-tiles`: [N, K,
 tokens, storage, launch, us], launch = null for the built-in choice or [tile tokens, tile weight rows, K split, deeper
-pipeline, way of row-major planes].  The layers taken in turn hold 700 MB: what the 256 MB memory-side cache keeps
-from one pass to the next makes non-temporal loads look slow and the others fast.
+pipeline, way of row-major planes]; above 256 tokens, where it serves to check the ways of row-major planes, tiles of 256
+are timed at their full height.  The layers taken in turn hold 700 MB: what the 256 MB memory-side cache keeps
+from one pass to the next makes non-temporal loads look slow and the others fast.  `time-tall`: launch = null or [tile tokens, tile
+weight rows, K split, deeper pipeline, height of the token tiles], those priced at less than 1.6 times the cheapest; FP8 mode with its
+quantisation, whose own time is taken off, so that rows of codes start on lines as they do in a call.
 `fit` mirrors price_small() and choose_tile64() of the library.  The constants minimise the time lost to the
 fastest candidate by a soft choice of the cheapest one, plus the error of the prices; the lines are searched on
 a grid for the time lost to the faster kernel, prices as the library has them compiled in.
@@ -203,6 +208,8 @@ def time_tiles(path, shapes, tokens):
                         pins = {} if launch is None else dict(zip(("large_bm", "large_bn", "large_split", "large_deep", "large_rows"), launch))
                         if not fp8:
                             pins.pop("large_deep", None)
+                        if pins and M > 256:
+                            pins["large_height"] = 256     # (up to 256 tokens it follows the batch)
                         for k, v in pins.items():
                             nfp.tune(k, v)
                         try:
@@ -216,6 +223,130 @@ def time_tiles(path, shapes, tokens):
                     timed(None)                                # the built-in choice
                     for launch in tile_launches(N, K, M, storage):
                         timed(launch)
+                del layers
+                torch.cuda.empty_cache()
+            print("N=%d K=%d  %.0f s" % (N, K, time.time() - t0), flush=True)
+
+
+TALL_TOKENS = (272, 300, 384, 449, 512, 600, 777, 1000, 1200, 1536, 1790, 2048, 2700, 3200, 4096, 5000, 8192)
+# kTallCost by weight class (1 FP16 operands through registers, 2 E4M3, 3 plain row-major FP16).  Shapes: tile tokens x weight rows, deeper
+# pipeline, microseconds per K-tile and per workgroup at the full height and at 160 tokens, per K-tile squared
+TALL = {
+    1: dict(shapes=((256, 256, 0, 1.11, 8.54, 0.773, 6.36, 0), (256, 128, 0, 0.573, 6.03, 0.351, 5.53, 0.309e-3), (128, 256, 0, 0.634, 6.39, 0, 0, 0.103e-3),
+                    (128, 128, 0, 0.285, 4.28, 0, 0, 0.466e-3)), pair=1.0, l2_rate=28.3, split=2.98, split_rate=6.93, odd=1.05),
+    2: dict(shapes=((256, 256, 0, 0.951, 9.83, 0.653, 7.57, 0), (256, 128, 1, 0.445, 7.46, 0, 0, 0.502e-3), (128, 256, 1, 0.598, 5.27, 0, 0, 0.026e-3),
+                    (128, 128, 0, 0.515, 4.75, 0, 0, 1.88e-3), (128, 128, 1, 0.247, 5.41, 0, 0, 1.19e-3)), pair=1.83, l2_rate=50.5, split=2.14, split_rate=5.55, odd=1.0),
+    3: dict(shapes=((256, 256, 0, 1.04, 7.72, 0.716, 5.68, 0), (256, 128, 1, 0.466, 7.05, 0, 0, 0.286e-3), (128, 256, 1, 0.578, 4.71, 0, 0, 0.168e-3),
+                    (128, 128, 0, 0.432, 4.88, 0, 0, 1.34e-3), (128, 128, 1, 0.223, 4.69, 0, 0, 1.00e-3)), pair=1.70, l2_rate=34.3, split=2.61, split_rate=6.13, odd=1.0),
+}
+
+
+def tall_class(storage):
+    return 3 if storage == "pr" else (2 if storage[0] == "8" else 1)
+
+
+def heights_of(cls, tm, tn):
+    return (160, 192, 224, 256) if tm == 256 and (cls == 1 or tn == 256) else (tm,)
+
+
+def tall_launches(cls, N, K, M):
+    """Every launch that choose_tall() prices, with what the price is made of."""
+    kt = -(-K // (128 if cls == 2 else 64))
+    for shape, (tm, tn, deep) in enumerate(e[:3] for e in TALL[cls]["shapes"]):
+        for height in heights_of(cls, tm, tn):
+            for split in SPLITS:
+                if split > 1 and split > kt // 4:
+                    break
+                per = -(-kt // split)
+                slices = -(-kt // per)
+                yield (tm, tn, split, deep, height), dict(
+                    N=N, K=K, M=M, shape=shape, tn=tn, height=height, per=per, slices=slices, wgs=-(-M // height) * -(-N // tn) * slices,
+                    cut=len(heights_of(cls, tm, tn)) > 1)
+
+
+def columns(launches):
+    return {k: np.array([g[k] for g in launches], float) for k in launches[0]}
+
+
+def price_tall(cls, f, p=None):
+    """What choose_tall() prices launches at; p: constants in the order of tall_start()."""
+    c = TALL[cls] if p is None else tall_constants(cls, p)
+    shape = f["shape"].astype(int)
+    tk, tfix, tk160, tfix160, tk2 = np.array([e[3:] for e in c["shapes"]]).T[:, shape]
+    at = np.where(f["cut"] > 0, (f["height"] - 160) / 96, 1.0)
+    tk, tfix = tk160 + at * (tk - tk160), tfix160 + at * (tfix - tfix160)
+    paired = np.array([e[:3] == (128, 128, 0) for e in c["shapes"]])[shape]
+    rounds = np.ceil(f["wgs"] / 256)
+    t = rounds * (tfix + f["per"] * tk) / np.where((rounds > 1) & paired, c["pair"], 1.0) + rounds * f["per"] ** 2 * tk2
+    t = t + f["wgs"] * f["per"] * (f["height"] + f["tn"]) * 128 / (c["l2_rate"] * 1e6)
+    split = f["slices"] > 1
+    t = t + np.where(split, c["split"] + 8 * f["M"] * f["N"] * f["slices"] / (c["split_rate"] * 1e6), 0.0)
+    return t * np.where(split & (f["per"] % 2 == 1) & (f["K"] % 128 == 0), c["odd"], 1.0)
+
+
+def tall_start(cls):
+    c = TALL[cls]
+    return np.array([v for e in c["shapes"] for v in e[3:] if v] + [c[k] for k in ("pair", "l2_rate", "split", "split_rate", "odd")])
+
+
+def tall_constants(cls, p):
+    it = iter(p)
+    shapes = tuple(e[:3] + tuple(next(it) if v else 0 for v in e[3:]) for e in TALL[cls]["shapes"])
+    return dict(shapes=shapes, **dict(zip(("pair", "l2_rate", "split", "split_rate", "odd"), it)))
+
+
+def time_tall(path, shapes, tokens):
+    import torch
+
+    from . import binding as nfp, workloads
+
+    dev = torch.device("cuda:0")
+    t0 = time.time()
+    with open(path, "w") as out:
+        for N, K in shapes:
+            for storage in STORAGES:
+                cls = tall_class(storage)
+                copies = max(2, min(64, int(700e6 / (N * K * (1 if cls == 2 else 2))) + 1))
+                layers = []
+                for i in range(copies):
+                    W = workloads.weight_device(N, K, 0.02, seed=i)
+                    layers.append(W if cls == 3 else nfp.decompose(W, check=False, packed=storage[-1] == "p"))
+                    del W
+                for M in tokens:
+                    X = workloads.act_device(M, K, seed=2)
+                    Y = torch.empty((M, N), dtype=torch.float16, device=dev)
+                    ws = nfp.new_workspace(8 * M * (N + 4) * 4 + M * (K + 128) + 4 * M + (1 << 20), dev)
+                    reps = copies if copies * M * N * K < 4e13 else max(2, int(4e13 / (M * N * K)))
+
+                    def call(i):
+                        layer = layers[i % copies]
+                        if cls == 3:
+                            nfp.plain_gemm_fp16(X, layer, out=Y, workspace=ws)
+                        else:
+                            nfp.gemm(X, layer[0], layer[1], nfp.MODE_FP8 if cls == 2 else nfp.MODE_FP16, out=Y, workspace=ws)
+
+                    def timed(pins, call=call):
+                        for k, v in pins.items():
+                            nfp.tune(k, v)
+                        try:
+                            graph = graph_of(call, reps)
+                        finally:
+                            for k in pins:
+                                nfp.tune(k, -1)
+                        return float(np.median([microseconds(graph, reps) for _ in range(5)]))
+
+                    timed({})                                  # (the first launches of a batch size run at another clock: 1.5 % slower)
+                    off = timed({}, lambda i: nfp.quantize_act(X)) if cls == 2 else 0.0
+                    out.write(json.dumps([N, K, M, storage, None, round(timed({}) - off, 2)]) + "\n")
+                    launches, geo = zip(*tall_launches(cls, N, K, M))
+                    priced = price_tall(cls, columns(geo))
+                    for launch, t in zip(launches, priced):
+                        if t > 1.6 * priced.min():
+                            continue
+                        pins = dict(zip(("large_bm", "large_bn", "large_split", "large_deep", "large_height"), launch))
+                        if cls == 1:
+                            del pins["large_deep"]
+                        out.write(json.dumps([N, K, M, storage, launch, round(timed(pins) - off, 2)]) + "\n")
                 del layers
                 torch.cuda.empty_cache()
             print("N=%d K=%d  %.0f s" % (N, K, time.time() - t0), flush=True)
@@ -312,6 +443,40 @@ def fit_lines(path):
               % (key + (a, unsplit, split, 100 * mean, 100 * most, 100 * np.log(t / best).mean(), 100 * np.log(s / best).mean())))
 
 
+def behind(v):
+    v = np.array(v)
+    return "%.1f %% behind on average, 95th percentile %.0f %%, at most %.0f %%" % (
+        100 * (np.exp(np.log(v).mean()) - 1), 100 * (np.percentile(v, 95) - 1), 100 * (v.max() - 1))
+
+
+def fit_prices(price, start, us, group):
+    """Constants that lose the least time to the fastest launch of a problem (group) by a soft choice of the cheapest, and price launches
+    near the fastest well; with what the choice loses by the constants at the start and by the new ones."""
+    from scipy.optimize import minimize
+
+    best = np.full(group.max() + 1, 1e30)
+    np.minimum.at(best, group, us)
+    lost = np.log(us / best[group])
+    weight = np.exp(-4 * lost)
+    weight /= weight.sum()
+
+    def objective(logp):
+        lp = np.log(price(np.exp(logp)))
+        low = np.full(len(best), 1e30)
+        np.minimum.at(low, group, lp)
+        e = np.exp(-(lp - low[group]) / 0.02)
+        soft = np.bincount(group, e * (lost + 3 * np.maximum(lost - 0.04, 0))) / np.bincount(group, e)
+        return soft.mean() + 0.3 * np.sqrt((weight * (lp - np.log(us)) ** 2).sum())
+
+    def regret(p):
+        order = np.lexsort((price(p), group))
+        first = order[np.unique(group[order], return_index=True)[1]]
+        return behind(us[first] / best[group[first]])
+
+    p = np.exp(minimize(objective, np.log(start), method="L-BFGS-B", options=dict(maxiter=150)).x)
+    return p, regret(np.array(start)), regret(p)
+
+
 # kShortCost: per tile shape microseconds per K-tile and per workgroup (tiles of 256 tokens: also at a height of 160), then the rest
 SHORT_PARAMS = ("pair128", "pair64", "base", "w_rate", "l2_rate", "cu_rate", "split", "split_rate")
 SHORT_START = {False: (0.725, 6.05, 0.556, 3.47, 0.421, 2.63, 0.314, 1.28, 0.5, 2.61, 0.2785, 0.83, 0.271, 0.51, 1.045, 1.045, 3.0, 15.2, 219, 167, 3.45, 5.28),
@@ -336,8 +501,6 @@ def price_short(p, f, fp8):
 
 
 def fit_tiles(path):
-    from scipy.optimize import minimize
-
     from . import binding
 
     through = binding.lib()._ZN3nfp16rows_through_ldsEiillli                      # nfp::rows_through_lds
@@ -346,11 +509,6 @@ def fit_tiles(path):
     for line in open(path):
         N, K, M, storage, launch, us = json.loads(line)
         problems.setdefault((N, K, M, storage), {})[None if launch is None else tuple(launch)] = us
-
-    def behind(v):
-        v = np.array(v)
-        return "%.1f %% behind on average, 95th percentile %.0f %%, at most %.0f %%" % (
-            100 * (np.exp(np.log(v).mean()) - 1), 100 * (np.percentile(v, 95) - 1), 100 * (v.max() - 1))
 
     for storage in STORAGES[:4]:
         v = [d[None] / min(us for launch, us in d.items() if launch) for key, d in problems.items() if key[3] == storage]
@@ -391,47 +549,64 @@ def fit_tiles(path):
             continue
         f = {k: np.array([g[k] for g in geo], float) for k in geo[0]}
         us, group = np.array(us), np.array(group)
-        best = np.full(len(groups), 1e30)
-        np.minimum.at(best, group, us)
-        lost = np.log(us / best[group])
-        weight = np.exp(-4 * lost)
-        weight /= weight.sum()
-
-        def objective(logp):
-            lp = np.log(price_short(np.exp(logp), f, fp8))
-            low = np.full(len(groups), 1e30)
-            np.minimum.at(low, group, lp)
-            e = np.exp(-(lp - low[group]) / 0.02)
-            soft = np.bincount(group, e * (lost + 3 * np.maximum(lost - 0.04, 0))) / np.bincount(group, e)
-            return soft.mean() + 0.3 * np.sqrt((weight * (lp - np.log(us)) ** 2).sum())
-
-        def regret(p):
-            order = np.lexsort((price_short(p, f, fp8), group))
-            first = order[np.unique(group[order], return_index=True)[1]]
-            return behind(us[first] / best[group[first]])
-
-        start = np.array(SHORT_START[fp8])
-        p = np.exp(minimize(objective, np.log(start), method="L-BFGS-B", options=dict(maxiter=150)).x)
-        print("// %s: %d timings; constants as they are: %s; fitted: %s" % ("E4M3" if fp8 else "FP16", len(us), regret(start), regret(p)))
+        p, before, after = fit_prices(lambda p: price_short(p, f, fp8), SHORT_START[fp8], us, group)
+        print("// %s: %d timings; constants as they are: %s; fitted: %s" % ("E4M3" if fp8 else "FP16", len(us), before, after))
         print("tiles {%s}, %s" % (", ".join("%.3g" % v for v in p[:14]), ", ".join("%s %.4g" % v for v in zip(SHORT_PARAMS, p[14:]))))
+
+
+def fit_tall(path):
+    problems = {}
+    for line in open(path):
+        N, K, M, storage, launch, us = json.loads(line)
+        problems.setdefault((N, K, M, storage), {})[None if launch is None else tuple(launch)] = us
+    for cls, name in ((1, "FP16 operands through registers"), (2, "E4M3"), (3, "plain FP16")):
+        geo, us, group, built_in, n = [], [], [], [], 0
+        for (N, K, M, storage), d in problems.items():
+            if tall_class(storage) != cls or len(d) < 2:
+                continue
+            built_in.append(d[None] / min(t for launch, t in d.items() if launch))
+            for launch, g in tall_launches(cls, N, K, M):
+                if launch in d:
+                    geo.append(g)
+                    us.append(d[launch])
+                    group.append(n)
+            n += 1
+        if not geo:
+            continue
+        f = columns(geo)
+        p, before, after = fit_prices(lambda p: price_tall(cls, f, p), tall_start(cls), np.array(us), np.array(group))
+        print("// %s: %d timings of %d problems; the library's choice %s; prices as they are %s; fitted %s" % (name, len(us), n, behind(built_in), before, after))
+        c = tall_constants(cls, p)
+        print("{%d, {%s}, %.3g, %.3ge6, %.3g, %.3ge6, %.3g, 0}" % (
+            len(c["shapes"]), ", ".join("{%d, %d, %d, %s}" % (e[:3] + (", ".join("%.3g" % v for v in e[3:]),)) for e in c["shapes"]),
+            c["pair"], c["l2_rate"], c["split"], c["split_rate"], c["odd"]))
 
 
 def main():
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
-    ap.add_argument("do", choices=("time", "fit", "time-tiles", "fit-tiles"))
-    ap.add_argument("files", nargs="+", help="candidates.jsonl routes.jsonl, or tiles.jsonl")
+    ap.add_argument("do", choices=("time", "fit", "time-tiles", "fit-tiles", "time-tall", "fit-tall"))
+    ap.add_argument("files", nargs="+", help="candidates.jsonl routes.jsonl, tiles.jsonl or tall.jsonl")
     ap.add_argument("--shapes", nargs="*", default=None, help="N,K pairs instead of the built-in layer shapes")
-    ap.add_argument("--tokens", nargs="*", type=int, default=TILE_TOKENS, help="batch sizes of time-tiles")
+    ap.add_argument("--tokens", nargs="*", type=int, default=None, help="batch sizes of time-tiles and time-tall")
     args = ap.parse_args()
     shapes = [tuple(int(v) for v in s.split(",")) for s in args.shapes] if args.shapes else \
         sorted({s for v in MODEL_SHAPES.values() for s in v} | set(OTHER_SHAPES))
-    if len(args.files) != (1 if "tiles" in args.do else 2):
-        ap.error("%s takes %s" % (args.do, "one file" if "tiles" in args.do else "two files"))
+    one = args.do not in ("time", "fit")
+    if len(args.files) != (1 if one else 2):
+        ap.error("%s takes %s" % (args.do, "one file" if one else "two files"))
+    if args.do == "time-tall" and min(args.tokens or TALL_TOKENS) <= 256:
+        ap.error("time-tall is for more than 256 tokens")
     if args.do == "time":
         time_all(args.files[0], args.files[1], shapes)
         return
     if args.do == "time-tiles":
-        time_tiles(args.files[0], shapes, args.tokens)
+        time_tiles(args.files[0], shapes, args.tokens or TILE_TOKENS)
+        return
+    if args.do == "time-tall":
+        time_tall(args.files[0], shapes, args.tokens or TALL_TOKENS)
+        return
+    if args.do == "fit-tall":
+        fit_tall(args.files[0])
         return
     if args.do == "fit-tiles":
         fit_tiles(args.files[0])

@@ -147,3 +147,32 @@ def test_room_for_padded_codes_stays_inside_the_fixed_scratch(L):
             held_back += 1
         assert got in (dense, lines)                            # and for no other room
     assert padded > 1000 and decode > 500 and held_back > 5, (padded, decode, held_back)
+
+
+@pytest.mark.parametrize("kind,cls", [(4, 1), (5, 2), (0, 3)])
+def test_prices_above_256_tokens_can_be_fitted_again(L, kind, cls):
+    # the model that fit_costs.py fits picks the launches that the library does, so its constants are the library's
+    import random
+
+    from paper_2506_02024_amd import fit_costs
+
+    height = L._ZN3nfp17large_gemm_heightEilll                  # nfp::large_gemm_height
+    height.restype, height.argtypes = ctypes.c_int, [ctypes.c_int] + 3 * [ctypes.c_int64]
+    rng = random.Random(cls)
+    heights, splits = set(), set()
+    for _ in range(400):
+        M, N, K = int(257 * 30 ** rng.random()), rng.randrange(1, 30000), 16 * rng.randrange(20, 1500)
+        launches, geo = zip(*fit_costs.tall_launches(cls, N, K, M))
+        if max(g["slices"] for g in geo) * M * N * 4 + M * K > 30 << 20:
+            geo, launches = zip(*((g, l) for g, l in zip(geo, launches) if g["slices"] == 1))
+            if partial_bytes(L, kind, M, N, K) > 0:
+                continue                                        # (rules of the fixed scratch decide as well)
+        prices = fit_costs.price_tall(cls, fit_costs.columns(geo))
+        (tm, tn, split, deep, tall), lowest = launches[prices.argmin()], prices.min()
+        if sorted(prices)[1:2] and sorted(prices)[1] < lowest * (1 + 1e-9):
+            continue
+        assert height(kind, M, N, K) == tall, (M, N, K)
+        assert partial_bytes(L, kind, M, N, K) == (split * M * ((N + 3) // 4 * 4) * 4 if split > 1 else 0), (M, N, K)
+        heights.add(tall)
+        splits.add(split)
+    assert len(heights) >= 4 and len(splits) >= 4, (heights, splits)
