@@ -196,11 +196,12 @@ int nestedfp_gemm_packed(const uint16_t *X, int64_t M, int64_t K, int64_t ldx,
 /*
  * nestedfp_gemm for callers that cannot allocate device memory or pass a workspace (code
  * under HIP graph capture that owns no scratch, tight serving loops, harnesses that forbid
- * hipMalloc): row-major planes, same arguments without the workspace, same results.  The
- * scratch is a fixed array inside the library's device image (NESTEDFP_STATIC_SCRATCH_BYTES
- * per GPU, held until the process ends).  A problem whose workspace query exceeds it is
- * refused with NESTEDFP_ERR_WORKSPACE, but for batches of more than 64 tokens whose query exceeds it
- * for the K split alone: these run in a smaller split (the same products, summed in another
+ * hipMalloc): row-major planes, same arguments without the workspace.  The scratch is a fixed
+ * array inside the library's device image (NESTEDFP_STATIC_SCRATCH_BYTES per GPU, held until
+ * the process ends).  Where nestedfp_gemm_workspace_size is at most that, the results are those of
+ * nestedfp_gemm bit for bit.  A problem whose query exceeds it is refused with
+ * NESTEDFP_ERR_WORKSPACE, but for batches of more than 64 tokens whose query exceeds it for the
+ * K split alone: these run in a smaller split (the same products, summed in another
  * order).  The call itself allocates nothing.  All calls on one
  * GPU share that array: calls that may overlap in time on one GPU (different streams) race.
  */
