@@ -1702,30 +1702,32 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K, bool b
 // 73 us so, 60 in slices.  The choice is 0.5 % (FP16 mode) and 0.6 % (E4M3, plain FP16) behind the fastest launch on average, 3.3
 // to 4.4 % at the 95th percentile, and as much on layers that were left out of the fit; the model before it, which knew no
 // heights, 3.3, 4.1 and 4.3 %, 15 to 20 %.
-// That model still serves plain FP16 weights at 65 to 256 tokens, with the weights' one pass over the memory bus as a floor.
+// That model still serves plain FP16 weights at 65 to 256 tokens, with the weights' one pass over the memory bus as a floor.  Launches
+// that the floor prices alike are taken in the table's order, the larger tile first: (16142, 8128) at 125 tokens 80.7 us on 256 x 128
+// tiles, 96.0 on 128 x 128 ones, and 12 to 25 % on 26 more of 65 to 128 tokens.
 struct TallShape { int tm, tn, deep; double tk, tfix, tk160, tfix160, tk2; };       // as ShortShape; tk2: per K-tile squared
 struct TallCost {
     int shapes;
     TallShape shape[7];
     double pair;                        // 128 x 128 workgroups of a CU that run together, from the second round on
-    double l2_rate, split, split_rate;
+    double l2_rate, split, split_rate;  // (no l2_rate: operands from L2 are not priced)
     double odd;                         // register path, rows on lines: slices of an odd number of K-tiles (see rows_through_lds)
-    double floor_rate;                  // of the memory bus, slower while the chip is not full
+    double floor_rate, floor_rate512;   // of the memory bus, slower while the chip is not full (from 512 workgroups on)
     bool both_depths;                   // every tile below 256 x 256 is priced in both pipelines, not 128 x 128 alone
 };
 static const TallCost kTallCost[4] = {
     // plain FP16 of up to 256 tokens
     {7, {{256, 256, 0, 1.353, 0, 1.353, 0, 0}, {256, 128, 0, 1.053, 0.07, 0, 0, 0}, {256, 128, 1, 0.863, 1.56, 0, 0, 0}, {128, 256, 0, 1.098, 0, 0, 0, 0},
-         {128, 256, 1, 0.900, 1.71, 0, 0, 0}, {128, 128, 0, 0.848, 0, 0, 0, 0}, {128, 128, 1, 0.585, 2.50, 0, 0, 0}}, 1.58, 1e15, 3.18, 4.44e6, 1.0, 4.57e6, true},
+         {128, 256, 1, 0.900, 1.71, 0, 0, 0}, {128, 128, 0, 0.848, 0, 0, 0, 0}, {128, 128, 1, 0.585, 2.50, 0, 0, 0}}, 1.58, 0, 3.18, 4.44e6, 1.0, 4.57e6, 4.44e6, true},
     // FP16 operands through registers
     {4, {{256, 256, 0, 1.11, 8.54, 0.773, 6.36, 0}, {256, 128, 0, 0.573, 6.03, 0.351, 5.53, 0.309e-3}, {128, 256, 0, 0.634, 6.39, 0, 0, 0.103e-3},
-         {128, 128, 0, 0.285, 4.28, 0, 0, 0.466e-3}}, 1.0, 28.3e6, 2.98, 6.93e6, 1.05, 0, false},
+         {128, 128, 0, 0.285, 4.28, 0, 0, 0.466e-3}}, 1.0, 28.3e6, 2.98, 6.93e6, 1.05, 0, 0, false},
     // E4M3
     {5, {{256, 256, 0, 0.951, 9.83, 0.653, 7.57, 0}, {256, 128, 1, 0.445, 7.46, 0, 0, 0.502e-3}, {128, 256, 1, 0.598, 5.27, 0, 0, 0.026e-3},
-         {128, 128, 0, 0.515, 4.75, 0, 0, 1.88e-3}, {128, 128, 1, 0.247, 5.41, 0, 0, 1.19e-3}}, 1.83, 50.5e6, 2.14, 5.55e6, 1.0, 0, false},
+         {128, 128, 0, 0.515, 4.75, 0, 0, 1.88e-3}, {128, 128, 1, 0.247, 5.41, 0, 0, 1.19e-3}}, 1.83, 50.5e6, 2.14, 5.55e6, 1.0, 0, 0, false},
     // plain FP16 above
     {5, {{256, 256, 0, 1.04, 7.72, 0.716, 5.68, 0}, {256, 128, 1, 0.466, 7.05, 0, 0, 0.286e-3}, {128, 256, 1, 0.578, 4.71, 0, 0, 0.168e-3},
-         {128, 128, 0, 0.432, 4.88, 0, 0, 1.34e-3}, {128, 128, 1, 0.223, 4.69, 0, 0, 1.00e-3}}, 1.70, 34.3e6, 2.61, 6.13e6, 1.0, 0, false},
+         {128, 128, 0, 0.432, 4.88, 0, 0, 1.34e-3}, {128, 128, 1, 0.223, 4.69, 0, 0, 1.00e-3}}, 1.70, 34.3e6, 2.61, 6.13e6, 1.0, 0, 0, false},
 };
 // A split whose partial sums outgrow the fixed scratch of nestedfp_gemm_static is taken where it is priced 4 % below what fits,
 // and by that entry point (bounded) nowhere: FP16 mode is 0.5 % behind the fastest launch so, 0.9 % if nothing beyond
@@ -1770,11 +1772,11 @@ static LargeConfig choose_tall(int cls, int64_t M, int64_t N, int64_t K, bool bo
                 if (rounds > 1 && e.tm == 128 && e.tn == 128 && !deep) time /= m.pair;
                 time += (double)rounds * per * per * e.tk2;
                 if (M <= 256 && cls == 0) {
-                    double floor_t = (double)N * (double)K * 2.0 / m.floor_rate;
+                    double floor_t = (double)N * (double)K * 2.0 / (wgs < 512 ? m.floor_rate : m.floor_rate512);
                     if (wgs < 256) floor_t *= std::sqrt(256.0 / (double)wgs);
                     if (time < floor_t) time = floor_t;
                 }
-                time += (double)wgs * per * (height + e.tn) * 128.0 / m.l2_rate;
+                if (m.l2_rate > 0) time += (double)wgs * per * (height + e.tn) * 128.0 / m.l2_rate;
                 if (slices > 1) {
                     time += split_cost(M, N, slices, m.split, m.split_rate);
                     if ((per & 1) && (K & 127) == 0) time *= m.odd;

@@ -181,3 +181,14 @@ def test_prices_above_256_tokens_can_be_fitted_again(L, kind, cls):
         heights.add(tall)
         splits.add(split)
     assert len(heights) >= 4 and len(splits) >= 4, (heights, splits)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    # plain FP16, microseconds on 256 x 128 tiles and on 128 x 128 ones, which the floor of the memory bus prices alike: 80.7 / 96.0,
+    # 91.0 / 102.9, 46.6 / 52.3, 76.2 / 96.1, 54.0 / 64.2, 56.2 / 65.3
+    (125, 16142, 8128), (97, 15874, 9968), (97, 8118, 9456), (88, 10549, 15936), (113, 5328, 20160), (66, 16197, 6384),
+])
+def test_plain_fp16_layers_that_the_memory_bus_bounds(L, M, N, K):
+    height = L._ZN3nfp17large_gemm_heightEilll                  # nfp::large_gemm_height
+    height.restype, height.argtypes = ctypes.c_int, [ctypes.c_int] + 3 * [ctypes.c_int64]
+    assert height(0, M, N, K) == 256
