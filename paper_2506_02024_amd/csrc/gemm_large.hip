@@ -1699,9 +1699,12 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K, bool b
 // height and split worth one on 150 layers of 1 to 300 Mi weights at 272 to 8192 tokens, both storage orders, and to 40 000 more
 // of FP8 mode with padded rows of codes (fit_costs.py time-tall and fit-tall take such timings and fit them).  Long K loops of the
 // smaller tiles take more than their share (tk2): E4M3 on 128 x 128 tiles 13 % more at 100 K-tiles; (4064, 12208) at 589 tokens
-// 73 us so, 60 in slices.  The choice is 0.5 % (FP16 mode) and 0.6 % (E4M3, plain FP16) behind the fastest launch on average, 3.3
-// to 4.4 % at the 95th percentile, and as much on layers that were left out of the fit; the model before it, which knew no
-// heights, 3.3, 4.1 and 4.3 %, 15 to 20 %.
+// 73 us so, 60 in slices.  On the layers of the fit, and some left out of it, the choice was 0.5 to 0.6 % behind the fastest launch on
+// average and 3.3 to 4.4 % at the 95th percentile; timed again on 159 layers, half of them drawn at random (114 000 timings of
+// 4560 problems), 1.0 % (FP16 mode), 0.8 % (E4M3) and 1.1 % (plain FP16), and 6 to 9 %.  The model before it, which knew no
+// heights, is 3.9, 4.3 and 4.5 % behind there, 16 to 19 %, but ahead by more than 3 % on 3 to 6 % of the problems, mostly small
+// ones.  Constants fitted to these timings, with a term for rows that start inside lines, won 0.0 to 0.2 % on 855 further layers and slowed
+// down as many calls as they sped up: not taken.
 // That model still serves plain FP16 weights at 65 to 256 tokens, with the weights' one pass over the memory bus as a floor.  Launches
 // that the floor prices alike are taken in the table's order, the larger tile first: (16142, 8128) at 125 tokens 80.7 us on 256 x 128
 // tiles, 96.0 on 128 x 128 ones, and 12 to 25 % on 26 more of 65 to 128 tokens.

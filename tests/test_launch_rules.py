@@ -165,8 +165,8 @@ def test_prices_above_256_tokens_can_be_fitted_again(L, kind, cls):
     height.restype, height.argtypes = ctypes.c_int, [ctypes.c_int] + 3 * [ctypes.c_int64]
     rng = random.Random(cls)
     heights, splits = set(), set()
-    for _ in range(400):
-        M, N, K = int(257 * 30 ** rng.random()), rng.randrange(1, 30000), 16 * rng.randrange(20, 1500)
+    for _ in range(800):
+        M, N, K = int(257 * 30 ** rng.random()), int(100 * 300 ** rng.random()), 16 * rng.randrange(20, 1500)
         launches, geo = zip(*fit_costs.tall_launches(cls, N, K, M))
         if max(g["slices"] for g in geo) * M * N * 4 + M * K > 30 << 20:
             geo, launches = zip(*((g, l) for g, l in zip(geo, launches) if g["slices"] == 1))
