@@ -1705,6 +1705,14 @@ static LargeConfig choose_short(int cls, int64_t M, int64_t N, int64_t K, bool b
 // heights, is 3.9, 4.3 and 4.5 % behind there, 16 to 19 %, but ahead by more than 3 % on 3 to 6 % of the problems, mostly small
 // ones.  Constants fitted to these timings, with a term for rows that start inside lines, won 0.0 to 0.2 % on 855 further layers and slowed
 // down as many calls as they sped up: not taken.
+// Tiles of 128 tokens that all run at once, unsplit, read the same 128 bytes of K at the same time, and wait for memory
+// together; a last token tile of few rows, which has half as much to load, runs ahead of the others and fetches their weights.
+// Plain (2560, 2560) takes 28.5 us at 504 tokens, 28.9 at 767, but 21.5 at 649 and 776; in three and two slices, which start at
+// other columns, 20.2 and 24.3.  Hence their price (lone, lone256; 2/5 is where the residuals of the prices part).  Timed with
+// and without, weights cold, on 5622 problems drawn at 257 to 8192 tokens: behind the fastest launch 0.59 instead of 0.72 %
+// (FP16 mode), 0.44 and 0.51 % (E4M3), 0.78 and 1.20 % (plain FP16), at the 95th percentile 4.0 and 4.8, 3.1 and 3.3, 5.4 and
+// 8.0 %; slower by more than 3 % than the model without heights on 1.7 instead of 2.6, 0.9 and 1.3, 3.3 and 5.7 % of them.  The
+// 140 problems whose launch it changes take 0.94 of the time; 22 of them are slower by 3 to 18 %, 90 faster by 3 to 22 %.
 // That model still serves plain FP16 weights at 65 to 256 tokens, with the weights' one pass over the memory bus as a floor.  Launches
 // that the floor prices alike are taken in the table's order, the larger tile first: (16142, 8128) at 125 tokens 80.7 us on 256 x 128
 // tiles, 96.0 on 128 x 128 ones, and 12 to 25 % on 26 more of 65 to 128 tokens.
@@ -1715,22 +1723,23 @@ struct TallCost {
     double pair;                        // 128 x 128 workgroups of a CU that run together, from the second round on
     double l2_rate, split, split_rate;  // (no l2_rate: operands from L2 are not priced)
     double odd;                         // register path, rows on lines: slices of an odd number of K-tiles (see rows_through_lds)
+    double lone, lone256;               // unsplit on 128 x 128 and 128 x 256 tiles, at most one workgroup per CU, the last token tile more than 2/5 full
     double floor_rate, floor_rate512;   // of the memory bus, slower while the chip is not full (from 512 workgroups on)
     bool both_depths;                   // every tile below 256 x 256 is priced in both pipelines, not 128 x 128 alone
 };
 static const TallCost kTallCost[4] = {
     // plain FP16 of up to 256 tokens
     {7, {{256, 256, 0, 1.353, 0, 1.353, 0, 0}, {256, 128, 0, 1.053, 0.07, 0, 0, 0}, {256, 128, 1, 0.863, 1.56, 0, 0, 0}, {128, 256, 0, 1.098, 0, 0, 0, 0},
-         {128, 256, 1, 0.900, 1.71, 0, 0, 0}, {128, 128, 0, 0.848, 0, 0, 0, 0}, {128, 128, 1, 0.585, 2.50, 0, 0, 0}}, 1.58, 0, 3.18, 4.44e6, 1.0, 4.57e6, 4.44e6, true},
+         {128, 256, 1, 0.900, 1.71, 0, 0, 0}, {128, 128, 0, 0.848, 0, 0, 0, 0}, {128, 128, 1, 0.585, 2.50, 0, 0, 0}}, 1.58, 0, 3.18, 4.44e6, 1.0, 1.0, 1.0, 4.57e6, 4.44e6, true},
     // FP16 operands through registers
     {4, {{256, 256, 0, 1.11, 8.54, 0.773, 6.36, 0}, {256, 128, 0, 0.573, 6.03, 0.351, 5.53, 0.309e-3}, {128, 256, 0, 0.634, 6.39, 0, 0, 0.103e-3},
-         {128, 128, 0, 0.285, 4.28, 0, 0, 0.466e-3}}, 1.0, 28.3e6, 2.98, 6.93e6, 1.05, 0, 0, false},
+         {128, 128, 0, 0.285, 4.28, 0, 0, 0.466e-3}}, 1.0, 28.3e6, 2.98, 6.93e6, 1.05, 1.07, 1.0, 0, 0, false},
     // E4M3
     {5, {{256, 256, 0, 0.951, 9.83, 0.653, 7.57, 0}, {256, 128, 1, 0.445, 7.46, 0, 0, 0.502e-3}, {128, 256, 1, 0.598, 5.27, 0, 0, 0.026e-3},
-         {128, 128, 0, 0.515, 4.75, 0, 0, 1.88e-3}, {128, 128, 1, 0.247, 5.41, 0, 0, 1.19e-3}}, 1.83, 50.5e6, 2.14, 5.55e6, 1.0, 0, 0, false},
+         {128, 128, 0, 0.515, 4.75, 0, 0, 1.88e-3}, {128, 128, 1, 0.247, 5.41, 0, 0, 1.19e-3}}, 1.83, 50.5e6, 2.14, 5.55e6, 1.0, 1.09, 1.0, 0, 0, false},
     // plain FP16 above
     {5, {{256, 256, 0, 1.04, 7.72, 0.716, 5.68, 0}, {256, 128, 1, 0.466, 7.05, 0, 0, 0.286e-3}, {128, 256, 1, 0.578, 4.71, 0, 0, 0.168e-3},
-         {128, 128, 0, 0.432, 4.88, 0, 0, 1.34e-3}, {128, 128, 1, 0.223, 4.69, 0, 0, 1.00e-3}}, 1.70, 34.3e6, 2.61, 6.13e6, 1.0, 0, 0, false},
+         {128, 128, 0, 0.432, 4.88, 0, 0, 1.34e-3}, {128, 128, 1, 0.223, 4.69, 0, 0, 1.00e-3}}, 1.70, 34.3e6, 2.61, 6.13e6, 1.0, 1.12, 1.05, 0, 0, false},
 };
 // A split whose partial sums outgrow the fixed scratch of nestedfp_gemm_static is taken where it is priced 4 % below what fits,
 // and by that entry point (bounded) nowhere: FP16 mode is 0.5 % behind the fastest launch so, 0.9 % if nothing beyond
@@ -1783,6 +1792,8 @@ static LargeConfig choose_tall(int cls, int64_t M, int64_t N, int64_t K, bool bo
                 if (slices > 1) {
                     time += split_cost(M, N, slices, m.split, m.split_rate);
                     if ((per & 1) && (K & 127) == 0) time *= m.odd;
+                } else if (e.tm == 128 && wgs <= 256 && 5 * ((M - 1) % 128 + 1) > 2 * 128) {
+                    time *= e.tn == 128 ? m.lone : m.lone256;
                 }
                 if (!fits) time /= 0.96;
                 if (time < best) { best = time;  c.tm = e.tm;  c.tn = e.tn;  c.split = split;  c.deep = deep;  c.height = height; }

@@ -233,11 +233,11 @@ TALL_TOKENS = (272, 300, 384, 449, 512, 600, 777, 1000, 1200, 1536, 1790, 2048, 
 # pipeline, microseconds per K-tile and per workgroup at the full height and at 160 tokens, per K-tile squared
 TALL = {
     1: dict(shapes=((256, 256, 0, 1.11, 8.54, 0.773, 6.36, 0), (256, 128, 0, 0.573, 6.03, 0.351, 5.53, 0.309e-3), (128, 256, 0, 0.634, 6.39, 0, 0, 0.103e-3),
-                    (128, 128, 0, 0.285, 4.28, 0, 0, 0.466e-3)), pair=1.0, l2_rate=28.3, split=2.98, split_rate=6.93, odd=1.05),
+                    (128, 128, 0, 0.285, 4.28, 0, 0, 0.466e-3)), pair=1.0, l2_rate=28.3, split=2.98, split_rate=6.93, odd=1.05, lone=1.07, lone256=1.0),
     2: dict(shapes=((256, 256, 0, 0.951, 9.83, 0.653, 7.57, 0), (256, 128, 1, 0.445, 7.46, 0, 0, 0.502e-3), (128, 256, 1, 0.598, 5.27, 0, 0, 0.026e-3),
-                    (128, 128, 0, 0.515, 4.75, 0, 0, 1.88e-3), (128, 128, 1, 0.247, 5.41, 0, 0, 1.19e-3)), pair=1.83, l2_rate=50.5, split=2.14, split_rate=5.55, odd=1.0),
+                    (128, 128, 0, 0.515, 4.75, 0, 0, 1.88e-3), (128, 128, 1, 0.247, 5.41, 0, 0, 1.19e-3)), pair=1.83, l2_rate=50.5, split=2.14, split_rate=5.55, odd=1.0, lone=1.09, lone256=1.0),
     3: dict(shapes=((256, 256, 0, 1.04, 7.72, 0.716, 5.68, 0), (256, 128, 1, 0.466, 7.05, 0, 0, 0.286e-3), (128, 256, 1, 0.578, 4.71, 0, 0, 0.168e-3),
-                    (128, 128, 0, 0.432, 4.88, 0, 0, 1.34e-3), (128, 128, 1, 0.223, 4.69, 0, 0, 1.00e-3)), pair=1.70, l2_rate=34.3, split=2.61, split_rate=6.13, odd=1.0),
+                    (128, 128, 0, 0.432, 4.88, 0, 0, 1.34e-3), (128, 128, 1, 0.223, 4.69, 0, 0, 1.00e-3)), pair=1.70, l2_rate=34.3, split=2.61, split_rate=6.13, odd=1.0, lone=1.12, lone256=1.05),
 }
 
 
@@ -281,18 +281,20 @@ def price_tall(cls, f, p=None):
     t = t + f["wgs"] * f["per"] * (f["height"] + f["tn"]) * 128 / (c["l2_rate"] * 1e6)
     split = f["slices"] > 1
     t = t + np.where(split, c["split"] + 8 * f["M"] * f["N"] * f["slices"] / (c["split_rate"] * 1e6), 0.0)
-    return t * np.where(split & (f["per"] % 2 == 1) & (f["K"] % 128 == 0), c["odd"], 1.0)
+    t = t * np.where(split & (f["per"] % 2 == 1) & (f["K"] % 128 == 0), c["odd"], 1.0)
+    lone = ~split & (f["height"] == 128) & (f["wgs"] <= 256) & (5 * ((f["M"] - 1) % 128 + 1) > 2 * 128)
+    return t * np.where(lone, np.where(f["tn"] == 128, c["lone"], c["lone256"]), 1.0)
 
 
 def tall_start(cls):
     c = TALL[cls]
-    return np.array([v for e in c["shapes"] for v in e[3:] if v] + [c[k] for k in ("pair", "l2_rate", "split", "split_rate", "odd")])
+    return np.array([v for e in c["shapes"] for v in e[3:] if v] + [c[k] for k in ("pair", "l2_rate", "split", "split_rate", "odd", "lone", "lone256")])
 
 
 def tall_constants(cls, p):
     it = iter(p)
     shapes = tuple(e[:3] + tuple(next(it) if v else 0 for v in e[3:]) for e in TALL[cls]["shapes"])
-    return dict(shapes=shapes, **dict(zip(("pair", "l2_rate", "split", "split_rate", "odd"), it)))
+    return dict(shapes=shapes, **dict(zip(("pair", "l2_rate", "split", "split_rate", "odd", "lone", "lone256"), it)))
 
 
 def time_tall(path, shapes, tokens):
@@ -577,9 +579,9 @@ def fit_tall(path):
         p, before, after = fit_prices(lambda p: price_tall(cls, f, p), tall_start(cls), np.array(us), np.array(group))
         print("// %s: %d timings of %d problems; the library's choice %s; prices as they are %s; fitted %s" % (name, len(us), n, behind(built_in), before, after))
         c = tall_constants(cls, p)
-        print("{%d, {%s}, %.3g, %.3ge6, %.3g, %.3ge6, %.3g, 0}" % (
+        print("{%d, {%s}, %.3g, %.3ge6, %.3g, %.3ge6, %.3g, %.3g, %.3g, 0, 0, false}" % (
             len(c["shapes"]), ", ".join("{%d, %d, %d, %s}" % (e[:3] + (", ".join("%.3g" % v for v in e[3:]),)) for e in c["shapes"]),
-            c["pair"], c["l2_rate"], c["split"], c["split_rate"], c["odd"]))
+            c["pair"], c["l2_rate"], c["split"], c["split_rate"], c["odd"], c["lone"], c["lone256"]))
 
 
 def main():

@@ -192,3 +192,19 @@ def test_plain_fp16_layers_that_the_memory_bus_bounds(L, M, N, K):
     height = L._ZN3nfp17large_gemm_heightEilll                  # nfp::large_gemm_height
     height.restype, height.argtypes = ctypes.c_int, [ctypes.c_int] + 3 * [ctypes.c_int64]
     assert height(0, M, N, K) == 256
+
+
+@pytest.mark.parametrize("kind,M,N,K", [
+    # microseconds unsplit and in slices: plain FP16 28.5 / 20.2, 28.9 / 24.3, 29.5 / 23.7, FP16 mode 22.9 / 18.5, 19.2 / 14.9,
+    # E4M3 40.1 / 32.9, 31.0 / 27.3
+    (0, 504, 2560, 2560), (0, 767, 2560, 2560), (0, 377, 4224, 2816), (4, 470, 2432, 2432), (4, 310, 1456, 1456),
+    (5, 995, 2016, 5872), (5, 379, 4864, 4864),
+])
+def test_workgroups_that_would_wait_for_memory_together_are_split(L, kind, M, N, K):
+    assert partial_bytes(L, kind, M, N, K) > 0
+
+
+@pytest.mark.parametrize("M", [649, 776])
+def test_a_last_token_tile_of_few_rows_keeps_a_launch_unsplit(L, M):
+    # the same layer with 9 and 8 rows in it: 21.5 us unsplit, 21.7 in two slices
+    assert partial_bytes(L, 0, M, 2560, 2560) == 0
